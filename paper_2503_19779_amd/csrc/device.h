@@ -1,0 +1,328 @@
+// device.h -- device-side helpers shared by the kernel files: storage formats, vector loads and stores,
+// the wave64 reduction, the elementwise operations.  gfx950 only.
+#pragma once
+
+#include "kernels.h"
+
+#include <cstddef>
+
+namespace pgk {
+namespace {
+
+constexpr int kBlock = 256;   // threads per workgroup = 4 waves of 64
+
+#define PG_GLOBAL __attribute__((address_space(1)))
+#define PG_CONSTANT __attribute__((address_space(4)))
+
+// ---- operand resolution -------------------------------------------------------------------
+template <bool IND>
+__device__ __forceinline__ const void* resolve(const void* p) {
+    if constexpr (IND) {
+        // uniform address: one scalar load.  What a slot holds is a tensor in global memory; saying so lets the
+        // compiler use global loads where it would otherwise fall back to generic ones (which also count as LDS operations)
+        return (const void*)(const void PG_GLOBAL*)*reinterpret_cast<const uintptr_t*>(p);
+    } else {
+        return p;
+    }
+}
+
+__device__ __forceinline__ bool aligned_to(const void* p, unsigned bytes) {
+    return (reinterpret_cast<uintptr_t>(p) & (bytes - 1u)) == 0;
+}
+
+// ---- storage formats ------------------------------------------------------------------------
+// Two fp32 values to a packed pair of bf16: round to nearest, ties to even, NaN stays a quiet NaN.
+// One gfx950 conversion instruction instead of a dozen integer ones: these kernels are latency
+// bound, every instruction on the path from the last load to the store counts.
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned pack2_bf16(float lo, float hi) {
+    v2f x;
+    x.x = lo;
+    x.y = hi;
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(x, v2bf));
+}
+__device__ __forceinline__ unsigned f32_to_bf16(float f) { return pack2_bf16(f, 0.f) & 0xffffu; }
+
+typedef unsigned short bf16_t;
+
+// A "vector" is VB bytes (16 or 4) = NV elements, carried in NW 32-bit words.
+template <typename T, int VB> struct Vec;
+template <int VB> struct Vec<float, VB> {
+    static constexpr int NV = VB / 4, NW = VB / 4;
+    static __device__ __forceinline__ void unpack(const unsigned* w, float* f) {
+#pragma unroll
+        for (int i = 0; i < NV; i++) f[i] = __uint_as_float(w[i]);
+    }
+    static __device__ __forceinline__ void pack(const float* f, unsigned* w) {
+#pragma unroll
+        for (int i = 0; i < NV; i++) w[i] = __float_as_uint(f[i]);
+    }
+};
+template <int VB> struct Vec<bf16_t, VB> {
+    static constexpr int NV = VB / 2, NW = VB / 4;
+    static __device__ __forceinline__ void unpack(const unsigned* w, float* f) {
+#pragma unroll
+        for (int i = 0; i < NW; i++) {
+            f[2 * i] = __uint_as_float(w[i] << 16);
+            f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+        }
+    }
+    static __device__ __forceinline__ void pack(const float* f, unsigned* w) {
+#pragma unroll
+        for (int i = 0; i < NW; i++) w[i] = pack2_bf16(f[2 * i], f[2 * i + 1]);
+    }
+};
+
+__device__ __forceinline__ unsigned load_raw(const float* p) { return *reinterpret_cast<const unsigned*>(p); }
+__device__ __forceinline__ unsigned load_raw(const bf16_t* p) { return *p; }
+template <typename T> __device__ __forceinline__ float from_raw(unsigned r) {
+    return __uint_as_float(sizeof(T) == 4 ? r : r << 16);
+}
+__device__ __forceinline__ float load_elem(const float* p) { return *p; }
+__device__ __forceinline__ float load_elem(const bf16_t* p) { return __uint_as_float((unsigned)*p << 16); }
+__device__ __forceinline__ void store_elem(float* p, float v) { *p = v; }
+__device__ __forceinline__ void store_elem(bf16_t* p, float v) { *p = (bf16_t)f32_to_bf16(v); }
+
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+// Fetch one vector of VB bytes as words.  AL: the address is VB-aligned; otherwise the same bytes
+// arrive through element-sized loads (a tensor is always element aligned).  Loads only: nothing here
+// consumes the data, so a caller can issue many of these before the first wait.
+template <typename T, int VB, bool AL, bool NT = false>
+__device__ __forceinline__ void load_vec(const T* p, unsigned* w) {
+    constexpr int NW = VB / 4;
+    if constexpr (AL) {
+        if constexpr (VB == 16) {
+            v4u t;
+            if constexpr (NT) t = __builtin_nontemporal_load(reinterpret_cast<const v4u*>(p));
+            else t = *reinterpret_cast<const v4u*>(p);
+            w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+        } else {
+            w[0] = *reinterpret_cast<const unsigned*>(p);
+        }
+    } else if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int i = 0; i < NW; i++) w[i] = reinterpret_cast<const unsigned*>(p)[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < NW; i++)
+            w[i] = (unsigned)reinterpret_cast<const unsigned short*>(p)[2 * i] |
+                   ((unsigned)reinterpret_cast<const unsigned short*>(p)[2 * i + 1] << 16);
+    }
+}
+
+// The same fetch through a pointer that says "global memory" outright.  A tensor address that reached the
+// kernel through a pointer-table slot or a run-time choice is a generic pointer to the compiler; generic
+// loads are slower and are counted as LDS operations as well, so a wait for LDS would wait for them too.
+template <typename T, bool AL, bool NT = false>
+__device__ __forceinline__ void load_vec_global(const T* p, unsigned* w) {
+    if constexpr (AL) {
+        v4u t;
+        if constexpr (NT) t = __builtin_nontemporal_load((const v4u PG_GLOBAL*)(uintptr_t)p);
+        else t = *(const v4u PG_GLOBAL*)(uintptr_t)p;
+        w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+    } else if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) w[i] = ((const unsigned PG_GLOBAL*)(uintptr_t)p)[i];
+    } else {
+        const unsigned short PG_GLOBAL* q = (const unsigned short PG_GLOBAL*)(uintptr_t)p;
+#pragma unroll
+        for (int i = 0; i < 4; i++) w[i] = (unsigned)q[2 * i] | ((unsigned)q[2 * i + 1] << 16);
+    }
+}
+// The 4-byte vector (one fp32 or two bf16 elements) through a global pointer.
+template <typename T, bool AL>
+__device__ __forceinline__ void load_vec4_global(const T* p, unsigned* w) {
+    if constexpr (sizeof(T) == 4 || AL) w[0] = *(const unsigned PG_GLOBAL*)(uintptr_t)p;
+    else {
+        const unsigned short PG_GLOBAL* q = (const unsigned short PG_GLOBAL*)(uintptr_t)p;
+        w[0] = (unsigned)q[0] | ((unsigned)q[1] << 16);
+    }
+}
+template <typename T>
+__device__ __forceinline__ unsigned load_raw_global(const T* p) {
+    if constexpr (sizeof(T) == 4) return *(const unsigned PG_GLOBAL*)(uintptr_t)p;
+    else return *(const unsigned short PG_GLOBAL*)(uintptr_t)p;
+}
+// Element i of a tensor whose address is the same in every lane: the address stays in scalar registers and
+// the load takes the lane's offset beside it, with no vector arithmetic on 64-bit addresses.
+template <typename T>
+__device__ __forceinline__ unsigned load_raw_global_at(const T* base, unsigned i) {
+    if constexpr (sizeof(T) == 4) return ((const unsigned PG_GLOBAL*)(uintptr_t)base)[i];
+    else return ((const unsigned short PG_GLOBAL*)(uintptr_t)base)[i];
+}
+__device__ __forceinline__ void store_vec_global(void* p, const unsigned* w) {
+    v4u t;
+    t.x = w[0]; t.y = w[1]; t.z = w[2]; t.w = w[3];
+    *(v4u PG_GLOBAL*)(uintptr_t)p = t;
+}
+// A pointer-table slot, or the tensor address itself: decided at run time (the merged kernels; the
+// stand-alone ones decide at compile time, resolve<IND>).  The slot is read as constant memory -- nothing
+// writes the table while a graph runs -- which makes it a scalar load that no vector-memory wait covers.
+__device__ __forceinline__ const void* resolve_rt(const void* p, unsigned is_slot) {
+    return is_slot ? *(const void* const PG_CONSTANT*)(uintptr_t)p : p;
+}
+
+// Rows of `cols` elements in 16-byte vectors: nfull = cols / NV full vectors, then (RAGGED shapes
+// only) one partial vector.  Fetching is split in two so that all loads of a kernel can be in flight
+// together: row_vec_issue loads vector min(v, nfull-1) -- always inside the row, no branch -- and
+// row_vec_finish unpacks it, zeroes it if v lies beyond the full vectors, and reads the partial
+// vector's elements one by one.
+template <typename T, bool AL, bool NT = false>
+__device__ __forceinline__ void row_vec_issue(const T* row, int nfull, int v, unsigned* w) {
+    constexpr int NV = Vec<T, 16>::NV;
+    const int vc = v < nfull ? v : nfull - 1;
+    load_vec<T, 16, AL, NT>(row + (size_t)vc * NV, w);
+}
+// Words of vector v after the fact: zero beyond the full vectors, and (RAGGED) the partial vector
+// read element by element.
+template <typename T, bool RAGGED>
+__device__ __forceinline__ void row_vec_fix(const T* row, int cols, int nfull, int v, unsigned* w) {
+    constexpr int NV = Vec<T, 16>::NV;
+    if (v >= nfull) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) w[i] = 0u;
+        if constexpr (RAGGED) {
+            if (v == nfull) {
+                const int left = cols - nfull * NV;
+#pragma unroll
+                for (int i = 0; i < NV; i++) {
+                    if (i < left) {
+                        const unsigned r = load_raw(row + (size_t)nfull * NV + i);
+                        if constexpr (sizeof(T) == 4) w[i] = r;
+                        else w[i / 2] |= r << (16 * (i & 1));
+                    }
+                }
+            }
+        }
+    }
+}
+template <typename T, bool RAGGED>
+__device__ __forceinline__ void row_vec_finish(const T* row, int cols, int nfull, int v, unsigned* w, float* f) {
+    row_vec_fix<T, RAGGED>(row, cols, nfull, v, w);
+    Vec<T, 16>::unpack(w, f);
+}
+
+// acc += sum of the products of two vectors' elements, in element order.  bf16: one packed
+// two-element dot product (fp32 accumulate) per word; fp32: one fused multiply-add per element.
+template <typename T>
+__device__ __forceinline__ float dot_acc(const unsigned* a, const unsigned* b, float acc) {
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) acc = __builtin_fmaf(__uint_as_float(a[i]), __uint_as_float(b[i]), acc);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2bf, a[i]), __builtin_bit_cast(v2bf, b[i]), acc, false);
+    }
+    return acc;
+}
+
+template <int VB>
+__device__ __forceinline__ void store_vec(void* p, const unsigned* w) {
+    if constexpr (VB == 16) {
+        v4u t;
+        t.x = w[0]; t.y = w[1]; t.z = w[2]; t.w = w[3];
+        *reinterpret_cast<v4u*>(p) = t;
+    } else {
+        *reinterpret_cast<unsigned*>(p) = w[0];
+    }
+}
+
+// ---- wave64 reduction -----------------------------------------------------------------------
+// Butterfly over the 16 lanes of a DPP row, then the four row sums are read out and added in a
+// fixed order.  Every lane performs the same additions on the same values, so all lanes hold the
+// same bits.  Needs all 64 lanes active.
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    int t = __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false);
+    return v + __int_as_float(t);
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    v = dpp_add<0xB1>(v);    // quad_perm [1,0,3,2]: lane ^ 1
+    v = dpp_add<0x4E>(v);    // quad_perm [2,3,0,1]: lane ^ 2
+    v = dpp_add<0x141>(v);   // row_half_mirror: the other quad of each 8
+    v = dpp_add<0x140>(v);   // row_mirror: the other half of each 16
+    float r0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
+    float r1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16));
+    float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
+    float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
+    return ((r0 + r1) + r2) + r3;
+}
+
+// Workgroup barrier for an exchange through LDS only: waits for this wave's LDS operations, not for its
+// outstanding global stores (which __syncthreads would, at about a microsecond apiece).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// ---- elementwise ----------------------------------------------------------------------------
+// GELU(a) = a * Phi(a) with Phi(a) = erfc(-a / sqrt 2) / 2 (keeps relative accuracy in the left
+// tail).  For fp32 tensors it is evaluated in fp64 and rounded once, so that the result is the
+// correctly rounded one except within ~1e-16 of a rounding boundary: an fp32 erfc is a few ulp off,
+// and a chain of multiplies and cancelling adds amplifies that beyond 1e-5.  For bf16 tensors fp32
+// is far more than the 8 stored bits need, and the library erfcf (a few hundred instructions over
+// several branches, which a wave of mixed values all takes) made large GELU kernels ALU-bound at a
+// quarter of the HBM rate; gelu_bf16 below is branch-free and about 40 instructions.
+//
+// erfc(z), z >= 0, as (1 - u) * exp(-z^2 + u * Q(u)) with u = z / (2 + z) in [0, 1): the exponent's
+// second term is log(erfc(z) exp(z^2) (1 + z/2)), smooth in u and zero at u = 0, so that erfc(0) = 1
+// comes out exactly and tiny inputs give a/2 exactly.  Q: degree 9, a Chebyshev fit on z <= 9.7
+// (beyond, a * Phi(a) is below the smallest normal number), max error 8e-9 in the exponent.  z^2 is
+// taken with its rounding error (one fma), the exponential as 2^k * exp2(r) with |r| <= 0.51 after a
+// two-constant reduction, so the relative error stays near 2e-7 into the tail.  Checked against the
+// fp64 definition on every finite bf16 input: the bf16 result is the correctly rounded one for all
+// of them (the closest any exact value comes to a rounding boundary is 8e-7, at a = -0.336).
+__device__ __forceinline__ float gelu_bf16(float a) {
+    const float x = a * -0.70710678118654752440f;
+    const float z = __builtin_fminf(__builtin_fabsf(x), 14.0f);      // erfc(14) = 0 in fp32; keeps z * z finite (and a NaN out of the exponent)
+    const float u = z * __builtin_amdgcn_rcpf(2.0f + z);
+    const float t = 1.0f - u;
+    float p = -0.153892517f;
+    p = __builtin_fmaf(p, u, 0.49560681f);
+    p = __builtin_fmaf(p, u, -0.509543419f);
+    p = __builtin_fmaf(p, u, 0.182105958f);
+    p = __builtin_fmaf(p, u, -0.144903973f);
+    p = __builtin_fmaf(p, u, 0.072065711f);
+    p = __builtin_fmaf(p, u, 0.19142893f);
+    p = __builtin_fmaf(p, u, 0.161542267f);
+    p = __builtin_fmaf(p, u, -0.303239733f);
+    p = __builtin_fmaf(p, u, -1.25675833f);
+    p = p * u;
+    const float s = z * z, e = __builtin_fmaf(z, z, -s);               // z^2 = s + e exactly
+    constexpr float kLog2e = 1.4426950408889634f, kLn2Hi = 0.693145751953125f, kLn2Lo = 1.42860682030941723212e-6f;
+    const float kf = __builtin_rintf((p - s) * kLog2e);
+    float r = __builtin_fmaf(kf, -kLn2Hi, -s);
+    r = r + p;
+    r = r - e;
+    r = __builtin_fmaf(kf, -kLn2Lo, r);
+    const float v = __builtin_ldexpf(t * __builtin_amdgcn_exp2f(r * kLog2e), (int)kf);
+    const float erfc_x = x < 0.f ? 2.0f - v : v;
+    return (0.5f * a) * erfc_x;      // a NaN comes back through this product; -inf * 0 = NaN as in the definition
+}
+
+template <int OP, bool WIDE>
+__device__ __forceinline__ float ew_apply(float a, float b) {
+    if constexpr (OP == kAdd) {
+        return a + b;
+    } else if constexpr (OP == kMul) {
+        return a * b;
+    } else if constexpr (WIDE) {
+        const double x = (double)a;
+        return (float)((0.5 * x) * erfc(x * -0.70710678118654752440));
+    } else {
+        return gelu_bf16(a);
+    }
+}
+
+// ---- host side ------------------------------------------------------------------------------
+#define PG_FN(...) reinterpret_cast<const void*>(&__VA_ARGS__)
+
+inline unsigned blocks_for(long long n, long long per_block) {
+    const long long g = (n + per_block - 1) / per_block;
+    return (unsigned)(g < 1 ? 1 : g);
+}
+
+}  // namespace
+}  // namespace pgk

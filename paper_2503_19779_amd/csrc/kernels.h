@@ -148,6 +148,7 @@ struct Shape {
 // choice depends on the shape alone, never on the mask or on pointer values, so the direct and the
 // indirect form of a kernel run the same schedule.  False if there is no such kernel.
 bool plan(int op, int dtype, int ind_mask, const Shape& shape, Launch* out);
+bool plan_gemv(int dtype, int ind_mask, int rows, int n, int cols, Launch* out);    // its part for kGemv (gemv.hip)
 const void* copy_kernel();
 const void* table_kernel();
 // Can this kernel be part of a merged dispatch?  From op, dtype and shape alone.  On success *n_out is
