@@ -56,6 +56,7 @@ union ArgBlock {
     pgk::EwArgs ew;
     pgk::RmsArgs rms;
     pgk::GemvArgs gemv;
+    pgk::GemvEpiArgs epi;           // starts with the GemvArgs; for the GEMV kernels that take the whole block
     pgk::SbrArgs sbr;
     // every block starts with: out, in0, in1, (in2)
     const void* ptr[4];
@@ -280,7 +281,7 @@ pgk::Shape shape_of(const pg_kernel_desc& d) {
 }
 
 // Split kernels [k0, k1) of a segment into the runs a captured graph plays with one dispatch each.
-// Two kinds of run: a GEMV (the shape k_gemv_shared serves) followed by up to kEpiMaxPhases elementwise
+// Two kinds of run: a GEMV (of a shape pgk::merge_head names) followed by up to kEpiMaxPhases elementwise
 // kernels over its [rows, n] outputs, which become its epilogue -- and preceded, if the kernel before it
 // is the RMSNorm that produces its input, by that RMSNorm as a prologue; and up to kMergeMaxPhases
 // element-for-element kernels (add / mul / GELU, RMSNorm over rows of one unit) for one workgroup per unit.
@@ -304,7 +305,7 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
         if (d.op == PG_ADD || d.op == PG_MUL) return j == 0 || (d.m ? d.m : d.n) == n;
         return j == 0;                                                  // GELU a, RMSNORM x
     };
-    // Is kernel i an RMSNorm [few rows, 2048] straight into a GEMV of the epilogue kernel's shape (its prologue)?
+    // Is kernel i an RMSNorm of few rows straight into a GEMV of the epilogue kernels' shapes (its prologue)?
     auto prologue_at = [&](int i) {
         if (!(k[i].op == PG_RMSNORM && k[i].dtype == PG_BF16 && i + 1 < k1 && k[i].rows >= 1 && k[i].rows <= pgk::kPrologueMaxRows)) return false;
         const pg_kernel_desc& v = k[i + 1];
@@ -563,7 +564,11 @@ pg_status make_records(pg_chain* c) {
                 a.ew.n = d.n; a.ew.m = (d.op == PG_GELU) ? d.n : (d.m ? d.m : d.n);
                 break;
             case PG_RMSNORM: a.rms.rows = (int)d.rows; a.rms.cols = (int)d.cols; a.rms.eps = d.eps; break;
-            case PG_GEMV: a.gemv.rows = (int)d.rows; a.gemv.n = (int)d.n; a.gemv.cols = (int)d.cols; break;
+            case PG_GEMV:
+                a.gemv.rows = (int)d.rows; a.gemv.n = (int)d.n; a.gemv.cols = (int)d.cols;
+                a.epi.head = pgk::kEpiHeadStore | (mode == 2 ? (unsigned)r.ind_mask : 0u);          // no prologue, no epilogue
+                for (auto& ph : a.epi.ph) ph.meta = (unsigned)PG_GELU;                              // operands "from slot 0": fetches nothing, never played
+                break;
             case PG_SCALE_BIAS_RELU:
                 a.sbr.n = d.n; a.sbr.inner = (unsigned)d.inner;
                 a.sbr.channels = (unsigned)(d.in[1].kind == PG_REF_EXT ? c->ext[d.in[1].index].numel
@@ -585,7 +590,7 @@ pg_status make_records(pg_chain* c) {
             g.launch = pgk::Launch();
             g.launch.block = dim3(256);
             if (g.head) {
-                g.launch.fn = pgk::gemv_epilogue_kernel((int)c->k[g.gemv()].rows, g.pro);
+                g.launch.fn = pgk::gemv_epilogue_kernel(shape_of(c->k[g.gemv()]), g.pro);
                 g.launch.arg_bytes = sizeof(pgk::GemvEpiArgs);
                 g.launch.grid = c->rec[g.gemv()].direct.grid;               // the GEMV's own launch shape: same workgroups, same lanes
                 if (c->rec[g.gemv()].direct.block.x != 256) return fail(PG_EINVAL, "kernel %d: unexpected GEMV launch shape", g.gemv());

@@ -85,6 +85,7 @@ __device__ __forceinline__ void store_elem(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store_elem(bf16_t* p, float v) { *p = (bf16_t)f32_to_bf16(v); }
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Fetch one vector of VB bytes as words.  AL: the address is VB-aligned; otherwise the same bytes
 // arrive through element-sized loads (a tensor is always element aligned).  Loads only: nothing here
@@ -249,6 +250,51 @@ __device__ __forceinline__ float wave_sum(float v) {
     float r2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 32));
     float r3 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48));
     return ((r0 + r1) + r2) + r3;
+}
+
+// N sums at once, each the same additions in the same shape as wave_sum (the same bits).  The first two steps of
+// the butterfly hand over one value for every value kept, so that the later steps carry one value per lane instead
+// of N: about 17 instructions for four sums where four wave_sums take 44.  Lane l returns the sum sums_index<N>(l);
+// the mirrored steps reach lanes whose index bits are flipped, hence the flip in every other quad.
+template <int N>
+__device__ __forceinline__ int sums_index(int lane) {
+    const int i4 = (lane ^ ((lane & 4) ? 3 : 0)) & 3;
+    return N == 1 ? 0 : N == 2 ? (i4 & 1) : N <= 4 ? i4 : i4 + (lane & 4);
+}
+constexpr int sums_lanes(int n) { return n == 1 ? 1 : n == 2 ? 2 : n <= 4 ? 4 : 8; }   // lanes 0 .. that - 1 hold every sum once
+template <int CTRL>
+__device__ __forceinline__ float dpp_take(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum_rows(float v) {       // ((row 0 + row 1) + row 2) + row 3 of the four DPP rows, in every lane
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    const auto a = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false), b = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+    return ((__uint_as_float(a[0]) + __uint_as_float(a[1])) + __uint_as_float(b[0])) + __uint_as_float(b[1]);
+}
+template <int N>
+__device__ __forceinline__ float wave_sums(const float* s, int lane) {
+    static_assert(N >= 2 && N <= 8, "two to eight sums");
+    const bool odd = sums_index<2>(lane) != 0, high = (sums_index<4>(lane) & 2) != 0;
+    auto four = [&](float s0, float s1, float s2, float s3, bool two_only) {
+        const float r01 = (odd ? s1 : s0) + dpp_take<0xB1>(odd ? s0 : s1);
+        float v;
+        if (two_only) {
+            v = r01 + dpp_take<0x4E>(r01);
+        } else {
+            const float r23 = (odd ? s3 : s2) + dpp_take<0xB1>(odd ? s2 : s3);
+            v = (high ? r23 : r01) + dpp_take<0x4E>(high ? r01 : r23);
+        }
+        v += dpp_take<0x141>(v);
+        v += dpp_take<0x140>(v);
+        return sum_rows(v);
+    };
+    const float lo = four(s[0], s[1], N > 2 ? s[N > 2 ? 2 : 0] : 0.f, N > 3 ? s[N > 3 ? 3 : 0] : 0.f, N == 2);
+    if constexpr (N <= 4) {
+        return lo;
+    } else {
+        const float hi = four(s[4], N > 5 ? s[N > 5 ? 5 : 0] : 0.f, N > 6 ? s[N > 6 ? 6 : 0] : 0.f, N > 7 ? s[N > 7 ? 7 : 0] : 0.f, false);
+        return (lane & 4) ? hi : lo;
+    }
 }
 
 // Workgroup barrier for an exchange through LDS only: waits for this wave's LDS operations, not for its

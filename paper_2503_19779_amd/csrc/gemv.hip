@@ -98,83 +98,24 @@ __global__ __launch_bounds__(kBlock) void k_gemv(GemvArgs p) {
 // over long before the first weight arrives.  Same lanes, same products, same order as gemv_body and
 // gemvb_body: the results are bit-identical.
 static_assert(kBlock == 64 * kGemvChunk, "one vector of h per lane of the workgroup");
-// `after_issue()` runs once every weight load of the wave has been asked for (the epilogue form of the
-// kernel fetches its own operands there: every instruction in front of the weight loads delays the whole
-// kernel -- asking for the epilogue's operands first, so that they would be back before the weights,
-// measured 0.17 us slower per launch); sums[r][rr] receives the finished dot products, the same bits in
-// every lane.
-// GLOBAL: W and h reached the kernel as generic pointers (through a run-time choice); fetch them with loads
-// that say "global memory" outright.
-// PRO: h is not loaded but computed here -- `h` points at the rows x to normalise, `gain` and `eps` are
-// RMSNorm's; the arithmetic is rms_body's for a row of one vector per lane (fused multiply-add sum of
-// squares in element order, wave_sum, the four wave sums added in a fixed order through LDS,
-// 1 / sqrt(mean + eps), (x * scale) * gain, one rounding), and lane t's vector of the result goes where
-// lane t's vector of h would have gone.  hstore != nullptr: this workgroup also stores the rows there.
-// (eps by reference: the epilogue kernel reads it from its arguments inside the hook.)
-template <typename T, int R, int RB, bool AL, bool GLOBAL, bool PRO, class Hook>
-__device__ __forceinline__ void gemv_sums_shared(const T* W, const T* h, int n, int j0, int lane, int tid, v4u* hs /* [RB][kBlock] */,
-                                                 Hook after_issue, float (*sums)[RB],
-                                                 const T* gain = nullptr, const float& eps = 0.f, T* hstore = nullptr, float* part = nullptr) {
+template <typename T, int R, int RB, bool AL>
+__device__ __forceinline__ void gemv_body_shared(const T* W, const T* h, T* y, int n, int j0, int lane, int tid, v4u* hs /* [RB][kBlock] */) {
     constexpr int NV = Vec<T, 16>::NV;
     constexpr int kCols = 64 * kGemvChunk * NV;
-    unsigned hv[RB][4], ww[R][kGemvChunk][4], wh[RB][kGemvChunk][4], wg[4];
+    unsigned hv[RB][4], ww[R][kGemvChunk][4], wh[RB][kGemvChunk][4];
 #pragma unroll
-    for (int rr = 0; rr < RB; rr++) {
-        if constexpr (GLOBAL) load_vec_global<T, AL, false>(h + (size_t)rr * kCols + (size_t)tid * NV, hv[rr]);
-        else load_vec<T, 16, AL, false>(h + (size_t)rr * kCols + (size_t)tid * NV, hv[rr]);
-    }
-    if constexpr (PRO) load_vec_global<T, AL, false>(gain + (size_t)tid * NV, wg);
+    for (int rr = 0; rr < RB; rr++) load_vec<T, 16, AL, false>(h + (size_t)rr * kCols + (size_t)tid * NV, hv[rr]);
     __builtin_amdgcn_sched_barrier(0);   // h first: loads come back in the order they were issued
 #pragma unroll
     for (int r = 0; r < R; r++) {
         const T* wrow = W + (size_t)((j0 + r < n) ? j0 + r : n - 1) * kCols;   // a ragged last group re-reads the last row
 #pragma unroll
-        for (int u = 0; u < kGemvChunk; u++) {
-            if constexpr (GLOBAL) load_vec_global<T, AL, true>(wrow + (size_t)(u * 64 + lane) * NV, ww[r][u]);
-            else load_vec<T, 16, AL, true>(wrow + (size_t)(u * 64 + lane) * NV, ww[r][u]);
-        }
+        for (int u = 0; u < kGemvChunk; u++) load_vec<T, 16, AL, true>(wrow + (size_t)(u * 64 + lane) * NV, ww[r][u]);
     }
     __builtin_amdgcn_sched_barrier(0);
-    after_issue();
-    if constexpr (PRO) {
-        float fg[NV];
-        Vec<T, 16>::unpack(wg, fg);
-        // every row's sum of squares first, then one barrier for all rows (a row of partial sums per row of x)
 #pragma unroll
-        for (int rr = 0; rr < RB; rr++) {
-            float fx[NV];
-            Vec<T, 16>::unpack(hv[rr], fx);
-            float acc = 0.f;
-#pragma unroll
-            for (int e = 0; e < NV; e++) acc = __builtin_fmaf(fx[e], fx[e], acc);
-            acc = wave_sum(acc);
-            if ((tid & 63) == 0) part[rr * (kBlock / 64) + (tid >> 6)] = acc;
-        }
-        lds_barrier();
-#pragma unroll
-        for (int rr = 0; rr < RB; rr++) {
-            float fx[NV], fo[NV];
-            Vec<T, 16>::unpack(hv[rr], fx);
-            const float* prow = part + rr * (kBlock / 64);
-            const float total = ((prow[0] + prow[1]) + prow[2]) + prow[3];
-            const float scale = 1.0f / sqrtf(total / (float)kCols + eps);
-#pragma unroll
-            for (int e = 0; e < NV; e++) fo[e] = (fx[e] * scale) * fg[e];
-            Vec<T, 16>::pack(fo, hv[rr]);
-        }
-    }
-#pragma unroll
-    for (int rr = 0; rr < RB; rr++) {
-        v4u t;
-        t.x = hv[rr][0]; t.y = hv[rr][1]; t.z = hv[rr][2]; t.w = hv[rr][3];
-        hs[rr * kBlock + tid] = t;
-    }
+    for (int rr = 0; rr < RB; rr++) hs[rr * kBlock + tid] = v4u{hv[rr][0], hv[rr][1], hv[rr][2], hv[rr][3]};
     __syncthreads();      // every wave of the workgroup gets here: none leaves early
-    if constexpr (PRO) {  // after the barrier, which would otherwise wait for these stores
-        if (hstore)
-#pragma unroll
-            for (int rr = 0; rr < RB; rr++) store_vec_global(hstore + (size_t)rr * kCols + (size_t)tid * NV, hv[rr]);
-    }
 #pragma unroll
     for (int rr = 0; rr < RB; rr++)
 #pragma unroll
@@ -194,18 +135,10 @@ __device__ __forceinline__ void gemv_sums_shared(const T* W, const T* h, int n, 
 #pragma unroll
     for (int rr = 0; rr < RB; rr++)
 #pragma unroll
-        for (int r = 0; r < R; r++) sums[r][rr] = wave_sum(acc[r][rr]);
-}
-
-template <typename T, int R, int RB, bool AL>
-__device__ __forceinline__ void gemv_body_shared(const T* W, const T* h, T* y, int n, int j0, int lane, int tid, v4u* hs /* [RB][kBlock] */) {
-    float sums[R][RB];
-    gemv_sums_shared<T, R, RB, AL, false, false>(W, h, n, j0, lane, tid, hs, [] {}, sums);
-#pragma unroll
-    for (int rr = 0; rr < RB; rr++)
-#pragma unroll
-        for (int r = 0; r < R; r++)
-            if (lane == 0 && j0 + r < n) store_elem(y + (size_t)rr * n + j0 + r, sums[r][rr]);
+        for (int r = 0; r < R; r++) {
+            const float sum = wave_sum(acc[r][rr]);
+            if (lane == 0 && j0 + r < n) store_elem(y + (size_t)rr * n + j0 + r, sum);
+        }
 }
 
 // RB = rows of h: 1 to 4
@@ -316,7 +249,6 @@ __global__ __launch_bounds__(kBlock) void k_gemv_batched(GemvArgs p) {
 //   - per tile the 4 waves' partial sums meet in LDS and are added in a fixed order; lane l of a tile
 //     holds column (l & 15), rows 4 * (l >> 4) .. + 3.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMmSteps = 16;        // K-steps per wave per super-chunk (4 waves x 16 steps x 32 = 2048 columns)
 constexpr int kMmSlotBytes = 272;   // 16 rows x 16 B + 16 B of padding
 constexpr int kMmWaveLds = 64 * kMmSlotBytes;   // one wave's staging area: one tile, 64 slots
@@ -394,7 +326,7 @@ struct MmStore {
 };
 // MmEpilogue: the kernels that follow the GEMV in the chain, element for element, ride along (kernels.h,
 // GemvEpiArgs): prepare() reads their table out of the kernel arguments and resolves pointer-table slots --
-// the bodies call it once their weight loads are on their way, as k_gemv_epilogue does, so that nothing but
+// the bodies call it once their weight loads are on their way, as k_gemv_rows does, so that nothing but
 // the first 64 bytes of the arguments stands between the start of the kernel and those loads; begin() asks
 // for the operands, so that they arrive while the tile is staged and multiplied and the partial sums are
 // exchanged; end() plays the kernels on the lane's outputs, rounding to bf16 after each as the stand-alone
@@ -459,7 +391,7 @@ struct MmEpilogue {
         }
         any = __builtin_amdgcn_readfirstlane(any);
         asm volatile("" : "+s"(any));       // keeps what follows behind the weight loads
-        {   // the decoder block's tail, recognised here so that end() runs it straight through (see k_gemv_epilogue)
+        {   // the decoder block's tail, recognised here so that end() runs it straight through (see k_gemv_rows)
             auto add_of = [](unsigned mt, unsigned q) {
                 const unsigned a = (mt >> 8) & 0xffu, b = (mt >> 16) & 0xffu;
                 return (mt & 0xffu) == (unsigned)kAdd && ((a == q && b == kMergeFromMemory) || (a == kMergeFromMemory && b == q));
@@ -548,7 +480,7 @@ struct MmEpilogue {
     __device__ __forceinline__ void end() {
         unsigned bits[NE];
         float slot[kMergeSlots][NE];
-        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): every operand, before the first store (see k_gemv_epilogue)
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): every operand, before the first store (see k_gemv_rows)
 #pragma unroll
         for (int e = 0; e < NE; e++) {
             bits[e] = f32_to_bf16(v[e]);
@@ -955,7 +887,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_mfma_bf16(GemvArgs p) {
 template <int FORM, bool PRO = false>
 __global__ __launch_bounds__(kBlock, (FORM == 3 || PRO) ? 1 : 2) void k_gemm_mfma_epilogue(GemvEpiArgs p) {
     static_assert(!PRO || FORM <= 2, "a prologue exists for the forms with one tile of rows per workgroup");
-    // As in k_gemv_epilogue: the first 64 bytes of the arguments hold everything that is needed before the
+    // As in k_gemv_rows: the first 64 bytes of the arguments hold everything that is needed before the
     // loads of h and the weights can go out, and only those are waited for here, in one batch of scalar loads;
     // the epilogue's table and eps are read once the weights are on their way (MmEpilogue::prepare).
     static_assert(offsetof(GemvEpiArgs, gain) + sizeof(void*) == 64, "what the kernel needs first sits in the first 64 bytes");
@@ -1008,10 +940,180 @@ __global__ __launch_bounds__(kBlock, (FORM == 3 || PRO) ? 1 : 2) void k_gemm_mfm
     }
 }
 
-// GEMV with an elementwise epilogue: k_gemv_shared's body, then lane e of each wave plays output e through
-// the kernels that follow (see kernels.h).  bf16 only.
-template <int RB, bool PRO>
-__global__ __launch_bounds__(kBlock) void k_gemv_epilogue(GemvEpiArgs p) {
+// ---- one to four rows of h, rows of any width: the sums, and in front of them optionally the RMSNorm ------
+// bf16.  A wave computes R output columns (R weight rows of up to U * 64 vectors, U per lane); h is fetched once per
+// workgroup (lane t vectors t, t + 256, ..., asked for before the weights) and shared by the four waves through
+// LDS.  Every load of the wave is in flight before the first wait.  Same products in the same order as gemv_body
+// and gemvb_body.
+// What bounds it: at 2048 columns and below the latency of one dispatch (1.55 us of graph node, then x from memory,
+// the reduction, the weights, the tail, the store), not bytes; the sums of all rows and columns are therefore
+// reduced together (wave_sums) and the rows' scales worked out side by side.  From about 4096 columns on, the
+// weights: 4096 x 4096 at four rows takes 9.8 us with its node, 3.4 TB/s.  Decode chains with one dispatch per
+// sub-block against the four to five they took before, us per iteration: 520 columns, 3 rows, 120 sub-blocks
+// 1108 -> 440; 4096 columns, 4 rows, 30 sub-blocks 504 -> 294; 2048 columns, 1 row, 120 sub-blocks 439 -> 431 (this
+// width was merged already; the rest is the scalar row addresses and the common reduction).
+// EXACT: a row is exactly 512 * U columns.  Otherwise rows end anywhere: a vector that reaches past
+// the end is fetched from the row's last eight columns instead (no load leaves the row, whatever its alignment:
+// vector loads here take any element boundary) and shifted into place, zeros behind.
+// PRO: h is not loaded but computed here -- `h` points at the rows x to normalise, `gain` and `eps` are
+// RMSNorm's; the arithmetic is rms_body's (fused multiply-add sum of squares in element order over the lane's
+// vectors, wave_sum, the four wave sums added in a fixed order through LDS, 1 / sqrt(mean + eps), (x * scale) *
+// gain, one rounding), and what lane t computes goes where lane t's vectors of h would have gone.
+// hstore != nullptr: this workgroup also stores the rows there.
+// `after_issue()` runs once every weight load of the wave has been asked for (the kernel reads the epilogue's
+// table and asks for its operands there: every instruction in front of the weight loads delays the whole kernel
+// -- asking for the epilogue's operands first, so that they would be back before the weights, measured 0.17 us
+// slower per launch); sums[rr * R + r] receives the lane's part of the dot products.
+// (eps by reference: the kernel reads it from its arguments inside the hook.)
+typedef v4u v4u_any __attribute__((aligned(2)));      // 16 bytes at any element boundary: one load or store instruction all the same
+template <bool NT>
+__device__ __forceinline__ void load_any(const bf16_t* base /* uniform */, unsigned elem, unsigned* w) {
+    const v4u_any PG_GLOBAL* q = (const v4u_any PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)base + elem);
+    v4u t;
+    if constexpr (NT) t = __builtin_nontemporal_load(q);
+    else t = *q;
+    w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+}
+// vector v of a row of `cols` >= 8 elements: where it is fetched ...
+template <bool EXACT>
+__device__ __forceinline__ unsigned span_at(int cols, int v) {
+    if constexpr (EXACT) return (unsigned)v * 8u;
+    const int at = v * 8;
+    return (unsigned)(at < cols - 8 ? at : cols - 8);
+}
+// ... and what becomes of it: elements past the row's end are zeros
+template <bool EXACT>
+__device__ __forceinline__ void span_fix(int cols, int v, unsigned* w) {
+    if constexpr (!EXACT) {
+        const int over = v * 8 + 8 - cols;
+        if (over > 0) {                                  // the fetched vector lies `over` elements before its place
+            const unsigned s = (unsigned)(over < 8 ? over : 8);
+            if (s & 1u) { w[0] = (w[0] >> 16) | (w[1] << 16); w[1] = (w[1] >> 16) | (w[2] << 16); w[2] = (w[2] >> 16) | (w[3] << 16); w[3] >>= 16; }
+            if (s & 2u) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
+            if (s & 4u) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0u; }
+            if (s & 8u) w[0] = w[1] = w[2] = w[3] = 0u;
+        }
+    }
+}
+__device__ __forceinline__ void span_store(bf16_t* row, int cols, int v, const unsigned* w) {
+    if (v * 8 + 8 <= cols) {
+        *(v4u_any PG_GLOBAL*)(uintptr_t)(row + (size_t)v * 8) = v4u{w[0], w[1], w[2], w[3]};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+            if (v * 8 + e < cols) *(unsigned short PG_GLOBAL*)(uintptr_t)(row + (size_t)v * 8 + e) = (unsigned short)(w[e / 2] >> (16 * (e & 1)));
+    }
+}
+
+template <int R, int RB, int U, bool EXACT, bool PRO, class Hook>
+__device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h, int n, int cols, int j0 /* uniform */, int lane, int tid, v4u* hs /* [RB][U * 64] */,
+                                               Hook after_issue, float (&sums)[R * RB],
+                                               const bf16_t* gain, const float& eps, bf16_t* hstore, f32x4* part /* [4]: four wave sums per row */) {
+    constexpr int KC = (U + 3) / 4;                      // vectors per lane of the workgroup
+    if constexpr (EXACT) cols = 512 * U;
+    // vector c of lane tid exists for every lane unless U is no multiple of four: then the last waves have none of the last
+    auto mine = [&](int c) { return U % 4 == 0 || c < KC - 1 || tid < 64 * (U % 4); };
+    unsigned hv[RB][KC][4], wg[KC][4], ww[R][U][4];
+#pragma unroll
+    for (int rr = 0; rr < RB; rr++)
+#pragma unroll
+        for (int c = 0; c < KC; c++) load_any<false>(h + (size_t)rr * cols, mine(c) ? span_at<EXACT>(cols, c * kBlock + tid) : 0u, hv[rr][c]);
+    if constexpr (PRO)
+#pragma unroll
+        for (int c = 0; c < KC; c++) load_any<false>(gain, mine(c) ? span_at<EXACT>(cols, c * kBlock + tid) : 0u, wg[c]);
+    __builtin_amdgcn_sched_barrier(0);   // h first: loads come back in the order they were issued
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const bf16_t* wrow = W + (size_t)((j0 + r < n) ? j0 + r : n - 1) * cols;   // a ragged last group re-reads the last row
+#pragma unroll
+        for (int u = 0; u < U; u++) load_any<true>(wrow, span_at<EXACT>(cols, u * 64 + lane), ww[r][u]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    after_issue();
+#pragma unroll
+    for (int rr = 0; rr < RB; rr++)
+#pragma unroll
+        for (int c = 0; c < KC; c++) {
+            span_fix<EXACT>(cols, c * kBlock + tid, hv[rr][c]);
+            if (!mine(c)) hv[rr][c][0] = hv[rr][c][1] = hv[rr][c][2] = hv[rr][c][3] = 0u;
+        }
+    if constexpr (PRO) {
+        // every row's sum of squares first, then one barrier for all rows (a row of partial sums per row of x), and one
+        // square root and division for all rows: lane r works out row r's scale (each row's own took 0.1 us)
+        float sq[RB];
+#pragma unroll
+        for (int rr = 0; rr < RB; rr++) {
+            sq[rr] = 0.f;
+#pragma unroll
+            for (int c = 0; c < KC; c++) {
+                float fx[8];
+                Vec<bf16_t, 16>::unpack(hv[rr][c], fx);
+#pragma unroll
+                for (int e = 0; e < 8; e++) sq[rr] = __builtin_fmaf(fx[e], fx[e], sq[rr]);
+            }
+        }
+        float wsum;
+        if constexpr (RB == 1) wsum = wave_sum(sq[0]);
+        else wsum = wave_sums<RB>(sq, lane);
+        if (lane < RB) reinterpret_cast<float*>(part)[lane * (kBlock / 64) + (tid >> 6)] = wsum;      // sums_index(lane) == lane here
+        lds_barrier();
+        const f32x4 p4 = part[lane & 3];           // rows beyond RB: nothing reads what comes of them
+        const float total = ((p4.x + p4.y) + p4.z) + p4.w;
+        const float my_scale = 1.0f / sqrtf(total / (float)cols + eps);
+#pragma unroll
+        for (int rr = 0; rr < RB; rr++) {
+            const float scale = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_scale), rr));
+#pragma unroll
+            for (int c = 0; c < KC; c++) {
+                float fx[8], fg[8], fo[8];
+                Vec<bf16_t, 16>::unpack(hv[rr][c], fx);
+                if (rr == 0) span_fix<EXACT>(cols, c * kBlock + tid, wg[c]);
+                Vec<bf16_t, 16>::unpack(wg[c], fg);
+#pragma unroll
+                for (int e = 0; e < 8; e++) fo[e] = (fx[e] * scale) * fg[e];
+                Vec<bf16_t, 16>::pack(fo, hv[rr][c]);
+            }
+        }
+    }
+#pragma unroll
+    for (int rr = 0; rr < RB; rr++)
+#pragma unroll
+        for (int c = 0; c < KC; c++) if (mine(c)) hs[rr * (U * 64) + c * kBlock + tid] = v4u{hv[rr][c][0], hv[rr][c][1], hv[rr][c][2], hv[rr][c][3]};
+    lds_barrier();        // every wave of the workgroup gets here: none leaves early
+    if constexpr (PRO) {  // after the barrier: nothing waits for these stores
+        if (hstore)
+#pragma unroll
+            for (int rr = 0; rr < RB; rr++)
+#pragma unroll
+                for (int c = 0; c < KC; c++) {
+                    if (!mine(c)) continue;
+                    if constexpr (EXACT) store_vec_global(hstore + (size_t)rr * cols + (size_t)(c * kBlock + tid) * 8, hv[rr][c]);
+                    else span_store(hstore + (size_t)rr * cols, cols, c * kBlock + tid, hv[rr][c]);
+                }
+    }
+#pragma unroll
+    for (int e = 0; e < R * RB; e++) sums[e] = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        unsigned wh[RB][4];
+#pragma unroll
+        for (int rr = 0; rr < RB; rr++) {
+            const v4u t = hs[rr * (U * 64) + u * 64 + lane];
+            wh[rr][0] = t.x; wh[rr][1] = t.y; wh[rr][2] = t.z; wh[rr][3] = t.w;
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            span_fix<EXACT>(cols, u * 64 + lane, ww[r][u]);
+#pragma unroll
+            for (int rr = 0; rr < RB; rr++) sums[rr * R + r] = dot_acc<bf16_t>(ww[r][u], wh[rr], sums[rr * R + r]);
+        }
+    }
+}
+
+// GEMV with an elementwise epilogue: one lane of each wave per output e (row e / R of h, column j0 + e % R) plays it
+// through the kernels that follow (see kernels.h; none of them: the plain GEMV).
+template <int R, int RB, int U, bool EXACT, bool PRO>
+__global__ __launch_bounds__(kBlock) void k_gemv_rows(GemvEpiArgs p) {
     constexpr int P = kEpiMaxPhases;
     // The GEMV's own arguments first, in one batch of scalar loads (see args_up_front): nothing else stands
     // between the start of the kernel and the weight loads.  The epilogue's table is read once those are on
@@ -1024,12 +1126,12 @@ __global__ __launch_bounds__(kBlock) void k_gemv_epilogue(GemvEpiArgs p) {
     const void* Wa = p.g.W;
     const void* ha = p.g.h;
     bf16_t* y = static_cast<bf16_t*>(p.g.out);
-    int n = p.g.n;
+    int n = p.g.n, cols = p.g.cols;
     unsigned head = p.head;
     int n_epi = p.n_epi;
     const void* xa = p.x;
     const void* ga = p.gain;
-    asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(n), "+s"(head), "+s"(n_epi), "+s"(xa), "+s"(ga));
+    asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(n), "+s"(cols), "+s"(head), "+s"(n_epi), "+s"(xa), "+s"(ga));
     const void* a0[P];
     const void* a1[P];
     bf16_t* outs[P];
@@ -1055,10 +1157,10 @@ __global__ __launch_bounds__(kBlock) void k_gemv_epilogue(GemvEpiArgs p) {
     const bf16_t* h = static_cast<const bf16_t*>(PRO ? xa : ha);
     const bf16_t* gain = PRO ? static_cast<const bf16_t*>(ga) : nullptr;
     bf16_t* hstore = (PRO && (head & kEpiStoreH) && blockIdx.x == 0) ? static_cast<bf16_t*>(const_cast<void*>(ha)) : nullptr;
-    __shared__ v4u hs[RB * kBlock];
-    __shared__ float part[RB * (kBlock / 64)];
+    __shared__ v4u hs[RB * U * 64];
+    __shared__ f32x4 part[4];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int j0 = (blockIdx.x * (kBlock / 64) + (tid >> 6)) * 2;
+    const int j0 = (blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(tid >> 6)) * R;   // uniform: the weight rows' addresses stay in scalar registers
     unsigned ld0[P], ld1[P];
     bool mine = false;
     unsigned idx = 0;
@@ -1083,8 +1185,9 @@ __global__ __launch_bounds__(kBlock) void k_gemv_epilogue(GemvEpiArgs p) {
                               "+s"(a0[1]), "+s"(a1[1]), "+s"(outs[1]), "+s"(ms[1]), "+s"(metas[1]), "+s"(inds[1]),
                               "+s"(a0[2]), "+s"(a1[2]), "+s"(outs[2]), "+s"(ms[2]), "+s"(metas[2]), "+s"(inds[2]));
         }
-        mine = lane < 2 * RB && j0 + (lane & 1) < n;
-        idx = mine ? (unsigned)(lane >> 1) * (unsigned)n + (unsigned)(j0 + (lane & 1)) : 0u;
+        const int e = sums_index<R * RB>(lane);
+        mine = lane < sums_lanes(R * RB) && e < R * RB && j0 + e % R < n;
+        idx = mine ? (unsigned)(e / R) * (unsigned)n + (unsigned)(j0 + e % R) : 0u;
         const unsigned total = (unsigned)RB * (unsigned)n;
         bool f0[P], f1[P], s0[P], s1[P];
         unsigned any = 0;
@@ -1149,17 +1252,11 @@ __global__ __launch_bounds__(kBlock) void k_gemv_epilogue(GemvEpiArgs p) {
             }
         }
     };
-    float sums[2][RB];
-    if (__builtin_expect(aligned_to(W, 16) && aligned_to(h, 16) && (!PRO || aligned_to(gain, 16)), 1))
-        gemv_sums_shared<bf16_t, 2, RB, true, true, PRO>(W, h, n, j0, lane, tid, hs, fetch, sums, gain, eps, hstore, part);
-    else
-        gemv_sums_shared<bf16_t, 2, RB, false, true, PRO>(W, h, n, j0, lane, tid, hs, fetch, sums, gain, eps, hstore, part);
-    float v = sums[0][0];
-#pragma unroll
-    for (int rr = 0; rr < RB; rr++)
-#pragma unroll
-        for (int r = 0; r < 2; r++)
-            if (lane == rr * 2 + r) v = sums[r][rr];
+    float sums[R * RB];
+    gemv_rows_sums<R, RB, U, EXACT, PRO>(W, h, n, cols, j0, lane, tid, hs, fetch, sums, gain, eps, hstore, part);
+    float v;
+    if constexpr (R * RB == 1) v = wave_sum(sums[0]);
+    else v = wave_sums<R * RB>(sums, lane);
     unsigned bits = f32_to_bf16(v);
     // The epilogue's operands have been on their way since before the weights were used; claim them all now,
     // before the first store of the tail.  Loads and stores complete in one queue, in order, so a wait for
@@ -1303,17 +1400,62 @@ const void* gemm_narrow_by_ind(int ind) {
     }
 }
 
+// k_gemv_rows: up to 4 rows of h, rows of 8 to 8192 columns (all of a wave's loads are in registers at once);
+// two weight rows per wave once half the waves fill the chip, and only then rows beyond 2048 columns.
+constexpr int kRowsTwoFrom = 1024;
+bool rows_served(long long rows, long long n, long long cols) {
+    return rows >= 1 && rows <= 4 && n >= 1 && cols >= 8 && cols <= (n >= kRowsTwoFrom ? 8192 : 2048);
+}
+template <bool PRO, int RB>
+const void* rows_kernel_rb(int n, int cols) {
+    const int u = (cols + 511) / 512;
+    if (n < kRowsTwoFrom) {
+        switch (u) {
+        case 1: return PG_FN(k_gemv_rows<1, RB, 1, false, PRO>);
+        case 2: return PG_FN(k_gemv_rows<1, RB, 2, false, PRO>);
+        case 3: return PG_FN(k_gemv_rows<1, RB, 3, false, PRO>);
+        default: return PG_FN(k_gemv_rows<1, RB, 4, false, PRO>);
+        }
+    }
+    switch (cols) {
+    case 1024: return PG_FN(k_gemv_rows<2, RB, 2, true, PRO>);
+    case 2048: return PG_FN(k_gemv_rows<2, RB, 4, true, PRO>);
+    case 4096: return PG_FN(k_gemv_rows<2, RB, 8, true, PRO>);
+    case 8192: return PG_FN(k_gemv_rows<2, RB, 16, true, PRO>);
+    default: break;
+    }
+    if (u <= 3) return PG_FN(k_gemv_rows<2, RB, 3, false, PRO>);
+    if (u <= 4) return PG_FN(k_gemv_rows<2, RB, 4, false, PRO>);
+    if (u <= 8) return PG_FN(k_gemv_rows<2, RB, 8, false, PRO>);
+    if (u <= 12) return PG_FN(k_gemv_rows<2, RB, 12, false, PRO>);
+    return PG_FN(k_gemv_rows<2, RB, 16, false, PRO>);
+}
+template <bool PRO>
+const void* rows_kernel(int rows, int n, int cols) {
+    switch (rows) {
+    case 1: return rows_kernel_rb<PRO, 1>(n, cols);
+    case 2: return rows_kernel_rb<PRO, 2>(n, cols);
+    case 3: return rows_kernel_rb<PRO, 3>(n, cols);
+    default: return rows_kernel_rb<PRO, 4>(n, cols);
+    }
+}
+
 template <typename T>
 bool plan_gemv_t(int ind, int rows, int n, int cols, Launch* out) {
     constexpr int NV = 16 / (int)sizeof(T);
     if constexpr (sizeof(T) == 2) {
-        // A dense contraction: matrix cores from 5 rows on, and for 3 and 4 rows where the narrow form
-        // applies and the vector form that shares h through LDS does not (measured at 2048 x 2048, us
-        // per launch at 2 / 3 / 4 rows: vector with shared h 3.3 / 3.5 / 3.7, narrow matrix-core form
-        // 3.9 / 4.0 / 4.0, vector with h per wave 3.8 / 4.4 / 4.5).
+        // Three and four rows go to the form that shares h through LDS (at 2048 x 2048, us per launch at 2 / 3 / 4 rows: 3.3 / 3.5 /
+        // 3.7; vector with h per wave 3.8 / 4.4 / 4.5; matrix-core form with 8 columns per workgroup 3.9 / 4.0 / 4.0).
+        if ((rows == 3 || rows == 4) && rows_served(rows, n, cols) && !(n >= 1024 && cols == 64 * kGemvChunk * NV)) {
+            out->fn = rows_kernel<false>(rows, n, cols);
+            out->arg_bytes = sizeof(GemvEpiArgs);
+            out->block = dim3(kBlock);
+            out->grid = dim3(blocks_for(n, (kBlock / 64) * (n >= kRowsTwoFrom ? 2 : 1)));
+            return true;
+        }
+        // A dense contraction: matrix cores from 5 rows on.
         const bool narrow_ok = rows <= 16 && cols <= 32 * 4 * kMmSteps && n >= 16;
-        const bool shared_ok = rows <= 4 && n >= 1024 && cols == 64 * kGemvChunk * NV;
-        if (cols % 8 == 0 && (rows > 4 || (rows >= 3 && narrow_ok && !shared_ok))) {
+        if (cols % 8 == 0 && rows > 4) {
             out->block = dim3(kBlock);
             // row groups of 16-row tiles: enough workgroups to fill the chip twice over at most
             const int ntiles = (rows + 15) / 16;
@@ -1331,9 +1473,8 @@ bool plan_gemv_t(int ind, int rows, int n, int cols, Launch* out) {
                 }
             } else if (narrow_ok) {
                 out->grid = dim3(blocks_for(n, 8));
-                const int nrh = rows <= 4 ? 4 : rows <= 8 ? 8 : 16;
-                out->fn = cols == kSuper ? (nrh == 4 ? gemm_narrow_by_ind<true, 4>(ind) : nrh == 8 ? gemm_narrow_by_ind<true, 8>(ind) : gemm_narrow_by_ind<true, 16>(ind))
-                                         : (nrh == 4 ? gemm_narrow_by_ind<false, 4>(ind) : nrh == 8 ? gemm_narrow_by_ind<false, 8>(ind) : gemm_narrow_by_ind<false, 16>(ind));
+                out->fn = cols == kSuper ? (rows <= 8 ? gemm_narrow_by_ind<true, 8>(ind) : gemm_narrow_by_ind<true, 16>(ind))
+                                         : (rows <= 8 ? gemm_narrow_by_ind<false, 8>(ind) : gemm_narrow_by_ind<false, 16>(ind));
             } else if (cols == kSuper) out->fn = gemm_by_ind<true, true>(ind);
             else if (cols < kSuper) out->fn = gemm_by_ind<false, true>(ind);
             else if (cols % kSuper == 0) out->fn = gemm_by_ind<true, false>(ind);
@@ -1355,44 +1496,33 @@ bool plan_gemv(int dtype, int ind, int rows, int n, int cols, Launch* out) {
 }
 
 bool merge_head(int op, int dtype, const Shape& s, long long* n_out) {
-    if (op != kGemv || dtype != kBF16 || s.cols != 64 * kGemvChunk * 8 || s.rows < 1) return false;
+    if (op != kGemv || dtype != kBF16 || s.rows < 1) return false;
     if (s.rows <= 4) {
-        // exactly the shapes plan_gemv gives to k_gemv_shared<bf16, IND, 2, rows>
-        if (s.n < 1024) return false;
+        if (!rows_served(s.rows, s.n, s.cols)) return false;
     } else {
         // the matrix-core forms plan_gemv picks for rows of 2048 columns: narrow (up to 16 rows), 16 columns per
-        // workgroup, wide (from kMmWideRows rows); element indices are kept in 32 bits
-        if (s.n < 32 || s.rows * s.n > (1ll << 31)) return false;
+        // workgroup, wide (from kMmWideRows rows)
+        if (s.cols != 64 * kGemvChunk * 8 || s.n < 32) return false;
     }
+    if (s.rows * s.n > (1ll << 31)) return false;          // element indices are kept in 32 bits
     *n_out = s.rows * s.n;
     return true;
 }
 
 static_assert(kPrologueMaxRows < kMmWideRows, "a prologue exists only where a workgroup owns one tile of rows");
-const void* gemv_epilogue_kernel(int rows_of_h, bool with_prologue) {
-    if (rows_of_h > 4) {
-        if (with_prologue) {
-            if (rows_of_h <= 8) return reinterpret_cast<const void*>(&k_gemm_mfma_epilogue<0, true>);
-            if (rows_of_h <= 16) return reinterpret_cast<const void*>(&k_gemm_mfma_epilogue<1, true>);
-            if (rows_of_h <= kPrologueMaxRows) return reinterpret_cast<const void*>(&k_gemm_mfma_epilogue<2, true>);
-            return nullptr;
-        }
-        if (rows_of_h <= 8) return reinterpret_cast<const void*>(&k_gemm_mfma_epilogue<0>);
-        if (rows_of_h <= 16) return reinterpret_cast<const void*>(&k_gemm_mfma_epilogue<1>);
-        if (rows_of_h < kMmWideRows) return reinterpret_cast<const void*>(&k_gemm_mfma_epilogue<2>);
-        return reinterpret_cast<const void*>(&k_gemm_mfma_epilogue<3>);
+const void* gemv_epilogue_kernel(const Shape& s, bool with_prologue) {
+    const int rows = (int)s.rows;
+    if (rows <= 4) return with_prologue ? rows_kernel<true>(rows, (int)s.n, (int)s.cols) : rows_kernel<false>(rows, (int)s.n, (int)s.cols);
+    if (with_prologue) {
+        if (rows <= 8) return PG_FN(k_gemm_mfma_epilogue<0, true>);
+        if (rows <= 16) return PG_FN(k_gemm_mfma_epilogue<1, true>);
+        if (rows <= kPrologueMaxRows) return PG_FN(k_gemm_mfma_epilogue<2, true>);
+        return nullptr;
     }
-    switch (rows_of_h * 2 + (with_prologue ? 1 : 0)) {
-    case 2: return reinterpret_cast<const void*>(&k_gemv_epilogue<1, false>);
-    case 3: return reinterpret_cast<const void*>(&k_gemv_epilogue<1, true>);
-    case 4: return reinterpret_cast<const void*>(&k_gemv_epilogue<2, false>);
-    case 5: return reinterpret_cast<const void*>(&k_gemv_epilogue<2, true>);
-    case 6: return reinterpret_cast<const void*>(&k_gemv_epilogue<3, false>);
-    case 7: return reinterpret_cast<const void*>(&k_gemv_epilogue<3, true>);
-    case 8: return reinterpret_cast<const void*>(&k_gemv_epilogue<4, false>);
-    case 9: return reinterpret_cast<const void*>(&k_gemv_epilogue<4, true>);
-    default: return nullptr;
-    }
+    if (rows <= 8) return PG_FN(k_gemm_mfma_epilogue<0>);
+    if (rows <= 16) return PG_FN(k_gemm_mfma_epilogue<1>);
+    if (rows < kMmWideRows) return PG_FN(k_gemm_mfma_epilogue<2>);
+    return PG_FN(k_gemm_mfma_epilogue<3>);
 }
 
 }  // namespace pgk

@@ -163,15 +163,15 @@ bool merge_candidate(int op, int dtype, const Shape& shape, bool whole_vectors, 
 constexpr long long kMergeNarrowMax = 16384;        // elements
 bool merge_narrow(int dtype, long long n);
 const void* merged_kernel(int dtype, bool narrow);
-// Is this a GEMV shape an epilogue form exists for?  bf16, rows of 2048 columns: up to 4 rows of h (the
-// shape k_gemv_shared<bf16, ., 2, rows> serves; n >= 1024), or 5 rows and more (the matrix-core forms
-// plan() picks for such rows; n >= 32).  *n_out = rows * n.
+// Is this a GEMV shape an epilogue form exists for?  bf16: up to 4 rows of h of 8 to 8192 columns (k_gemv_rows;
+// beyond 2048 columns only for n >= 1024), or 5 rows and more of 2048 columns (the matrix-core forms plan() picks
+// for such rows; n >= 32).  *n_out = rows * n.
 bool merge_head(int op, int dtype, const Shape& shape, long long* n_out);
-// The epilogue form for that many rows of h; launched with the grid and row groups plan() gives the plain
-// GEMV of the same shape.  A prologue exists up to kPrologueMaxRows rows (null otherwise).
+// The epilogue form for a GEMV of that shape; launched with the grid and row groups plan() gives the plain GEMV of
+// the same shape.  A prologue exists up to kPrologueMaxRows rows (null otherwise).
 // Up to two tiles of 16 rows, one per workgroup, fill the 256 CUs once; beyond, two workgroups share a CU and each
 // normalises its tile, which costs more than the dispatch it saves (decode chain at 48 rows: 1261 -> 1336 us).
 constexpr int kPrologueMaxRows = 32;
-const void* gemv_epilogue_kernel(int rows_of_h, bool with_prologue);
+const void* gemv_epilogue_kernel(const Shape& shape, bool with_prologue);
 
 }  // namespace pgk

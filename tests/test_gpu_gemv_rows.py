@@ -1,0 +1,31 @@
+"""GEMV dispatches with prologue and epilogue at one to four rows of any width: around every edge of the
+kernel's forms (rows that end inside a vector, inside a chunk of 2048 columns, on it; one and two weight rows
+per wave; one to four chunks), graphs equal eager bit for bit and every kernel matches the oracle."""
+import pytest
+
+from gpu_util import Harness, same_bits, say, stepwise_check
+from pg_workloads import decode_chain
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,hidden", [(r, h) for h in (7, 8, 9, 61, 520, 1023, 1024, 1030, 2047, 2049, 2056, 4091, 4096) for r in (1, 2, 3, 4)] +
+                         [(r, h) for h in (6142, 6151, 8191, 8192, 8200) for r in (1, 4)])
+def test_rows_of_any_width(rows, hidden):
+    spec = decode_chain(batch=rows, layers=3, blocks_per_layer=1, hidden=hidden, n_ext=3)
+    h = Harness(spec, capture=False)
+    merged, unmerged = h.chain.graph_dispatches()
+    say(f"{spec.name}: {unmerged} kernels in {merged} dispatches")
+    # sub-block 0 reads an external, the other two rename the stream: one dispatch each
+    assert merged == 3 if 8 <= hidden <= 8192 else merged > 3
+    h.chain.capture(h.stream)
+    for t in range(2):
+        x_np, x_dev = h.inputs(t)
+        outs = {}
+        for mode in ("eager", "copy", "indirect"):
+            h.scrub()
+            outs[mode] = h.run(mode, x_dev)[0]
+        assert same_bits(outs["eager"], outs["copy"]) and same_bits(outs["eager"], outs["indirect"]), t
+    h.scrub()
+    stepwise_check(h, x_np, x_dev, rtol=2.0 ** -7)      # one bf16 ulp, every kernel
+    h.close()
