@@ -88,12 +88,13 @@ struct MergeGroup {
     bool head = false;               // the run is a GEMV's dispatch: the kernels after the GEMV ride in it as an epilogue
     bool pro = false;                // (head) kernel k0 is the RMSNorm that feeds the GEMV k0 + 1, and rides in front of it as a prologue
     int rename = -1;                 // (pro) internal buffer the RMSNorm reads and the run overwrites: the run writes its other copy
+    bool sbr = false;                // the run is a chain of scale + bias + ReLU kernels
     bool narrow = false;             // (not head) one 4-byte element per lane instead of a 16-byte vector
     long long n = 0;                 // elements every kernel of the run produces
     int gemv() const { return k0 + (pro ? 1 : 0); }
     // per kernel of the run: where its operands come from (a register slot or memory), which slot keeps its
     // output, and whether the output is stored (not if a later kernel of the run overwrites the buffer)
-    static constexpr int kMax = pgk::kMergeMaxPhases > pgk::kEpiMaxPhases + 2 ? pgk::kMergeMaxPhases : pgk::kEpiMaxPhases + 2;
+    static constexpr int kMax = std::max({pgk::kMergeMaxPhases, pgk::kEpiMaxPhases + 2, pgk::kSbrRunMax});
     unsigned char src0[kMax] = {}, src1[kMax] = {}, dst[kMax] = {};
     bool store[kMax] = {};
     pgk::Launch launch;
@@ -299,8 +300,38 @@ pgk::Shape shape_of(const pg_kernel_desc& d) {
 // (capture_segment keeps track) -- allowed when the run rewrites the whole buffer.  At the end of a
 // segment every buffer must be back in its first copy, where the other modes and the caller look for it:
 // a buffer renamed an odd number of times has its last renaming run split back into RMSNorm + GEMV run.
-void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* ints, std::vector<MergeGroup>& out) {
+//
+// A third kind: scale + bias + ReLU kernels that each read, element for element, what the one before wrote (`channels`
+// gives the length of a kernel's scale vector).  Every lane carries its own elements from x to the last output, so a
+// run may overwrite the buffer it reads x from; a scale or bias that is an internal buffer must not be one that the
+// run writes.
+void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* ints, const std::vector<long long>& channels,
+                 std::vector<MergeGroup>& out) {
     out.clear();
+    auto sbr_run_end = [&](int i) {          // one past the last kernel of the run that starts at i
+        const pg_kernel_desc& f = k[i];
+        auto joins = [&](const pg_kernel_desc& d, int at) {
+            return d.op == PG_SCALE_BIAS_RELU && d.dtype == f.dtype && d.n == f.n && d.inner == f.inner && channels[at] == channels[i] &&
+                   pgk::sbr_run_candidate(d.dtype, d.n, d.inner, channels[at]);
+        };
+        if (!joins(f, i)) return i + 1;
+        std::vector<int> tables, written;    // internal buffers that are scales or biases of the run / that it writes
+        auto has = [](const std::vector<int>& v, int x) { return std::find(v.begin(), v.end(), x) != v.end(); };
+        int e = i;
+        for (; e < k1 && e < i + pgk::kSbrRunMax && joins(k[e], e); e++) {
+            const pg_kernel_desc& d = k[e];
+            if (e > i && !(d.in[0].kind == PG_REF_INT && d.in[0].index == k[e - 1].out.index)) break;
+            bool ok = true;
+            for (int j = 1; j < 3; j++)
+                if (d.in[j].kind == PG_REF_INT) {
+                    ok = ok && !has(written, d.in[j].index) && d.in[j].index != d.out.index;
+                    tables.push_back(d.in[j].index);
+                }
+            if (!ok || has(tables, d.out.index)) break;
+            written.push_back(d.out.index);
+        }
+        return std::max(e, i + 1);
+    };
     auto whole = [&](const pg_kernel_desc& d, int j, long long n) {   // operand j is read element for element over all n
         if (d.op == PG_ADD || d.op == PG_MUL) return j == 0 || (d.m ? d.m : d.n) == n;
         return j == 0;                                                  // GELU a, RMSNORM x
@@ -322,6 +353,19 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
         MergeGroup g;
         g.k0 = i;
         long long n = 0;
+        if (const int e = sbr_run_end(i); e - i >= 2) {
+            g.sbr = true;
+            g.n = k[i].n;
+            g.k1 = e;
+            for (int a = i; a < e; a++) {
+                bool& st = g.store[a - i];
+                st = true;
+                for (int t = a + 1; t < e; t++) if (k[t].out.index == k[a].out.index) st = false;
+            }
+            out.push_back(g);
+            i = e;
+            continue;
+        }
         const bool pro = prologue_at(i);
         const int hk = i + (pro ? 1 : 0);
         const bool head = pro || pgk::merge_head(k[i].op, k[i].dtype, shape_of(k[i]), &n);
@@ -479,7 +523,14 @@ void build_copy_list(CopyList& L, const pg_tensor_desc* ext, const std::vector<s
 // Lay out the workspace.  ws may be null (size query).  eager_only: the chain will never be captured
 // or replayed, so it gets internal buffers only -- no placeholders, pointer table or copy job lists.
 void make_layout(const pg_kernel_desc* k, int nk, const pg_tensor_desc* ext, int n_ext,
-                 const pg_tensor_desc* ints, int n_int, char* ws, Layout& L, bool eager_only = false) {
+                 const pg_tensor_desc* ints, int n_int, const pg_tensor_desc* w, char* ws, Layout& L, bool eager_only = false) {
+    // channels of each scale + bias + ReLU kernel; 0 (no runs of them are planned: they take no room) without the weights
+    std::vector<long long> channels(nk, 0);
+    for (int i = 0; w && i < nk; i++) {
+        const pg_ref& r = k[i].in[1];
+        if (k[i].op == PG_SCALE_BIAS_RELU)
+            channels[i] = r.kind == PG_REF_EXT ? ext[r.index].numel : r.kind == PG_REF_INT ? ints[r.index].numel : w[r.index].numel;
+    }
     size_t off = 0;
     L.ph_off.assign(n_ext, 0);
     if (!eager_only)
@@ -515,7 +566,7 @@ void make_layout(const pg_kernel_desc* k, int nk, const pg_tensor_desc* ext, int
     if (eager_only) { L.lists.clear(); L.total = off; return; }
     L.shadow_off.assign(n_int, kNoShadow);
     for (auto& sg : L.seg) {
-        plan_groups(k, sg.k0, sg.k1, ints, sg.groups);
+        plan_groups(k, sg.k0, sg.k1, ints, channels, sg.groups);
         for (const auto& g : sg.groups)
             if (g.rename >= 0 && L.shadow_off[g.rename] == kNoShadow) {
                 L.shadow_off[g.rename] = off;
@@ -589,7 +640,9 @@ pg_status make_records(pg_chain* c) {
             if (g.k1 - g.k0 < 2) continue;
             g.launch = pgk::Launch();
             g.launch.block = dim3(256);
-            if (g.head) {
+            if (g.sbr) {
+                if (!pgk::plan_sbr_run(c->k[g.k0].dtype, g.n, c->k[g.k0].inner, &g.launch)) return fail(PG_EINVAL, "kernel %d: no kernel for this run", g.k0);
+            } else if (g.head) {
                 g.launch.fn = pgk::gemv_epilogue_kernel(shape_of(c->k[g.gemv()]), g.pro);
                 g.launch.arg_bytes = sizeof(pgk::GemvEpiArgs);
                 g.launch.grid = c->rec[g.gemv()].direct.grid;               // the GEMV's own launch shape: same workgroups, same lanes
@@ -842,6 +895,26 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             }
             continue;
         }
+        if (grp.sbr) {
+            pgk::SbrRunArgs m;
+            memset(&m, 0, sizeof m);
+            for (int i = grp.k0; i < grp.k1; i++, m.n_phase++) {
+                KernelRec& r = c->rec[i];
+                const ArgBlock a = versioned(i, nullptr);
+                pgk::SbrRunPhase& ph = m.ph[m.n_phase];
+                if (i == grp.k0) {
+                    m.x = a.ptr[1];
+                    m.n = (unsigned)a.sbr.n; m.inner = a.sbr.inner; m.channels = a.sbr.channels;
+                    m.x_slot = kind == kGraphCopy ? 0u : (unsigned)r.ind_mask & 1u;
+                }
+                ph.out = const_cast<void*>(a.ptr[0]);
+                ph.s = a.ptr[2];
+                ph.b = a.ptr[3];
+                ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (grp.store[m.n_phase] ? pgk::kEpiStore : 0u);
+            }
+            le = launch(grp.launch, &m, s);
+            continue;
+        }
         if (grp.head) {
             // the GEMV's dispatch with the following elementwise kernels as its epilogue (and the RMSNorm before it as its prologue)
             pgk::GemvEpiArgs e;
@@ -1022,7 +1095,8 @@ pg_status build_chain(const pg_kernel_desc* kernels, int32_t nk, const pg_tensor
     c->ws = static_cast<char*>(workspace_dev);
     c->ws_bytes = workspace_bytes;
     Layout L;
-    make_layout(c->k.data(), nk, c->ext.data(), n_ext, c->ints.data(), n_int, c->ws, L, eager_only);
+    const pg_tensor_desc no_weights{};
+    make_layout(c->k.data(), nk, c->ext.data(), n_ext, c->ints.data(), n_int, c->w.empty() ? &no_weights : c->w.data(), c->ws, L, eager_only);
     c->ws_need = L.total;
     if (workspace_bytes < L.total) {
         delete c;
@@ -1098,7 +1172,7 @@ pg_status pg_chain_workspace_bytes(const pg_kernel_desc* kernels, int32_t nk, co
     for (int i = 0; i < n_ext; i++) if (ext[i].numel <= 0 || ext[i].numel > (1ll << 40) || (ext[i].dtype != PG_F32 && ext[i].dtype != PG_BF16)) return fail(PG_EINVAL, "ext %d: bad descriptor", i);
     for (int i = 0; i < n_int; i++) if (ints[i].numel <= 0 || ints[i].numel > (1ll << 40) || (ints[i].dtype != PG_F32 && ints[i].dtype != PG_BF16)) return fail(PG_EINVAL, "int %d: bad descriptor", i);
     Layout L;
-    make_layout(kernels, nk, ext, n_ext, ints, n_int, nullptr, L);
+    make_layout(kernels, nk, ext, n_ext, ints, n_int, nullptr, nullptr, L);
     *bytes_out = L.total;
     return PG_OK;
 }

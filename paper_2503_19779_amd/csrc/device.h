@@ -158,6 +158,8 @@ __device__ __forceinline__ void store_vec_global(void* p, const unsigned* w) {
     t.x = w[0]; t.y = w[1]; t.z = w[2]; t.w = w[3];
     *(v4u PG_GLOBAL*)(uintptr_t)p = t;
 }
+// 16 bytes at any element boundary: one load or store instruction all the same
+typedef v4u v4u_any __attribute__((aligned(2)));
 // A pointer-table slot, or the tensor address itself: decided at run time (the merged kernels; the
 // stand-alone ones decide at compile time, resolve<IND>).  The slot is read as constant memory -- nothing
 // writes the table while a graph runs -- which makes it a scalar load that no vector-memory wait covers.

@@ -965,7 +965,6 @@ __global__ __launch_bounds__(kBlock, (FORM == 3 || PRO) ? 1 : 2) void k_gemm_mfm
 // -- asking for the epilogue's operands first, so that they would be back before the weights, measured 0.17 us
 // slower per launch); sums[rr * R + r] receives the lane's part of the dot products.
 // (eps by reference: the kernel reads it from its arguments inside the hook.)
-typedef v4u v4u_any __attribute__((aligned(2)));      // 16 bytes at any element boundary: one load or store instruction all the same
 template <bool NT>
 __device__ __forceinline__ void load_any(const bf16_t* base /* uniform */, unsigned elem, unsigned* w) {
     const v4u_any PG_GLOBAL* q = (const v4u_any PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)base + elem);

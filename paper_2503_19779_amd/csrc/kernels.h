@@ -131,6 +131,29 @@ struct GemvEpiArgs {
     MergePhase ph[kEpiMaxPhases];   // m: period of in1 (rows * n = element for element)
 };
 
+// A run of consecutive per-channel scale + bias + ReLU kernels over one tensor (each reads what the one before it
+// wrote, element for element; same length, same channels): one dispatch that reads x once and keeps the elements in
+// registers from kernel to kernel.  Outputs that a later kernel of the run overwrites are not stored.
+constexpr int kSbrRunMax = 16;              // kernels per run
+constexpr int kSbrRunMaxChannels = 128;     // one lane per scale and per bias of a kernel when the run's tables are loaded
+struct SbrRunPhase {
+    void* out;
+    const void* s;
+    const void* b;
+    unsigned ind;           // bit 1 / 2: s / b hold the address of a pointer-table slot; kEpiStore
+    unsigned reserved;
+};
+struct SbrRunArgs {
+    const void* x;
+    unsigned n;
+    unsigned inner;
+    unsigned channels;
+    unsigned x_slot;        // x holds the address of a pointer-table slot
+    int n_phase;
+    int reserved;
+    SbrRunPhase ph[kSbrRunMax];
+};
+
 struct Launch {
     const void* fn = nullptr;        // host-side kernel handle
     hipFunction_t mod_fn = nullptr;  // the same kernel as a module function, resolved on first launch
@@ -163,6 +186,10 @@ bool merge_candidate(int op, int dtype, const Shape& shape, bool whole_vectors, 
 constexpr long long kMergeNarrowMax = 16384;        // elements
 bool merge_narrow(int dtype, long long n);
 const void* merged_kernel(int dtype, bool narrow);
+// Can this scale + bias + ReLU kernel be part of a run of such kernels?  A 16-byte vector may touch two channels at
+// most, the tables of all channels fit the run's LDS, and element indices fit 32 bits.
+bool sbr_run_candidate(int dtype, long long n, long long inner, long long channels);
+bool plan_sbr_run(int dtype, long long n, long long inner, Launch* out);
 // Is this a GEMV shape an epilogue form exists for?  bf16: up to 4 rows of h of 8 to 8192 columns (k_gemv_rows;
 // beyond 2048 columns only for n >= 1024), or 5 rows and more of 2048 columns (the matrix-core forms plan() picks
 // for such rows; n >= 32).  *n_out = rows * n.
