@@ -341,7 +341,7 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
         if (!(k[i].op == PG_RMSNORM && k[i].dtype == PG_BF16 && i + 1 < k1 && k[i].rows >= 1 && k[i].rows <= pgk::kPrologueMaxRows)) return false;
         const pg_kernel_desc& v = k[i + 1];
         long long nv = 0;
-        if (!(pgk::merge_head(v.op, v.dtype, shape_of(v), &nv) && k[i].cols == v.cols && k[i].rows == v.rows &&
+        if (!(pgk::merge_head(v.op, v.dtype, shape_of(v), &nv) && pgk::merge_prologue(shape_of(v)) && k[i].cols == v.cols && k[i].rows == v.rows &&
               v.in[1].kind == PG_REF_INT && v.in[1].index == k[i].out.index &&
               !(v.in[0].kind == PG_REF_INT && v.in[0].index == k[i].out.index))) return false;
         // the GEMV itself may overwrite x: renamed like an epilogue kernel's write, if it covers the buffer
@@ -594,6 +594,41 @@ const void* operand_ptr(const pg_chain* c, const pg_ref& r, int mode /*0 eager,1
     }
 }
 
+// The flags and stand-in operands that spare the device the reading of the table (kernels.h).  Once per argument block.
+void seal_epilogue(pgk::GemvEpiArgs& e) {
+    const unsigned total = (unsigned)e.g.rows * (unsigned)e.g.n;
+    bool mem0[pgk::kEpiMaxPhases], mem1[pgk::kEpiMaxPhases];
+    for (int i = 0; i < pgk::kEpiMaxPhases; i++) {
+        pgk::MergePhase& ph = e.ph[i];
+        const bool used = i < e.n_epi;
+        mem0[i] = used && ((ph.meta >> 8) & 0xffu) == pgk::kMergeFromMemory;
+        mem1[i] = used && (ph.meta & 0xffu) != (unsigned)pgk::kGelu && ((ph.meta >> 16) & 0xffu) == pgk::kMergeFromMemory;
+        if (!mem0[i]) { ph.in0 = e.g.out; ph.ind &= ~1u; }
+        if (!mem1[i]) { ph.in1 = e.g.out; ph.ind &= ~2u; ph.m = total; }
+    }
+    auto adds = [&](int i, unsigned q) {         // kernel i is an add of what slot q holds and an operand from memory
+        const unsigned mt = e.ph[i].meta, a = (mt >> 8) & 0xffu, b = (mt >> 16) & 0xffu;
+        return (mt & 0xffu) == (unsigned)pgk::kAdd && ((a == q && mem1[i]) || (mem0[i] && b == q));
+    };
+    const unsigned m0 = e.ph[0].meta;
+    if ((e.n_epi == 2 || e.n_epi == 3) && (m0 & 0xffu) == (unsigned)pgk::kGelu && ((m0 >> 8) & 0xffu) == ((e.head >> 8) & 0xffu) &&
+        adds(1, m0 >> 24) && (e.n_epi == 2 || adds(2, e.ph[1].meta >> 24))) {
+        e.head |= pgk::kEpiDecoder;
+        for (int i = 1; i < e.n_epi; i++)
+            if (mem0[i]) {
+                pgk::MergePhase& ph = e.ph[i];
+                std::swap(ph.in0, ph.in1);
+                ph.ind = (ph.ind & ~3u) | ((ph.ind & 1u) << 1) | pgk::kEpiMemFirst;
+            }
+    }
+    bool plain = true;
+    for (const auto& ph : e.ph) {
+        plain = plain && ph.m == total;
+        if (ph.ind & 3u) e.head |= pgk::kEpiAnySlot;
+    }
+    if (plain) e.head |= pgk::kEpiPlain;
+}
+
 pg_status make_records(pg_chain* c) {
     const int nk = (int)c->k.size();
     c->rec.assign(nk, KernelRec());
@@ -633,7 +668,7 @@ pg_status make_records(pg_chain* c) {
         if (r.direct.grid.x != r.indirect.grid.x || r.direct.block.x != r.indirect.block.x)
             return fail(PG_EINVAL, "kernel %d: direct and indirect forms disagree on the launch shape", i);
         if (d.op == PG_GEMV)
-            for (ArgBlock* a : {&r.a_eager, &r.a_copy, &r.a_ind}) a->gemv.row_groups = (int)r.direct.gemm_row_groups;
+            for (ArgBlock* a : {&r.a_eager, &r.a_copy, &r.a_ind}) { a->gemv.row_groups = (int)r.direct.gemm_row_groups; seal_epilogue(a->epi); }
     }
     for (auto& sg : c->seg)
         for (auto& g : sg.groups) {
@@ -643,10 +678,7 @@ pg_status make_records(pg_chain* c) {
             if (g.sbr) {
                 if (!pgk::plan_sbr_run(c->k[g.k0].dtype, g.n, c->k[g.k0].inner, &g.launch)) return fail(PG_EINVAL, "kernel %d: no kernel for this run", g.k0);
             } else if (g.head) {
-                g.launch.fn = pgk::gemv_epilogue_kernel(shape_of(c->k[g.gemv()]), g.pro);
-                g.launch.arg_bytes = sizeof(pgk::GemvEpiArgs);
-                g.launch.grid = c->rec[g.gemv()].direct.grid;               // the GEMV's own launch shape: same workgroups, same lanes
-                if (c->rec[g.gemv()].direct.block.x != 256) return fail(PG_EINVAL, "kernel %d: unexpected GEMV launch shape", g.gemv());
+                pgk::plan_gemv_epilogue(shape_of(c->k[g.gemv()]), g.pro, &g.launch);
             } else {
                 g.launch.fn = pgk::merged_kernel(c->k[g.k0].dtype, g.narrow);
                 g.launch.arg_bytes = sizeof(pgk::MergedArgs);
@@ -923,6 +955,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             KernelRec& hr = c->rec[hk];
             const ArgBlock ha = versioned(hk, &grp);
             e.g = ha.gemv;
+            e.g.row_groups = (int)grp.launch.gemm_row_groups;
             e.head = (kind == kGraphCopy ? 0u : (unsigned)hr.ind_mask) | ((unsigned)grp.dst[hk - grp.k0] << 8) |
                      (grp.store[hk - grp.k0] ? pgk::kEpiHeadStore : 0u);
             if (grp.pro) {
@@ -949,6 +982,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
                 ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (grp.store[t] ? pgk::kEpiStore : 0u);
             }
             for (int q = e.n_epi; q < pgk::kEpiMaxPhases; q++) e.ph[q].meta = (unsigned)PG_GELU;   // operands "from slot 0": fetches nothing, never played
+            seal_epilogue(e);
             le = launch(grp.launch, &e, s);
             if (grp.rename >= 0) second[grp.rename] ^= 1;
             continue;

@@ -226,745 +226,29 @@ __global__ __launch_bounds__(kBlock) void k_gemv_batched(GemvArgs p) {
     else gemvb_body<T, R, RB, RS, false>(W, h, y, p.rows, p.n, p.cols, j0, lane);
 }
 
-// Batched bf16 with whole 16-byte vectors per row: y[rows, n] = h[rows, cols] * W[n, cols]^T is a
-// dense contraction once rows > 1, so it goes to the matrix cores (v_mfma_f32_16x16x32_bf16, fp32
-// accumulate).  Still weight-streaming bound up to rows ~ 128: every weight is read once from HBM.
-//   - a workgroup owns 16 output columns and one group of 16-row tiles of h; the grid is
-//     (column blocks) x (row groups), column block fastest, so that the row groups of one column
-//     block land on the same XCD (workgroups go to the 8 XCDs round-robin) and all but the first find
-//     the weights in its L2;
-//   - its 4 waves split K: of every 8 consecutive 32-wide K-steps wave w takes steps 2w and 2w+1 (128
-//     contiguous bytes of each row), 16 steps per 2048 columns;
-//   - a fragment (A: lane l holds row l & 15, B: column l & 15; the 8 consecutive k's of chunk l >> 4
-//     of a step) read straight from global memory would touch 16 rows x 64 bytes per instruction, all
-//     4 KB apart: half cache lines, one cache channel (measured: 0.3 - 1.1 us slower per launch).
-//     Instead each wave loads its own K-slices of 16 rows -- a tile of h, or the weights of the 16
-//     columns -- row by row (one row = 8 x 128 contiguous bytes per instruction) and transposes them
-//     through its private slice of LDS into fragment order.  The weight fragments stay in registers
-//     when cols <= 2048 (SINGLE) and are re-read per tile (from cache) otherwise; the next tile's rows
-//     of h are in flight while the matrix cores work on this one.  LDS slot (lane of the load) holds 16 rows x 16 bytes and is padded to 272
-//     bytes so that 16 consecutive lanes hit all banks.  74 KB of LDS per workgroup: two fit a CU, and
-//     one's staging overlaps the other's multiplies;
-//   - rows beyond the batch re-read the last row and are never stored;
-//   - per tile the 4 waves' partial sums meet in LDS and are added in a fixed order; lane l of a tile
-//     holds column (l & 15), rows 4 * (l >> 4) .. + 3.
+// Workgroups go to the 8 XCDs in turn, each with an L2 of its own.  The index of the work that workgroup b of `total` takes,
+// such that an XCD takes a contiguous stretch of it.
+__device__ __forceinline__ unsigned xcd_stretch(unsigned b, unsigned total) {
+    const unsigned x = b & 7u, q = total >> 3, r = total & 7u;
+    return x * q + (x < r ? x : r) + (b >> 3);
+}
+
+// ---- five rows of h and more: the matrix cores ----------------------------------------------------------
+// bf16, v_mfma_f32_16x16x32_bf16 with fp32 accumulation.  A GEMV's output has the same bits whichever launch of it
+// computes it (eager, merged, with a prologue): k_gemm_rows and k_gemm_cols cut K into blocks of 64; wave w of the
+// workgroup's four takes blocks w, w + 4, ... in order, two K-steps of 32 each; the four partial sums are added as
+// ((p0 + p1) + p2) + p3.  k_gemm_tile deals the blocks out to eight parts instead.  (Fragments -- A: lane l holds row l & 15, B: column l & 15;
+// the eight consecutive k's of chunk l >> 4 of a step; accumulators: lane l holds column l & 15, rows 4 * (l >> 4) .. + 3.)
+// Elements beyond a row's end are zeros on both sides: zeroing the weight side alone would turn an Inf or NaN of h
+// into NaN in every output (0 * Inf).  Rows beyond the batch and columns beyond n repeat the last one and are never
+// stored.
+//   - k_gemm_rows: one tile of 8 or 16 rows of h per workgroup, up to 2048 columns, all loads in flight at once; the
+//     form that can carry the RMSNorm in front;
+//   - k_gemm_cols: 17 to 80 rows of up to 2048 columns;
+//   - k_gemm_tile: everything else, K streamed through a ring in LDS.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-constexpr int kMmSteps = 16;        // K-steps per wave per super-chunk (4 waves x 16 steps x 32 = 2048 columns)
-constexpr int kMmSlotBytes = 272;   // 16 rows x 16 B + 16 B of padding
-constexpr int kMmWaveLds = 64 * kMmSlotBytes;   // one wave's staging area: one tile, 64 slots
-constexpr int kMmMaxRowGroups = 4;
-constexpr int kMmWideRows = 81;     // rows from which the 32-column form is used (measured: the 16-column form is faster up to 5 tiles of rows, slower from 6)
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-// k offset of the 16-byte chunk that lane `l` of wave `wave` loads from a row (super-chunk at step s0);
-// the same chunk is fragment step l >> 2, k-chunk l & 3 of that wave.
-__device__ __forceinline__ int mm_k0(int s0, int wave, int l) {
-    return (s0 + (l >> 3) * 8 + wave * 2 + ((l >> 2) & 1)) * 32 + (l & 3) * 8;
-}
-
-// 16 rows of a row-major matrix (a tile of h, or the weights of 16 output columns), this wave's
-// K-slices: one row per instruction; rows beyond the matrix repeat its last row
-template <bool FULL, bool AL, int NR = 16>
-__device__ __forceinline__ void mm_load_rows(const bf16_t* h, int rows, int cols, int r0, int s0, int wave, int lane, unsigned (*g)[4]) {
-    const int k0 = mm_k0(s0, wave, lane);
-    const int koff = (FULL || k0 < cols) ? k0 : 0;      // an out-of-range chunk is read from column 0 and zeroed on both sides later
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-        const int R = r0 + r < rows ? r0 + r : rows - 1;
-        load_vec_global<bf16_t, AL, false>(h + (size_t)R * cols + koff, g[r]);     // global outright: see load_vec_global
-    }
-}
-
-// LDS operations of one wave execute in order: these writes cannot overtake the previous tile's reads
-template <int NR = 16>
-__device__ __forceinline__ void mm_stage(char* lds /* this wave's */, int lane, const unsigned (*g)[4]) {
-#pragma unroll
-    for (int r = 0; r < NR; r++) {
-        v4u t;
-        t.x = g[r][0]; t.y = g[r][1]; t.z = g[r][2]; t.w = g[r][3];
-        *reinterpret_cast<v4u*>(lds + lane * kMmSlotBytes + r * 16) = t;
-    }
-}
-
-// fragment (step i, k-chunk lane >> 4, row or column lane & 15) of the tile staged in `lds`
-__device__ __forceinline__ void mm_read_frags(const char* lds, int lane, v4u* f) {
-#pragma unroll
-    for (int i = 0; i < kMmSteps; i++)
-        f[i] = *reinterpret_cast<const v4u*>(lds + (i * 4 + (lane >> 4)) * kMmSlotBytes + (lane & 15) * 16);
-}
-// chunks beyond cols are zeroed on both sides (the loads fetched column 0 in their place): zeroing the
-// weight side alone would turn an Inf or NaN of h[:, 0:8] into NaN in every output (0 * Inf)
-template <bool FULL>
-__device__ __forceinline__ void mm_zero_tail(v4u* b, int cols, int s0, int wave, int kq) {
-    if constexpr (!FULL) {
-#pragma unroll
-        for (int i = 0; i < kMmSteps; i++)      // cols is a multiple of 8: a chunk is all in or all out
-            if ((s0 + (i >> 1) * 8 + wave * 2 + (i & 1)) * 32 + kq * 8 >= cols) b[i] = v4u{0u, 0u, 0u, 0u};
-    }
-}
-__device__ __forceinline__ void mm_mfma(const v4u* a, const v4u* b, f32x4& acc) {
-#pragma unroll
-    for (int i = 0; i < kMmSteps; i++)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[i]), acc, 0, 0, 0);
-}
-
-// What becomes of a finished tile.  All four waves share the output stage: a lane is given NE consecutive
-// rows of one column -- begin(r, j, ok) before the partial sums are exchanged (or earlier), put(k, v) for
-// each of its sums, end().
-// MmStore: the stand-alone kernels -- each sum is rounded and stored.
-template <int NE>
-struct MmStore {
-    static constexpr bool kEarly = false;
-    bf16_t* y;
-    int rows, n;
-    size_t at = 0;
-    int r = 0;
-    bool col_ok = false;
-    __device__ __forceinline__ void prepare() {}
-    __device__ __forceinline__ void begin(int r_, int j, bool ok) { r = r_; col_ok = ok; at = (size_t)r_ * n + j; }
-    __device__ __forceinline__ void put(int k, float v) { if (col_ok && r + k < rows) store_elem(y + at + (size_t)k * n, v); }
-    __device__ __forceinline__ void end() {}
-};
-// MmEpilogue: the kernels that follow the GEMV in the chain, element for element, ride along (kernels.h,
-// GemvEpiArgs): prepare() reads their table out of the kernel arguments and resolves pointer-table slots --
-// the bodies call it once their weight loads are on their way, as k_gemv_rows does, so that nothing but
-// the first 64 bytes of the arguments stands between the start of the kernel and those loads; begin() asks
-// for the operands, so that they arrive while the tile is staged and multiplied and the partial sums are
-// exchanged; end() plays the kernels on the lane's outputs, rounding to bf16 after each as the stand-alone
-// kernels do, with the GELU as the only branch.
-// EARLY (the narrow forms, whose few loads leave the operands' latency exposed): begin() comes right behind the
-// weight loads and always issues the same number of loads -- an operand that comes from a register slot is
-// fetched from the GEMV's own output buffer instead and ignored -- so that every wait on the rows and weights
-// knows exactly how many younger loads are outstanding.  Otherwise the loads are conditional, which the compiler
-// cannot count (a wait for an older load placed behind them would wait for more than it needs), and begin() comes
-// once the rows and weights of the tile have been taken out of their registers, in front of the multiplies.
-template <int NE, bool EARLY>
-struct MmEpilogue {
-    static constexpr bool kEarly = EARLY;
-    static constexpr int P = kEpiMaxPhases;
-    bf16_t* y;
-    int rows, n;
-    unsigned head;
-    int n_epi;
-    const void PG_CONSTANT* ka;   // the kernel-argument segment (a GemvEpiArgs)
-    float eps = 0.f;              // the prologue's, read with the table
-    const bf16_t* q0[P];        // operand addresses, pointer-table slots resolved; null: comes from a register slot
-    const bf16_t* q1[P];
-    bf16_t* outs[P];
-    unsigned ms[P], metas[P], inds[P];
-    bool plain = true;          // EARLY: no operand has a broadcast period
-    bool decoder = false;       // the kernels are GELU of the GEMV's result, then one or two adds with an operand from memory
-    // per call
-    unsigned idx[NE];
-    bool ok[NE];
-    unsigned ld0[P][NE], ld1[P][NE];
-    float v[NE];
-    __device__ __forceinline__ void prepare() {
-        static_assert(P == 3, "the argument batch names every phase");
-        using SlotPtr = const void* const PG_CONSTANT*;
-        const void* a0[P];
-        const void* a1[P];
-        {   // through the segment's address made opaque: otherwise the compiler moves these loads (invariant
-            // memory) to the top of the kernel, in front of the weight loads
-            const GemvEpiArgs PG_CONSTANT* kp = (const GemvEpiArgs PG_CONSTANT*)ka;
-            asm volatile("" : "+s"(kp));
-            eps = kp->eps;
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                a0[i] = kp->ph[i].in0; a1[i] = kp->ph[i].in1; outs[i] = static_cast<bf16_t*>(kp->ph[i].out);
-                ms[i] = kp->ph[i].m; metas[i] = kp->ph[i].meta; inds[i] = kp->ph[i].ind;
-            }
-            asm volatile("" : "+s"(eps),
-                              "+s"(a0[0]), "+s"(a1[0]), "+s"(outs[0]), "+s"(ms[0]), "+s"(metas[0]), "+s"(inds[0]),
-                              "+s"(a0[1]), "+s"(a1[1]), "+s"(outs[1]), "+s"(ms[1]), "+s"(metas[1]), "+s"(inds[1]),
-                              "+s"(a0[2]), "+s"(a1[2]), "+s"(outs[2]), "+s"(ms[2]), "+s"(metas[2]), "+s"(inds[2]));
-        }
-        bool f0[P], f1[P], s0[P], s1[P];
-        unsigned any = 0;
-#pragma unroll
-        for (int i = 0; i < P; i++) {
-            const unsigned mt = metas[i];
-            f0[i] = ((mt >> 8) & 0xffu) == kMergeFromMemory;
-            f1[i] = (mt & 0xffu) != kGelu && ((mt >> 16) & 0xffu) == kMergeFromMemory;
-            s0[i] = f0[i] && (inds[i] & 1u);
-            s1[i] = f1[i] && (inds[i] & 2u);
-            any |= (f0[i] ? inds[i] & 1u : 0u) | (f1[i] ? inds[i] & 2u : 0u);
-        }
-        any = __builtin_amdgcn_readfirstlane(any);
-        asm volatile("" : "+s"(any));       // keeps what follows behind the weight loads
-        {   // the decoder block's tail, recognised here so that end() runs it straight through (see k_gemv_rows)
-            auto add_of = [](unsigned mt, unsigned q) {
-                const unsigned a = (mt >> 8) & 0xffu, b = (mt >> 16) & 0xffu;
-                return (mt & 0xffu) == (unsigned)kAdd && ((a == q && b == kMergeFromMemory) || (a == kMergeFromMemory && b == q));
-            };
-            const unsigned hq = (head >> 8) & 0xffu, d0 = metas[0] >> 24, d1 = metas[1] >> 24;
-            decoder = (n_epi == 2 || n_epi == 3) && (metas[0] & 0xffu) == (unsigned)kGelu && ((metas[0] >> 8) & 0xffu) == hq &&
-                      add_of(metas[1], d0) && (n_epi == 2 || add_of(metas[2], d1));
-        }
-        if (any) {                           // some operand is a pointer-table slot: all in one batch, without branches
-            auto slot_addr = [&](const void* q, bool is_slot) -> SlotPtr { return is_slot ? (SlotPtr)(uintptr_t)q : (SlotPtr)ka; };
-            SlotPtr at0[P], at1[P];
-            const void* t0[P];
-            const void* t1[P];
-#pragma unroll
-            for (int i = 0; i < P; i++) { at0[i] = slot_addr(a0[i], s0[i]); at1[i] = slot_addr(a1[i], s1[i]); }
-#pragma unroll
-            for (int i = 0; i < P; i++) { t0[i] = *at0[i]; t1[i] = *at1[i]; }
-            asm volatile("" : "+s"(t0[0]), "+s"(t1[0]), "+s"(t0[1]), "+s"(t1[1]), "+s"(t0[2]), "+s"(t1[2]));
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                if (s0[i]) a0[i] = t0[i];
-                if (s1[i]) a1[i] = t1[i];
-            }
-        }
-        if constexpr (EARLY) {
-            const unsigned total = (unsigned)rows * (unsigned)n;
-            plain = true;
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                q0[i] = f0[i] ? static_cast<const bf16_t*>(a0[i]) : y;
-                q1[i] = f1[i] ? static_cast<const bf16_t*>(a1[i]) : y;
-                ms[i] = f1[i] ? ms[i] : total;
-                plain = plain && ms[i] == total;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                q0[i] = f0[i] ? static_cast<const bf16_t*>(a0[i]) : nullptr;
-                q1[i] = f1[i] ? static_cast<const bf16_t*>(a1[i]) : nullptr;
-#pragma unroll
-                for (int k = 0; k < NE; k++) ld0[i][k] = ld1[i][k] = 0u;
-            }
-        }
-    }
-    __device__ __forceinline__ void begin(int r, int j, bool col_ok) {
-        const unsigned total = (unsigned)rows * (unsigned)n;
-#pragma unroll
-        for (int e = 0; e < NE; e++) {
-            ok[e] = col_ok && r + e < rows;
-            idx[e] = ok[e] ? (unsigned)(r + e) * (unsigned)n + (unsigned)j : 0u;
-        }
-        if constexpr (EARLY) {
-            if (__builtin_expect(plain, 1)) {      // the usual case, one branch for all
-#pragma unroll
-                for (int i = 0; i < P; i++)
-#pragma unroll
-                    for (int e = 0; e < NE; e++) {
-                        ld0[i][e] = load_raw_global_at(q0[i], idx[e]);
-                        ld1[i][e] = load_raw_global_at(q1[i], idx[e]);
-                    }
-            } else {
-#pragma unroll
-                for (int i = 0; i < P; i++)
-#pragma unroll
-                    for (int e = 0; e < NE; e++) {
-                        ld0[i][e] = load_raw_global_at(q0[i], idx[e]);
-                        ld1[i][e] = load_raw_global_at(q1[i], idx[e] % ms[i]);
-                    }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                if (i < n_epi && q0[i]) {
-#pragma unroll
-                    for (int e = 0; e < NE; e++) ld0[i][e] = load_raw_global_at(q0[i], idx[e]);
-                }
-                if (i < n_epi && q1[i]) {
-                    const unsigned m = ms[i];
-#pragma unroll
-                    for (int e = 0; e < NE; e++) ld1[i][e] = load_raw_global_at(q1[i], m == total ? idx[e] : idx[e] % m);
-                }
-            }
-        }
-    }
-    __device__ __forceinline__ void put(int e, float sum) { v[e] = sum; }
-    __device__ __forceinline__ void end() {
-        unsigned bits[NE];
-        float slot[kMergeSlots][NE];
-        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): every operand, before the first store (see k_gemv_rows)
-#pragma unroll
-        for (int e = 0; e < NE; e++) {
-            bits[e] = f32_to_bf16(v[e]);
-            if (ok[e] && (head & kEpiHeadStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(y + idx[e]) = (unsigned short)bits[e];
-        }
-        if (__builtin_expect(decoder, 1)) {
-            // the same kernels with the same arithmetic and roundings, operands known: GELU of the GEMV's rounded result,
-            // then each add takes the value before it and its operand from memory, in the order its descriptor names
-            const bool mf1 = ((metas[1] >> 8) & 0xffu) == kMergeFromMemory, mf2 = ((metas[2] >> 8) & 0xffu) == kMergeFromMemory;
-#pragma unroll
-            for (int e = 0; e < NE; e++) {
-                float val = ew_apply<kGelu, false>(from_raw<bf16_t>(bits[e]), 0.f);
-                unsigned b = f32_to_bf16(val);
-                if (ok[e] && (inds[0] & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[0] + idx[e]) = (unsigned short)b;
-                val = from_raw<bf16_t>(b);
-                {
-                    const float fa = mf1 ? from_raw<bf16_t>(ld0[1][e]) : val, fb = mf1 ? val : from_raw<bf16_t>(ld1[1][e]);
-                    b = f32_to_bf16(ew_apply<kAdd, false>(fa, fb));
-                    if (ok[e] && (inds[1] & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[1] + idx[e]) = (unsigned short)b;
-                    val = from_raw<bf16_t>(b);
-                }
-                if (n_epi == 3) {
-                    const float fa = mf2 ? from_raw<bf16_t>(ld0[2][e]) : val, fb = mf2 ? val : from_raw<bf16_t>(ld1[2][e]);
-                    b = f32_to_bf16(ew_apply<kAdd, false>(fa, fb));
-                    if (ok[e] && (inds[2] & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[2] + idx[e]) = (unsigned short)b;
-                }
-            }
-            return;
-        }
-        {
-            const unsigned dst = (head >> 8) & 0xffu;
-#pragma unroll
-            for (int q = 0; q < kMergeSlots; q++)
-#pragma unroll
-                for (int e = 0; e < NE; e++) slot[q][e] = dst == (unsigned)q ? from_raw<bf16_t>(bits[e]) : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < P; i++) {
-            if (i >= n_epi) break;
-            const unsigned mt = metas[i], ind = inds[i];
-            const unsigned op = mt & 0xffu, src0 = (mt >> 8) & 0xffu, src1 = (mt >> 16) & 0xffu, dst = mt >> 24;
-            float fa[NE], fb[NE], fo[NE];
-#pragma unroll
-            for (int e = 0; e < NE; e++) {
-                fa[e] = from_raw<bf16_t>(ld0[i][e]);
-                fb[e] = from_raw<bf16_t>(ld1[i][e]);
-#pragma unroll
-                for (int q = 0; q < kMergeSlots; q++) {
-                    if (src0 == (unsigned)q) fa[e] = slot[q][e];
-                    if (src1 == (unsigned)q) fb[e] = slot[q][e];
-                }
-            }
-            if (op == kGelu) {
-#pragma unroll
-                for (int e = 0; e < NE; e++) fo[e] = ew_apply<kGelu, false>(fa[e], 0.f);
-            } else {
-#pragma unroll
-                for (int e = 0; e < NE; e++) {
-                    const float sum = ew_apply<kAdd, false>(fa[e], fb[e]), prod = ew_apply<kMul, false>(fa[e], fb[e]);
-                    fo[e] = op == kAdd ? sum : prod;
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < NE; e++) {
-                bits[e] = f32_to_bf16(fo[e]);
-                if (ok[e] && (ind & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[i] + idx[e]) = (unsigned short)bits[e];
-#pragma unroll
-                for (int q = 0; q < kMergeSlots; q++)
-                    if (dst == (unsigned)q) slot[q][e] = from_raw<bf16_t>(bits[e]);
-            }
-        }
-    }
-};
-
-// where the output stage of the 16-column forms puts a lane: wave w takes row w of the four that an
-// accumulator lane holds
-template <int NC = 16, class Emit>
-__device__ __forceinline__ void mm_emit_begin(Emit& emit, int n, int r0, int j0, int wave, int lane) {
-    emit.begin(r0 + (lane >> 4) * 4 + wave, j0 + (lane & 15), j0 + (lane & 15) < n && (NC == 16 || (lane & 15) < NC));
-}
-// sum the 4 waves' partial tiles in a fixed order and hand rows r0 .. r0 + 15 of the 16 columns at j0 to `emit`
-// (mm_emit_begin has been called for this tile)
-template <class Emit>
-__device__ __forceinline__ void mm_reduce_store(float* red, f32x4 acc, Emit& emit, int wave, int lane) {
-    // A matrix-core result may not be read by an LDS write until the instruction has drained (up to
-    // 19 wait states for the longest forms).  The compiler inserts those itself inside a block, but
-    // it was seen to omit them when the last multiply of a K loop and this write sit in different
-    // blocks (loop exit): the write then stored a stale accumulator.  32 idle cycles, tied to `acc`
-    // so that they stay between the two, make it independent of that.
-    asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc));
-    float* dst = red + ((size_t)wave * 64 + lane) * 4;
-    dst[0] = acc.x; dst[1] = acc.y; dst[2] = acc.z; dst[3] = acc.w;
-    __syncthreads();
-    {
-        const int e = wave;
-        const float p0 = red[((size_t)0 * 64 + lane) * 4 + e], p1 = red[((size_t)1 * 64 + lane) * 4 + e];
-        const float p2 = red[((size_t)2 * 64 + lane) * 4 + e], p3 = red[((size_t)3 * 64 + lane) * 4 + e];
-        emit.put(0, ((p0 + p1) + p2) + p3);
-    }
-    __syncthreads();      // `red` is free again
-    emit.end();
-}
-
-// mm_rmsnorm_rows is defined with the narrow form below
-template <int NRH>
-__device__ __forceinline__ void mm_rmsnorm_rows(unsigned (*g)[4], const unsigned* wg, float eps, bf16_t* hstore, int rows, int wave, int lane, float* scratch);
-
-// PRO (SINGLE, FULL, one tile of rows per workgroup -- rows < kMmWideRows): h points at the rows to normalise,
-// the workgroups of column block 0 store the normalised rows to hstore (see mm_rmsnorm_rows).
-template <bool FULL, bool SINGLE, bool AL, bool PRO = false, class Emit>
-__device__ __forceinline__ void gemm_mfma_body(const bf16_t* W, const bf16_t* h, Emit& emit, int rows, int n, int cols, int row_groups,
-                                               char* stage /* LDS: 4 x kMmWaveLds */, float* red /* LDS: [4 waves][64 lanes][4] */,
-                                               const bf16_t* gain = nullptr, const float& eps = 0.f /* read by emit.prepare() */, bf16_t* hstore = nullptr) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kq = lane >> 4;
-    const int ncb = (n + 15) / 16;
-    const int cb = blockIdx.x % ncb, rg = blockIdx.x / ncb;
-    const int ntiles = (rows + 15) / 16, per = (ntiles + row_groups - 1) / row_groups;
-    const int t0 = rg * per, t1 = (t0 + per < ntiles) ? t0 + per : ntiles;
-    if (t0 >= t1) return;                                  // whole workgroup: nothing waits on it
-    const int j0 = cb * 16;
-    char* lds = stage + wave * kMmWaveLds;
-    unsigned g[16][4], gw[16][4];
-    v4u a[kMmSteps], b[kMmSteps];
-    if constexpr (SINGLE) {
-        // The h rows (from L2) are asked for before the weights (from HBM): loads return in order, so
-        // the tile is staged and its fragments are back in registers while the weights are still on
-        // their way; then the same LDS slice takes the weights.  The weight fragments stay in registers
-        // for all tiles of the workgroup, and a later tile's rows are in flight across the multiplies
-        // of the one before.
-        mm_load_rows<FULL, AL>(h, rows, cols, t0 * 16, 0, wave, lane, g);
-        unsigned wg[4] = {0u, 0u, 0u, 0u};
-        if constexpr (PRO) load_vec_global<bf16_t, AL, false>(gain + mm_k0(0, wave, lane), wg);   // before the weights: loads come back in order
-        mm_load_rows<FULL, AL>(W, n, cols, j0, 0, wave, lane, gw);
-        emit.prepare();                                      // the epilogue's table right behind the weight loads
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (PRO) {
-            static_assert(FULL && SINGLE, "the prologue exists for rows of 2048 columns");
-            bf16_t* tile_store = (hstore && cb == 0) ? hstore + (size_t)t0 * 16 * (32 * 4 * kMmSteps) : nullptr;
-            mm_rmsnorm_rows<16>(g, wg, eps, tile_store, rows - t0 * 16, wave, lane, reinterpret_cast<float*>(stage));
-            lds_barrier();        // the sums are read: the staging area takes the rows now
-        }
-        mm_stage(lds, lane, g);
-        mm_read_frags(lds, lane, a);
-        mm_zero_tail<FULL>(a, cols, 0, wave, kq);
-        if (t1 - t0 > 1) mm_load_rows<FULL, AL>(h, rows, cols, (t0 + 1) * 16, 0, wave, lane, g);
-        mm_stage(lds, lane, gw);
-        mm_read_frags(lds, lane, b);
-        mm_zero_tail<FULL>(b, cols, 0, wave, kq);
-        __builtin_amdgcn_sched_barrier(0);   // all fragment reads before the first multiply, not one LDS latency per pair
-        mm_emit_begin(emit, n, t0 * 16, j0, wave, lane);
-        mm_mfma(a, b, acc);
-        mm_reduce_store(red, acc, emit, wave, lane);
-#pragma unroll 1
-        for (int t = t0 + 1; t < t1; t++) {
-            acc = f32x4{0.f, 0.f, 0.f, 0.f};
-            mm_stage(lds, lane, g);
-            if (t + 1 < t1) mm_load_rows<FULL, AL>(h, rows, cols, (t + 1) * 16, 0, wave, lane, g);
-            mm_read_frags(lds, lane, a);
-            mm_zero_tail<FULL>(a, cols, 0, wave, kq);
-            __builtin_amdgcn_sched_barrier(0);
-            mm_emit_begin(emit, n, t * 16, j0, wave, lane);
-            mm_mfma(a, b, acc);
-            mm_reduce_store(red, acc, emit, wave, lane);
-        }
-    } else {
-        emit.prepare();
-#pragma unroll 1
-        for (int t = t0; t < t1; t++) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-            for (int s0 = 0; s0 * 32 < cols; s0 += 4 * kMmSteps) {
-                mm_load_rows<FULL, AL>(h, rows, cols, t * 16, s0, wave, lane, g);
-                mm_load_rows<FULL, AL>(W, n, cols, j0, s0, wave, lane, gw);
-                mm_stage(lds, lane, g);
-                mm_read_frags(lds, lane, a);
-                mm_zero_tail<FULL>(a, cols, s0, wave, kq);
-                mm_stage(lds, lane, gw);
-                mm_read_frags(lds, lane, b);
-                mm_zero_tail<FULL>(b, cols, s0, wave, kq);
-                __builtin_amdgcn_sched_barrier(0);
-                mm_mfma(a, b, acc);
-            }
-            mm_emit_begin(emit, n, t * 16, j0, wave, lane);
-            mm_reduce_store(red, acc, emit, wave, lane);
-        }
-    }
-}
-
-// Narrow form for one tile of rows (rows <= 16) and cols <= 2048: 8 output columns per workgroup, so
-// that 2048 columns make 256 workgroups and every CU pulls weights (a loads-only kernel takes in the
-// same bytes 0.35 us faster from 256 CUs than from 128); half of each multiply is idle, which costs
-// nothing here.  Only the 8 weight rows are loaded and staged: fragment columns 8-15 are whatever the
-// slot held before and their results are never stored.  NRH = 8 (4) when rows <= 8 (4): the absent
-// rows of the tile are not loaded either.  With two tiles of rows (8 columns x 2 tiles = 512
-// workgroups, measured) it loses to the 16-column form: 5.7 against 4.9 us at 32 rows.
-// RMSNorm of the rows the narrow form has just loaded, as a prologue (FULL, 2048 columns): lane (wave, l)
-// holds 16-byte chunk c of every row, where c runs over all 256 chunks of a row across the workgroup, but
-// not in lane order.  The stand-alone kernel's sums must be reproduced bit for bit: per chunk the fused
-// sum of squares in element order (any lane can do that); then the stand-alone kernel's reduction, which
-// is a tree of fixed shape over the chunk sums in chunk order -- wave_sum adds neighbours, then pairs of
-// pairs, of quads, of eights (a floating-point add does not care which operand is which), then the four
-// sixteens in order, and the four wave sums in order.  Here the chunk sums go to LDS in chunk order and
-// the workgroup's 16 * NRH subtrees of sixteen leaves are spread over its lanes, one each; lane r < NRH
-// then finishes row r (four sixteens per wave sum, four wave sums) and turns the total into the row's
-// scale; every lane scales its own chunks: (x * scale) * gain, one rounding.  `scratch`: NRH * 336 + NRH
-// floats of LDS that nothing else uses until the rows are staged.  hstore: this workgroup also stores the rows.
-template <int NRH>
-__device__ __forceinline__ void mm_rmsnorm_rows(unsigned (*g)[4], const unsigned* wg /* the lane's chunk of the gain */, float eps, bf16_t* hstore,
-                                                int rows, int wave, int lane, float* scratch) {
-    constexpr int kCols = 32 * 4 * kMmSteps;
-    constexpr int kRow = 256 + 64;             // a row of chunk sums, 8 floats of padding after every 32: the lanes of a wave hold
-                                               // chunks 32 apart, which would otherwise all fall into the same eight banks
-    const int tid = wave * 64 + lane;
-    const int k0 = mm_k0(0, wave, lane);
-    float* sq = scratch;                       // [NRH][kRow]: chunk sums in chunk order
-    float* six = scratch + NRH * kRow;         // [NRH][16]: sums of sixteen chunks
-    float* scale = six + NRH * 16;             // [NRH]
-    auto at = [](int c) { return c + 8 * (c >> 5); };
-    float fx[NRH][8];
-#pragma unroll
-    for (int r = 0; r < NRH; r++) {
-        Vec<bf16_t, 16>::unpack(g[r], fx[r]);
-        float acc = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; e++) acc = __builtin_fmaf(fx[r][e], fx[r][e], acc);
-        sq[r * kRow + at(k0 >> 3)] = acc;
-    }
-    lds_barrier();
-    if (tid < 16 * NRH) {                      // subtree tid: row tid / 16, chunks 16 * (tid % 16) .. + 15
-        const f32x4* leaf = reinterpret_cast<const f32x4*>(sq + (tid >> 4) * kRow + at((tid & 15) * 16));
-        const f32x4 l0 = leaf[0], l1 = leaf[1], l2 = leaf[2], l3 = leaf[3];
-        const float q0 = (l0.x + l0.y) + (l0.z + l0.w), q1 = (l1.x + l1.y) + (l1.z + l1.w);
-        const float q2 = (l2.x + l2.y) + (l2.z + l2.w), q3 = (l3.x + l3.y) + (l3.z + l3.w);
-        six[tid] = (q0 + q1) + (q2 + q3);
-    }
-    lds_barrier();
-    if (tid < NRH) {
-        const f32x4* sx = reinterpret_cast<const f32x4*>(six + tid * 16);
-        float wsum[4];
-#pragma unroll
-        for (int w = 0; w < 4; w++) wsum[w] = ((sx[w].x + sx[w].y) + sx[w].z) + sx[w].w;
-        const float total = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
-        scale[tid] = 1.0f / sqrtf(total / (float)kCols + eps);
-    }
-    lds_barrier();
-    float fg[8];
-    Vec<bf16_t, 16>::unpack(wg, fg);
-#pragma unroll
-    for (int r = 0; r < NRH; r++) {
-        float fo[8];
-        const float sc = scale[r];
-#pragma unroll
-        for (int e = 0; e < 8; e++) fo[e] = (fx[r][e] * sc) * fg[e];
-        Vec<bf16_t, 16>::pack(fo, g[r]);
-    }
-    if (hstore) {
-#pragma unroll
-        for (int r = 0; r < NRH; r++)
-            if (r < rows) store_vec_global(hstore + (size_t)r * kCols + k0, g[r]);
-    }
-}
-
-template <bool FULL, bool AL, int NRH, bool PRO = false, class Emit>
-__device__ __forceinline__ void gemm_mfma_narrow_body(const bf16_t* W, const bf16_t* h, Emit& emit, int rows, int n, int cols,
-                                                      char* stage, float* red, const bf16_t* gain = nullptr, const float& eps = 0.f /* read by emit.prepare() */,
-                                                      bf16_t* hstore = nullptr) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int kq = lane >> 4;
-    const int j0 = blockIdx.x * 8, r0 = 0;
-    char* lds = stage + wave * kMmWaveLds;
-    unsigned g[NRH][4], gw[8][4];
-    v4u a[kMmSteps], b[kMmSteps];
-    mm_load_rows<FULL, AL, NRH>(h, rows, cols, r0, 0, wave, lane, g);      // with a prologue: the rows to normalise
-    unsigned wg[4] = {0u, 0u, 0u, 0u};
-    if constexpr (PRO) load_vec_global<bf16_t, AL, false>(gain + mm_k0(0, wave, lane), wg);   // before the weights: loads come back in order
-    mm_load_rows<FULL, AL, 8>(W, n, cols, j0, 0, wave, lane, gw);
-    emit.prepare();                                          // the epilogue's table right behind the weight loads
-    if constexpr (Emit::kEarly) mm_emit_begin<8>(emit, n, r0, j0, wave, lane);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (PRO) {
-        static_assert(FULL, "the prologue exists for rows of 2048 columns");
-        static_assert((NRH * 336 + NRH) * sizeof(float) <= 4 * kMmWaveLds, "the prologue's sums fit the staging area");
-        mm_rmsnorm_rows<NRH>(g, wg, eps, hstore, rows, wave, lane, reinterpret_cast<float*>(stage));
-        lds_barrier();        // the sums are read: the staging area takes the rows now
-    }
-    mm_stage<NRH>(lds, lane, g);
-    mm_read_frags(lds, lane, a);
-    mm_zero_tail<FULL>(a, cols, 0, wave, kq);
-    mm_stage<8>(lds, lane, gw);
-    mm_read_frags(lds, lane, b);
-    mm_zero_tail<FULL>(b, cols, 0, wave, kq);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!Emit::kEarly) mm_emit_begin<8>(emit, n, r0, j0, wave, lane);
-    mm_mfma(a, b, acc);
-    mm_reduce_store(red, acc, emit, wave, lane);
-}
-
-template <int IND, bool FULL, int NRH>
-__global__ __launch_bounds__(kBlock, 2) void k_gemm_mfma_bf16_narrow(GemvArgs p) {
-    const bf16_t* W = static_cast<const bf16_t*>(resolve<(IND & 1) != 0>(p.W));
-    const bf16_t* h = static_cast<const bf16_t*>(resolve<(IND & 2) != 0>(p.h));
-    bf16_t* y = static_cast<bf16_t*>(p.out);
-    MmStore<1> emit{y, p.rows, p.n};
-    __shared__ __attribute__((aligned(16))) char stage[4 * kMmWaveLds];
-    __shared__ float red[4 * 64 * 4];
-    const bool al = aligned_to(W, 16) && aligned_to(h, 16);
-    if (__builtin_expect(al, 1)) gemm_mfma_narrow_body<FULL, true, NRH>(W, h, emit, p.rows, p.n, p.cols, stage, red);
-    else gemm_mfma_narrow_body<FULL, false, NRH>(W, h, emit, p.rows, p.n, p.cols, stage, red);
-}
-
-// Wide form for many rows and cols == 2048: 32 output columns per workgroup, i.e. two sets of weight
-// fragments and two accumulators against every staged tile of h, which halves the h traffic per
-// output (the bound once there are many rows).  One workgroup per CU (the fragments of 32 columns do not fit
-// the register budget of two), waves 0 and 1 each finish one 16-column half.
-template <bool AL, class Emit>
-__device__ __forceinline__ void gemm_mfma_wide_body(const bf16_t* W, const bf16_t* h, Emit& emit, int rows, int n, int cols, int row_groups,
-                                                    char* stage, float* red /* LDS: [2 halves][4 waves][64 lanes][4] */) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ncb = (n + 31) / 32;
-    const int cb = blockIdx.x % ncb, rg = blockIdx.x / ncb;
-    const int ntiles = (rows + 15) / 16, per = (ntiles + row_groups - 1) / row_groups;
-    const int t0 = rg * per, t1 = (t0 + per < ntiles) ? t0 + per : ntiles;
-    if (t0 >= t1) return;
-    const int j0 = cb * 32;
-    char* lds = stage + wave * kMmWaveLds;
-    unsigned g[16][4], gw0[16][4], gw1[16][4];
-    v4u a[kMmSteps], b0[kMmSteps], b1[kMmSteps];
-    mm_load_rows<true, AL>(h, rows, cols, t0 * 16, 0, wave, lane, g);
-    mm_load_rows<true, AL>(W, n, cols, j0, 0, wave, lane, gw0);
-    mm_load_rows<true, AL>(W, n, cols, j0 + 16, 0, wave, lane, gw1);
-    emit.prepare();      // the epilogue's table right behind the weight loads
-    mm_stage(lds, lane, g);
-    mm_read_frags(lds, lane, a);
-    if (t1 - t0 > 1) mm_load_rows<true, AL>(h, rows, cols, (t0 + 1) * 16, 0, wave, lane, g);
-    mm_stage(lds, lane, gw0);
-    mm_read_frags(lds, lane, b0);
-    mm_stage(lds, lane, gw1);
-    mm_read_frags(lds, lane, b1);
-    for (int t = t0;;) {
-        f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-        __builtin_amdgcn_sched_barrier(0);
-        // output stage: wave w finishes rows 2 * (w >> 1), + 1 of each accumulator lane's four, in 16-column half w & 1
-        emit.begin(t * 16 + (lane >> 4) * 4 + (wave >> 1) * 2, j0 + (wave & 1) * 16 + (lane & 15), j0 + (wave & 1) * 16 + (lane & 15) < n);
-#pragma unroll
-        for (int i = 0; i < kMmSteps; i++) {
-            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b0[i]), acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b1[i]), acc1, 0, 0, 0);
-        }
-        asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc0), "+v"(acc1));   // see mm_reduce_store
-        float* d0 = red + ((size_t)(0 * 4 + wave) * 64 + lane) * 4;
-        float* d1 = red + ((size_t)(1 * 4 + wave) * 64 + lane) * 4;
-        d0[0] = acc0.x; d0[1] = acc0.y; d0[2] = acc0.z; d0[3] = acc0.w;
-        d1[0] = acc1.x; d1[1] = acc1.y; d1[2] = acc1.z; d1[3] = acc1.w;
-        __syncthreads();
-        {
-            const float* src = red + (size_t)(wave & 1) * 4 * 64 * 4;
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                const int e = (wave >> 1) * 2 + k;
-                const float p0 = src[((size_t)0 * 64 + lane) * 4 + e], p1 = src[((size_t)1 * 64 + lane) * 4 + e];
-                const float p2 = src[((size_t)2 * 64 + lane) * 4 + e], p3 = src[((size_t)3 * 64 + lane) * 4 + e];
-                emit.put(k, ((p0 + p1) + p2) + p3);
-            }
-        }
-        __syncthreads();
-        emit.end();
-        if (++t >= t1) break;
-        mm_stage(lds, lane, g);
-        if (t + 1 < t1) mm_load_rows<true, AL>(h, rows, cols, (t + 1) * 16, 0, wave, lane, g);
-        mm_read_frags(lds, lane, a);
-    }
-}
-
-template <int IND>
-__global__ __launch_bounds__(kBlock, 1) void k_gemm_mfma_bf16_wide(GemvArgs p) {
-    const bf16_t* W = static_cast<const bf16_t*>(resolve<(IND & 1) != 0>(p.W));
-    const bf16_t* h = static_cast<const bf16_t*>(resolve<(IND & 2) != 0>(p.h));
-    bf16_t* y = static_cast<bf16_t*>(p.out);
-    MmStore<2> emit{y, p.rows, p.n};
-    __shared__ __attribute__((aligned(16))) char stage[4 * kMmWaveLds];
-    __shared__ float red[2 * 4 * 64 * 4];
-    const bool al = aligned_to(W, 16) && aligned_to(h, 16);
-    if (__builtin_expect(al, 1)) gemm_mfma_wide_body<true>(W, h, emit, p.rows, p.n, p.cols, p.row_groups, stage, red);
-    else gemm_mfma_wide_body<false>(W, h, emit, p.rows, p.n, p.cols, p.row_groups, stage, red);
-}
-
-template <int IND, bool FULL, bool SINGLE>
-__global__ __launch_bounds__(kBlock, 2) void k_gemm_mfma_bf16(GemvArgs p) {
-    const bf16_t* W = static_cast<const bf16_t*>(resolve<(IND & 1) != 0>(p.W));
-    const bf16_t* h = static_cast<const bf16_t*>(resolve<(IND & 2) != 0>(p.h));
-    bf16_t* y = static_cast<bf16_t*>(p.out);
-    MmStore<1> emit{y, p.rows, p.n};
-    __shared__ __attribute__((aligned(16))) char stage[4 * kMmWaveLds];
-    __shared__ float red[4 * 64 * 4];
-    const bool al = aligned_to(W, 16) && aligned_to(h, 16);   // rows keep the alignment: cols is a multiple of 8
-    if (__builtin_expect(al, 1)) gemm_mfma_body<FULL, SINGLE, true>(W, h, emit, p.rows, p.n, p.cols, p.row_groups, stage, red);
-    else gemm_mfma_body<FULL, SINGLE, false>(W, h, emit, p.rows, p.n, p.cols, p.row_groups, stage, red);
-}
-
-// The matrix-core forms with an elementwise epilogue (kernels.h, GemvEpiArgs; no prologue): the same bodies,
-// with MmEpilogue in place of the plain store.  Only for rows of 2048 columns.  FORM 0: narrow, 8 rows of h
-// loaded; 1: narrow, 16; 2: 16 columns per workgroup, one pass over K; 3: wide.
-template <int FORM, bool PRO = false>
-__global__ __launch_bounds__(kBlock, (FORM == 3 || PRO) ? 1 : 2) void k_gemm_mfma_epilogue(GemvEpiArgs p) {
-    static_assert(!PRO || FORM <= 2, "a prologue exists for the forms with one tile of rows per workgroup");
-    // As in k_gemv_rows: the first 64 bytes of the arguments hold everything that is needed before the
-    // loads of h and the weights can go out, and only those are waited for here, in one batch of scalar loads;
-    // the epilogue's table and eps are read once the weights are on their way (MmEpilogue::prepare).
-    static_assert(offsetof(GemvEpiArgs, gain) + sizeof(void*) == 64, "what the kernel needs first sits in the first 64 bytes");
-    const void* Wa = p.g.W;
-    const void* ha = p.g.h;
-    bf16_t* y = static_cast<bf16_t*>(p.g.out);
-    int rows = p.g.rows, n = p.g.n, cols = p.g.cols, row_groups = p.g.row_groups;
-    unsigned head = p.head;
-    int n_epi = p.n_epi;
-    const void* xa = p.x;
-    const void* ga = p.gain;
-    asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(rows), "+s"(n), "+s"(cols), "+s"(row_groups), "+s"(head), "+s"(n_epi), "+s"(xa), "+s"(ga));
-    const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();   // a readable address for a load whose result is not used
-    using SlotPtr = const void* const PG_CONSTANT*;
-    auto slot_addr = [&](const void* q, bool is_slot) -> SlotPtr { return is_slot ? (SlotPtr)(uintptr_t)q : (SlotPtr)ka; };
-    // with a prologue the GEMV's input is computed from x and the gain; p.g.h is where the normalised rows are stored
-    if (head & (1u | (PRO ? kEpiXSlot | kEpiGainSlot : 2u))) {      // some operand is a pointer-table slot: all in one batch, without branches
-        const bool sw = head & 1u, sh = head & (PRO ? kEpiXSlot : 2u), sg = PRO && (head & kEpiGainSlot);
-        SlotPtr aw = slot_addr(Wa, sw), ah = slot_addr(PRO ? xa : ha, sh), ag = slot_addr(ga, sg);
-        const void* tw = *aw;
-        const void* th = *ah;
-        const void* tg = PRO ? *ag : nullptr;
-        asm volatile("" : "+s"(tw), "+s"(th), "+s"(tg));
-        if (sw) Wa = tw;
-        if (sh) { if (PRO) xa = th; else ha = th; }
-        if (sg) ga = tg;
-    }
-    const bf16_t* W = static_cast<const bf16_t*>(Wa);
-    const bf16_t* h = static_cast<const bf16_t*>(PRO ? xa : ha);
-    const bf16_t* gain = PRO ? static_cast<const bf16_t*>(ga) : nullptr;
-    // the narrow forms have one workgroup per column block: the first stores; the 16-column form picks its column block 0 itself
-    bf16_t* hstore = (PRO && (head & kEpiStoreH) && (FORM == 2 || blockIdx.x == 0)) ? static_cast<bf16_t*>(const_cast<void*>(ha)) : nullptr;
-    __shared__ __attribute__((aligned(16))) char stage[4 * kMmWaveLds];
-    __shared__ float red[(FORM == 3 ? 2 : 1) * 4 * 64 * 4];
-    MmEpilogue<FORM == 3 ? 2 : 1, FORM <= 1> emit;
-    emit.y = y; emit.rows = rows; emit.n = n; emit.head = head; emit.n_epi = n_epi; emit.ka = ka;
-    const bool al = aligned_to(W, 16) && aligned_to(h, 16) && (!PRO || aligned_to(gain, 16));
-    if constexpr (FORM == 0) {
-        if (__builtin_expect(al, 1)) gemm_mfma_narrow_body<true, true, 8, PRO>(W, h, emit, rows, n, cols, stage, red, gain, emit.eps, hstore);
-        else gemm_mfma_narrow_body<true, false, 8, PRO>(W, h, emit, rows, n, cols, stage, red, gain, emit.eps, hstore);
-    } else if constexpr (FORM == 1) {
-        if (__builtin_expect(al, 1)) gemm_mfma_narrow_body<true, true, 16, PRO>(W, h, emit, rows, n, cols, stage, red, gain, emit.eps, hstore);
-        else gemm_mfma_narrow_body<true, false, 16, PRO>(W, h, emit, rows, n, cols, stage, red, gain, emit.eps, hstore);
-    } else if constexpr (FORM == 2) {
-        if (__builtin_expect(al, 1)) gemm_mfma_body<true, true, true, PRO>(W, h, emit, rows, n, cols, row_groups, stage, red, gain, emit.eps, hstore);
-        else gemm_mfma_body<true, true, false, PRO>(W, h, emit, rows, n, cols, row_groups, stage, red, gain, emit.eps, hstore);
-    } else {
-        if (__builtin_expect(al, 1)) gemm_mfma_wide_body<true>(W, h, emit, rows, n, cols, row_groups, stage, red);
-        else gemm_mfma_wide_body<false>(W, h, emit, rows, n, cols, row_groups, stage, red);
-    }
-}
-
-// ---- one to four rows of h, rows of any width: the sums, and in front of them optionally the RMSNorm ------
-// bf16.  A wave computes R output columns (R weight rows of up to U * 64 vectors, U per lane); h is fetched once per
-// workgroup (lane t vectors t, t + 256, ..., asked for before the weights) and shared by the four waves through
-// LDS.  Every load of the wave is in flight before the first wait.  Same products in the same order as gemv_body
-// and gemvb_body.
-// What bounds it: at 2048 columns and below the latency of one dispatch (1.55 us of graph node, then x from memory,
-// the reduction, the weights, the tail, the store), not bytes; the sums of all rows and columns are therefore
-// reduced together (wave_sums) and the rows' scales worked out side by side.  From about 4096 columns on, the
-// weights: 4096 x 4096 at four rows takes 9.8 us with its node, 3.4 TB/s.  Decode chains with one dispatch per
-// sub-block against the four to five they took before, us per iteration: 520 columns, 3 rows, 120 sub-blocks
-// 1108 -> 440; 4096 columns, 4 rows, 30 sub-blocks 504 -> 294; 2048 columns, 1 row, 120 sub-blocks 439 -> 431 (this
-// width was merged already; the rest is the scalar row addresses and the common reduction).
-// EXACT: a row is exactly 512 * U columns.  Otherwise rows end anywhere: a vector that reaches past
-// the end is fetched from the row's last eight columns instead (no load leaves the row, whatever its alignment:
-// vector loads here take any element boundary) and shifted into place, zeros behind.
-// PRO: h is not loaded but computed here -- `h` points at the rows x to normalise, `gain` and `eps` are
-// RMSNorm's; the arithmetic is rms_body's (fused multiply-add sum of squares in element order over the lane's
-// vectors, wave_sum, the four wave sums added in a fixed order through LDS, 1 / sqrt(mean + eps), (x * scale) *
-// gain, one rounding), and what lane t computes goes where lane t's vectors of h would have gone.
-// hstore != nullptr: this workgroup also stores the rows there.
-// `after_issue()` runs once every weight load of the wave has been asked for (the kernel reads the epilogue's
-// table and asks for its operands there: every instruction in front of the weight loads delays the whole kernel
-// -- asking for the epilogue's operands first, so that they would be back before the weights, measured 0.17 us
-// slower per launch); sums[rr * R + r] receives the lane's part of the dot products.
-// (eps by reference: the kernel reads it from its arguments inside the hook.)
 template <bool NT>
 __device__ __forceinline__ void load_any(const bf16_t* base /* uniform */, unsigned elem, unsigned* w) {
     const v4u_any PG_GLOBAL* q = (const v4u_any PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)base + elem);
@@ -973,7 +257,9 @@ __device__ __forceinline__ void load_any(const bf16_t* base /* uniform */, unsig
     else t = *q;
     w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
 }
-// vector v of a row of `cols` >= 8 elements: where it is fetched ...
+// Rows of any number of columns (eight at least) in 16-byte vectors: a vector that reaches past the row's end is
+// fetched from the row's last eight elements instead (no load leaves the row, whatever its alignment) and shifted
+// into place, zeros behind.  Vector v of a row of `cols` elements: where it is fetched ...
 template <bool EXACT>
 __device__ __forceinline__ unsigned span_at(int cols, int v) {
     if constexpr (EXACT) return (unsigned)v * 8u;
@@ -1004,6 +290,745 @@ __device__ __forceinline__ void span_store(bf16_t* row, int cols, int v, const u
     }
 }
 
+// What becomes of a finished tile: a lane is given NE consecutive columns of one row -- begin(r, j, ok), put(e, v) for
+// each of its sums, end().
+// The kernels that follow the GEMV in the chain, element for element, ride along (kernels.h,
+// GemvEpiArgs): prepare() reads their table out of the kernel arguments and resolves pointer-table slots --
+// the bodies call it once their weight loads are on their way, so that nothing but
+// the first 64 bytes of the arguments stands between the start of the kernel and those loads; begin() asks
+// for the operands, so that they arrive while the tile is staged and multiplied and the partial sums are
+// exchanged; end() plays the kernels on the lane's outputs, rounding to bf16 after each as the stand-alone
+// kernels do, with the GELU as the only branch.
+// What the table says is worked out on the host (GemvEpiArgs::head: the decoder block's tail, slots, periods): in a
+// kernel of one wave per SIMD every scalar instruction counts, and recognising the tail here cost 0.1 - 0.15 us per
+// dispatch.  begin() always issues the same loads -- an operand that comes from a register slot is fetched from the
+// GEMV's own output buffer instead and ignored -- so that every wait on the rows and weights knows how
+// many younger loads are outstanding.
+template <int NE>
+struct MmEpilogue {
+    static constexpr int P = kEpiMaxPhases;
+    bf16_t* y;
+    int rows, n;
+    unsigned head;
+    int n_epi;
+    const void PG_CONSTANT* ka;   // the kernel-argument segment (a GemvEpiArgs)
+    float eps = 0.f;              // the prologue's, read with the table
+    const bf16_t* q0[P];          // operand addresses, pointer-table slots resolved
+    const bf16_t* q1[P];
+    bf16_t* outs[P];
+    unsigned ms[P], metas[P], inds[P];
+    // NE even: four (two) columns at a time are aligned 8-byte (4-byte) words of every operand and output
+    static constexpr int VW = NE % 4 == 0 ? 4 : 2;
+    bool vec = false;
+    // per call
+    unsigned idx[NE];
+    bool ok[NE];
+    unsigned ld0[P][NE], ld1[P][NE];
+    float v[NE];
+    __device__ __forceinline__ void prepare() {
+        static_assert(P == 3, "the argument batch names every phase");
+        using SlotPtr = const void* const PG_CONSTANT*;
+        const void* a0[P];
+        const void* a1[P];
+        {   // through the segment's address made opaque: otherwise the compiler moves these loads (invariant
+            // memory) to the top of the kernel, in front of the weight loads
+            const GemvEpiArgs PG_CONSTANT* kp = (const GemvEpiArgs PG_CONSTANT*)ka;
+            asm volatile("" : "+s"(kp));
+            eps = kp->eps;
+#pragma unroll
+            for (int i = 0; i < P; i++) {
+                a0[i] = kp->ph[i].in0; a1[i] = kp->ph[i].in1; outs[i] = static_cast<bf16_t*>(kp->ph[i].out);
+                ms[i] = kp->ph[i].m; metas[i] = kp->ph[i].meta; inds[i] = kp->ph[i].ind;
+            }
+            asm volatile("" : "+s"(eps),
+                              "+s"(a0[0]), "+s"(a1[0]), "+s"(outs[0]), "+s"(ms[0]), "+s"(metas[0]), "+s"(inds[0]),
+                              "+s"(a0[1]), "+s"(a1[1]), "+s"(outs[1]), "+s"(ms[1]), "+s"(metas[1]), "+s"(inds[1]),
+                              "+s"(a0[2]), "+s"(a1[2]), "+s"(outs[2]), "+s"(ms[2]), "+s"(metas[2]), "+s"(inds[2]));
+        }
+        if (head & kEpiAnySlot) {            // some operand is a pointer-table slot: all in one batch, without branches
+            auto slot_addr = [&](const void* q, unsigned is_slot) -> SlotPtr { return is_slot ? (SlotPtr)(uintptr_t)q : (SlotPtr)ka; };
+            SlotPtr at0[P], at1[P];
+            const void* t0[P];
+            const void* t1[P];
+#pragma unroll
+            for (int i = 0; i < P; i++) { at0[i] = slot_addr(a0[i], inds[i] & 1u); at1[i] = slot_addr(a1[i], inds[i] & 2u); }
+#pragma unroll
+            for (int i = 0; i < P; i++) { t0[i] = *at0[i]; t1[i] = *at1[i]; }
+            asm volatile("" : "+s"(t0[0]), "+s"(t1[0]), "+s"(t0[1]), "+s"(t1[1]), "+s"(t0[2]), "+s"(t1[2]));
+#pragma unroll
+            for (int i = 0; i < P; i++) {
+                if (inds[i] & 1u) a0[i] = t0[i];
+                if (inds[i] & 2u) a1[i] = t1[i];
+            }
+        }
+        uintptr_t low = (uintptr_t)y;
+#pragma unroll
+        for (int i = 0; i < P; i++) {
+            q0[i] = static_cast<const bf16_t*>(a0[i]);
+            q1[i] = static_cast<const bf16_t*>(a1[i]);
+            if (i < n_epi) low |= (uintptr_t)q0[i] | (uintptr_t)q1[i] | (uintptr_t)outs[i];
+        }
+        if constexpr (NE % 2 == 0) vec = (head & kEpiPlain) && n % VW == 0 && (low & (2u * VW - 1)) == 0;
+    }
+    __device__ __forceinline__ void begin(int r, int j, bool col_ok) {
+#pragma unroll
+        for (int e = 0; e < NE; e++) {
+            ok[e] = col_ok && r < rows && j + e < n;
+            idx[e] = ok[e] ? (unsigned)r * (unsigned)n + (unsigned)(j + e) : 0u;
+        }
+        if (__builtin_expect((head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec), 1)) {      // two operands, in in1 (see kernels.h)
+            fetch(q1[1], ld1[1]);
+            fetch(q1[2], ld1[2]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < P; i++) {
+                const unsigned m = ms[i];
+#pragma unroll
+                for (int e = 0; e < NE; e++) {
+                    ld0[i][e] = load_raw_global_at(q0[i], idx[e]);
+                    ld1[i][e] = load_raw_global_at(q1[i], (head & kEpiPlain) ? idx[e] : idx[e] % m);
+                }
+            }
+        }
+    }
+    // NE columns of a tensor read element for element
+    __device__ __forceinline__ void fetch(const bf16_t* q, unsigned* raw) {
+        if constexpr (NE % 2 == 1) {
+#pragma unroll
+            for (int e = 0; e < NE; e++) raw[e] = load_raw_global_at(q, idx[e]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < NE; e += VW) {
+                const unsigned short PG_GLOBAL* at = (const unsigned short PG_GLOBAL*)(uintptr_t)q + idx[e];
+                if constexpr (VW == 4) {
+                    const v2u t = *(const v2u PG_GLOBAL*)at;
+                    raw[e] = t.x & 0xffffu; raw[e + 1] = t.x >> 16; raw[e + 2] = t.y & 0xffffu; raw[e + 3] = t.y >> 16;
+                } else {
+                    const unsigned t = *(const unsigned PG_GLOBAL*)at;
+                    raw[e] = t & 0xffffu; raw[e + 1] = t >> 16;
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void store(bf16_t* o, const unsigned* b) {
+        if constexpr (NE % 2 == 0) {
+            if (__builtin_expect(vec, 1)) {
+#pragma unroll
+                for (int e = 0; e < NE; e += VW) {
+                    unsigned short PG_GLOBAL* at = (unsigned short PG_GLOBAL*)(uintptr_t)o + idx[e];
+                    if constexpr (VW == 4) { if (ok[e]) *(v2u PG_GLOBAL*)at = v2u{b[e] | (b[e + 1] << 16), b[e + 2] | (b[e + 3] << 16)}; }
+                    else { if (ok[e]) *(unsigned PG_GLOBAL*)at = b[e] | (b[e + 1] << 16); }
+                }
+                return;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < NE; e++)
+            if (ok[e]) *(unsigned short PG_GLOBAL*)(uintptr_t)(o + idx[e]) = (unsigned short)b[e];
+    }
+    __device__ __forceinline__ void put(int e, float sum) { v[e] = sum; }
+    __device__ __forceinline__ void end() {
+        unsigned bits[NE];
+        float slot[kMergeSlots][NE];
+        // Claim every operand before the first store: loads and stores complete in one queue, in order, so a wait for
+        // an operand placed after a store would wait for that store to be acknowledged as well.
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+#pragma unroll
+        for (int e = 0; e < NE; e++) bits[e] = f32_to_bf16(v[e]);
+        if (head & kEpiHeadStore) store(y, bits);
+        if (__builtin_expect((head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec), 1)) {
+            // the same kernels with the same arithmetic and roundings, operands known: GELU of the GEMV's rounded result,
+            // then each add takes the value before it and its operand from memory, in the order its descriptor names
+#pragma unroll
+            for (int e = 0; e < NE; e++) bits[e] = f32_to_bf16(ew_apply<kGelu, false>(from_raw<bf16_t>(bits[e]), 0.f));
+            if (inds[0] & kEpiStore) store(outs[0], bits);
+#pragma unroll
+            for (int i = 1; i < P; i++) {
+                if (i >= n_epi) break;
+                const bool mem_first = inds[i] & kEpiMemFirst;
+#pragma unroll
+                for (int e = 0; e < NE; e++) {
+                    const float val = from_raw<bf16_t>(bits[e]), mem = from_raw<bf16_t>(ld1[i][e]);
+                    bits[e] = f32_to_bf16(ew_apply<kAdd, false>(mem_first ? mem : val, mem_first ? val : mem));
+                }
+                if (inds[i] & kEpiStore) store(outs[i], bits);
+            }
+            return;
+        }
+        {
+            const unsigned dst = (head >> 8) & 0xffu;
+#pragma unroll
+            for (int q = 0; q < kMergeSlots; q++)
+#pragma unroll
+                for (int e = 0; e < NE; e++) slot[q][e] = dst == (unsigned)q ? from_raw<bf16_t>(bits[e]) : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < P; i++) {
+            if (i >= n_epi) break;
+            const unsigned mt = metas[i], ind = inds[i];
+            const unsigned op = mt & 0xffu, dst = mt >> 24;
+            // (a tail whose memory operand the host moved to in1 but whose layout keeps it off the straight path above)
+            const bool moved = (head & kEpiDecoder) && (ind & kEpiMemFirst);
+            const unsigned src0 = (mt >> 8) & 0xffu, src1 = (mt >> 16) & 0xffu;
+            float fa[NE], fb[NE], fo[NE];
+#pragma unroll
+            for (int e = 0; e < NE; e++) {
+                fa[e] = from_raw<bf16_t>(moved ? ld1[i][e] : ld0[i][e]);
+                fb[e] = from_raw<bf16_t>(ld1[i][e]);
+#pragma unroll
+                for (int q = 0; q < kMergeSlots; q++) {
+                    if (src0 == (unsigned)q) fa[e] = slot[q][e];
+                    if (src1 == (unsigned)q) fb[e] = slot[q][e];
+                }
+            }
+            if (op == kGelu) {
+#pragma unroll
+                for (int e = 0; e < NE; e++) fo[e] = ew_apply<kGelu, false>(fa[e], 0.f);
+            } else {
+#pragma unroll
+                for (int e = 0; e < NE; e++) {
+                    const float sum = ew_apply<kAdd, false>(fa[e], fb[e]), prod = ew_apply<kMul, false>(fa[e], fb[e]);
+                    fo[e] = op == kAdd ? sum : prod;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < NE; e++) {
+                bits[e] = f32_to_bf16(fo[e]);
+#pragma unroll
+                for (int q = 0; q < kMergeSlots; q++)
+                    if (dst == (unsigned)q) slot[q][e] = from_raw<bf16_t>(bits[e]);
+            }
+            if (ind & kEpiStore) store(outs[i], bits);
+        }
+    }
+};
+
+// A matrix-core result may not be read by an LDS write until the instruction has drained (up to
+// 19 wait states for the longest forms).  The compiler inserts those itself inside a block, but
+// it was seen to omit them when the last multiply of a K loop and this write sit in different
+// blocks (loop exit): the write then stored a stale accumulator.  32 idle cycles, tied to `acc`
+// so that they stay between the two, make it independent of that.
+__device__ __forceinline__ void mm_drained(f32x4& acc) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc)); }
+
+
+// What the two families read first: the first 64 bytes of the arguments hold everything that is needed before the
+// loads of h and the weights can go out, and only those are waited for here, in one batch of scalar loads; the
+// epilogue's table and eps are read once the weights are on their way (MmEpilogue::prepare).  PRO: h is computed from x and
+// the gain; p.g.h is where the normalised rows are stored.
+struct MmHead {
+    const bf16_t* W;
+    const bf16_t* h;          // PRO: x
+    const bf16_t* gain;
+    bf16_t* hstore;           // PRO: where the normalised rows go, or null
+    bf16_t* y;
+    int rows, n, cols, row_groups, n_epi;
+    unsigned head;
+    const void PG_CONSTANT* ka;
+};
+template <bool PRO>
+__device__ __forceinline__ MmHead mm_head(const GemvEpiArgs& p) {
+    static_assert(offsetof(GemvEpiArgs, gain) + sizeof(void*) == 64, "what the kernel needs first sits in the first 64 bytes");
+    const void* Wa = p.g.W;
+    const void* ha = p.g.h;
+    bf16_t* y = static_cast<bf16_t*>(p.g.out);
+    int rows = p.g.rows, n = p.g.n, cols = p.g.cols, row_groups = p.g.row_groups;
+    unsigned head = p.head;
+    int n_epi = p.n_epi;
+    const void* xa = p.x;
+    const void* ga = p.gain;
+    asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(rows), "+s"(n), "+s"(cols), "+s"(row_groups), "+s"(head), "+s"(n_epi), "+s"(xa), "+s"(ga));
+    const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();   // a readable address for a load whose result is not used
+    using SlotPtr = const void* const PG_CONSTANT*;
+    auto slot_addr = [&](const void* q, bool is_slot) -> SlotPtr { return is_slot ? (SlotPtr)(uintptr_t)q : (SlotPtr)ka; };
+    if (head & (1u | (PRO ? kEpiXSlot | kEpiGainSlot : 2u))) {      // some operand is a pointer-table slot: all in one batch, without branches
+        const bool sw = head & 1u, sh = head & (PRO ? kEpiXSlot : 2u), sg = PRO && (head & kEpiGainSlot);
+        SlotPtr aw = slot_addr(Wa, sw), ah = slot_addr(PRO ? xa : ha, sh), ag = slot_addr(ga, sg);
+        const void* tw = *aw;
+        const void* th = *ah;
+        const void* tg = PRO ? *ag : nullptr;
+        asm volatile("" : "+s"(tw), "+s"(th), "+s"(tg));
+        if (sw) Wa = tw;
+        if (sh) { if (PRO) xa = th; else ha = th; }
+        if (sg) ga = tg;
+    }
+    MmHead m;
+    m.W = static_cast<const bf16_t*>(Wa);
+    m.h = static_cast<const bf16_t*>(PRO ? xa : ha);
+    m.gain = PRO ? static_cast<const bf16_t*>(ga) : nullptr;
+    m.hstore = (PRO && (head & kEpiStoreH)) ? static_cast<bf16_t*>(const_cast<void*>(ha)) : nullptr;
+    m.y = y; m.rows = rows; m.n = n; m.cols = cols; m.row_groups = row_groups; m.n_epi = n_epi; m.head = head; m.ka = ka;
+    return m;
+}
+
+// ---- k_gemm_rows ------------------------------------------------------------------------------------------
+// One tile of NR (8 or 16) rows of h and NC (8 or 16) output columns per workgroup, rows of up to 128 * KS columns
+// (KS K-steps per wave).  Few rows are bound by the latency of one dispatch and, at 2048 columns, by the stream of weights:
+//   - 8 columns per workgroup make 2048 columns 256 workgroups, so that every CU pulls weights; half of each multiply
+//     is idle, which costs nothing here.  From 17 rows on, two tiles of rows: 16 columns per workgroup fill the chip;
+//   - a fragment read straight from global memory would touch 16 rows x 64 bytes per instruction, at 2048 columns all 4 KB
+//     apart: half cache lines, one cache channel (measured: 0.3 - 1.1 us slower per launch).  Instead each wave loads
+//     its own K-slices of the rows, contiguous bytes of one row (KS = 16) or two (KS = 8) per instruction, and transposes them through its
+//     private slice of LDS into fragment order: slot (lane of the load) holds 16 rows x 16 bytes, padded to 272 bytes so
+//     that 16 consecutive lanes hit all banks;
+//   - the rows of h (from L2) are asked for before the weights (from HBM): loads return in order, so h is normalised
+//     and staged while the weights are still on their way; then the same LDS slice takes the weights.
+// TAIL: the row does not have exactly 128 * KS columns; vectors at any element boundary.
+// Decode chains of 120 sub-blocks, us per iteration: 32 rows of 1024 columns 1406 -> 613 (one dispatch per sub-block, where only
+// 2048 columns had that; half the K-steps); 8 / 16 / 32 rows of 2048 columns 651 / 787 / 915 -> 627 / 771 / 862 (the epilogue's
+// table worked out on the host, two operand loads instead of six, workgroups in XCD order).
+constexpr int kMmSlotBytes = 272;   // 16 rows x 16 B + 16 B of padding
+
+// k offset of the 16-byte chunk that lane `l` (of 4 * KS) of wave `wave` loads from a row; the same chunk is fragment
+// step l >> 2, k-chunk l & 3 of that wave.
+__device__ __forceinline__ int mm_k0(int wave, int l) { return ((l >> 3) * 8 + wave * 2 + ((l >> 2) & 1)) * 32 + (l & 3) * 8; }
+
+// NR rows of a row-major matrix from row r0 (inside it), this wave's K-slices; rows beyond the matrix repeat its last row
+template <int KS, bool TAIL, int NR>
+__device__ __forceinline__ void mm_load_rows(const bf16_t* m, int rows, int cols, int r0, int wave, int lane, unsigned (*g)[4]) {
+    constexpr int L = 4 * KS, RPI = 64 / L;             // lanes per row, rows per instruction
+    const int sub = lane / L;
+    const unsigned koff = span_at<!TAIL>(cols, mm_k0(wave, lane % L) >> 3);
+#pragma unroll
+    for (int q = 0; q < NR / RPI; q++) {
+        if constexpr (RPI == 1) {
+            const int R = r0 + q < rows ? r0 + q : rows - 1;
+            load_any<false>(m + (size_t)R * cols, koff, g[q]);
+        } else {
+            const int R = r0 + q * RPI + sub < rows ? q * RPI + sub : rows - 1 - r0;
+            load_any<false>(m + (size_t)r0 * cols, (unsigned)R * (unsigned)cols + koff, g[q]);
+        }
+    }
+}
+template <int KS, bool TAIL, int NR>
+__device__ __forceinline__ void mm_fix_rows(int cols, int wave, int lane, unsigned (*g)[4]) {
+    if constexpr (TAIL)
+#pragma unroll
+        for (int q = 0; q < NR * KS / 16; q++) span_fix<false>(cols, mm_k0(wave, lane % (4 * KS)) >> 3, g[q]);
+}
+
+// LDS operations of one wave execute in order: these writes cannot overtake the reads before them
+template <int KS, int NR>
+__device__ __forceinline__ void mm_stage(char* lds /* this wave's */, int lane, const unsigned (*g)[4]) {
+    constexpr int L = 4 * KS, RPI = 64 / L;
+#pragma unroll
+    for (int q = 0; q < NR / RPI; q++)
+        *reinterpret_cast<v4u*>(lds + (lane % L) * kMmSlotBytes + (q * RPI + lane / L) * 16) = v4u{g[q][0], g[q][1], g[q][2], g[q][3]};
+}
+// fragment (step i, k-chunk lane >> 4, row or column lane & 15) of what is staged in `lds`
+template <int KS>
+__device__ __forceinline__ void mm_read_frags(const char* lds, int lane, v4u* f) {
+#pragma unroll
+    for (int i = 0; i < KS; i++)
+        f[i] = *reinterpret_cast<const v4u*>(lds + (i * 4 + (lane >> 4)) * kMmSlotBytes + (lane & 15) * 16);
+}
+
+// RMSNorm of the rows just loaded.  A lane holds 16-byte chunk c of every row (every other row at KS = 8), where c runs
+// over a row's chunks across the workgroup, but not in lane order.  The stand-alone kernel's sums must be reproduced bit for bit: per chunk
+// the fused sum of squares in element order (any lane can do that); then the stand-alone kernel's reduction, which
+// is a tree of fixed shape over the chunk sums in chunk order (absent chunks are zeros) -- wave_sum adds neighbours, then pairs of
+// pairs, of quads, of eights (a floating-point add does not care which operand is which), then the four
+// sixteens in order, and the four wave sums in order.  Here the chunk sums go to LDS in chunk order and
+// the workgroup's KS * NR subtrees of sixteen leaves are spread over its lanes, one each; lane r < NR
+// then finishes row r (four sixteens per wave sum, four wave sums) and turns the total into the row's
+// scale; every lane scales its own chunks: (x * scale) * gain, one rounding.  `scratch`: NR * (21 * KS + 1)
+// floats of LDS that nothing else uses until the rows are staged.  hstore: this workgroup also stores the rows.
+template <int KS, bool TAIL, int NR>
+__device__ __forceinline__ void mm_rmsnorm_rows(unsigned (*g)[4], const unsigned* wg /* the lane's chunk of the gain */, float eps, bf16_t* hstore,
+                                                int rows, int cols, int wave, int lane, float* scratch) {
+    constexpr int L = 4 * KS, RPI = 64 / L, Q = NR / RPI;
+    constexpr int kRow = 20 * KS;              // a row of 16 * KS chunk sums, 8 floats of padding after every 32: the lanes of a wave hold
+                                               // chunks 32 apart, which would otherwise all fall into the same eight banks
+    const int tid = wave * 64 + lane, sub = lane / L;
+    const int k0 = mm_k0(wave, lane % L);
+    float* sq = scratch;                       // [NR][kRow]: chunk sums in chunk order
+    float* six = scratch + NR * kRow;          // [NR][KS]: sums of sixteen chunks
+    float* scale = six + NR * KS;              // [NR]
+    auto at = [](int c) { return c + 8 * (c >> 5); };
+    float fx[Q][8];
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        Vec<bf16_t, 16>::unpack(g[q], fx[q]);
+        float acc = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; e++) acc = __builtin_fmaf(fx[q][e], fx[q][e], acc);
+        sq[(q * RPI + sub) * kRow + at(k0 >> 3)] = acc;
+    }
+    lds_barrier();
+    if (tid < KS * NR) {                       // subtree tid: row tid / KS, chunks 16 * (tid % KS) .. + 15
+        const f32x4* leaf = reinterpret_cast<const f32x4*>(sq + (tid / KS) * kRow + at((tid % KS) * 16));
+        const f32x4 l0 = leaf[0], l1 = leaf[1], l2 = leaf[2], l3 = leaf[3];
+        const float q0 = (l0.x + l0.y) + (l0.z + l0.w), q1 = (l1.x + l1.y) + (l1.z + l1.w);
+        const float q2 = (l2.x + l2.y) + (l2.z + l2.w), q3 = (l3.x + l3.y) + (l3.z + l3.w);
+        six[tid] = (q0 + q1) + (q2 + q3);
+    }
+    lds_barrier();
+    if (tid < NR) {
+        const f32x4* sx = reinterpret_cast<const f32x4*>(six + tid * KS);
+        float total = 0.f;
+#pragma unroll
+        for (int w = 0; w < KS / 4; w++) {
+            const float wsum = ((sx[w].x + sx[w].y) + sx[w].z) + sx[w].w;
+            total = w == 0 ? wsum : total + wsum;
+        }
+        scale[tid] = 1.0f / sqrtf(total / (float)cols + eps);
+    }
+    lds_barrier();
+    float fg[8];
+    Vec<bf16_t, 16>::unpack(wg, fg);
+#pragma unroll
+    for (int q = 0; q < Q; q++) {
+        float fo[8];
+        const float sc = scale[q * RPI + sub];
+#pragma unroll
+        for (int e = 0; e < 8; e++) fo[e] = (fx[q][e] * sc) * fg[e];
+        Vec<bf16_t, 16>::pack(fo, g[q]);
+    }
+    if (hstore) {
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            const int r = q * RPI + sub;
+            if (r < rows) {
+                if constexpr (TAIL) span_store(hstore + (size_t)r * cols, cols, k0 >> 3, g[q]);
+                else store_vec_global(hstore + (size_t)r * cols + k0, g[q]);
+            }
+        }
+    }
+}
+
+// NC = 8: one tile of rows, the grid is the column blocks; NC = 16: (column blocks) x (tiles of rows), column block
+// fastest, so that the tiles of one column block share an XCD's L2.  The workgroups of column block 0 store the
+// normalised rows.
+template <int KS, bool TAIL, int NR, int NC, bool PRO>
+__global__ __launch_bounds__(kBlock, (PRO && KS > 8) ? 1 : 2) void k_gemm_rows(GemvEpiArgs p) {
+    const MmHead m = mm_head<PRO>(p);
+    constexpr int kWaveLds = 4 * KS * kMmSlotBytes;
+    __shared__ __attribute__((aligned(16))) char stage[4 * kWaveLds];
+    __shared__ float red[4 * 64 * 4];
+    static_assert((NR * (21 * KS + 1)) * sizeof(float) <= sizeof stage, "the prologue's sums fit the staging area");
+    MmEpilogue<1> emit;
+    emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ncb = (m.n + NC - 1) / NC;
+    const int ntiles = NC == 8 ? 1 : (m.rows + 15) / 16;
+    const int at = (int)xcd_stretch(blockIdx.x, (unsigned)(ncb * ntiles)), cb = at / ntiles, tile = at % ntiles;
+    const int cols = TAIL ? m.cols : 128 * KS;
+    const int j0 = cb * NC, r0 = tile * 16;
+    if (r0 >= m.rows) return;                            // whole workgroup: nothing waits on it
+    char* lds = stage + wave * kWaveLds;
+    unsigned g[NR * KS / 16][4], gw[NC * KS / 16][4];
+    v4u a[KS], b[KS];
+    mm_load_rows<KS, TAIL, NR>(m.h, m.rows, cols, r0, wave, lane, g);      // PRO: the rows to normalise
+    unsigned wg[4] = {0u, 0u, 0u, 0u};
+    if constexpr (PRO) load_any<false>(m.gain, span_at<!TAIL>(cols, mm_k0(wave, lane % (4 * KS)) >> 3), wg);   // before the weights: loads come back in order
+    __builtin_amdgcn_sched_barrier(0);
+    mm_load_rows<KS, TAIL, NC>(m.W, m.n, cols, j0, wave, lane, gw);
+    emit.prepare();                                      // the epilogue's table right behind the weight loads
+    // output stage: wave w finishes row w of the four that an accumulator lane holds
+    auto emit_begin = [&] { emit.begin(r0 + (lane >> 4) * 4 + wave, j0 + (lane & 15), NC == 16 || (lane & 15) < NC); };
+    if constexpr (NC == 8) emit_begin();
+    mm_fix_rows<KS, TAIL, NR>(cols, wave, lane, g);
+    if constexpr (PRO) {
+        span_fix<!TAIL>(cols, mm_k0(wave, lane % (4 * KS)) >> 3, wg);
+        bf16_t* hs = (m.hstore && cb == 0) ? m.hstore + (size_t)r0 * cols : nullptr;
+        mm_rmsnorm_rows<KS, TAIL, NR>(g, wg, emit.eps, hs, m.rows - r0, cols, wave, lane, reinterpret_cast<float*>(stage));
+        lds_barrier();        // the sums are read: the staging area takes the rows now
+    }
+    mm_stage<KS, NR>(lds, lane, g);
+    mm_read_frags<KS>(lds, lane, a);
+    mm_fix_rows<KS, TAIL, NC>(cols, wave, lane, gw);
+    mm_stage<KS, NC>(lds, lane, gw);
+    mm_read_frags<KS>(lds, lane, b);
+    __builtin_amdgcn_sched_barrier(0);   // all fragment reads before the first multiply, not one LDS latency per pair
+    if constexpr (NC != 8) emit_begin();
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < KS; i++)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[i]), acc, 0, 0, 0);
+    mm_drained(acc);
+    float* dst = red + ((size_t)wave * 64 + lane) * 4;
+    dst[0] = acc.x; dst[1] = acc.y; dst[2] = acc.z; dst[3] = acc.w;
+    __syncthreads();
+    const float p0 = red[((size_t)0 * 64 + lane) * 4 + wave], p1 = red[((size_t)1 * 64 + lane) * 4 + wave];
+    const float p2 = red[((size_t)2 * 64 + lane) * 4 + wave], p3 = red[((size_t)3 * 64 + lane) * 4 + wave];
+    emit.put(0, ((p0 + p1) + p2) + p3);
+    emit.end();
+}
+
+// ---- k_gemm_cols ------------------------------------------------------------------------------------------
+// The same staging for more rows: 16 output columns per workgroup, whose weight fragments stay in registers while its
+// tiles of 16 rows of h pass by, the next tile's rows in flight across the multiplies of this one.  Two workgroups per CU.
+template <int KS, bool TAIL>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(GemvEpiArgs p) {
+    const MmHead m = mm_head<false>(p);
+    constexpr int kWaveLds = 4 * KS * kMmSlotBytes, kRedRow = 20;
+    __shared__ __attribute__((aligned(16))) char stage[4 * kWaveLds];
+    __shared__ float red[4][16 * kRedRow];
+    MmEpilogue<1> emit;
+    emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ncb = (m.n + 15) / 16;
+    const int at = (int)xcd_stretch(blockIdx.x, (unsigned)(ncb * m.row_groups)), cb = at / m.row_groups, rg = at % m.row_groups;
+    const int ntiles = (m.rows + 15) / 16, per = (ntiles + m.row_groups - 1) / m.row_groups;
+    const int t0 = rg * per, t1 = (t0 + per < ntiles) ? t0 + per : ntiles;
+    if (t0 >= t1) return;                                // whole workgroup: nothing waits on it
+    const int cols = TAIL ? m.cols : 128 * KS;
+    const int j0 = cb * 16;
+    char* lds = stage + wave * kWaveLds;
+    unsigned g[KS][4], gw[KS][4];
+    v4u a[KS], b[KS];
+    mm_load_rows<KS, TAIL, 16>(m.h, m.rows, cols, t0 * 16, wave, lane, g);
+    mm_load_rows<KS, TAIL, 16>(m.W, m.n, cols, j0, wave, lane, gw);
+    emit.prepare();                                      // the epilogue's table right behind the weight loads
+    mm_fix_rows<KS, TAIL, 16>(cols, wave, lane, g);
+    mm_stage<KS, 16>(lds, lane, g);
+    mm_read_frags<KS>(lds, lane, a);
+    if (t1 - t0 > 1) mm_load_rows<KS, TAIL, 16>(m.h, m.rows, cols, (t0 + 1) * 16, wave, lane, g);
+    mm_fix_rows<KS, TAIL, 16>(cols, wave, lane, gw);
+    mm_stage<KS, 16>(lds, lane, gw);
+    mm_read_frags<KS>(lds, lane, b);
+    const int er = tid >> 4, ec = tid & 15;              // output stage: a lane finishes one column of one row
+#pragma unroll 1
+    for (int t = t0;;) {
+        __builtin_amdgcn_sched_barrier(0);   // all fragment reads before the first multiply, not one LDS latency per pair
+        emit.begin(t * 16 + er, j0 + ec, true);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < KS; i++)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[i]), acc, 0, 0, 0);
+        mm_drained(acc);
+        float* dst = red[wave] + (lane >> 4) * 4 * kRedRow + (lane & 15);
+        dst[0] = acc.x; dst[kRedRow] = acc.y; dst[2 * kRedRow] = acc.z; dst[3 * kRedRow] = acc.w;
+        lds_barrier();
+        const int q = er * kRedRow + ec;
+        emit.put(0, ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q]);
+        emit.end();
+        if (++t >= t1) break;
+        lds_barrier();                       // the sums are read: `red` is free again
+        mm_fix_rows<KS, TAIL, 16>(cols, wave, lane, g);
+        mm_stage<KS, 16>(lds, lane, g);
+        if (t + 1 < t1) mm_load_rows<KS, TAIL, 16>(m.h, m.rows, cols, (t + 1) * 16, wave, lane, g);
+        mm_read_frags<KS>(lds, lane, a);
+    }
+}
+
+// ---- k_gemm_tile --------------------------------------------------------------------------------------------
+// RT x CT tiles of 16 rows x 16 columns per workgroup, any number of columns of h and W.  Each wave streams its own
+// K-blocks (64 columns of all the workgroup's rows of h and W, (RT + CT) * 2 KB) through a ring of S blocks in its own part
+// of LDS, loaded from global memory into LDS directly: no registers are held by loads in flight (S blocks per wave, so
+// latency is covered without a second workgroup), no wave waits for another until the partial sums meet.  A load
+// instruction covers whole 128-byte lines of eight rows; lane l's line position is swapped with its row (chunk c of
+// row r sits at c ^ (r & 7)), so that the fragment reads of eight consecutive lanes touch all banks once.
+// What bounds it is what a CU takes in through its cache ((RT + CT) * 32 bytes * cols per RT * CT * 256 outputs), hence larger
+// tiles where there are enough of them (plan_gemm); a CU holds no more than its 32 KB cache's worth of lines in flight.
+// K is cut into blocks of 64 and dealt out to eight parts in turn, whose sums are added in order.  Eight waves, one part
+// each, so that one wave's fragment reads and multiplies hide behind another's (with four waves a round of one block
+// cost them 0.3 us in turn); the stand-alone launches of an eager loop keep the four-wave workgroups
+// (two parts a wave, one after the other): the same bits.
+// Decode chains, us per iteration, before and after: 128 rows of 2048 columns, 120 sub-blocks 1529 -> 1380; 100 x 2000 (100
+// sub-blocks) 1290 -> 850, 128 x 1024 1282 -> 793 (there also one dispatch instead of three around the GEMV); one GEMV
+// of 128 rows by 4096 x 4096 33.6 -> 19.3 with four waves, the 16-column form it replaces there re-reads W per tile.
+// Rows that 16-byte loads cannot reach (cols no multiple of 8, a misaligned external) go through registers instead,
+// one block ahead.
+template <int N>
+__device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// The fragments of one K-block, both steps, of F tiles 2 KB apart: read and waited for in one piece (left to the compiler,
+// reads of LDS that direct loads may be filling wait for all of those first)
+template <int F>
+__device__ __forceinline__ void ring_frags(unsigned at0, unsigned at1, v4u (&f)[2 * F]) {
+    static_assert(F == 2 || F == 4 || F == 6, "tiles per block");
+    if constexpr (F == 2)
+        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:2048\n\tds_read_b128 %2, %5\n\tds_read_b128 %3, %5 offset:2048\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]) : "v"(at0), "v"(at1) : "memory");
+    else if constexpr (F == 4)
+        asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:2048\n\tds_read_b128 %2, %8 offset:4096\n\tds_read_b128 %3, %8 offset:6144\n\t"
+                     "ds_read_b128 %4, %9\n\tds_read_b128 %5, %9 offset:2048\n\tds_read_b128 %6, %9 offset:4096\n\tds_read_b128 %7, %9 offset:6144\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7])
+                     : "v"(at0), "v"(at1) : "memory");
+    else
+        asm volatile("ds_read_b128 %0, %12\n\tds_read_b128 %1, %12 offset:2048\n\tds_read_b128 %2, %12 offset:4096\n\tds_read_b128 %3, %12 offset:6144\n\t"
+                     "ds_read_b128 %4, %12 offset:8192\n\tds_read_b128 %5, %12 offset:10240\n\t"
+                     "ds_read_b128 %6, %13\n\tds_read_b128 %7, %13 offset:2048\n\tds_read_b128 %8, %13 offset:4096\n\tds_read_b128 %9, %13 offset:6144\n\t"
+                     "ds_read_b128 %10, %13 offset:8192\n\tds_read_b128 %11, %13 offset:10240\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7]), "=&v"(f[8]), "=&v"(f[9]),
+                       "=&v"(f[10]), "=&v"(f[11])
+                     : "v"(at0), "v"(at1) : "memory");
+}
+
+template <int RT, int CT, int S, int NW>
+__global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gemm_tile(GemvEpiArgs p) {
+    constexpr int F = RT + CT, NL = 2 * F, kBlockLds = F * 2048, kWaveLds = S * kBlockLds;
+    constexpr int PK = 8 / NW;                           // eighths of K per wave
+    constexpr int kRedRow = 16 * CT + 4;                 // floats of a row of partial sums, padded: rows 4 apart fall into other banks
+    constexpr int kRed = 16 * RT * kRedRow;              // floats of one eighth's partial sums
+    constexpr int NE = RT * CT * 4 >= NW ? RT * CT * 4 / NW : 1, kPerRow = 16 * CT / NE;  // outputs per lane (consecutive columns), lanes per row of the tile
+    static_assert(PK * kRed * 4 <= kWaveLds, "a wave's partial sums fit its ring");
+    static_assert(S == 1 || S == 2, "the waits below name the blocks in flight");
+    const MmHead m = mm_head<false>(p);
+    __shared__ __attribute__((aligned(128))) char ring[NW * kWaveLds];
+    MmEpilogue<NE> emit;
+    emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = m.rows, n = m.n, cols = m.cols;
+    const int ncb = (n + 16 * CT - 1) / (16 * CT);
+    const int at = (int)xcd_stretch(blockIdx.x, (unsigned)(ncb * m.row_groups)), cb = at / m.row_groups, rg = at % m.row_groups;
+    // tiles of rows per workgroup: a multiple of RT, so that no two workgroups compute (and update in place) the same rows
+    const int ntiles = (rows + 15) / 16, per = (ntiles + RT * m.row_groups - 1) / (RT * m.row_groups) * RT;
+    const int t0 = rg * per, t1 = (t0 + per < ntiles) ? t0 + per : ntiles;
+    if (t0 >= t1) return;                                // whole workgroup: nothing waits on it
+    const int j0 = cb * 16 * CT;
+    const int nkb = (cols + 63) / 64;
+    char* mine = ring + wave * kWaveLds;
+    const int r8 = lane >> 3;                            // row within the eight of a load instruction
+    const bool direct = cols % 8 == 0 && aligned_to(m.W, 16) && aligned_to(m.h, 16);
+    const int chunk = direct ? (lane & 7) ^ r8 : lane & 7;             // 16-byte chunk of the K-block this lane loads
+    const int rem = cols & 63;                           // columns of the last K-block, if it is a partial one
+    // where a lane finds its fragments: row (or column) lane & 15 of a tile, chunk lane >> 4 of each step
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)mine;
+    const unsigned f0 = lds0 + (lane & 15) * 128 + (((lane >> 4) ^ (lane & 7)) * 16), f1 = lds0 + (lane & 15) * 128 + (((4 + (lane >> 4)) ^ (lane & 7)) * 16);
+    const bf16_t* wb = m.W + (size_t)j0 * cols;
+    const int er = tid / kPerRow, ec = (tid % kPerRow) * NE;           // output stage: a lane finishes NE consecutive columns of one row
+#pragma unroll 1
+    for (int t = t0; t < t1; t += RT) {
+        const int r0 = t * 16;
+        const bf16_t* hb = m.h + (size_t)r0 * cols;
+        unsigned row_at[NL];                             // element offset of the row each load instruction takes here
+#pragma unroll
+        for (int q = 0; q < NL; q++) {
+            const int r = (q < 2 * RT ? q : q - 2 * RT) * 8 + r8, last = (q < 2 * RT ? rows - r0 : n - j0) - 1;
+            row_at[q] = (unsigned)(r < last ? r : last) * (unsigned)cols;
+        }
+        f32x4 acc[PK][RT][CT];
+        // the epilogue's table behind the first block's loads: asked for behind all of them it came 1.1 us later
+        auto epilogue_begin = [&] {
+            if (t == t0) emit.prepare();
+            emit.begin(r0 + er, j0 + ec, er < 16 * RT);
+        };
+#pragma unroll
+        for (int pk = 0; pk < PK; pk++) {
+            const int first = wave + pk * NW, nw = (nkb - first + 7) / 8;      // this eighth's K-blocks: first, first + 8, ...
+#pragma unroll
+            for (int i = 0; i < RT; i++)
+#pragma unroll
+                for (int j = 0; j < CT; j++) acc[pk][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            auto multiply = [&](v4u (&f)[2 * F]) {
+#pragma unroll
+                for (int s = 0; s < 2; s++)
+#pragma unroll
+                    for (int i = 0; i < RT; i++)
+#pragma unroll
+                        for (int j = 0; j < CT; j++)
+                            acc[pk][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[s * F + i]), __builtin_bit_cast(bf16x8, f[s * F + RT + j]),
+                                                                                    acc[pk][i][j], 0, 0, 0);
+            };
+            if (__builtin_expect(direct, 1)) {
+                auto issue = [&](int j, int slot) {
+                    const int k = (first + 8 * j) * 64 + chunk * 8;
+                    const unsigned ke = k < cols ? (unsigned)k : 0u;       // a chunk past the end is read from column 0 and zeroed later
+#pragma unroll
+                    for (int q = 0; q < NL; q++)
+                        __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)(q < 2 * RT ? hb : wb) + (row_at[q] + ke)),
+                                                         (__attribute__((address_space(3))) void*)(mine + slot * kBlockLds + q * 1024), 16, 0, 0);
+                };
+                if (nw > 0) issue(0, 0);
+                if (pk == 0) epilogue_begin();
+                if (S == 2 && nw > 1) issue(1, 1);
+                int slot = 0;
+#pragma unroll 1
+                for (int j = 0; j < nw; j++) {
+                    // loads complete in order: block j is in once at most the younger block's loads are outstanding (other loads
+                    // among them only make the wait stricter)
+                    if (S == 2 && j + 1 < nw) vm_wait<NL>();
+                    else vm_wait<0>();
+                    v4u f[2 * F];
+                    ring_frags<F>(f0 + slot * kBlockLds, f1 + slot * kBlockLds, f);
+                    if (j + S < nw) issue(j + S, slot);                    // the slot has been read
+                    if (rem && first + 8 * j == nkb - 1) {
+#pragma unroll
+                        for (int s = 0; s < 2; s++)
+                            if ((s * 4 + (lane >> 4)) * 8 >= rem)
+#pragma unroll
+                                for (int i = 0; i < F; i++) f[s * F + i] = v4u{0u, 0u, 0u, 0u};
+                    }
+                    multiply(f);
+                    slot = slot + 1 == S ? 0 : slot + 1;
+                }
+            } else {
+                unsigned g[NL][4];
+                auto fetch = [&](int j) {
+                    const unsigned ke = span_at<false>(cols, (first + 8 * j) * 8 + chunk);
+#pragma unroll
+                    for (int q = 0; q < NL; q++) load_any<false>(q < 2 * RT ? hb : wb, row_at[q] + ke, g[q]);
+                };
+                if (nw > 0) fetch(0);
+                if (pk == 0) epilogue_begin();
+#pragma unroll 1
+                for (int j = 0; j < nw; j++) {
+#pragma unroll
+                    for (int q = 0; q < NL; q++) {
+                        span_fix<false>(cols, (first + 8 * j) * 8 + chunk, g[q]);
+                        *reinterpret_cast<v4u*>(mine + (q * 8 + r8) * 128 + ((chunk ^ r8) * 16)) = v4u{g[q][0], g[q][1], g[q][2], g[q][3]};
+                    }
+                    if (j + 1 < nw) fetch(j + 1);
+                    v4u f[2 * F];
+                    ring_frags<F>(f0, f1, f);                              // behind the writes above: one wave's LDS operations execute in order
+                    multiply(f);
+                }
+            }
+        }
+#pragma unroll
+        for (int pk = 0; pk < PK; pk++)
+#pragma unroll
+            for (int i = 0; i < RT; i++)
+#pragma unroll
+                for (int j = 0; j < CT; j++) {
+                    mm_drained(acc[pk][i][j]);
+                    float* dst = reinterpret_cast<float*>(mine) + pk * kRed + (i * 16 + (lane >> 4) * 4) * kRedRow + j * 16 + (lane & 15);
+                    const f32x4 v = acc[pk][i][j];
+                    dst[0] = v.x; dst[kRedRow] = v.y; dst[2 * kRedRow] = v.z; dst[3 * kRedRow] = v.w;
+                }
+        lds_barrier();
+        if (er < 16 * RT) {
+#pragma unroll
+            for (int e = 0; e < NE; e++) {
+                float sum = 0.f;
+#pragma unroll
+                for (int w = 0; w < 8; w++) {
+                    const float part = reinterpret_cast<const float*>(ring + (w % NW) * kWaveLds)[(w / NW) * kRed + er * kRedRow + ec + e];
+                    sum = w == 0 ? part : sum + part;
+                }
+                emit.put(e, sum);
+            }
+            emit.end();
+        }
+        if (t + RT < t1) __syncthreads();      // the sums are read: the rings are free again
+    }
+}
+
+// ---- one to four rows of h, rows of any width: the sums, and in front of them optionally the RMSNorm ------
+// bf16.  A wave computes R output columns (R weight rows of up to U * 64 vectors, U per lane); h is fetched once per
+// workgroup (lane t vectors t, t + 256, ..., asked for before the weights) and shared by the four waves through
+// LDS.  Every load of the wave is in flight before the first wait.  Same products in the same order as gemv_body
+// and gemvb_body.
+// What bounds it: at 2048 columns and below the latency of one dispatch (1.55 us of graph node, then x from memory,
+// the reduction, the weights, the tail, the store), not bytes; the sums of all rows and columns are therefore
+// reduced together (wave_sums) and the rows' scales worked out side by side.  From about 4096 columns on, the
+// weights: 4096 x 4096 at four rows takes 9.8 us with its node, 3.4 TB/s.  Decode chains with one dispatch per
+// sub-block against the four to five they took before, us per iteration: 520 columns, 3 rows, 120 sub-blocks
+// 1108 -> 440; 4096 columns, 4 rows, 30 sub-blocks 504 -> 294; 2048 columns, 1 row, 120 sub-blocks 439 -> 431 (this
+// width was merged already; the rest is the scalar row addresses and the common reduction).
+// EXACT: a row is exactly 512 * U columns.  Otherwise rows end anywhere: a vector that reaches past
+// the end is fetched from the row's last eight columns instead (no load leaves the row, whatever its alignment:
+// vector loads here take any element boundary) and shifted into place, zeros behind.
+// PRO: h is not loaded but computed here -- `h` points at the rows x to normalise, `gain` and `eps` are
+// RMSNorm's; the arithmetic is rms_body's (fused multiply-add sum of squares in element order over the lane's
+// vectors, wave_sum, the four wave sums added in a fixed order through LDS, 1 / sqrt(mean + eps), (x * scale) *
+// gain, one rounding), and what lane t computes goes where lane t's vectors of h would have gone.
+// hstore != nullptr: this workgroup also stores the rows there.
+// `after_issue()` runs once every weight load of the wave has been asked for (the kernel reads the epilogue's
+// table and asks for its operands there: every instruction in front of the weight loads delays the whole kernel
+// -- asking for the epilogue's operands first, so that they would be back before the weights, measured 0.17 us
+// slower per launch); sums[rr * R + r] receives the lane's part of the dot products.
+// (eps by reference: the kernel reads it from its arguments inside the hook.)
 template <int R, int RB, int U, bool EXACT, bool PRO, class Hook>
 __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h, int n, int cols, int j0 /* uniform */, int lane, int tid, v4u* hs /* [RB][U * 64] */,
                                                Hook after_issue, float (&sums)[R * RB],
@@ -1113,213 +1138,27 @@ __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h,
 // through the kernels that follow (see kernels.h; none of them: the plain GEMV).
 template <int R, int RB, int U, bool EXACT, bool PRO>
 __global__ __launch_bounds__(kBlock) void k_gemv_rows(GemvEpiArgs p) {
-    constexpr int P = kEpiMaxPhases;
-    // The GEMV's own arguments first, in one batch of scalar loads (see args_up_front): nothing else stands
-    // between the start of the kernel and the weight loads.  The epilogue's table is read once those are on
-    // their way (`fetch`), and kept in scalar registers from then on.
-    // The first 64 bytes of the arguments hold everything that is needed before the weight loads can go out,
-    // and only those are waited for here, in one batch of scalar loads (see args_up_front; the start of the
-    // argument buffer arrives in under 0.1 us, the lines behind it take 0.3 us more).  The epilogue's table
-    // and eps are read once the weights are on their way (`fetch`).
-    static_assert(offsetof(GemvEpiArgs, gain) + sizeof(void*) == 64, "what the kernel needs first sits in the first 64 bytes");
-    const void* Wa = p.g.W;
-    const void* ha = p.g.h;
-    bf16_t* y = static_cast<bf16_t*>(p.g.out);
-    int n = p.g.n, cols = p.g.cols;
-    unsigned head = p.head;
-    int n_epi = p.n_epi;
-    const void* xa = p.x;
-    const void* ga = p.gain;
-    asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(n), "+s"(cols), "+s"(head), "+s"(n_epi), "+s"(xa), "+s"(ga));
-    const void* a0[P];
-    const void* a1[P];
-    bf16_t* outs[P];
-    unsigned ms[P], metas[P], inds[P];
-    float eps = 0.f;
-    static_assert(P == 3, "the argument batch in fetch names every phase");
-    const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();   // a readable address for a load whose result is not used
-    using SlotPtr = const void* const PG_CONSTANT*;
-    auto slot_addr = [&](const void* q, bool is_slot) -> SlotPtr { return is_slot ? (SlotPtr)(uintptr_t)q : (SlotPtr)ka; };
-    // with a prologue the GEMV's input is computed from x and the gain; p.g.h is where workgroup 0 stores it
-    if (head & (1u | (PRO ? kEpiXSlot | kEpiGainSlot : 2u))) {      // some operand is a pointer-table slot: all in one batch, without branches
-        const bool sw = head & 1u, sh = head & (PRO ? kEpiXSlot : 2u), sg = PRO && (head & kEpiGainSlot);
-        SlotPtr aw = slot_addr(Wa, sw), ah = slot_addr(PRO ? xa : ha, sh), ag = slot_addr(ga, sg);
-        const void* tw = *aw;
-        const void* th = *ah;
-        const void* tg = PRO ? *ag : nullptr;
-        asm volatile("" : "+s"(tw), "+s"(th), "+s"(tg));
-        if (sw) Wa = tw;
-        if (sh) { if (PRO) xa = th; else ha = th; }
-        if (sg) ga = tg;
-    }
-    const bf16_t* W = static_cast<const bf16_t*>(Wa);
-    const bf16_t* h = static_cast<const bf16_t*>(PRO ? xa : ha);
-    const bf16_t* gain = PRO ? static_cast<const bf16_t*>(ga) : nullptr;
-    bf16_t* hstore = (PRO && (head & kEpiStoreH) && blockIdx.x == 0) ? static_cast<bf16_t*>(const_cast<void*>(ha)) : nullptr;
+    const MmHead m = mm_head<PRO>(p);
+    const int n = m.n;
+    // up to 2048 columns an XCD takes a contiguous stretch of the columns (decode chain, 2048 columns, 1 row 430 -> 406 us, 4 rows
+    // 482 -> 472; 1024 columns, 1 row 347 -> 326); longer rows stream better dealt out in turn (4096 columns, 4 rows 289 against 304)
+    const unsigned bid = U <= 4 ? xcd_stretch(blockIdx.x, (unsigned)(n + 4 * R - 1) / (4 * R)) : blockIdx.x;
+    bf16_t* hstore = bid == 0 ? m.hstore : nullptr;
     __shared__ v4u hs[RB * U * 64];
     __shared__ f32x4 part[4];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int j0 = (blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(tid >> 6)) * R;   // uniform: the weight rows' addresses stay in scalar registers
-    unsigned ld0[P], ld1[P];
-    bool mine = false;
-    unsigned idx = 0;
-    bool decoder = false;       // the tail is GELU of the GEMV's result, then one or two adds with an operand from memory
-    // The epilogue's operands: asked for once the weights are on their way (pointer-table slots first, with
-    // scalar loads, all at once).  Always the same number of loads -- an operand that comes from a register
-    // slot is fetched from the GEMV's own output buffer instead and ignored -- so that every wait on the
-    // weights knows exactly how many younger loads are outstanding.
-    auto fetch = [&] {
-        {   // the rest of the arguments, through the kernel-argument segment's address made opaque: otherwise the
-            // compiler moves these loads (invariant memory) to the top of the kernel, in front of the weight loads
-            const GemvEpiArgs PG_CONSTANT* kp = (const GemvEpiArgs PG_CONSTANT*)ka;
-            asm volatile("" : "+s"(kp));
-            eps = kp->eps;
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                a0[i] = kp->ph[i].in0; a1[i] = kp->ph[i].in1; outs[i] = static_cast<bf16_t*>(kp->ph[i].out);
-                ms[i] = kp->ph[i].m; metas[i] = kp->ph[i].meta; inds[i] = kp->ph[i].ind;
-            }
-            asm volatile("" : "+s"(eps),
-                              "+s"(a0[0]), "+s"(a1[0]), "+s"(outs[0]), "+s"(ms[0]), "+s"(metas[0]), "+s"(inds[0]),
-                              "+s"(a0[1]), "+s"(a1[1]), "+s"(outs[1]), "+s"(ms[1]), "+s"(metas[1]), "+s"(inds[1]),
-                              "+s"(a0[2]), "+s"(a1[2]), "+s"(outs[2]), "+s"(ms[2]), "+s"(metas[2]), "+s"(inds[2]));
-        }
-        const int e = sums_index<R * RB>(lane);
-        mine = lane < sums_lanes(R * RB) && e < R * RB && j0 + e % R < n;
-        idx = mine ? (unsigned)(e / R) * (unsigned)n + (unsigned)(j0 + e % R) : 0u;
-        const unsigned total = (unsigned)RB * (unsigned)n;
-        bool f0[P], f1[P], s0[P], s1[P];
-        unsigned any = 0;
-#pragma unroll
-        for (int i = 0; i < P; i++) {
-            const unsigned mt = metas[i];
-            f0[i] = ((mt >> 8) & 0xffu) == kMergeFromMemory;
-            f1[i] = (mt & 0xffu) != kGelu && ((mt >> 16) & 0xffu) == kMergeFromMemory;
-            s0[i] = f0[i] && (inds[i] & 1u);
-            s1[i] = f1[i] && (inds[i] & 2u);
-            any |= (f0[i] ? inds[i] & 1u : 0u) | (f1[i] ? inds[i] & 2u : 0u);
-        }
-        any = __builtin_amdgcn_readfirstlane(any);
-        asm volatile("" : "+s"(any));       // keeps what follows behind the weight loads
-        {   // the decoder block's tail, recognised here (scalar arithmetic under the weights' latency) so that the
-            // tail itself runs it straight through, without the operand and slot selection of the general form
-            auto add_of = [](unsigned mt, unsigned q) {
-                const unsigned a = (mt >> 8) & 0xffu, b = (mt >> 16) & 0xffu;
-                return (mt & 0xffu) == (unsigned)kAdd && ((a == q && b == kMergeFromMemory) || (a == kMergeFromMemory && b == q));
-            };
-            const unsigned hq = (head >> 8) & 0xffu, d0 = metas[0] >> 24, d1 = metas[1] >> 24;
-            decoder = (n_epi == 2 || n_epi == 3) && (metas[0] & 0xffu) == (unsigned)kGelu && ((metas[0] >> 8) & 0xffu) == hq &&
-                      add_of(metas[1], d0) && (n_epi == 2 || add_of(metas[2], d1));
-        }
-        if (any) {
-            SlotPtr at0[P], at1[P];
-            const void* t0[P];
-            const void* t1[P];
-#pragma unroll
-            for (int i = 0; i < P; i++) { at0[i] = slot_addr(a0[i], s0[i]); at1[i] = slot_addr(a1[i], s1[i]); }
-#pragma unroll
-            for (int i = 0; i < P; i++) { t0[i] = *at0[i]; t1[i] = *at1[i]; }
-            asm volatile("" : "+s"(t0[0]), "+s"(t1[0]), "+s"(t0[1]), "+s"(t1[1]), "+s"(t0[2]), "+s"(t1[2]));
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                if (s0[i]) a0[i] = t0[i];
-                if (s1[i]) a1[i] = t1[i];
-            }
-        }
-        const bf16_t* q0[P];
-        const bf16_t* q1[P];
-        unsigned mm[P];
-        bool plain = true;      // no operand has a broadcast period: the usual case, one branch for all
-#pragma unroll
-        for (int i = 0; i < P; i++) {
-            q0[i] = f0[i] ? static_cast<const bf16_t*>(a0[i]) : y;
-            q1[i] = f1[i] ? static_cast<const bf16_t*>(a1[i]) : y;
-            mm[i] = f1[i] ? ms[i] : total;
-            plain = plain && mm[i] == total;
-        }
-        if (__builtin_expect(plain, 1)) {
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                ld0[i] = load_raw_global_at(q0[i], idx);
-                ld1[i] = load_raw_global_at(q1[i], idx);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                ld0[i] = load_raw_global_at(q0[i], idx);
-                ld1[i] = load_raw_global_at(q1[i], idx % mm[i]);
-            }
-        }
-    };
+    const int j0 = (bid * (kBlock / 64) + __builtin_amdgcn_readfirstlane(tid >> 6)) * R;   // uniform: the weight rows' addresses stay in scalar registers
+    MmEpilogue<1> emit;
+    emit.y = m.y; emit.rows = RB; emit.n = n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     float sums[R * RB];
-    gemv_rows_sums<R, RB, U, EXACT, PRO>(W, h, n, cols, j0, lane, tid, hs, fetch, sums, gain, eps, hstore, part);
-    float v;
-    if constexpr (R * RB == 1) v = wave_sum(sums[0]);
-    else v = wave_sums<R * RB>(sums, lane);
-    unsigned bits = f32_to_bf16(v);
-    // The epilogue's operands have been on their way since before the weights were used; claim them all now,
-    // before the first store of the tail.  Loads and stores complete in one queue, in order, so a wait for
-    // an operand placed after a store would wait for that store to be acknowledged as well.
-    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
-    if (mine && (head & kEpiHeadStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(y + idx) = (unsigned short)bits;
-    float slot[kMergeSlots];
-#pragma unroll
-    for (int q = 0; q < kMergeSlots; q++) slot[q] = 0.f;
-    {
-        const unsigned dst = (head >> 8) & 0xffu;
-#pragma unroll
-        for (int q = 0; q < kMergeSlots; q++)
-            if (dst == (unsigned)q) slot[q] = from_raw<bf16_t>(bits);
-    }
-    if (__builtin_expect(decoder, 1)) {
-        // the same kernels with the same arithmetic and roundings, operands known: GELU of the GEMV's rounded result,
-        // then each add takes the value before it and its operand from memory, in the order its descriptor names
-        const bool st = mine;
-        float val = ew_apply<kGelu, false>(from_raw<bf16_t>(bits), 0.f);
-        bits = f32_to_bf16(val);
-        if (st && (inds[0] & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[0] + idx) = (unsigned short)bits;
-        val = from_raw<bf16_t>(bits);
-        {
-            const bool mem_first = ((metas[1] >> 8) & 0xffu) == kMergeFromMemory;
-            const float fa = mem_first ? from_raw<bf16_t>(ld0[1]) : val, fb = mem_first ? val : from_raw<bf16_t>(ld1[1]);
-            bits = f32_to_bf16(ew_apply<kAdd, false>(fa, fb));
-            if (st && (inds[1] & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[1] + idx) = (unsigned short)bits;
-            val = from_raw<bf16_t>(bits);
-        }
-        if (n_epi == 3) {
-            const bool mem_first = ((metas[2] >> 8) & 0xffu) == kMergeFromMemory;
-            const float fa = mem_first ? from_raw<bf16_t>(ld0[2]) : val, fb = mem_first ? val : from_raw<bf16_t>(ld1[2]);
-            bits = f32_to_bf16(ew_apply<kAdd, false>(fa, fb));
-            if (st && (inds[2] & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[2] + idx) = (unsigned short)bits;
-        }
-        return;
-    }
-    // Unrolled, with the one big choice (GELU or not) as the only branch inside a phase: a taken branch costs
-    // this one-wave-per-SIMD tail more than a dozen arithmetic instructions.
-#pragma unroll
-    for (int i = 0; i < P; i++) {
-        if (i >= n_epi) break;
-        const unsigned mt = metas[i], ind = inds[i];
-        const unsigned op = mt & 0xffu, src0 = (mt >> 8) & 0xffu, src1 = (mt >> 16) & 0xffu, dst = mt >> 24;
-        float fa = from_raw<bf16_t>(ld0[i]), fb = from_raw<bf16_t>(ld1[i]);
-#pragma unroll
-        for (int q = 0; q < kMergeSlots; q++) {
-            if (src0 == (unsigned)q) fa = slot[q];
-            if (src1 == (unsigned)q) fb = slot[q];
-        }
-        float fo;
-        if (op == kGelu) {
-            fo = ew_apply<kGelu, false>(fa, 0.f);
-        } else {
-            const float sum = ew_apply<kAdd, false>(fa, fb), prod = ew_apply<kMul, false>(fa, fb);
-            fo = op == kAdd ? sum : prod;
-        }
-        bits = f32_to_bf16(fo);
-        if (mine && (ind & kEpiStore)) *(unsigned short PG_GLOBAL*)(uintptr_t)(outs[i] + idx) = (unsigned short)bits;
-#pragma unroll
-        for (int q = 0; q < kMergeSlots; q++)
-            if (dst == (unsigned)q) slot[q] = from_raw<bf16_t>(bits);
-    }
+    gemv_rows_sums<R, RB, U, EXACT, PRO>(m.W, m.h, n, m.cols, j0, lane, tid, hs, [&] {
+        emit.prepare();
+        const int e = sums_index<R * RB>(lane);
+        emit.begin(e / R, j0 + e % R, lane < sums_lanes(R * RB) && e < R * RB);
+    }, sums, m.gain, emit.eps, hstore, part);
+    if constexpr (R * RB == 1) emit.put(0, wave_sum(sums[0]));
+    else emit.put(0, wave_sums<R * RB>(sums, lane));
+    emit.end();
 }
 
 // ---- host side: pick the instantiation and the launch shape from the kernel's shape alone ----------
@@ -1377,33 +1216,13 @@ bool plan_gemv_rs(int ind, int rows, int n, int cols, Launch* out) {
     return out->fn != nullptr;
 }
 
-template <bool FULL, bool SINGLE>
-const void* gemm_by_ind(int ind) {
-    switch (ind) {
-    case 0: return PG_FN(k_gemm_mfma_bf16<0, FULL, SINGLE>);
-    case 1: return PG_FN(k_gemm_mfma_bf16<1, FULL, SINGLE>);
-    case 2: return PG_FN(k_gemm_mfma_bf16<2, FULL, SINGLE>);
-    case 3: return PG_FN(k_gemm_mfma_bf16<3, FULL, SINGLE>);
-    default: return nullptr;
-    }
-}
-
-template <bool FULL, int NRH>
-const void* gemm_narrow_by_ind(int ind) {
-    switch (ind) {
-    case 0: return PG_FN(k_gemm_mfma_bf16_narrow<0, FULL, NRH>);
-    case 1: return PG_FN(k_gemm_mfma_bf16_narrow<1, FULL, NRH>);
-    case 2: return PG_FN(k_gemm_mfma_bf16_narrow<2, FULL, NRH>);
-    case 3: return PG_FN(k_gemm_mfma_bf16_narrow<3, FULL, NRH>);
-    default: return nullptr;
-    }
-}
+constexpr int kMmWideRows = 81;     // rows from which the 32 x 32 tile is used (see plan_gemm)
 
 // k_gemv_rows: up to 4 rows of h, rows of 8 to 8192 columns (all of a wave's loads are in registers at once);
 // two weight rows per wave once half the waves fill the chip, and only then rows beyond 2048 columns.
 constexpr int kRowsTwoFrom = 1024;
 bool rows_served(long long rows, long long n, long long cols) {
-    return rows >= 1 && rows <= 4 && n >= 1 && cols >= 8 && cols <= (n >= kRowsTwoFrom ? 8192 : 2048);
+    return rows >= 1 && rows <= 4 && n >= 1 && cols >= 8 && cols <= (n >= kRowsTwoFrom ? 8192 : 2048) && rows * n <= (1ll << 31);
 }
 template <bool PRO, int RB>
 const void* rows_kernel_rb(int n, int cols) {
@@ -1439,6 +1258,58 @@ const void* rows_kernel(int rows, int n, int cols) {
     }
 }
 
+// Matrix cores: from 5 rows on, rows of h of any length that element offsets within a tile reach (32 bits, as are the outputs' indices).
+bool mm_served(long long rows, long long n, long long cols) { return rows > 4 && n >= 16 && cols >= 8 && cols < (1ll << 24) && rows * n <= (1ll << 31); }
+
+template <int KS, bool TAIL, bool PRO>
+const void* gemm_rows_kernel(int rows) {
+    if (rows <= 8) return PG_FN(k_gemm_rows<KS, TAIL, 8, 8, PRO>);
+    if (rows <= 16) return PG_FN(k_gemm_rows<KS, TAIL, 16, 8, PRO>);
+    if constexpr (PRO) return PG_FN(k_gemm_rows<KS, TAIL, 16, 16, true>);
+    else return nullptr;
+}
+template <bool PRO>
+const void* gemm_rows_form(int rows, int cols) {
+    if (cols <= 1024) return cols == 1024 ? gemm_rows_kernel<8, false, PRO>(rows) : gemm_rows_kernel<8, true, PRO>(rows);
+    return cols == 2048 ? gemm_rows_kernel<16, false, PRO>(rows) : gemm_rows_kernel<16, true, PRO>(rows);
+}
+// merged: with an epilogue (and, pro, a prologue), in a captured graph; otherwise the stand-alone GEMV
+void plan_gemm(int rows, int n, int cols, bool merged, bool pro, Launch* out) {
+    const int ntiles = (rows + 15) / 16;
+    out->arg_bytes = sizeof(GemvEpiArgs);
+    out->block = dim3(kBlock);
+    out->gemm_row_groups = (unsigned)ntiles;
+    if (pro || (rows <= 16 && cols <= 2048)) {
+        out->fn = pro ? gemm_rows_form<true>(rows, cols) : gemm_rows_form<false>(rows, cols);
+        out->grid = rows <= 16 ? dim3(blocks_for(n, 8)) : dim3(blocks_for(n, 16) * (unsigned)ntiles);
+        return;
+    }
+    // (decode chain of 2048 columns at 48 / 64 rows: 1175 / 1188 us, with k_gemm_tile's 16 x 16 tiles 1254 / 1261)
+    if (cols <= 2048 && rows < kMmWideRows) {
+        out->gemm_row_groups = (unsigned)(ntiles < 4 ? ntiles : 4);
+        out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
+        if (cols <= 1024) out->fn = cols == 1024 ? PG_FN(k_gemm_cols<8, false>) : PG_FN(k_gemm_cols<8, true>);
+        else out->fn = cols == 2048 ? PG_FN(k_gemm_cols<16, false>) : PG_FN(k_gemm_cols<16, true>);
+        return;
+    }
+    // The largest tile that still gives every CU a workgroup, 32 x 32 from kMmWideRows rows.
+    const long long wide = blocks_for(n, 32), two = (ntiles + 1) / 2, four = (ntiles + 3) / 4;
+    if (merged) out->block = dim3(512);
+    if (ntiles > 2 && wide * four >= 256) {
+        out->fn = merged ? PG_FN(k_gemm_tile<4, 2, 1, 8>) : PG_FN(k_gemm_tile<4, 2, 2, 4>);
+        out->gemm_row_groups = (unsigned)four;
+        out->grid = dim3((unsigned)(wide * four));
+    } else if (rows >= kMmWideRows || (ntiles > 1 && wide * two >= 256)) {
+        out->fn = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8>) : PG_FN(k_gemm_tile<2, 2, 2, 4>);
+        out->gemm_row_groups = (unsigned)(two == 3 ? 4 : two);
+        out->grid = dim3((unsigned)wide * out->gemm_row_groups);
+    } else {
+        out->fn = merged ? PG_FN(k_gemm_tile<1, 1, 2, 8>) : PG_FN(k_gemm_tile<1, 1, 2, 4>);
+        out->gemm_row_groups = (unsigned)(ntiles < 4 ? ntiles : 4);
+        out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
+    }
+}
+
 template <typename T>
 bool plan_gemv_t(int ind, int rows, int n, int cols, Launch* out) {
     constexpr int NV = 16 / (int)sizeof(T);
@@ -1452,33 +1323,9 @@ bool plan_gemv_t(int ind, int rows, int n, int cols, Launch* out) {
             out->grid = dim3(blocks_for(n, (kBlock / 64) * (n >= kRowsTwoFrom ? 2 : 1)));
             return true;
         }
-        // A dense contraction: matrix cores from 5 rows on.
-        const bool narrow_ok = rows <= 16 && cols <= 32 * 4 * kMmSteps && n >= 16;
-        if (cols % 8 == 0 && rows > 4) {
-            out->block = dim3(kBlock);
-            // row groups of 16-row tiles: enough workgroups to fill the chip twice over at most
-            const int ntiles = (rows + 15) / 16;
-            out->gemm_row_groups = (unsigned)(ntiles < kMmMaxRowGroups ? ntiles : kMmMaxRowGroups);
-            out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
-            constexpr int kSuper = 32 * 4 * kMmSteps;   // columns one pass of the 4 waves covers
-            if (cols == kSuper && rows >= kMmWideRows && n >= 32) {
-                out->grid = dim3(blocks_for(n, 32) * out->gemm_row_groups);
-                switch (ind) {
-                case 0: out->fn = PG_FN(k_gemm_mfma_bf16_wide<0>); break;
-                case 1: out->fn = PG_FN(k_gemm_mfma_bf16_wide<1>); break;
-                case 2: out->fn = PG_FN(k_gemm_mfma_bf16_wide<2>); break;
-                case 3: out->fn = PG_FN(k_gemm_mfma_bf16_wide<3>); break;
-                default: out->fn = nullptr;
-                }
-            } else if (narrow_ok) {
-                out->grid = dim3(blocks_for(n, 8));
-                out->fn = cols == kSuper ? (rows <= 8 ? gemm_narrow_by_ind<true, 8>(ind) : gemm_narrow_by_ind<true, 16>(ind))
-                                         : (rows <= 8 ? gemm_narrow_by_ind<false, 8>(ind) : gemm_narrow_by_ind<false, 16>(ind));
-            } else if (cols == kSuper) out->fn = gemm_by_ind<true, true>(ind);
-            else if (cols < kSuper) out->fn = gemm_by_ind<false, true>(ind);
-            else if (cols % kSuper == 0) out->fn = gemm_by_ind<true, false>(ind);
-            else out->fn = gemm_by_ind<false, false>(ind);
-            return out->fn != nullptr;
+        if (mm_served(rows, n, cols)) {      // a dense contraction: matrix cores from 5 rows on
+            plan_gemm(rows, n, cols, false, false, out);
+            return true;
         }
     }
     if (cols % (64 * kGemvChunk * NV) == 0) return plan_gemv_rs<T, 0>(ind, rows, n, cols, out);
@@ -1496,32 +1343,22 @@ bool plan_gemv(int dtype, int ind, int rows, int n, int cols, Launch* out) {
 
 bool merge_head(int op, int dtype, const Shape& s, long long* n_out) {
     if (op != kGemv || dtype != kBF16 || s.rows < 1) return false;
-    if (s.rows <= 4) {
-        if (!rows_served(s.rows, s.n, s.cols)) return false;
-    } else {
-        // the matrix-core forms plan_gemv picks for rows of 2048 columns: narrow (up to 16 rows), 16 columns per
-        // workgroup, wide (from kMmWideRows rows)
-        if (s.cols != 64 * kGemvChunk * 8 || s.n < 32) return false;
-    }
-    if (s.rows * s.n > (1ll << 31)) return false;          // element indices are kept in 32 bits
+    if (s.rows <= 4 ? !rows_served(s.rows, s.n, s.cols) : !mm_served(s.rows, s.n, s.cols)) return false;
     *n_out = s.rows * s.n;
     return true;
 }
 
-static_assert(kPrologueMaxRows < kMmWideRows, "a prologue exists only where a workgroup owns one tile of rows");
-const void* gemv_epilogue_kernel(const Shape& s, bool with_prologue) {
-    const int rows = (int)s.rows;
-    if (rows <= 4) return with_prologue ? rows_kernel<true>(rows, (int)s.n, (int)s.cols) : rows_kernel<false>(rows, (int)s.n, (int)s.cols);
-    if (with_prologue) {
-        if (rows <= 8) return PG_FN(k_gemm_mfma_epilogue<0, true>);
-        if (rows <= 16) return PG_FN(k_gemm_mfma_epilogue<1, true>);
-        if (rows <= kPrologueMaxRows) return PG_FN(k_gemm_mfma_epilogue<2, true>);
-        return nullptr;
-    }
-    if (rows <= 8) return PG_FN(k_gemm_mfma_epilogue<0>);
-    if (rows <= 16) return PG_FN(k_gemm_mfma_epilogue<1>);
-    if (rows < kMmWideRows) return PG_FN(k_gemm_mfma_epilogue<2>);
-    return PG_FN(k_gemm_mfma_epilogue<3>);
+bool merge_prologue(const Shape& s) { return s.rows <= 4 || (s.rows <= kPrologueMaxRows && s.cols <= 2048); }
+
+void plan_gemv_epilogue(const Shape& s, bool with_prologue, Launch* out) {
+    const int rows = (int)s.rows, n = (int)s.n, cols = (int)s.cols;
+    out->mod_fn = nullptr;
+    out->gemm_row_groups = 0;
+    if (rows > 4) { plan_gemm(rows, n, cols, true, with_prologue, out); return; }
+    out->fn = with_prologue ? rows_kernel<true>(rows, n, cols) : rows_kernel<false>(rows, n, cols);
+    out->arg_bytes = sizeof(GemvEpiArgs);
+    out->block = dim3(kBlock);
+    out->grid = dim3(blocks_for(n, (kBlock / 64) * (n >= kRowsTwoFrom ? 2 : 1)));
 }
 
 }  // namespace pgk

@@ -120,9 +120,15 @@ constexpr unsigned kEpiHeadStore = 1u << 16;    // GemvEpiArgs::head: store the 
 constexpr unsigned kEpiPrologue = 1u << 17;     // h is not loaded but computed: RMSNorm of x with gain and eps
 constexpr unsigned kEpiXSlot = 1u << 18, kEpiGainSlot = 1u << 19;   // x / gain are pointer-table slots
 constexpr unsigned kEpiStoreH = 1u << 20;       // workgroup 0 stores the normalised rows to g.h
+// Worked out on the host, once (chain.hip, seal_epilogue).  In the table every operand has an address that can be read: one that comes
+// from a register slot, or does not exist, names the GEMV's output buffer, with the period rows * n.
+constexpr unsigned kEpiDecoder = 1u << 21;      // the kernels are GELU of the GEMV's result, then one or two adds with an operand from memory, which is in1
+constexpr unsigned kEpiMemFirst = 1u << 9;      // MergePhase::ind: that operand is the add's first
+constexpr unsigned kEpiAnySlot = 1u << 22;      // some operand of the epilogue is a pointer-table slot
+constexpr unsigned kEpiPlain = 1u << 23;        // no operand of the epilogue has a broadcast period
 struct GemvEpiArgs {
     GemvArgs g;             // with a prologue g.h is where the normalised rows are stored, not read
-    unsigned head;          // bit 0 / 1: W / h are pointer-table slots; bits 8-15: slot that keeps the GEMV's result; bits 16-20 above
+    unsigned head;          // bit 0 / 1: W / h are pointer-table slots; bits 8-15: slot that keeps the GEMV's result; bits 16-23 above
     int n_epi;
     const void* x;          // prologue: [rows, cols] to normalise
     const void* gain;       // prologue: [cols]
@@ -191,14 +197,15 @@ const void* merged_kernel(int dtype, bool narrow);
 bool sbr_run_candidate(int dtype, long long n, long long inner, long long channels);
 bool plan_sbr_run(int dtype, long long n, long long inner, Launch* out);
 // Is this a GEMV shape an epilogue form exists for?  bf16: up to 4 rows of h of 8 to 8192 columns (k_gemv_rows;
-// beyond 2048 columns only for n >= 1024), or 5 rows and more of 2048 columns (the matrix-core forms plan() picks
-// for such rows; n >= 32).  *n_out = rows * n.
+// beyond 2048 columns only for n >= 1024), 5 rows and more of 8 columns and more (the matrix-core forms; n >= 16).
+// *n_out = rows * n.
 bool merge_head(int op, int dtype, const Shape& shape, long long* n_out);
-// The epilogue form for a GEMV of that shape; launched with the grid and row groups plan() gives the plain GEMV of
-// the same shape.  A prologue exists up to kPrologueMaxRows rows (null otherwise).
-// Up to two tiles of 16 rows, one per workgroup, fill the 256 CUs once; beyond, two workgroups share a CU and each
+// ... and does it also take the RMSNorm in front?  The matrix-core forms up to 2048 columns, and up to kPrologueMaxRows rows:
+// two tiles of 16 rows, one per workgroup, fill the 256 CUs once; beyond, two workgroups share a CU and each
 // normalises its tile, which costs more than the dispatch it saves (decode chain at 48 rows: 1261 -> 1336 us).
 constexpr int kPrologueMaxRows = 32;
-const void* gemv_epilogue_kernel(const Shape& shape, bool with_prologue);
+bool merge_prologue(const Shape& shape);
+// The epilogue form for a GEMV of such a shape.
+void plan_gemv_epilogue(const Shape& shape, bool with_prologue, Launch* out);
 
 }  // namespace pgk

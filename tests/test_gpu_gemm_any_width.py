@@ -1,0 +1,69 @@
+"""Matrix-core GEMV dispatches at five rows and more of any width, around the edges of their forms: rows that end inside a
+vector, inside a K-block of 64 columns, on and around 1024 and 2048 columns (K-steps per wave; the prologue's limit),
+fewer K-blocks than waves, ragged column blocks, one and several tiles of rows, every tile size.  Graphs equal eager bit
+for bit and every kernel matches the oracle."""
+import pytest
+
+from gpu_util import Harness, same_bits, say, stepwise_check
+from pg_workloads import ChainSpec, KernelSpec, TensorSpec, Ref, EXT, INT, WEIGHT, decode_chain
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(h, rows=None):
+    for t in range(2):
+        x_np, x_dev = h.inputs(t)
+        outs = {}
+        for mode in ("eager", "copy", "indirect"):
+            h.scrub()
+            outs[mode] = h.run(mode, x_dev)
+        for o in range(len(h.spec.outputs)):
+            assert same_bits(outs["eager"][o], outs["copy"][o]) and same_bits(outs["eager"][o], outs["indirect"][o]), (t, o)
+    h.scrub()
+    stepwise_check(h, x_np, x_dev, rows=rows, rtol=2.0 ** -7)      # one bf16 ulp, every kernel
+    h.close()
+
+
+@pytest.mark.parametrize("rows,hidden", [(r, h) for h in (16, 31, 72, 520, 1023, 1024, 1030, 2047, 2056) for r in (5, 9, 16, 17, 32, 33, 64, 81, 100)] +
+                         [(r, h) for h in (127, 1016, 2041, 4096, 4107) for r in (8, 13, 25, 80, 130)])
+def test_square_chains(rows, hidden):
+    spec = decode_chain(batch=rows, layers=3, blocks_per_layer=1, hidden=hidden, n_ext=3)
+    h = Harness(spec, capture=False)
+    assert h.chain.graph_dispatches()[0] == (3 if rows <= 32 and hidden <= 2048 else 6)
+    h.chain.capture(h.stream)
+    _check(h, rows=sorted({0, rows // 2, rows - 1}))
+
+
+@pytest.mark.parametrize("rows,n,cols", [(6, 17, 40), (17, 4097, 33), (33, 8195, 136), (64, 8192, 200), (77, 8192, 71), (128, 8196, 64), (40, 4096, 72), (20, 8193, 1024),
+                                         (200, 40, 300), (96, 2050, 56), (11, 15, 64), (5, 300, 8)])
+def test_other_output_widths(rows, n, cols):
+    """RMSNorm -> GEMV -> GELU -> add -> add with a broadcast operand, n outputs per row; h then comes straight from
+    an external, at an address that is no multiple of 16 bytes."""
+    N, K = rows * n, rows * cols
+    ks = [KernelSpec("rmsnorm", "bf16", 0, (Ref(EXT, 0), Ref(WEIGHT, 1)), cols, rows=rows, cols=cols, eps=1e-6),
+          KernelSpec("gemv", "bf16", 1, (Ref(WEIGHT, 0), Ref(INT, 0)), n, rows=rows, cols=cols),
+          KernelSpec("gelu", "bf16", 1, (Ref(INT, 1),), N),
+          KernelSpec("add", "bf16", 2, (Ref(EXT, 1), Ref(INT, 1)), N, m=N),
+          KernelSpec("add", "bf16", 2, (Ref(INT, 2), Ref(WEIGHT, 2)), N, m=n),
+          KernelSpec("gemv", "bf16", 1, (Ref(WEIGHT, 0), Ref(EXT, 0)), n, rows=rows, cols=cols),
+          KernelSpec("mul", "bf16", 3, (Ref(INT, 1), Ref(INT, 2)), N, m=N)]
+    spec = ChainSpec(f"gemm_{rows}x{n}x{cols}", ks, [TensorSpec("bf16", K), TensorSpec("bf16", N)],
+                     [TensorSpec("bf16", K)] + [TensorSpec("bf16", N) for _ in range(3)],
+                     [TensorSpec("bf16", n * cols, ("normal", 0.0, 0.05)), TensorSpec("bf16", cols, ("normal", 1.0, 0.1)), TensorSpec("bf16", n)], [0, 1, 2, 3], 7200)
+    h = Harness(spec)
+    say(f"{spec.name}: {h.chain.graph_dispatches()}")
+    x_np, x_dev = h.inputs(5)
+    ref = h.run("eager", x_dev)
+    import torch
+    moved = []
+    for x in x_dev:
+        big = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)
+        big[1:1 + x.numel()].copy_(x)
+        moved.append(big[1:1 + x.numel()])
+    torch.cuda.synchronize()
+    for mode in ("eager", "copy", "indirect"):
+        h.scrub()
+        got = h.run(mode, moved)
+        for o in range(4):
+            assert same_bits(ref[o], got[o]), (mode, o)
+    _check(h)
