@@ -89,7 +89,11 @@ struct MergeGroup {
     bool pro = false;                // (head) kernel k0 is the RMSNorm that feeds the GEMV k0 + 1, and rides in front of it as a prologue
     int rename = -1;                 // (pro) internal buffer the RMSNorm reads and the run overwrites: the run writes its other copy
     bool sbr = false;                // the run is a chain of scale + bias + ReLU kernels
-    bool narrow = false;             // (not head) one 4-byte element per lane instead of a 16-byte vector
+    bool carry = false;              // the run hands on a carry (kernels.h, CarryRunArgs)
+    int carry_m = 0;                 // (carry) its period
+    unsigned carry_units = 0;        // (carry) CarryRunArgs::n_units
+    bool carry_aside = false;        // (carry) the first kernel's carry is what the run before set aside
+    bool narrow = false;             // (not head) 4 bytes per lane instead of a 16-byte vector
     long long n = 0;                 // elements every kernel of the run produces
     int gemv() const { return k0 + (pro ? 1 : 0); }
     // per kernel of the run: where its operands come from (a register slot or memory), which slot keeps its
@@ -139,6 +143,7 @@ struct pg_chain {
     std::vector<size_t> ph_off, int_off;
     std::vector<size_t> shadow_off;     // per internal buffer: its second copy (merged dispatches that rename), or kNoShadow
     size_t table_off = 0;
+    size_t carry_off = 0;               // two heads that runs with a carry set aside in turn
     std::vector<KernelRec> rec;
     std::vector<Segment> seg;
     std::vector<CopyList> copy_lists;   // [0] = all externals; then one per segment that has any
@@ -169,7 +174,7 @@ namespace {
 // ---- descriptor validation and layout ------------------------------------------------------------
 struct Layout {
     std::vector<size_t> ph_off, int_off, shadow_off;
-    size_t table_off = 0;
+    size_t table_off = 0, carry_off = 0;
     std::vector<CopyList> lists;
     std::vector<Segment> seg;
     size_t total = 0;
@@ -305,6 +310,11 @@ pgk::Shape shape_of(const pg_kernel_desc& d) {
 // gives the length of a kernel's scale vector).  Every lane carries its own elements from x to the last output, so a
 // run may overwrite the buffer it reads x from; a scale or bias that is an internal buffer must not be one that the
 // run writes.
+//
+// A fourth: bf16 add / mul / GELU kernels over tensors of their own lengths, whose second operand is the head of what the
+// kernel before wrote (kernels.h, CarryRunArgs).  A workgroup plays the whole run on its stretch of elements, so the
+// kernels' first operands must not be buffers that the run writes; the first kernel's carry may be one if the run
+// before set it aside.
 void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* ints, const std::vector<long long>& channels,
                  std::vector<MergeGroup>& out) {
     out.clear();
@@ -336,6 +346,41 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
         if (d.op == PG_ADD || d.op == PG_MUL) return j == 0 || (d.m ? d.m : d.n) == n;
         return j == 0;                                                  // GELU a, RMSNORM x
     };
+    auto carry_run = [&](int i, MergeGroup& g) {          // the run with a carry that starts at i; false if it is no longer than a kernel
+        std::vector<int> reads, written;
+        auto has = [](const std::vector<int>& v, int x) { return std::find(v.begin(), v.end(), x) != v.end(); };
+        long long m = 0;
+        int from = -1, e = i;                            // internal buffer the first kernel's carry comes from
+        bool aside = false;
+        for (; e < k1 && e < i + pgk::kCarryRunMax; e++) {
+            const pg_kernel_desc& d = k[e];
+            if (!pgk::carry_run_candidate(d.op, d.dtype, d.n)) break;
+            if (d.in[0].kind == PG_REF_INT && (has(written, d.in[0].index) || d.in[0].index == d.out.index)) break;
+            if (d.op != PG_GELU) {
+                const long long mm = d.m ? d.m : d.n;
+                if (mm < 8 || mm > pgk::kCarryMax || (mm & (mm - 1)) || (m && mm != m)) break;
+                if (e > i && !(d.in[1].kind == PG_REF_INT && d.in[1].index == k[e - 1].out.index && k[e - 1].n >= mm)) break;
+                if (e == i && d.in[1].kind == PG_REF_INT) from = d.in[1].index;
+                m = mm;
+            }
+            if (has(reads, d.out.index) || (d.in[0].kind == PG_REF_INT && d.in[0].index == from && from >= 0)) break;
+            if (d.out.index == from) {                   // overwrites what other workgroups may still be reading as their carry
+                const MergeGroup* before = out.empty() ? nullptr : &out.back();
+                if (!(before && before->carry && before->carry_m == m && k[before->k1 - 1].out.index == from && k[before->k1 - 1].n >= m)) break;
+                aside = true;
+            }
+            if (d.in[0].kind == PG_REF_INT) reads.push_back(d.in[0].index);
+            written.push_back(d.out.index);
+        }
+        if (e - i < 2 || m == 0) return false;
+        g.k0 = i;
+        g.k1 = e;
+        g.carry = true;
+        g.carry_m = (int)m;
+        g.carry_aside = aside;
+        for (int t = i; t < e; t++) g.n = std::max<long long>(g.n, k[t].n);
+        return true;
+    };
     // Is kernel i an RMSNorm of few rows straight into a GEMV of the epilogue kernels' shapes (its prologue)?
     auto prologue_at = [&](int i) {
         if (!(k[i].op == PG_RMSNORM && k[i].dtype == PG_BF16 && i + 1 < k1 && k[i].rows >= 1 && k[i].rows <= pgk::kPrologueMaxRows)) return false;
@@ -366,6 +411,11 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
             i = e;
             continue;
         }
+        if (carry_run(i, g)) {
+            out.push_back(g);
+            i = g.k1;
+            continue;
+        }
         const bool pro = prologue_at(i);
         const int hk = i + (pro ? 1 : 0);
         const bool head = pro || pgk::merge_head(k[i].op, k[i].dtype, shape_of(k[i]), &n);
@@ -387,7 +437,7 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
         int np = 0;
         int h_buf = -1;                              // (epilogue) the internal buffer the GEMV reads h from
         int x_buf = -1;                              // (prologue) the internal buffer the RMSNorm reads
-        const int max_phases = head ? pgk::kEpiMaxPhases + 1 + (pro ? 1 : 0) : pgk::kMergeMaxPhases;
+        const int max_phases = head ? pgk::kEpiMaxPhases + 1 + (pro ? 1 : 0) : pgk::merge_max_phases(k[i].dtype, n);
         if (head) {
             if (pro) {
                 if (k[i].in[0].kind == PG_REF_INT) x_buf = k[i].in[0].index;
@@ -472,6 +522,10 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
             g.store[a] = true;
             for (int t = a + 1; t < np; t++)
                 if (k[g.k0 + t].out.index == k[g.k0 + a].out.index) g.store[a] = false;
+        }
+        if (!head && k[g.k0].dtype == PG_BF16 && n <= pgk::kNarrowBf16Max) {
+            g.narrow = true;
+            for (int t = g.k0; t < i; t++) if (k[t].op == PG_RMSNORM) g.narrow = false;
         }
         if (head && np == 1) g.head = false;         // no prologue, no epilogue: the plain GEMV
         out.push_back(g);
@@ -573,6 +627,10 @@ void make_layout(const pg_kernel_desc* k, int nk, const pg_tensor_desc* ext, int
                 off = align_up(off + (size_t)ints[g.rename].numel * elem_bytes(ints[g.rename].dtype));
             }
     }
+    L.carry_off = off;
+    for (auto& sg : L.seg)
+        for (const auto& g : sg.groups)
+            if (g.carry && off == L.carry_off) off = align_up(off + 2 * 2 * (size_t)pgk::kCarryMax);
     for (auto& cl : L.lists) {
         build_copy_list(cl, ext, L.ph_off, ws);
         cl.tensors_off = off; off = align_up(off + std::max<size_t>(1, cl.tensors.size()) * sizeof(pgk::CopyTensor));
@@ -675,14 +733,16 @@ pg_status make_records(pg_chain* c) {
             if (g.k1 - g.k0 < 2) continue;
             g.launch = pgk::Launch();
             g.launch.block = dim3(256);
-            if (g.sbr) {
+            if (g.carry) {
+                pgk::plan_carry_run(g.n, &g.launch, &g.carry_units);
+            } else if (g.sbr) {
                 if (!pgk::plan_sbr_run(c->k[g.k0].dtype, g.n, c->k[g.k0].inner, &g.launch)) return fail(PG_EINVAL, "kernel %d: no kernel for this run", g.k0);
             } else if (g.head) {
                 pgk::plan_gemv_epilogue(shape_of(c->k[g.gemv()]), g.pro, &g.launch);
             } else {
-                g.launch.fn = pgk::merged_kernel(c->k[g.k0].dtype, g.narrow);
+                g.launch.fn = pgk::merged_kernel(c->k[g.k0].dtype, g.narrow, g.k1 - g.k0);
                 g.launch.arg_bytes = sizeof(pgk::MergedArgs);
-                const long long nvec = g.narrow ? g.n : g.n / (c->k[g.k0].dtype == PG_F32 ? 4 : 8);
+                const long long nv = (g.narrow ? 4 : 16) / (long long)elem_bytes(c->k[g.k0].dtype), nvec = (g.n + nv - 1) / nv;
                 g.launch.grid = dim3((unsigned)((nvec + 255) / 256));       // one workgroup per unit of 256 lanes x 16 bytes
             }
             if (!g.launch.fn) return fail(PG_EINVAL, "kernel %d: no merged kernel for this run", g.k0);
@@ -917,6 +977,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
         if (second[d.out.index] != renamed) a.ptr[0] = in_copy(d.out.index, true);
         return a;
     };
+    int n_carry = 0;                      // runs with a carry so far: two places for what they set aside, in turn
     for (auto& grp : sg.groups) {
         if (le != hipSuccess) break;
         if (!c->merge || grp.k1 - grp.k0 < 2) {
@@ -925,6 +986,36 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
                 ArgBlock a = versioned(i, nullptr);
                 le = launch(kind == kGraphCopy ? r.direct : r.indirect, &a, s);
             }
+            continue;
+        }
+        if (grp.carry) {
+            pgk::CarryRunArgs m;
+            memset(&m, 0, sizeof m);
+            auto place = [&](int i) { return c->ws + c->carry_off + (size_t)(i & 1) * 2 * pgk::kCarryMax; };
+            m.m = (unsigned)grp.carry_m;
+            m.n_units = grp.carry_units;
+            m.n_blocks = grp.launch.grid.x;
+            for (int i = grp.k0; i < grp.k1; i++, m.n_phase++) {
+                KernelRec& r = c->rec[i];
+                const pg_kernel_desc& d = c->k[i];
+                const ArgBlock a = versioned(i, nullptr);
+                const unsigned slots = kind == kGraphCopy ? 0u : (unsigned)r.ind_mask;
+                pgk::CarryPhase& ph = m.ph[m.n_phase];
+                ph.out = const_cast<void*>(a.ptr[0]);
+                ph.in0 = a.ptr[1];
+                ph.n = (unsigned)d.n;
+                ph.op = (unsigned)d.op;
+                ph.ind = slots & 1u;
+                for (int t = i + 1; t < grp.k1; t++) if (c->k[t].out.index == d.out.index) ph.cover = std::max(ph.cover, (unsigned)c->k[t].n);
+                if (i == grp.k0 && d.op != PG_GELU) {
+                    m.carry_in = grp.carry_aside ? place(n_carry + 1) : a.ptr[2];
+                    m.flags = grp.carry_aside ? 0u : (slots >> 1) & 1u;
+                }
+            }
+            if (c->k[grp.k1 - 1].n >= grp.carry_m) m.carry_out = place(n_carry);
+            n_carry++;
+            for (int q = m.n_phase; q < pgk::kCarryRunMax; q++) { m.ph[q] = m.ph[0]; m.ph[q].n = 0; }
+            le = launch(grp.launch, &m, s);
             continue;
         }
         if (grp.sbr) {
@@ -1141,6 +1232,7 @@ pg_status build_chain(const pg_kernel_desc* kernels, int32_t nk, const pg_tensor
     c->int_off = std::move(L.int_off);
     c->shadow_off = std::move(L.shadow_off);
     c->table_off = L.table_off;
+    c->carry_off = L.carry_off;
     c->copy_lists = std::move(L.lists);
     c->seg = std::move(L.seg);
     st = make_records(c);

@@ -160,6 +160,7 @@ __device__ __forceinline__ void store_vec_global(void* p, const unsigned* w) {
 }
 // 16 bytes at any element boundary: one load or store instruction all the same
 typedef v4u v4u_any __attribute__((aligned(2)));
+typedef unsigned u32_any __attribute__((aligned(2)));      // and 4
 // A pointer-table slot, or the tensor address itself: decided at run time (the merged kernels; the
 // stand-alone ones decide at compile time, resolve<IND>).  The slot is read as constant memory -- nothing
 // writes the table while a graph runs -- which makes it a scalar load that no vector-memory wait covers.

@@ -80,7 +80,9 @@ struct TableArgs {
 // the storage type, stores its output unless a later kernel of the run overwrites it, and hands the stored bits on to the next kernel in
 // registers when that kernel reads the same buffer element for element -- so the run costs one trip
 // to memory, not one per kernel.  Operands that no kernel of the run produces are fetched up front.
-constexpr int kMergeMaxPhases = 4;        // kernels per merged dispatch
+constexpr int kMergeShortPhases = 4;      // kernels per merged dispatch
+constexpr int kMergeMaxPhases = 8;        // ... of bf16 kernels from kMergeLongFrom elements on
+constexpr long long kMergeLongFrom = 16384;
 constexpr int kMergeSlots = 3;            // outputs a lane keeps in registers for later kernels of the run
 constexpr unsigned kMergeFromMemory = 255;
 
@@ -96,7 +98,7 @@ struct MergePhase {
     unsigned ind;           // bit 0 / 1: in0 / in1 hold the address of a pointer-table slot
 };
 struct MergedArgs {
-    unsigned n;             // elements every kernel of the run produces (a whole number of 16-byte vectors)
+    unsigned n;             // elements every kernel of the run produces
     int n_phase;
     MergePhase ph[kMergeMaxPhases];   // entries from n_phase on: meta says "operands from slots", nothing is fetched
 };
@@ -160,6 +162,31 @@ struct SbrRunArgs {
     SbrRunPhase ph[kSbrRunMax];
 };
 
+// A run of bf16 add / mul / GELU kernels, each over a tensor of its own length from memory, whose second operand (add, mul) is the
+// head of what the kernel before wrote, repeated with a short period: one dispatch.  The head of the run's last output
+// is also set aside for the run behind it, which cannot read it from the buffer while other workgroups overwrite that.
+constexpr int kCarryRunMax = 8;             // kernels per run
+constexpr int kCarryMax = 512;              // elements of a carry (two per lane of a workgroup); a power of two from 8 on
+struct CarryPhase {
+    void* out;
+    const void* in0;
+    unsigned n;
+    unsigned cover;         // elements of the output that later kernels of the run overwrite
+    unsigned op;
+    unsigned ind;           // bit 0: in0 is a pointer-table slot
+};
+struct CarryRunArgs {
+    const void* carry_in;   // the first kernel's second operand, or null
+    void* carry_out;        // where the last kernel's head is set aside, or null
+    unsigned m;             // the period
+    unsigned flags;         // bit 0: carry_in is a pointer-table slot
+    int n_phase;
+    unsigned n_units;       // units of 256 lanes in the longest kernel; workgroup b of n_blocks takes b, b + n_blocks, ...
+    unsigned n_blocks;
+    unsigned reserved;
+    CarryPhase ph[kCarryRunMax];    // entries from n_phase on: the first kernel's operand, n = 0
+};
+
 struct Launch {
     const void* fn = nullptr;        // host-side kernel handle
     hipFunction_t mod_fn = nullptr;  // the same kernel as a module function, resolved on first launch
@@ -182,7 +209,7 @@ const void* copy_kernel();
 const void* table_kernel();
 // Can this kernel be part of a merged dispatch?  From op, dtype and shape alone.  On success *n_out is
 // the number of elements it produces (all kernels of a run must agree on it and on the dtype).
-// whole_vectors: n must be a whole number of 16-byte vectors (runs of one workgroup per unit; a GEMV's
+// whole_vectors: fp32 tensors must be a whole number of 16-byte vectors (runs of one workgroup per unit; a GEMV's
 // epilogue works element by element and takes any n).
 bool merge_candidate(int op, int dtype, const Shape& shape, bool whole_vectors, long long* n_out);
 // Runs over small fp32 tensors work one element (4 bytes) per lane instead of a 16-byte vector: such
@@ -191,7 +218,14 @@ bool merge_candidate(int op, int dtype, const Shape& shape, bool whole_vectors, 
 // of 256 lanes x 16 bytes).
 constexpr long long kMergeNarrowMax = 16384;        // elements
 bool merge_narrow(int dtype, long long n);
-const void* merged_kernel(int dtype, bool narrow);
+// bf16 runs without an RMSNorm up to this many elements work on 4 bytes (two elements) per lane as well: a lane's elements
+// are worked out one after the other, and such a tensor makes few waves.
+constexpr long long kNarrowBf16Max = 1ll << 19;
+int merge_max_phases(int dtype, long long n);
+const void* merged_kernel(int dtype, bool narrow, int phases);
+// Can this kernel be part of a run with a carry (its operands aside)?  And the launch of a run whose longest kernel has n elements.
+bool carry_run_candidate(int op, int dtype, long long n);
+void plan_carry_run(long long n, Launch* out, unsigned* n_units);
 // Can this scale + bias + ReLU kernel be part of a run of such kernels?  A 16-byte vector may touch two channels at
 // most, the tables of all channels fit the run's LDS, and element indices fit 32 bits.
 bool sbr_run_candidate(int dtype, long long n, long long inner, long long channels);

@@ -373,17 +373,33 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm(RmsArgs p) {
 // conditional moves (one copy of the GELU and of the RMSNorm reduction for up to four kernels; an
 // unrolled form with every operand choice resolved at run time by branches was slower: a taken branch
 // costs a one-wave-per-SIMD kernel about as much as a dozen arithmetic instructions).
+// bf16 tensors of any length: the workgroup that owns the last, partial vector fetches element by element.  64 kernels on
+// 100003 bf16 elements: 154 us per iteration with a dispatch each, 81 in runs of eight on 16 bytes per lane, 52 on 4 bytes.
 
-template <typename T, int VB, bool AL>
+template <typename T, int VB, int P, bool TAIL>
 __device__ __forceinline__ void merged_body(const MergedArgs& p, const T* const* in0, const T* const* in1, float* part) {
     using V = Vec<T, VB>;
     constexpr int NV = V::NV, NW = VB / 4;
-    auto fetch = [](const T* q, unsigned* w) {
-        if constexpr (VB == 16) load_vec_global<T, AL>(q, w);
-        else load_vec4_global<T, AL>(q, w);
+    const unsigned n = p.n, nvec = n / NV, left = n - nvec * NV;      // left: elements of a last, partial vector
+    // TAIL: the workgroup that owns the partial vector fetches element by element (none past the end)
+    auto fetch = [](const T* q, unsigned room /* elements from q to the end of the tensor */, unsigned* w) {
+        if constexpr (VB == 4 && !TAIL) {
+            w[0] = *(const u32_any PG_GLOBAL*)(uintptr_t)q;
+        } else if constexpr (!TAIL) {
+            const v4u t = *(const v4u_any PG_GLOBAL*)(uintptr_t)q;
+            w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < NW; k++) w[k] = 0u;
+#pragma unroll
+            for (int e = 0; e < NV; e++) {
+                const unsigned r = load_raw_global(q + ((unsigned)e < room ? (unsigned)e : room - 1));
+                if constexpr (sizeof(T) == 4) w[e] = r;
+                else w[e / 2] |= r << (16 * (e & 1));
+            }
+        }
     };
     constexpr bool kWide = sizeof(T) == 4;
-    constexpr int P = kMergeMaxPhases;
     const unsigned tid = threadIdx.x;
     // the run's table, once, in scalar registers (read inside the loop below it would be indexed memory)
     T* outs[P];
@@ -396,25 +412,39 @@ __device__ __forceinline__ void merged_body(const MergedArgs& p, const T* const*
         inds[i] = p.ph[i].ind;
         epss[i] = p.ph[i].eps;
     }
-    const unsigned n = p.n, nvec = n / NV;
     const unsigned v = blockIdx.x * kBlock + tid;
-    const bool act = v < nvec;
-    const unsigned i0 = (act ? v : nvec - 1) * NV;
+    const bool act = v < nvec || (TAIL && v == nvec);
+    const unsigned i0 = (act ? v : nvec - (nvec ? 1u : 0u)) * NV;
+    const unsigned mine = TAIL && v == nvec ? left : (unsigned)NV;     // elements this lane owns
+    auto put = [&](T* out, const unsigned* w) {
+        if (!TAIL || mine == (unsigned)NV) {
+            if constexpr (VB == 4) *(unsigned PG_GLOBAL*)(uintptr_t)(out + i0) = w[0];
+            else store_vec_global(out + i0, w);
+        } else {
+#pragma unroll
+            for (int e = 0; e < NV - 1; e++)
+                if ((unsigned)e < mine) {
+                    if constexpr (sizeof(T) == 4) *(unsigned PG_GLOBAL*)(uintptr_t)(out + i0 + e) = w[e];
+                    else *(unsigned short PG_GLOBAL*)(uintptr_t)(out + i0 + e) = (unsigned short)(w[e / 2] >> (16 * (e & 1)));
+                }
+        }
+    };
     unsigned ld0[P][NW], ld1[P][NW];
 #pragma unroll
     for (int i = 0; i < P; i++) {
         const unsigned mt = metas[i], op = mt & 0xffu;
         if (((mt >> 8) & 0xffu) == kMergeFromMemory) {
-            fetch(in0[i] + i0, ld0[i]);
+            fetch(in0[i] + i0, n - i0, ld0[i]);
         } else {
 #pragma unroll
             for (int k = 0; k < NW; k++) ld0[i][k] = 0u;
         }
         if (op != kGelu && ((mt >> 16) & 0xffu) == kMergeFromMemory) {
             const unsigned m = p.ph[i].m;
-            if (op == kRmsNorm || m % NV == 0) {
+            if (op == kRmsNorm || m == n || m % NV == 0) {
                 // RMSNorm: a row is one unit, lane t holds vector t of the gain; add / mul: a vector of b never wraps around the period
-                fetch(in1[i] + (op == kRmsNorm ? tid * NV : (m == n ? i0 : i0 % m)), ld1[i]);
+                const unsigned at = op == kRmsNorm ? tid * NV : (m == n ? i0 : i0 % m);
+                fetch(in1[i] + at, m == n && op != kRmsNorm ? n - i0 : (unsigned)NV, ld1[i]);
             } else {
 #pragma unroll
                 for (int k = 0; k < NW; k++) ld1[i][k] = 0u;
@@ -481,10 +511,7 @@ __device__ __forceinline__ void merged_body(const MergedArgs& p, const T* const*
                     }
                 }
                 V::pack(fo, w);
-                if (act && (inds[i] & kEpiStore)) {
-                    if constexpr (VB == 16) store_vec_global(outs[i] + i0, w);
-                    else *(unsigned PG_GLOBAL*)(uintptr_t)(outs[i] + i0) = w[0];
-                }
+                if (act && (inds[i] & kEpiStore)) put(outs[i], w);
             }
             return;
         }
@@ -547,10 +574,7 @@ __device__ __forceinline__ void merged_body(const MergedArgs& p, const T* const*
             }
         }
         V::pack(fo, wo);
-        if (act && (ind & kEpiStore)) {      // not stored: a later kernel of the run overwrites it, and nothing reads memory in between
-            if constexpr (VB == 16) store_vec_global(out + i0, wo);
-            else *(unsigned PG_GLOBAL*)(uintptr_t)(out + i0) = wo[0];
-        }
+        if (act && (ind & kEpiStore)) put(out, wo);      // else a later kernel of the run overwrites it, and nothing reads memory in between
 #pragma unroll
         for (int q = 0; q < kMergeSlots; q++)
             if (dst == (unsigned)q)
@@ -559,29 +583,150 @@ __device__ __forceinline__ void merged_body(const MergedArgs& p, const T* const*
     }
 }
 
-template <typename T, int VB>
+template <typename T, int VB, int P>
 __global__ __launch_bounds__(kBlock) void k_merged(MergedArgs p) {
-    constexpr int P = kMergeMaxPhases;
     __shared__ float part[kBlock / 64];
     // operand addresses, once, before any store of this kernel: pointer-table slots are read with scalar loads
     const T* in0[P];
     const T* in1[P];
-    bool al = true;
 #pragma unroll
     for (int i = 0; i < P; i++) {
         in0[i] = in1[i] = nullptr;
         const unsigned mt = p.ph[i].meta;
         if (((mt >> 8) & 0xffu) == kMergeFromMemory) {
             in0[i] = static_cast<const T*>(resolve_rt(p.ph[i].in0, p.ph[i].ind & 1));
-            al = al && aligned_to(in0[i], VB);
         }
         if ((mt & 0xffu) != kGelu && ((mt >> 16) & 0xffu) == kMergeFromMemory) {
             in1[i] = static_cast<const T*>(resolve_rt(p.ph[i].in1, p.ph[i].ind & 2));
-            al = al && aligned_to(in1[i], VB);
         }
     }
-    if (__builtin_expect(al, 1)) merged_body<T, VB, true>(p, in0, in1, part);
-    else merged_body<T, VB, false>(p, in0, in1, part);
+    constexpr unsigned NV = Vec<T, VB>::NV;
+    const bool tail = NV > 1 && p.n % NV != 0 && blockIdx.x == p.n / NV / kBlock;
+    if (__builtin_expect(!tail, 1)) merged_body<T, VB, P, false>(p, in0, in1, part);
+    else if constexpr (NV > 1) merged_body<T, VB, P, true>(p, in0, in1, part);
+}
+
+// ---- runs of kernels that hand on a short carry ---------------------------------------------------------------
+// kernels.h, CarryRunArgs.  What bounds the kernels one by one is their dispatch (3 us a kernel, of which 1.5 the graph's
+// node), since all that makes one wait for the next is the head of its output, m <= 512 elements.  Here every workgroup
+// works that chain of heads out for itself -- two elements a lane, no lane needs another's -- and keeps each kernel's
+// carry in LDS; then it plays all kernels on its own stretch of elements, in order, so that what two of them write to the
+// same place lands in order.  Same arithmetic, one rounding per kernel.  VB bytes per lane: 4 for short
+// tensors (at one wave per SIMD eight elements a lane and kernel in sequence cost more than the memory trip), 16 for long ones,
+// where a workgroup takes every n_blocks-th unit, so that the units that all kernels have (the low ones) are spread out.
+// 256 tensors of 1 KB to 16 MB refreshed by copy and read by 256 kernels: 922 -> 574 us per iteration, of which the copies are 146
+// (four neighbouring units per workgroup 681); 96 tensors up to 1 MB through the pointer table 197 -> 82 (16 bytes per lane 99).
+template <int OP_MAX>
+__device__ __forceinline__ float carry_apply(unsigned op, float a, float b) {
+    static_assert(OP_MAX == kGelu, "add, mul, GELU");
+    if (op == (unsigned)kGelu) return ew_apply<kGelu, false>(a, 0.f);
+    const float sum = ew_apply<kAdd, false>(a, b), prod = ew_apply<kMul, false>(a, b);
+    return op == (unsigned)kAdd ? sum : prod;
+}
+template <int VB>
+__global__ __launch_bounds__(kBlock) void k_carry_run(CarryRunArgs p) {
+    using V = Vec<bf16_t, VB>;
+    constexpr int NV = V::NV, NW = V::NW;
+    constexpr int P = kCarryRunMax;
+    __shared__ __attribute__((aligned(16))) unsigned carry[P + 1][kCarryMax / 2];      // [i]: what kernel i takes; [i + 1]: what it hands on
+    using SlotPtr = const void* const PG_CONSTANT*;
+    const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();
+    const unsigned tid = threadIdx.x, m = p.m;
+    const int np = p.n_phase;
+    // operand addresses, slots resolved, in two batches of scalar loads (entries from n_phase on repeat the first)
+    const bf16_t* in[P];
+    const void* cin = p.carry_in;
+    {
+        SlotPtr at[P], atc = (p.flags & 1u) ? (SlotPtr)(uintptr_t)cin : (SlotPtr)ka;
+        const void* t[P];
+#pragma unroll
+        for (int i = 0; i < P; i++) at[i] = (p.ph[i].ind & 1u) ? (SlotPtr)(uintptr_t)p.ph[i].in0 : (SlotPtr)ka;
+#pragma unroll
+        for (int i = 0; i < P; i++) t[i] = *at[i];
+        const void* tc = *atc;
+#pragma unroll
+        for (int i = 0; i < P; i++) in[i] = static_cast<const bf16_t*>((p.ph[i].ind & 1u) ? t[i] : p.ph[i].in0);
+        if (p.flags & 1u) cin = tc;
+    }
+    unsigned w[P][NW];
+    auto fetch = [&](unsigned v) {
+#pragma unroll
+        for (int i = 0; i < P; i++) {
+#pragma unroll
+            for (int k = 0; k < NW; k++) w[i][k] = 0u;
+            if (v < p.ph[i].n / NV) {
+                if constexpr (VB == 16) {
+                    const v4u t = *(const v4u_any PG_GLOBAL*)(uintptr_t)(in[i] + (size_t)v * NV);
+                    w[i][0] = t.x; w[i][1] = t.y; w[i][2] = t.z; w[i][3] = t.w;
+                } else {
+                    w[i][0] = *(const u32_any PG_GLOBAL*)(uintptr_t)(in[i] + (size_t)v * NV);
+                }
+            }
+        }
+    };
+    // the heads first, then the first unit's elements
+    const bool chain = 2 * tid < m;
+    unsigned hd[P], c = 0u;
+#pragma unroll
+    for (int i = 0; i < P; i++) {
+        hd[i] = 0u;
+        if (chain && 2 * tid < p.ph[i].n) hd[i] = load_raw_global(in[i] + 2 * tid) | (load_raw_global(in[i] + 2 * tid + 1) << 16);
+    }
+    if (chain && cin) c = load_raw_global(static_cast<const bf16_t*>(cin) + 2 * tid) | (load_raw_global(static_cast<const bf16_t*>(cin) + 2 * tid + 1) << 16);
+    fetch(blockIdx.x * (unsigned)kBlock + tid);
+    if (chain) {
+        carry[0][tid] = c;
+#pragma unroll
+        for (int i = 0; i < P; i++) {
+            if (i < np) {
+                const unsigned op = p.ph[i].op;
+                c = pack2_bf16(carry_apply<kGelu>(op, __uint_as_float(hd[i] << 16), __uint_as_float(c << 16)),
+                               carry_apply<kGelu>(op, __uint_as_float(hd[i] & 0xffff0000u), __uint_as_float(c & 0xffff0000u)));
+                carry[i + 1][tid] = c;
+            }
+        }
+    }
+    lds_barrier();
+    if (chain && p.carry_out && blockIdx.x == 0) *(unsigned PG_GLOBAL*)((unsigned PG_GLOBAL*)(uintptr_t)p.carry_out + tid) = c;
+    const unsigned cv = (tid % (m / NV)) * NW;             // this lane's vector of a carry: a unit is a whole number of periods
+#pragma unroll 1
+    for (unsigned unit = blockIdx.x; unit < p.n_units; unit += p.n_blocks) {
+        const unsigned v = unit * (unsigned)kBlock + tid;
+        unsigned cur[P][NW];
+#pragma unroll
+        for (int i = 0; i < P; i++)
+#pragma unroll
+            for (int k = 0; k < NW; k++) cur[i][k] = w[i][k];
+        if (unit + p.n_blocks < p.n_units) fetch(v + p.n_blocks * (unsigned)kBlock);      // the next unit's elements under this one's arithmetic
+#pragma unroll
+        for (int i = 0; i < P; i++) {
+            if (i < np && unit * (unsigned)(kBlock * NV) < p.ph[i].n) {
+                const unsigned op = p.ph[i].op;
+                float fa[NV], fb[NV], fo[NV];
+                unsigned wb[NW], wo[NW];
+                V::unpack(cur[i], fa);
+                if (op == (unsigned)kGelu) {
+#pragma unroll
+                    for (int e = 0; e < NV; e++) fo[e] = ew_apply<kGelu, false>(fa[e], 0.f);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < NW; k++) wb[k] = carry[i][cv + k];
+                    V::unpack(wb, fb);
+#pragma unroll
+                    for (int e = 0; e < NV; e++) {
+                        const float sum = ew_apply<kAdd, false>(fa[e], fb[e]), prod = ew_apply<kMul, false>(fa[e], fb[e]);
+                        fo[e] = op == (unsigned)kAdd ? sum : prod;
+                    }
+                }
+                V::pack(fo, wo);
+                // not stored: a later kernel of the run overwrites it, and nothing reads it in between
+                if (v < p.ph[i].n / NV && v >= p.ph[i].cover / NV) {
+                    if constexpr (VB == 16) store_vec_global(static_cast<bf16_t*>(p.ph[i].out) + (size_t)v * NV, wo);
+                    else *(unsigned PG_GLOBAL*)(uintptr_t)(static_cast<bf16_t*>(p.ph[i].out) + (size_t)v * NV) = wo[0];
+                }
+            }
+        }
+    }
 }
 
 // ---- batched multi-tensor copy -----------------------------------------------------------------
@@ -789,17 +934,34 @@ bool merge_candidate(int op, int dtype, const Shape& s, bool whole_vectors, long
     } else {
         return false;
     }
-    if (n <= 0 || (whole_vectors && !merge_narrow(dtype, n) && n % nv != 0) || n > (1ll << 31)) return false;
+    // fp32 tensors of a ragged length beyond the narrow form's keep a dispatch per kernel
+    if (n <= 0 || (whole_vectors && dtype == kF32 && !merge_narrow(dtype, n) && n % nv != 0) || n > (1ll << 31)) return false;
     *n_out = n;
     return true;
 }
 
 bool merge_narrow(int dtype, long long n) { return dtype == kF32 && n > 0 && n <= kMergeNarrowMax; }
 
-const void* merged_kernel(int dtype, bool narrow) {
-    if (dtype == kF32) return narrow ? reinterpret_cast<const void*>(&k_merged<float, 4>) : reinterpret_cast<const void*>(&k_merged<float, 16>);
-    if (dtype == kBF16 && !narrow) return reinterpret_cast<const void*>(&k_merged<bf16_t, 16>);
-    return nullptr;
+int merge_max_phases(int dtype, long long n) { return dtype == kBF16 && n >= kMergeLongFrom ? kMergeMaxPhases : kMergeShortPhases; }
+
+const void* merged_kernel(int dtype, bool narrow, int phases) {
+    if (dtype == kF32) return narrow ? PG_FN(k_merged<float, 4, kMergeShortPhases>) : PG_FN(k_merged<float, 16, kMergeShortPhases>);
+    if (dtype != kBF16) return nullptr;
+    if (narrow) return phases <= kMergeShortPhases ? PG_FN(k_merged<bf16_t, 4, kMergeShortPhases>) : PG_FN(k_merged<bf16_t, 4, kMergeMaxPhases>);
+    return phases <= kMergeShortPhases ? PG_FN(k_merged<bf16_t, 16, kMergeShortPhases>) : PG_FN(k_merged<bf16_t, 16, kMergeMaxPhases>);
+}
+
+bool carry_run_candidate(int op, int dtype, long long n) {
+    return (op == kAdd || op == kMul || op == kGelu) && dtype == kBF16 && n > 0 && n % 8 == 0 && n < (1ll << 31);
+}
+void plan_carry_run(long long n, Launch* out, unsigned* n_units) {
+    const bool narrow = n <= kNarrowBf16Max;
+    const long long units = (n / (narrow ? 2 : 8) + kBlock - 1) / kBlock;
+    out->arg_bytes = sizeof(CarryRunArgs);
+    out->block = dim3(kBlock);
+    out->fn = narrow ? PG_FN(k_carry_run<4>) : PG_FN(k_carry_run<16>);
+    out->grid = dim3((unsigned)(units < 1024 ? units : 1024));
+    *n_units = (unsigned)units;
 }
 
 // One vector per lane until that makes four workgroups per CU, eight per lane from there on.
