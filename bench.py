@@ -252,7 +252,7 @@ def main() -> int:
     hb = profile_figures("gemv_and_copy_kernel_hbm_traffic.md")
     how = ("HIP events on the launch stream around 50 replays of a graph of the chain's 120 launches of this kernel (and one small add that "
            "initialises the stream, counted as a launch); the time per launch includes the dispatch gap between two dependent launches")
-    roofline = {"kernel": "k_gemv_epilogue<1, prologue>: bf16 GEMV 2048x2048, batch 1, with the RMSNorm as its prologue and GELU and the residual add as its epilogue (a decode sub-block in one graph node; the dominant kernel of graph replay)",
+    roofline = {"kernel": "k_gemv_rows<2, 1, 4, prologue>: bf16 GEMV 2048x2048, batch 1, with the RMSNorm as its prologue and GELU and the residual add as its epilogue (a decode sub-block in one graph node; the dominant kernel of graph replay)",
                 "bound": "hbm", "achieved": epi_bytes / epi_us / 1e3, "peak": HBM_PEAK, "unit": "GB/s", "frac": epi_bytes / epi_us / 1e3 / HBM_PEAK,
                 "frac_denominator": "avg_launch_us: " + how,
                 "bytes_per_launch": epi_bytes, "avg_launch_us": epi_us, "launches_timed": reps * epi_nodes,
