@@ -1258,8 +1258,10 @@ const void* rows_kernel(int rows, int n, int cols) {
     }
 }
 
-// Matrix cores: from 5 rows on, rows of h of any length that element offsets within a tile reach (32 bits, as are the outputs' indices).
-bool mm_served(long long rows, long long n, long long cols) { return rows > 4 && n >= 16 && cols >= 8 && cols < (1ll << 24) && rows * n <= (1ll << 31); }
+// Matrix cores: from 5 rows on, any number of outputs per row (us per launch on the matrix cores / the vector units: 128 rows
+// of 2048 columns, 8 outputs 6.8 / 31; 64 of 4096, 12 outputs 6.6 / 25.8), rows of h of any length that element offsets
+// within a tile of 64 rows reach (32 bits, as are the outputs' indices).
+bool mm_served(long long rows, long long n, long long cols) { return rows > 4 && cols >= 8 && cols <= (1ll << 26) && rows * n <= (1ll << 32); }
 
 template <int KS, bool TAIL, bool PRO>
 const void* gemm_rows_kernel(int rows) {
@@ -1343,7 +1345,8 @@ bool plan_gemv(int dtype, int ind, int rows, int n, int cols, Launch* out) {
 
 bool merge_head(int op, int dtype, const Shape& s, long long* n_out) {
     if (op != kGemv || dtype != kBF16 || s.rows < 1) return false;
-    if (s.rows <= 4 ? !rows_served(s.rows, s.n, s.cols) : !mm_served(s.rows, s.n, s.cols)) return false;
+    // (the epilogue counts all its elements in 32 bits)
+    if (s.rows <= 4 ? !rows_served(s.rows, s.n, s.cols) : !mm_served(s.rows, s.n, s.cols) || s.rows * s.n > (1ll << 31)) return false;
     *n_out = s.rows * s.n;
     return true;
 }

@@ -231,7 +231,7 @@ void plan_carry_run(long long n, Launch* out, unsigned* n_units);
 bool sbr_run_candidate(int dtype, long long n, long long inner, long long channels);
 bool plan_sbr_run(int dtype, long long n, long long inner, Launch* out);
 // Is this a GEMV shape an epilogue form exists for?  bf16: up to 4 rows of h of 8 to 8192 columns (k_gemv_rows;
-// beyond 2048 columns only for n >= 1024), 5 rows and more of 8 columns and more (the matrix-core forms; n >= 16).
+// beyond 2048 columns only for n >= 1024), 5 rows and more of 8 columns and more (the matrix-core forms).
 // *n_out = rows * n.
 bool merge_head(int op, int dtype, const Shape& shape, long long* n_out);
 // ... and does it also take the RMSNorm in front?  The matrix-core forms up to 2048 columns, and up to kPrologueMaxRows rows:
