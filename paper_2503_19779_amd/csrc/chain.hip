@@ -56,7 +56,7 @@ union ArgBlock {
     pgk::EwArgs ew;
     pgk::RmsArgs rms;
     pgk::GemvArgs gemv;
-    pgk::GemvEpiArgs epi;           // starts with the GemvArgs; for the GEMV kernels that take the whole block
+    pgk::GemvAloneArgs alone;       // starts with the GemvArgs; for the GEMV kernels that take the flags as well
     pgk::SbrArgs sbr;
     // every block starts with: out, in0, in1, (in2)
     const void* ptr[4];
@@ -710,8 +710,7 @@ pg_status make_records(pg_chain* c) {
             case PG_RMSNORM: a.rms.rows = (int)d.rows; a.rms.cols = (int)d.cols; a.rms.eps = d.eps; break;
             case PG_GEMV:
                 a.gemv.rows = (int)d.rows; a.gemv.n = (int)d.n; a.gemv.cols = (int)d.cols;
-                a.epi.head = pgk::kEpiHeadStore | (mode == 2 ? (unsigned)r.ind_mask : 0u);          // no prologue, no epilogue
-                for (auto& ph : a.epi.ph) ph.meta = (unsigned)PG_GELU;                              // operands "from slot 0": fetches nothing, never played
+                a.alone.head = pgk::kEpiHeadStore | (mode == 2 ? (unsigned)r.ind_mask : 0u);
                 break;
             case PG_SCALE_BIAS_RELU:
                 a.sbr.n = d.n; a.sbr.inner = (unsigned)d.inner;
@@ -726,7 +725,7 @@ pg_status make_records(pg_chain* c) {
         if (r.direct.grid.x != r.indirect.grid.x || r.direct.block.x != r.indirect.block.x)
             return fail(PG_EINVAL, "kernel %d: direct and indirect forms disagree on the launch shape", i);
         if (d.op == PG_GEMV)
-            for (ArgBlock* a : {&r.a_eager, &r.a_copy, &r.a_ind}) { a->gemv.row_groups = (int)r.direct.gemm_row_groups; seal_epilogue(a->epi); }
+            for (ArgBlock* a : {&r.a_eager, &r.a_copy, &r.a_ind}) a->gemv.row_groups = (int)r.direct.gemm_row_groups;
     }
     for (auto& sg : c->seg)
         for (auto& g : sg.groups) {

@@ -5,6 +5,8 @@
 // Built with -ffp-contract=off: fused multiply-adds appear only where written.
 #include "device.h"
 
+#include <type_traits>
+
 namespace pgk {
 namespace {
 
@@ -304,7 +306,8 @@ __device__ __forceinline__ void span_store(bf16_t* row, int cols, int v, const u
 // dispatch.  begin() always issues the same loads -- an operand that comes from a register slot is fetched from the
 // GEMV's own output buffer instead and ignored -- so that every wait on the rows and weights knows how
 // many younger loads are outstanding.
-template <int NE>
+// EPI = false: nothing rides behind the GEMV, and the stage reads no table, fetches nothing and stores what it is given.
+template <int NE, bool EPI>
 struct MmEpilogue {
     static constexpr int P = kEpiMaxPhases;
     bf16_t* y;
@@ -326,6 +329,10 @@ struct MmEpilogue {
     unsigned ld0[P][NE], ld1[P][NE];
     float v[NE];
     __device__ __forceinline__ void prepare() {
+        if constexpr (!EPI) {
+            if constexpr (NE % 2 == 0) vec = n % VW == 0 && aligned_to(y, 2 * VW);
+            return;
+        }
         static_assert(P == 3, "the argument batch names every phase");
         using SlotPtr = const void* const PG_CONSTANT*;
         const void* a0[P];
@@ -376,6 +383,7 @@ struct MmEpilogue {
             ok[e] = col_ok && r < rows && j + e < n;
             idx[e] = ok[e] ? (unsigned)r * (unsigned)n + (unsigned)(j + e) : 0u;
         }
+        if constexpr (!EPI) return;
         if (__builtin_expect((head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec), 1)) {      // two operands, in in1 (see kernels.h)
             fetch(q1[1], ld1[1]);
             fetch(q1[2], ld1[2]);
@@ -429,6 +437,12 @@ struct MmEpilogue {
     __device__ __forceinline__ void put(int e, float sum) { v[e] = sum; }
     __device__ __forceinline__ void end() {
         unsigned bits[NE];
+        if constexpr (!EPI) {
+#pragma unroll
+            for (int e = 0; e < NE; e++) bits[e] = f32_to_bf16(v[e]);
+            store(y, bits);
+            return;
+        }
         float slot[kMergeSlots][NE];
         // Claim every operand before the first store: loads and stores complete in one queue, in order, so a wait for
         // an operand placed after a store would wait for that store to be acknowledged as well.
@@ -511,6 +525,9 @@ struct MmEpilogue {
 __device__ __forceinline__ void mm_drained(f32x4& acc) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc)); }
 
 
+// What rides in a GEMV's dispatch: nothing, elementwise kernels behind it, or those and the RMSNorm in front.
+enum Ride { kAlone, kEpilogue, kPrologue };
+
 // What the two families read first: the first 64 bytes of the arguments hold everything that is needed before the
 // loads of h and the weights can go out, and only those are waited for here, in one batch of scalar loads; the
 // epilogue's table and eps are read once the weights are on their way (MmEpilogue::prepare).  PRO: h is computed from x and
@@ -525,18 +542,27 @@ struct MmHead {
     unsigned head;
     const void PG_CONSTANT* ka;
 };
-template <bool PRO>
-__device__ __forceinline__ MmHead mm_head(const GemvEpiArgs& p) {
-    static_assert(offsetof(GemvEpiArgs, gain) + sizeof(void*) == 64, "what the kernel needs first sits in the first 64 bytes");
+template <Ride RIDE> using RideArgs = std::conditional_t<RIDE == kAlone, GemvAloneArgs, GemvEpiArgs>;
+template <Ride RIDE>
+__device__ __forceinline__ MmHead mm_head(const RideArgs<RIDE>& p) {
+    constexpr bool PRO = RIDE == kPrologue;
+    static_assert(offsetof(GemvAloneArgs, head) == offsetof(GemvEpiArgs, head) && offsetof(GemvEpiArgs, gain) + sizeof(void*) == 64, "what the kernel needs first sits in the first 64 bytes");
     const void* Wa = p.g.W;
     const void* ha = p.g.h;
     bf16_t* y = static_cast<bf16_t*>(p.g.out);
     int rows = p.g.rows, n = p.g.n, cols = p.g.cols, row_groups = p.g.row_groups;
     unsigned head = p.head;
-    int n_epi = p.n_epi;
-    const void* xa = p.x;
-    const void* ga = p.gain;
-    asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(rows), "+s"(n), "+s"(cols), "+s"(row_groups), "+s"(head), "+s"(n_epi), "+s"(xa), "+s"(ga));
+    int n_epi = 0;
+    const void* xa = nullptr;
+    const void* ga = nullptr;
+    if constexpr (RIDE == kAlone) {
+        asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(rows), "+s"(n), "+s"(cols), "+s"(row_groups), "+s"(head));
+    } else {
+        n_epi = p.n_epi;
+        xa = p.x;
+        ga = p.gain;
+        asm volatile("" : "+s"(Wa), "+s"(ha), "+s"(y), "+s"(rows), "+s"(n), "+s"(cols), "+s"(row_groups), "+s"(head), "+s"(n_epi), "+s"(xa), "+s"(ga));
+    }
     const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();   // a readable address for a load whose result is not used
     using SlotPtr = const void* const PG_CONSTANT*;
     auto slot_addr = [&](const void* q, bool is_slot) -> SlotPtr { return is_slot ? (SlotPtr)(uintptr_t)q : (SlotPtr)ka; };
@@ -698,14 +724,15 @@ __device__ __forceinline__ void mm_rmsnorm_rows(unsigned (*g)[4], const unsigned
 // NC = 8: one tile of rows, the grid is the column blocks; NC = 16: (column blocks) x (tiles of rows), column block
 // fastest, so that the tiles of one column block share an XCD's L2.  The workgroups of column block 0 store the
 // normalised rows.
-template <int KS, bool TAIL, int NR, int NC, bool PRO>
-__global__ __launch_bounds__(kBlock, (PRO && KS > 8) ? 1 : 2) void k_gemm_rows(GemvEpiArgs p) {
-    const MmHead m = mm_head<PRO>(p);
+template <int KS, bool TAIL, int NR, int NC, Ride RIDE>
+__global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void k_gemm_rows(RideArgs<RIDE> p) {
+    constexpr bool PRO = RIDE == kPrologue;
+    const MmHead m = mm_head<RIDE>(p);
     constexpr int kWaveLds = 4 * KS * kMmSlotBytes;
     __shared__ __attribute__((aligned(16))) char stage[4 * kWaveLds];
     __shared__ float red[4 * 64 * 4];
     static_assert((NR * (21 * KS + 1)) * sizeof(float) <= sizeof stage, "the prologue's sums fit the staging area");
-    MmEpilogue<1> emit;
+    MmEpilogue<1, RIDE != kAlone> emit;
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ncb = (m.n + NC - 1) / NC;
@@ -757,13 +784,13 @@ __global__ __launch_bounds__(kBlock, (PRO && KS > 8) ? 1 : 2) void k_gemm_rows(G
 // ---- k_gemm_cols ------------------------------------------------------------------------------------------
 // The same staging for more rows: 16 output columns per workgroup, whose weight fragments stay in registers while its
 // tiles of 16 rows of h pass by, the next tile's rows in flight across the multiplies of this one.  Two workgroups per CU.
-template <int KS, bool TAIL>
-__global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(GemvEpiArgs p) {
-    const MmHead m = mm_head<false>(p);
+template <int KS, bool TAIL, Ride RIDE>
+__global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
+    const MmHead m = mm_head<RIDE>(p);
     constexpr int kWaveLds = 4 * KS * kMmSlotBytes, kRedRow = 20;
     __shared__ __attribute__((aligned(16))) char stage[4 * kWaveLds];
     __shared__ float red[4][16 * kRedRow];
-    MmEpilogue<1> emit;
+    MmEpilogue<1, RIDE != kAlone> emit;
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ncb = (m.n + 15) / 16;
@@ -855,7 +882,7 @@ __device__ __forceinline__ void ring_frags(unsigned at0, unsigned at1, v4u (&f)[
 }
 
 template <int RT, int CT, int S, int NW>
-__global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gemm_tile(GemvEpiArgs p) {
+__global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gemm_tile(RideArgs<NW == 8 ? kEpilogue : kAlone> p) {
     constexpr int F = RT + CT, NL = 2 * F, kBlockLds = F * 2048, kWaveLds = S * kBlockLds;
     constexpr int PK = 8 / NW;                           // eighths of K per wave
     constexpr int kRedRow = 16 * CT + 4;                 // floats of a row of partial sums, padded: rows 4 apart fall into other banks
@@ -863,9 +890,10 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
     constexpr int NE = RT * CT * 4 >= NW ? RT * CT * 4 / NW : 1, kPerRow = 16 * CT / NE;  // outputs per lane (consecutive columns), lanes per row of the tile
     static_assert(PK * kRed * 4 <= kWaveLds, "a wave's partial sums fit its ring");
     static_assert(S == 1 || S == 2, "the waits below name the blocks in flight");
-    const MmHead m = mm_head<false>(p);
+    constexpr Ride RIDE = NW == 8 ? kEpilogue : kAlone;  // four waves: a stand-alone launch
+    const MmHead m = mm_head<RIDE>(p);
     __shared__ __attribute__((aligned(128))) char ring[NW * kWaveLds];
-    MmEpilogue<NE> emit;
+    MmEpilogue<NE, RIDE != kAlone> emit;
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = m.rows, n = m.n, cols = m.cols;
@@ -1136,9 +1164,10 @@ __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h,
 
 // GEMV with an elementwise epilogue: one lane of each wave per output e (row e / R of h, column j0 + e % R) plays it
 // through the kernels that follow (see kernels.h; none of them: the plain GEMV).
-template <int R, int RB, int U, bool EXACT, bool PRO>
-__global__ __launch_bounds__(kBlock) void k_gemv_rows(GemvEpiArgs p) {
-    const MmHead m = mm_head<PRO>(p);
+template <int R, int RB, int U, bool EXACT, Ride RIDE>
+__global__ __launch_bounds__(kBlock) void k_gemv_rows(RideArgs<RIDE> p) {
+    constexpr bool PRO = RIDE == kPrologue;
+    const MmHead m = mm_head<RIDE>(p);
     const int n = m.n;
     // up to 2048 columns an XCD takes a contiguous stretch of the columns (decode chain, 2048 columns, 1 row 430 -> 406 us, 4 rows
     // 482 -> 472; 1024 columns, 1 row 347 -> 326); longer rows stream better dealt out in turn (4096 columns, 4 rows 289 against 304)
@@ -1148,7 +1177,7 @@ __global__ __launch_bounds__(kBlock) void k_gemv_rows(GemvEpiArgs p) {
     __shared__ f32x4 part[4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int j0 = (bid * (kBlock / 64) + __builtin_amdgcn_readfirstlane(tid >> 6)) * R;   // uniform: the weight rows' addresses stay in scalar registers
-    MmEpilogue<1> emit;
+    MmEpilogue<1, RIDE != kAlone> emit;
     emit.y = m.y; emit.rows = RB; emit.n = n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     float sums[R * RB];
     gemv_rows_sums<R, RB, U, EXACT, PRO>(m.W, m.h, n, m.cols, j0, lane, tid, hs, [&] {
@@ -1224,37 +1253,37 @@ constexpr int kRowsTwoFrom = 1024;
 bool rows_served(long long rows, long long n, long long cols) {
     return rows >= 1 && rows <= 4 && n >= 1 && cols >= 8 && cols <= (n >= kRowsTwoFrom ? 8192 : 2048) && rows * n <= (1ll << 31);
 }
-template <bool PRO, int RB>
+template <Ride RIDE, int RB>
 const void* rows_kernel_rb(int n, int cols) {
     const int u = (cols + 511) / 512;
     if (n < kRowsTwoFrom) {
         switch (u) {
-        case 1: return PG_FN(k_gemv_rows<1, RB, 1, false, PRO>);
-        case 2: return PG_FN(k_gemv_rows<1, RB, 2, false, PRO>);
-        case 3: return PG_FN(k_gemv_rows<1, RB, 3, false, PRO>);
-        default: return PG_FN(k_gemv_rows<1, RB, 4, false, PRO>);
+        case 1: return PG_FN(k_gemv_rows<1, RB, 1, false, RIDE>);
+        case 2: return PG_FN(k_gemv_rows<1, RB, 2, false, RIDE>);
+        case 3: return PG_FN(k_gemv_rows<1, RB, 3, false, RIDE>);
+        default: return PG_FN(k_gemv_rows<1, RB, 4, false, RIDE>);
         }
     }
     switch (cols) {
-    case 1024: return PG_FN(k_gemv_rows<2, RB, 2, true, PRO>);
-    case 2048: return PG_FN(k_gemv_rows<2, RB, 4, true, PRO>);
-    case 4096: return PG_FN(k_gemv_rows<2, RB, 8, true, PRO>);
-    case 8192: return PG_FN(k_gemv_rows<2, RB, 16, true, PRO>);
+    case 1024: return PG_FN(k_gemv_rows<2, RB, 2, true, RIDE>);
+    case 2048: return PG_FN(k_gemv_rows<2, RB, 4, true, RIDE>);
+    case 4096: return PG_FN(k_gemv_rows<2, RB, 8, true, RIDE>);
+    case 8192: return PG_FN(k_gemv_rows<2, RB, 16, true, RIDE>);
     default: break;
     }
-    if (u <= 3) return PG_FN(k_gemv_rows<2, RB, 3, false, PRO>);
-    if (u <= 4) return PG_FN(k_gemv_rows<2, RB, 4, false, PRO>);
-    if (u <= 8) return PG_FN(k_gemv_rows<2, RB, 8, false, PRO>);
-    if (u <= 12) return PG_FN(k_gemv_rows<2, RB, 12, false, PRO>);
-    return PG_FN(k_gemv_rows<2, RB, 16, false, PRO>);
+    if (u <= 3) return PG_FN(k_gemv_rows<2, RB, 3, false, RIDE>);
+    if (u <= 4) return PG_FN(k_gemv_rows<2, RB, 4, false, RIDE>);
+    if (u <= 8) return PG_FN(k_gemv_rows<2, RB, 8, false, RIDE>);
+    if (u <= 12) return PG_FN(k_gemv_rows<2, RB, 12, false, RIDE>);
+    return PG_FN(k_gemv_rows<2, RB, 16, false, RIDE>);
 }
-template <bool PRO>
+template <Ride RIDE>
 const void* rows_kernel(int rows, int n, int cols) {
     switch (rows) {
-    case 1: return rows_kernel_rb<PRO, 1>(n, cols);
-    case 2: return rows_kernel_rb<PRO, 2>(n, cols);
-    case 3: return rows_kernel_rb<PRO, 3>(n, cols);
-    default: return rows_kernel_rb<PRO, 4>(n, cols);
+    case 1: return rows_kernel_rb<RIDE, 1>(n, cols);
+    case 2: return rows_kernel_rb<RIDE, 2>(n, cols);
+    case 3: return rows_kernel_rb<RIDE, 3>(n, cols);
+    default: return rows_kernel_rb<RIDE, 4>(n, cols);
     }
 }
 
@@ -1263,26 +1292,31 @@ const void* rows_kernel(int rows, int n, int cols) {
 // within a tile of 64 rows reach (32 bits, as are the outputs' indices).
 bool mm_served(long long rows, long long n, long long cols) { return rows > 4 && cols >= 8 && cols <= (1ll << 26) && rows * n <= (1ll << 32); }
 
-template <int KS, bool TAIL, bool PRO>
+template <int KS, bool TAIL, Ride RIDE>
 const void* gemm_rows_kernel(int rows) {
-    if (rows <= 8) return PG_FN(k_gemm_rows<KS, TAIL, 8, 8, PRO>);
-    if (rows <= 16) return PG_FN(k_gemm_rows<KS, TAIL, 16, 8, PRO>);
-    if constexpr (PRO) return PG_FN(k_gemm_rows<KS, TAIL, 16, 16, true>);
+    if (rows <= 8) return PG_FN(k_gemm_rows<KS, TAIL, 8, 8, RIDE>);
+    if (rows <= 16) return PG_FN(k_gemm_rows<KS, TAIL, 16, 8, RIDE>);
+    if constexpr (RIDE == kPrologue) return PG_FN(k_gemm_rows<KS, TAIL, 16, 16, kPrologue>);
     else return nullptr;
 }
-template <bool PRO>
+template <Ride RIDE>
 const void* gemm_rows_form(int rows, int cols) {
-    if (cols <= 1024) return cols == 1024 ? gemm_rows_kernel<8, false, PRO>(rows) : gemm_rows_kernel<8, true, PRO>(rows);
-    return cols == 2048 ? gemm_rows_kernel<16, false, PRO>(rows) : gemm_rows_kernel<16, true, PRO>(rows);
+    if (cols <= 1024) return cols == 1024 ? gemm_rows_kernel<8, false, RIDE>(rows) : gemm_rows_kernel<8, true, RIDE>(rows);
+    return cols == 2048 ? gemm_rows_kernel<16, false, RIDE>(rows) : gemm_rows_kernel<16, true, RIDE>(rows);
 }
-// merged: with an epilogue (and, pro, a prologue), in a captured graph; otherwise the stand-alone GEMV
-void plan_gemm(int rows, int n, int cols, bool merged, bool pro, Launch* out) {
+template <Ride RIDE>
+const void* gemm_cols_form(int cols) {
+    if (cols <= 1024) return cols == 1024 ? PG_FN(k_gemm_cols<8, false, RIDE>) : PG_FN(k_gemm_cols<8, true, RIDE>);
+    return cols == 2048 ? PG_FN(k_gemm_cols<16, false, RIDE>) : PG_FN(k_gemm_cols<16, true, RIDE>);
+}
+void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
+    const bool merged = ride != kAlone;
     const int ntiles = (rows + 15) / 16;
-    out->arg_bytes = sizeof(GemvEpiArgs);
+    out->arg_bytes = merged ? sizeof(GemvEpiArgs) : sizeof(GemvAloneArgs);
     out->block = dim3(kBlock);
     out->gemm_row_groups = (unsigned)ntiles;
-    if (pro || (rows <= 16 && cols <= 2048)) {
-        out->fn = pro ? gemm_rows_form<true>(rows, cols) : gemm_rows_form<false>(rows, cols);
+    if (ride == kPrologue || (rows <= 16 && cols <= 2048)) {
+        out->fn = ride == kPrologue ? gemm_rows_form<kPrologue>(rows, cols) : merged ? gemm_rows_form<kEpilogue>(rows, cols) : gemm_rows_form<kAlone>(rows, cols);
         out->grid = rows <= 16 ? dim3(blocks_for(n, 8)) : dim3(blocks_for(n, 16) * (unsigned)ntiles);
         return;
     }
@@ -1290,8 +1324,7 @@ void plan_gemm(int rows, int n, int cols, bool merged, bool pro, Launch* out) {
     if (cols <= 2048 && rows < kMmWideRows) {
         out->gemm_row_groups = (unsigned)(ntiles < 4 ? ntiles : 4);
         out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
-        if (cols <= 1024) out->fn = cols == 1024 ? PG_FN(k_gemm_cols<8, false>) : PG_FN(k_gemm_cols<8, true>);
-        else out->fn = cols == 2048 ? PG_FN(k_gemm_cols<16, false>) : PG_FN(k_gemm_cols<16, true>);
+        out->fn = merged ? gemm_cols_form<kEpilogue>(cols) : gemm_cols_form<kAlone>(cols);
         return;
     }
     // The largest tile that still gives every CU a workgroup, 32 x 32 from kMmWideRows rows.
@@ -1319,14 +1352,14 @@ bool plan_gemv_t(int ind, int rows, int n, int cols, Launch* out) {
         // Three and four rows go to the form that shares h through LDS (at 2048 x 2048, us per launch at 2 / 3 / 4 rows: 3.3 / 3.5 /
         // 3.7; vector with h per wave 3.8 / 4.4 / 4.5; matrix-core form with 8 columns per workgroup 3.9 / 4.0 / 4.0).
         if ((rows == 3 || rows == 4) && rows_served(rows, n, cols) && !(n >= 1024 && cols == 64 * kGemvChunk * NV)) {
-            out->fn = rows_kernel<false>(rows, n, cols);
-            out->arg_bytes = sizeof(GemvEpiArgs);
+            out->fn = rows_kernel<kAlone>(rows, n, cols);
+            out->arg_bytes = sizeof(GemvAloneArgs);
             out->block = dim3(kBlock);
             out->grid = dim3(blocks_for(n, (kBlock / 64) * (n >= kRowsTwoFrom ? 2 : 1)));
             return true;
         }
         if (mm_served(rows, n, cols)) {      // a dense contraction: matrix cores from 5 rows on
-            plan_gemm(rows, n, cols, false, false, out);
+            plan_gemm(rows, n, cols, kAlone, out);
             return true;
         }
     }
@@ -1357,8 +1390,8 @@ void plan_gemv_epilogue(const Shape& s, bool with_prologue, Launch* out) {
     const int rows = (int)s.rows, n = (int)s.n, cols = (int)s.cols;
     out->mod_fn = nullptr;
     out->gemm_row_groups = 0;
-    if (rows > 4) { plan_gemm(rows, n, cols, true, with_prologue, out); return; }
-    out->fn = with_prologue ? rows_kernel<true>(rows, n, cols) : rows_kernel<false>(rows, n, cols);
+    if (rows > 4) { plan_gemm(rows, n, cols, with_prologue ? kPrologue : kEpilogue, out); return; }
+    out->fn = with_prologue ? rows_kernel<kPrologue>(rows, n, cols) : rows_kernel<kEpilogue>(rows, n, cols);
     out->arg_bytes = sizeof(GemvEpiArgs);
     out->block = dim3(kBlock);
     out->grid = dim3(blocks_for(n, (kBlock / 64) * (n >= kRowsTwoFrom ? 2 : 1)));

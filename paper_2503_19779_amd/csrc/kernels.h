@@ -128,6 +128,13 @@ constexpr unsigned kEpiDecoder = 1u << 21;      // the kernels are GELU of the G
 constexpr unsigned kEpiMemFirst = 1u << 9;      // MergePhase::ind: that operand is the add's first
 constexpr unsigned kEpiAnySlot = 1u << 22;      // some operand of the epilogue is a pointer-table slot
 constexpr unsigned kEpiPlain = 1u << 23;        // no operand of the epilogue has a broadcast period
+// A GEMV that nothing rides with takes this much of it (a launch from the host pays for every byte of the block:
+// 200 against 48 bytes cost 0.2 - 0.4 us per launch of an eager loop).
+struct GemvAloneArgs {
+    GemvArgs g;
+    unsigned head;          // bit 0 / 1: W / h are pointer-table slots; kEpiHeadStore
+    int reserved;
+};
 struct GemvEpiArgs {
     GemvArgs g;             // with a prologue g.h is where the normalised rows are stored, not read
     unsigned head;          // bit 0 / 1: W / h are pointer-table slots; bits 8-15: slot that keeps the GEMV's result; bits 16-23 above
