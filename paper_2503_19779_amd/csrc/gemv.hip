@@ -926,80 +926,89 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
             row_at[q] = (unsigned)(r < last ? r : last) * (unsigned)cols;
         }
         f32x4 acc[PK][RT][CT];
+#pragma unroll
+        for (int pk = 0; pk < PK; pk++)
+#pragma unroll
+            for (int i = 0; i < RT; i++)
+#pragma unroll
+                for (int j = 0; j < CT; j++) acc[pk][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         // the epilogue's table behind the first block's loads: asked for behind all of them it came 1.1 us later
         auto epilogue_begin = [&] {
             if (t == t0) emit.prepare();
             emit.begin(r0 + er, j0 + ec, er < 16 * RT);
         };
+        // this wave's K-blocks: wave, wave + NW, ...; number b of them belongs to its eighth b % PK
+        const int nb = (nkb - wave + NW - 1) / NW;
+        auto multiply = [&](f32x4 (&sum)[RT][CT], v4u (&f)[2 * F]) {
 #pragma unroll
-        for (int pk = 0; pk < PK; pk++) {
-            const int first = wave + pk * NW, nw = (nkb - first + 7) / 8;      // this eighth's K-blocks: first, first + 8, ...
+            for (int s = 0; s < 2; s++)
 #pragma unroll
-            for (int i = 0; i < RT; i++)
+                for (int i = 0; i < RT; i++)
 #pragma unroll
-                for (int j = 0; j < CT; j++) acc[pk][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            auto multiply = [&](v4u (&f)[2 * F]) {
+                    for (int j = 0; j < CT; j++)
+                        sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[s * F + i]), __builtin_bit_cast(bf16x8, f[s * F + RT + j]), sum[i][j], 0, 0, 0);
+        };
+        if (__builtin_expect(direct, 1)) {
+            auto issue = [&](int b, int slot) {
+                const int k = (wave + NW * b) * 64 + chunk * 8;
+                const unsigned ke = k < cols ? (unsigned)k : 0u;           // a chunk past the end is read from column 0 and zeroed later
 #pragma unroll
-                for (int s = 0; s < 2; s++)
-#pragma unroll
-                    for (int i = 0; i < RT; i++)
-#pragma unroll
-                        for (int j = 0; j < CT; j++)
-                            acc[pk][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[s * F + i]), __builtin_bit_cast(bf16x8, f[s * F + RT + j]),
-                                                                                    acc[pk][i][j], 0, 0, 0);
+                for (int q = 0; q < NL; q++)
+                    __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)(q < 2 * RT ? hb : wb) + (row_at[q] + ke)),
+                                                     (__attribute__((address_space(3))) void*)(mine + slot * kBlockLds + q * 1024), 16, 0, 0);
             };
-            if (__builtin_expect(direct, 1)) {
-                auto issue = [&](int j, int slot) {
-                    const int k = (first + 8 * j) * 64 + chunk * 8;
-                    const unsigned ke = k < cols ? (unsigned)k : 0u;       // a chunk past the end is read from column 0 and zeroed later
-#pragma unroll
-                    for (int q = 0; q < NL; q++)
-                        __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)(q < 2 * RT ? hb : wb) + (row_at[q] + ke)),
-                                                         (__attribute__((address_space(3))) void*)(mine + slot * kBlockLds + q * 1024), 16, 0, 0);
-                };
-                if (nw > 0) issue(0, 0);
-                if (pk == 0) epilogue_begin();
-                if (S == 2 && nw > 1) issue(1, 1);
-                int slot = 0;
+            if (nb > 0) issue(0, 0);
+            epilogue_begin();
+            if (S == 2 && nb > 1) issue(1, 1);
+            int slot = 0;
 #pragma unroll 1
-                for (int j = 0; j < nw; j++) {
-                    // loads complete in order: block j is in once at most the younger block's loads are outstanding (other loads
+            for (int b0 = 0; b0 < nb; b0 += PK) {
+#pragma unroll
+                for (int pk = 0; pk < PK; pk++) {
+                    const int b = b0 + pk;
+                    if (PK > 1 && b >= nb) break;
+                    // loads complete in order: block b is in once at most the younger block's loads are outstanding (other loads
                     // among them only make the wait stricter)
-                    if (S == 2 && j + 1 < nw) vm_wait<NL>();
+                    if (S == 2 && b + 1 < nb) vm_wait<NL>();
                     else vm_wait<0>();
                     v4u f[2 * F];
                     ring_frags<F>(f0 + slot * kBlockLds, f1 + slot * kBlockLds, f);
-                    if (j + S < nw) issue(j + S, slot);                    // the slot has been read
-                    if (rem && first + 8 * j == nkb - 1) {
+                    if (b + S < nb) issue(b + S, slot);                    // the slot has been read
+                    if (rem && wave + NW * b == nkb - 1) {
 #pragma unroll
                         for (int s = 0; s < 2; s++)
                             if ((s * 4 + (lane >> 4)) * 8 >= rem)
 #pragma unroll
                                 for (int i = 0; i < F; i++) f[s * F + i] = v4u{0u, 0u, 0u, 0u};
                     }
-                    multiply(f);
+                    multiply(acc[pk], f);
                     slot = slot + 1 == S ? 0 : slot + 1;
                 }
-            } else {
-                unsigned g[NL][4];
-                auto fetch = [&](int j) {
-                    const unsigned ke = span_at<false>(cols, (first + 8 * j) * 8 + chunk);
+            }
+        } else {
+            unsigned g[NL][4];
+            auto fetch = [&](int b) {
+                const unsigned ke = span_at<false>(cols, (wave + NW * b) * 8 + chunk);
 #pragma unroll
-                    for (int q = 0; q < NL; q++) load_any<false>(q < 2 * RT ? hb : wb, row_at[q] + ke, g[q]);
-                };
-                if (nw > 0) fetch(0);
-                if (pk == 0) epilogue_begin();
+                for (int q = 0; q < NL; q++) load_any<false>(q < 2 * RT ? hb : wb, row_at[q] + ke, g[q]);
+            };
+            if (nb > 0) fetch(0);
+            epilogue_begin();
 #pragma unroll 1
-                for (int j = 0; j < nw; j++) {
+            for (int b0 = 0; b0 < nb; b0 += PK) {
+#pragma unroll
+                for (int pk = 0; pk < PK; pk++) {
+                    const int b = b0 + pk;
+                    if (PK > 1 && b >= nb) break;
 #pragma unroll
                     for (int q = 0; q < NL; q++) {
-                        span_fix<false>(cols, (first + 8 * j) * 8 + chunk, g[q]);
+                        span_fix<false>(cols, (wave + NW * b) * 8 + chunk, g[q]);
                         *reinterpret_cast<v4u*>(mine + (q * 8 + r8) * 128 + ((chunk ^ r8) * 16)) = v4u{g[q][0], g[q][1], g[q][2], g[q][3]};
                     }
-                    if (j + 1 < nw) fetch(j + 1);
+                    if (b + 1 < nb) fetch(b + 1);
                     v4u f[2 * F];
                     ring_frags<F>(f0, f1, f);                              // behind the writes above: one wave's LDS operations execute in order
-                    multiply(f);
+                    multiply(acc[pk], f);
                 }
             }
         }
