@@ -794,7 +794,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ncb = (m.n + 15) / 16;
-    const int at = (int)xcd_stretch(blockIdx.x, (unsigned)(ncb * m.row_groups)), cb = at / m.row_groups, rg = at % m.row_groups;
+    const int at = (int)xcd_stretch(blockIdx.x, (unsigned)(ncb * m.row_groups)), cb = at / m.row_groups;
+    // Five tiles make row groups of two, two, one and none: the workgroups that follow each other onto a CU (32 later in an
+    // XCD's stretch) are not to be of the same group, or some CUs work out four tiles and some none (80 rows of 2048 columns
+    // 8.1 -> 7.2 us per launch)
+    const int rg = (at + cb * m.row_groups / 32 * 2) % m.row_groups;
     const int ntiles = (m.rows + 15) / 16, per = (ntiles + m.row_groups - 1) / m.row_groups;
     const int t0 = rg * per, t1 = (t0 + per < ntiles) ? t0 + per : ntiles;
     if (t0 >= t1) return;                                // whole workgroup: nothing waits on it
