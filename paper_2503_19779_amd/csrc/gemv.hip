@@ -1334,8 +1334,9 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         return;
     }
     // (decode chain of 2048 columns at 48 / 64 rows: 1175 / 1188 us, with k_gemm_tile's 16 x 16 tiles 1254 / 1261)
-    if (cols <= 2048 && rows < kMmWideRows) {
-        out->gemm_row_groups = (unsigned)(ntiles < 4 ? ntiles : 4);
+    // A 32-column tile of up to 16 outputs per row would be half empty; with so few workgroups, one tile of rows each.
+    if (cols <= 2048 && (rows < kMmWideRows || n <= 16)) {
+        out->gemm_row_groups = (unsigned)(ntiles < 4 || n <= 16 ? ntiles : 4);
         out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
         out->fn = merged ? gemm_cols_form<kEpilogue>(cols) : gemm_cols_form<kAlone>(cols);
         return;

@@ -299,10 +299,10 @@ def test_launch_shapes_of_other_kernels_and_bad_index():
         c2.close()
 
 
-@pytest.mark.parametrize("rows,n,cols,want", [(40, 8, 2048, 3), (64, 12, 4096, 4), (128, 8, 2048, 4), (33, 1, 136, 3), (5, 40, 1 << 24, 3), (9, 12, 1 << 26, 1)])
+@pytest.mark.parametrize("rows,n,cols,want", [(40, 8, 2048, 3), (64, 12, 4096, 4), (128, 8, 2048, 8), (200, 16, 1030, 13), (33, 1, 136, 3), (5, 40, 1 << 24, 3), (9, 12, 1 << 26, 1)])
 def test_matrix_cores_take_every_gemv_of_five_rows_and_more(rows, n, cols, want):
     """Few outputs per row, or very long rows, are no reason to leave the matrix cores: one workgroup per tile of rows and
-    16 (32 from 81 rows on) outputs, where the vector units' form would have one per four outputs."""
+    16 outputs, where the vector units' form would have one per four outputs."""
     ch = pg.Chain.host_only(_gemv_chain("bf16", rows, n, cols))
     assert ch.launch_shape(0) == (want, 256) != (-(-n // 4), 256)
     ch.close()
