@@ -669,8 +669,8 @@ void seal_epilogue(pgk::GemvEpiArgs& e) {
         return (mt & 0xffu) == (unsigned)pgk::kAdd && ((a == q && mem1[i]) || (mem0[i] && b == q));
     };
     const unsigned m0 = e.ph[0].meta;
-    if ((e.n_epi == 2 || e.n_epi == 3) && (m0 & 0xffu) == (unsigned)pgk::kGelu && ((m0 >> 8) & 0xffu) == ((e.head >> 8) & 0xffu) &&
-        adds(1, m0 >> 24) && (e.n_epi == 2 || adds(2, e.ph[1].meta >> 24))) {
+    if (e.n_epi >= 1 && (m0 & 0xffu) == (unsigned)pgk::kGelu && ((m0 >> 8) & 0xffu) == ((e.head >> 8) & 0xffu) &&
+        (e.n_epi < 2 || adds(1, m0 >> 24)) && (e.n_epi < 3 || adds(2, e.ph[1].meta >> 24))) {
         e.head |= pgk::kEpiDecoder;
         for (int i = 1; i < e.n_epi; i++)
             if (mem0[i]) {

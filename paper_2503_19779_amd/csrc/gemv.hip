@@ -387,6 +387,14 @@ struct MmEpilogue {
         if (__builtin_expect((head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec), 1)) {      // two operands, in in1 (see kernels.h)
             fetch(q1[1], ld1[1]);
             fetch(q1[2], ld1[2]);
+        } else if (head & kEpiPlain) {         // one branch for all: no division where no operand has a period
+#pragma unroll
+            for (int i = 0; i < P; i++)
+#pragma unroll
+                for (int e = 0; e < NE; e++) {
+                    ld0[i][e] = load_raw_global_at(q0[i], idx[e]);
+                    ld1[i][e] = load_raw_global_at(q1[i], idx[e]);
+                }
         } else {
 #pragma unroll
             for (int i = 0; i < P; i++) {
@@ -394,7 +402,7 @@ struct MmEpilogue {
 #pragma unroll
                 for (int e = 0; e < NE; e++) {
                     ld0[i][e] = load_raw_global_at(q0[i], idx[e]);
-                    ld1[i][e] = load_raw_global_at(q1[i], (head & kEpiPlain) ? idx[e] : idx[e] % m);
+                    ld1[i][e] = load_raw_global_at(q1[i], idx[e] % m);
                 }
             }
         }

@@ -124,7 +124,7 @@ constexpr unsigned kEpiXSlot = 1u << 18, kEpiGainSlot = 1u << 19;   // x / gain 
 constexpr unsigned kEpiStoreH = 1u << 20;       // workgroup 0 stores the normalised rows to g.h
 // Worked out on the host, once (chain.hip, seal_epilogue).  In the table every operand has an address that can be read: one that comes
 // from a register slot, or does not exist, names the GEMV's output buffer, with the period rows * n.
-constexpr unsigned kEpiDecoder = 1u << 21;      // the kernels are GELU of the GEMV's result, then one or two adds with an operand from memory, which is in1
+constexpr unsigned kEpiDecoder = 1u << 21;      // the kernels are GELU of the GEMV's result, then up to two adds with an operand from memory, which is in1
 constexpr unsigned kEpiMemFirst = 1u << 9;      // MergePhase::ind: that operand is the add's first
 constexpr unsigned kEpiAnySlot = 1u << 22;      // some operand of the epilogue is a pointer-table slot
 constexpr unsigned kEpiPlain = 1u << 23;        // no operand of the epilogue has a broadcast period
