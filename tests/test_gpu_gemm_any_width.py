@@ -75,3 +75,25 @@ def test_rows_of_sixteen_million_columns():
     k = KernelSpec("gemv", "bf16", 0, (Ref(WEIGHT, 0), Ref(EXT, 0)), n, rows=rows, cols=cols)
     h = Harness(ChainSpec("gemm_long", [k], [TensorSpec("bf16", rows * cols)], [TensorSpec("bf16", rows * n)], [TensorSpec("bf16", n * cols)], [0], 7201))
     _check(h)
+
+
+@pytest.mark.parametrize("rows,n,cols", [(1, 1030, 2048), (1, 5, 61), (2, 2056, 1024), (4, 2046, 520), (5, 2048, 2048), (16, 40, 1030), (20, 33, 520), (40, 48, 1024), (72, 2304, 2304),
+                                         (81, 37, 2048), (128, 2048, 256), (130, 8192, 136)])
+@pytest.mark.parametrize("tail", ["gelu", "add", "mul", "gelu mul", "add gelu"])
+def test_short_tails(rows, n, cols, tail):
+    """One or two kernels behind the GEMV, GELU alone, in front and last, out of place, with and without the RMSNorm in front."""
+    N = rows * n
+    ks = [KernelSpec("rmsnorm", "bf16", 0, (Ref(EXT, 0), Ref(WEIGHT, 1)), cols, rows=rows, cols=cols, eps=1e-6)]
+    for h in (Ref(INT, 0), Ref(EXT, 0)):
+        ks.append(KernelSpec("gemv", "bf16", 1, (Ref(WEIGHT, 0), h), n, rows=rows, cols=cols))
+        for op in tail.split():
+            src = Ref(INT, ks[-1].out)
+            ks.append(KernelSpec("gelu", "bf16", ks[-1].out + 1, (src,), N) if op == "gelu" else KernelSpec(op, "bf16", ks[-1].out + 1, (Ref(EXT, 1), src), N, m=N))
+    spec = ChainSpec(f"tail_{rows}x{n}x{cols}", ks, [TensorSpec("bf16", rows * cols), TensorSpec("bf16", N)],
+                     [TensorSpec("bf16", rows * cols)] + [TensorSpec("bf16", N) for _ in range(3)],
+                     [TensorSpec("bf16", n * cols, ("normal", 0.0, 0.05)), TensorSpec("bf16", cols, ("normal", 1.0, 0.1))], [], 7300)
+    spec.outputs[:] = sorted({k.out for k in spec.kernels})
+    h = Harness(spec)
+    merged, unmerged = h.chain.graph_dispatches()
+    assert merged < unmerged
+    _check(h)
