@@ -1193,9 +1193,11 @@ __global__ __launch_bounds__(kBlock) void k_gemv_rows(RideArgs<RIDE> p) {
     constexpr bool PRO = RIDE == kPrologue;
     const MmHead m = mm_head<RIDE>(p);
     const int n = m.n;
-    // up to 2048 columns an XCD takes a contiguous stretch of the columns (decode chain, 2048 columns, 1 row 430 -> 406 us, 4 rows
-    // 482 -> 472; 1024 columns, 1 row 347 -> 326); longer rows stream better dealt out in turn (4096 columns, 4 rows 289 against 304)
-    const unsigned bid = U <= 4 ? xcd_stretch(blockIdx.x, (unsigned)(n + 4 * R - 1) / (4 * R)) : blockIdx.x;
+    // up to 2048 columns an XCD takes a contiguous stretch of the outputs (decode chain, 2048 columns, 1 row 430 -> 406 us, 4 rows
+    // 482 -> 472; 1024 columns, 1 row 347 -> 326), at 2048 columns only while that is one workgroup per CU: eight distant streams of
+    // long rows are slower than one (1 row, 8192 outputs 9.2 against 7.9 us, 4 rows 9.8 against 9.1; below 1537 columns the
+    // stretch is the faster one up to 32768 outputs); longer rows the same (4096 columns, 4 rows 289 against 304)
+    const unsigned bid = U < 4 || (U == 4 && n <= 1024 * R) ? xcd_stretch(blockIdx.x, (unsigned)(n + 4 * R - 1) / (4 * R)) : blockIdx.x;
     bf16_t* hstore = bid == 0 ? m.hstore : nullptr;
     __shared__ v4u hs[RB * U * 64];
     __shared__ f32x4 part[4];
