@@ -81,8 +81,11 @@ struct TableArgs {
 // registers when that kernel reads the same buffer element for element -- so the run costs one trip
 // to memory, not one per kernel.  Operands that no kernel of the run produces are fetched up front.
 constexpr int kMergeShortPhases = 4;      // kernels per merged dispatch
-constexpr int kMergeMaxPhases = 8;        // ... of bf16 kernels from kMergeLongFrom elements on
-constexpr long long kMergeLongFrom = 16384;
+constexpr int kMergeMaxPhases = 8;        // ... of bf16 kernels over kMergeLongFrom to kMergeLongTo elements
+// Below, runs stay at four kernels (64 kernels on 4096 elements 52 us, on 16384 in runs of eight 48; longer runs of smaller
+// tensors were not measured); above, memory bounds the run and the wider kernel has fewer waves in flight (64 kernels, us in runs of eight / four: 2^20
+// elements 77 / 88, 2^21 108 / 113, 3 * 10^6 149 / 142, 2^23 335 / 306, 2^25 1171 / 994).
+constexpr long long kMergeLongFrom = 16384, kMergeLongTo = 1ll << 21;
 constexpr int kMergeSlots = 3;            // outputs a lane keeps in registers for later kernels of the run
 constexpr unsigned kMergeFromMemory = 255;
 

@@ -942,7 +942,7 @@ bool merge_candidate(int op, int dtype, const Shape& s, bool whole_vectors, long
 
 bool merge_narrow(int dtype, long long n) { return dtype == kF32 && n > 0 && n <= kMergeNarrowMax; }
 
-int merge_max_phases(int dtype, long long n) { return dtype == kBF16 && n >= kMergeLongFrom ? kMergeMaxPhases : kMergeShortPhases; }
+int merge_max_phases(int dtype, long long n) { return dtype == kBF16 && n >= kMergeLongFrom && n <= kMergeLongTo ? kMergeMaxPhases : kMergeShortPhases; }
 
 const void* merged_kernel(int dtype, bool narrow, int phases) {
     if (dtype == kF32) return narrow ? PG_FN(k_merged<float, 4, kMergeShortPhases>) : PG_FN(k_merged<float, 16, kMergeShortPhases>);

@@ -306,3 +306,10 @@ def test_matrix_cores_take_every_gemv_of_five_rows_and_more(rows, n, cols, want)
     ch = pg.Chain.host_only(_gemv_chain("bf16", rows, n, cols))
     assert ch.launch_shape(0) == (want, 256) != (-(-n // 4), 256)
     ch.close()
+
+
+@pytest.mark.parametrize("numel,want", [(16383, 16), (16384, 8), (1 << 21, 8), ((1 << 21) + 1, 16), (1 << 25, 16)])
+def test_runs_of_eight_bf16_kernels_only_where_they_are_faster(numel, want):
+    ch = pg.Chain.host_only(elementwise_chain(n_kernels=64, numel=numel, dtype="bf16"))
+    assert ch.graph_dispatches() == (want, 64)
+    ch.close()
