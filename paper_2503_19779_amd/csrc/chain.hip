@@ -373,6 +373,11 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
             written.push_back(d.out.index);
         }
         if (e - i < 2 || m == 0) return false;
+        // a few kernels whose carry is their whole tensor are element-for-element kernels: that kind of run holds them as well, and
+        // goes on where the next kernel takes their result as its first operand
+        bool whole_run = e - i <= pgk::merge_max_phases(k[i].dtype, k[i].n);
+        for (int t = i; t < e; t++) whole_run = whole_run && k[t].n == k[i].n && (k[t].op == PG_GELU || whole(k[t], 1, k[t].n));
+        if (whole_run) return false;
         g.k0 = i;
         g.k1 = e;
         g.carry = true;

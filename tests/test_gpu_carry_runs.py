@@ -38,6 +38,19 @@ def test_refresh_chains(tensors, log2_max, seed):
     _check(h, step=log2_max < 20)
 
 
+@pytest.mark.parametrize("n,kernels", [(8, 3), (256, 4), (512, 6), (512, 13)])
+def test_carries_that_are_whole_tensors(n, kernels):
+    """Every kernel takes what the one before wrote, whole, as its second operand -- and every fourth as its first."""
+    ks = [KernelSpec("gelu", "bf16", 0, (Ref(EXT, 0),), n)]
+    for i in range(1, kernels):
+        prev, own = Ref(INT, ks[-1].out), Ref(EXT, i % 3)
+        ks.append(KernelSpec("add" if i % 2 else "mul", "bf16", i % 2, (prev, own) if i % 4 == 2 else (own, prev), n, m=n))
+    spec = ChainSpec(f"whole_{n}_{kernels}", ks, [TensorSpec("bf16", n)] * 3, [TensorSpec("bf16", n)] * 2, [], [0, 1], 8200 + kernels)
+    h = Harness(spec)
+    assert h.chain.graph_dispatches()[0] <= -(-kernels // 4)
+    _check(h)
+
+
 @pytest.mark.parametrize("period", [8, 64, 256, 512])
 @pytest.mark.parametrize("seed", [1, 2, 3, 4])
 def test_random_runs(period, seed):

@@ -313,3 +313,17 @@ def test_runs_of_eight_bf16_kernels_only_where_they_are_faster(numel, want):
     ch = pg.Chain.host_only(elementwise_chain(n_kernels=64, numel=numel, dtype="bf16"))
     assert ch.graph_dispatches() == (want, 64)
     ch.close()
+
+
+def _mixed_chain(n):
+    """Element for element: the second kernel takes the first's result as its second operand, the others as their first."""
+    ks = [KernelSpec("gelu", "bf16", 0, (Ref(EXT, 0),), n), KernelSpec("add", "bf16", 1, (Ref(EXT, 1), Ref(INT, 0)), n, m=n),
+          KernelSpec("add", "bf16", 0, (Ref(INT, 1), Ref(EXT, 2)), n, m=n), KernelSpec("mul", "bf16", 1, (Ref(INT, 0), Ref(WEIGHT, 0)), n, m=n)]
+    return ChainSpec("mixed", ks, [TensorSpec("bf16", n)] * 3, [TensorSpec("bf16", n)] * 2, [TensorSpec("bf16", n)], [0, 1], 1)
+
+
+@pytest.mark.parametrize("n", [8, 256, 512, 1024, 1000])
+def test_short_element_for_element_kernels_stay_one_run(n):
+    ch = pg.Chain.host_only(_mixed_chain(n))
+    assert ch.graph_dispatches() == (1, 4)
+    ch.close()
