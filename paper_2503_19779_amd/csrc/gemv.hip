@@ -1411,7 +1411,21 @@ bool merge_head(int op, int dtype, const Shape& s, long long* n_out) {
     return true;
 }
 
-bool merge_prologue(const Shape& s) { return s.rows <= 4 || (s.rows <= kPrologueMaxRows && s.cols <= 2048); }
+// Every workgroup normalises its rows anew, which is free while the grid fills the chip once or twice and the more rows the
+// dearer beyond; the separate RMSNorm costs a node.  RMSNorm, GEMV and GELU, us with the RMSNorm in front / on its own, on both
+// sides of each line:
+//   3 to 8 rows    1024 workgroups: 4 rows of 1024 columns 5.8 / 7.0, 8 of 2048 12.1 / 13.0; 4096: 15.3 / 15.0, 36.1 / 34.3
+//                  longer than 4096 columns, 256 workgroups: 4 of 8192 10.5 / 11.4; 512: 19.5 / 17.2
+//   9 to 16 rows   512: 16 of 1024 5.9 / 6.7, 16 of 2048 8.7 / 8.7; 1024: 8.7 / 8.7, 14.5 / 13.6
+//   17 to 32 rows  1024: 32 of 1024 9.6 / 11.1; 4096: 28.7 / 28.6; above 1024 columns, 512: 32 of 2048 9.8 / 9.7; 1024: 15.7 / 15.5
+// One and two rows: 4096 workgroups of 2048 columns 23.4 / 25.2.
+bool merge_prologue(const Shape& s) {
+    if (s.rows <= 2) return true;
+    const long long blocks = s.rows <= 4 ? blocks_for(s.n, s.n >= kRowsTwoFrom ? 8 : 4) : s.rows <= 16 ? blocks_for(s.n, 8) : 2 * (long long)blocks_for(s.n, 16);
+    if (s.rows <= 4 && s.cols > 4096) return blocks <= 256;
+    if (s.rows > 4 && (s.rows > kPrologueMaxRows || s.cols > 2048)) return false;
+    return blocks <= (s.rows <= 8 || (s.rows > 16 && s.cols <= 1024) ? 1024 : 512);
+}
 
 void plan_gemv_epilogue(const Shape& s, bool with_prologue, Launch* out) {
     const int rows = (int)s.rows, n = (int)s.n, cols = (int)s.cols;

@@ -244,7 +244,8 @@ bool plan_sbr_run(int dtype, long long n, long long inner, Launch* out);
 // beyond 2048 columns only for n >= 1024), 5 rows and more of 8 columns and more (the matrix-core forms).
 // *n_out = rows * n.
 bool merge_head(int op, int dtype, const Shape& shape, long long* n_out);
-// ... and does it also take the RMSNorm in front?  The matrix-core forms up to 2048 columns, and up to kPrologueMaxRows rows:
+// ... and does it also take the RMSNorm in front?  While the grid is small enough (gemv.hip); the matrix-core forms up to 2048
+// columns, and up to kPrologueMaxRows rows:
 // two tiles of 16 rows, one per workgroup, fill the 256 CUs once; beyond, two workgroups share a CU and each
 // normalises its tile, which costs more than the dispatch it saves (decode chain at 48 rows: 1261 -> 1336 us).
 constexpr int kPrologueMaxRows = 32;

@@ -327,3 +327,17 @@ def test_short_element_for_element_kernels_stay_one_run(n):
     ch = pg.Chain.host_only(_mixed_chain(n))
     assert ch.graph_dispatches() == (1, 4)
     ch.close()
+
+
+@pytest.mark.parametrize("rows,n,cols,want", [(1, 32768, 2048, 1), (2, 32768, 1024, 1), (3, 8192, 520, 1), (4, 8200, 520, 2), (4, 2048, 8192, 1), (4, 2056, 8192, 2),
+                                              (8, 8192, 2048, 1), (8, 8200, 2048, 2), (9, 4096, 1024, 1), (16, 4104, 1024, 2), (32, 8192, 1024, 1), (32, 8208, 1024, 2),
+                                              (17, 4096, 1030, 1), (17, 4112, 1030, 2), (33, 16, 64, 2)])
+def test_rmsnorm_rides_in_front_only_while_the_grid_is_small(rows, n, cols, want):
+    ks = [KernelSpec("rmsnorm", "bf16", 0, (Ref(EXT, 0), Ref(WEIGHT, 1)), cols, rows=rows, cols=cols, eps=1e-6),
+          KernelSpec("gemv", "bf16", 1, (Ref(WEIGHT, 0), Ref(INT, 0)), n, rows=rows, cols=cols),
+          KernelSpec("gelu", "bf16", 1, (Ref(INT, 1),), rows * n)]
+    spec = ChainSpec("up", ks, [TensorSpec("bf16", rows * cols)], [TensorSpec("bf16", rows * cols), TensorSpec("bf16", rows * n)],
+                     [TensorSpec("bf16", n * cols), TensorSpec("bf16", cols)], [1], 1)
+    ch = pg.Chain.host_only(spec)
+    assert ch.graph_dispatches() == (want, 3)
+    ch.close()
