@@ -308,8 +308,7 @@ __device__ __forceinline__ void lds_barrier() {
 
 // ---- elementwise ----------------------------------------------------------------------------
 // GELU(a) = a * Phi(a) with Phi(a) = erfc(-a / sqrt 2) / 2 (keeps relative accuracy in the left
-// tail).  For fp32 tensors it is evaluated in fp64 and rounded once, so that the result is the
-// correctly rounded one except within ~1e-16 of a rounding boundary: an fp32 erfc is a few ulp off,
+// tail).  For fp32 tensors it is evaluated in fp64 and rounded once (gelu_f32 below): an fp32 erfc is a few ulp off,
 // and a chain of multiplies and cancelling adds amplifies that beyond 1e-5.  For bf16 tensors fp32
 // is far more than the 8 stored bits need, and the library erfcf (a few hundred instructions over
 // several branches, which a wave of mixed values all takes) made large GELU kernels ALU-bound at a
@@ -351,62 +350,66 @@ __device__ __forceinline__ float gelu_bf16(float a) {
     return (0.5f * a) * erfc_x;      // a NaN comes back through this product; -inf * 0 = NaN as in the definition
 }
 
-// The same form in fp64 for fp32 tensors: Q of degree 20 in the centred variable s = 2 u / u(28) - 1 (a Chebyshev fit on
-// z <= 28, beyond which erfc(z) is 0 in fp64), its even and odd terms in two chains; exp(r) on |r| <= 0.35 by a degree-11 fit.
-// erfc(z) comes out within 1.1e-14 of its value for |a| < 15.5 (6e-14 down to 1e-300); of half a million fp32 inputs
-// over both tails every rounded result is that of the exact product.  About 60 instructions and no branch, where the library's erfc
-// runs several branches of a wave of mixed values one after the other.
+// The same form in fp64 for fp32 tensors, with what the rounding of z would cost taken out: z^2 = a^2 / 2 is exact (a has 24 bits), 1 - u
+// keeps its rounding error, exp(r) enters as exp(r) - 1.  Q of degree 22 in the centred variable s = 2 u / u(10.4) - 1 (a
+// Chebyshev fit on z <= 10.4, beyond which the result rounds to zero whatever Q is), its even and odd terms in two chains;
+// exp(r) - 1 on |r| <= 0.352 by a fit of degree 11.  The fp64 result is within 7.1e-16 of a * Phi(a), relative, for every a > -14.3
+// (1.5e-16 in the mean below -6, 2.7e-16 at most above -0.1); the formula with the library's erfc at a rounded z, several branches that a
+// wave of mixed values takes one after the other, is within 5.5e-16 about zero and 3.2e-14 towards -14.3.  Of the 580 million
+// fp32 inputs of 5e-10 <= |a| < 14.5 one result is not the correctly rounded one (two with that formula).  About 65 instructions,
+// no branch.
 __device__ __forceinline__ float gelu_f32(float a) {
-    const double d = (double)a, x = d * -0.70710678118654752440;
-    const double z = __builtin_fmin(__builtin_fabs(x), 28.0);
-    const double w = 2.0 + z;
+    const double d = (double)a;
+    const double z = __builtin_fmin(__builtin_fabs(d) * 0.70710678118654752440, 10.4);
+    const double w = 2.0 + z, w_lo = z - (w - 2.0);                    // 2 + z = w + w_lo exactly
     double y = __builtin_amdgcn_rcp(w);
     y = __builtin_fma(__builtin_fma(-w, y, 1.0), y, y);
     y = __builtin_fma(__builtin_fma(-w, y, 1.0), y, y);
-    const double u = z * y, t = 2.0 * y;                               // t = 1 - u
-    const double s = __builtin_fma(u, 2.142857142857143, -1.0), s2 = s * s;
-    double pe = 5.1469897284113406e-08;
-    pe = __builtin_fma(pe, s2, -4.601968487444969e-07);
-    pe = __builtin_fma(pe, s2, 2.246724383389986e-06);
-    pe = __builtin_fma(pe, s2, -7.060637336547474e-06);
-    pe = __builtin_fma(pe, s2, 1.0309358636166363e-05);
-    pe = __builtin_fma(pe, s2, 3.840485899558906e-05);
-    pe = __builtin_fma(pe, s2, -0.00040875583843036264);
-    pe = __builtin_fma(pe, s2, 0.0023733790953262);
-    pe = __builtin_fma(pe, s2, -0.012692411912592745);
-    pe = __builtin_fma(pe, s2, 0.08401770351322346);
-    pe = __builtin_fma(pe, s2, -1.3430461414518076);
-    double po = -5.483273040448299e-08;
-    po = __builtin_fma(po, s2, 1.3441151878668944e-07);
-    po = __builtin_fma(po, s2, 1.5507677602442915e-06);
-    po = __builtin_fma(po, s2, -1.4618058877969567e-05);
-    po = __builtin_fma(po, s2, 7.134147933531289e-05);
-    po = __builtin_fma(po, s2, -0.0002518449117441309);
-    po = __builtin_fma(po, s2, 0.0006943424204250014);
-    po = __builtin_fma(po, s2, -0.001435238879633228);
-    po = __builtin_fma(po, s2, 0.0015729916678614312);
-    po = __builtin_fma(po, s2, -0.013593004892545762);
+    const double t = 2.0 * y, t_lo = y * __builtin_fma(-w_lo, t, __builtin_fma(-w, t, 2.0));      // 1 - u = t + t_lo
+    const double u = z * y, s = __builtin_fma(u, 2.3846153846153846, -1.0), s2 = s * s;
+    double pe = 6.096496283622283e-10;
+    pe = __builtin_fma(pe, s2, -4.3704153493283935e-09);
+    pe = __builtin_fma(pe, s2, -1.41491445058183e-09);
+    pe = __builtin_fma(pe, s2, 1.9394376933458417e-07);
+    pe = __builtin_fma(pe, s2, -1.4974665463589925e-06);
+    pe = __builtin_fma(pe, s2, 6.261681705770192e-06);
+    pe = __builtin_fma(pe, s2, -1.0497636139937293e-05);
+    pe = __builtin_fma(pe, s2, -7.345319204153287e-05);
+    pe = __builtin_fma(pe, s2, 0.0009401958958586842);
+    pe = __builtin_fma(pe, s2, -0.007581680008508557);
+    pe = __builtin_fma(pe, s2, 0.06684199270480724);
+    pe = __builtin_fma(pe, s2, -1.3408074426393273);
+    double po = 1.3835186521888504e-09;
+    po = __builtin_fma(po, s2, -1.8127755043420434e-08);
+    po = __builtin_fma(po, s2, 1.0624132699881106e-07);
+    po = __builtin_fma(po, s2, -2.5500292430170833e-07);
+    po = __builtin_fma(po, s2, -1.095015580580727e-06);
+    po = __builtin_fma(po, s2, 1.542531630549678e-05);
+    po = __builtin_fma(po, s2, -9.697377010041972e-05);
+    po = __builtin_fma(po, s2, 0.00044017709978370716);
+    po = __builtin_fma(po, s2, -0.0015871845088182162);
+    po = __builtin_fma(po, s2, 0.004735528189346559);
+    po = __builtin_fma(po, s2, -0.02743330950618046);
     const double p = __builtin_fma(po, s, pe) * u;
-    const double q = z * z, e = __builtin_fma(z, z, -q);               // z^2 = q + e exactly
+    const double q = __builtin_fmin(0.5 * d * d, 1100.0);              // z^2, exact: a has 24 bits
     constexpr double kLog2e = 1.4426950408889634, kLn2Hi = 0x1.62e42fefa0000p-1, kLn2Lo = 1.6465949582897082e-12;
     const double kf = __builtin_rint((p - q) * kLog2e);
     double r = __builtin_fma(kf, -kLn2Hi, -q);
     r = r + p;
-    r = r - e;
     r = __builtin_fma(kf, -kLn2Lo, r);
-    double ex = 2.5132282980221963e-08;
-    ex = __builtin_fma(ex, r, 2.7625457822035487e-07);
-    ex = __builtin_fma(ex, r, 2.7557186121323636e-06);
-    ex = __builtin_fma(ex, r, 2.4801509529176997e-05);
-    ex = __builtin_fma(ex, r, 0.0001984126993240594);
-    ex = __builtin_fma(ex, r, 0.001388888892510718);
-    ex = __builtin_fma(ex, r, 0.008333333333309321);
-    ex = __builtin_fma(ex, r, 0.04166666666660774);
-    ex = __builtin_fma(ex, r, 0.16666666666666688);
-    ex = __builtin_fma(ex, r, 0.5000000000000002);
-    ex = 1.0 + __builtin_fma(r * r, ex, r);
-    const double v = __builtin_ldexp(t * ex, (int)kf);
-    return (float)((0.5 * d) * (x < 0.0 ? 2.0 - v : v));
+    double ex = 2.5096918075802424e-08;
+    ex = __builtin_fma(ex, r, 2.761557975513923e-07);
+    ex = __builtin_fma(ex, r, 2.7557277571635357e-06);
+    ex = __builtin_fma(ex, r, 2.480153314383674e-05);
+    ex = __builtin_fma(ex, r, 0.0001984126985560737);
+    ex = __builtin_fma(ex, r, 0.0013888888907531355);
+    ex = __builtin_fma(ex, r, 0.008333333333332001);
+    ex = __builtin_fma(ex, r, 0.041666666666649345);
+    ex = __builtin_fma(ex, r, 0.16666666666666666);
+    ex = __builtin_fma(ex, r, 0.5);
+    const double em1 = __builtin_fma(r * r, ex, r);                    // exp(r) - 1
+    const double v = __builtin_ldexp(t + __builtin_fma(t, em1, t_lo), (int)kf);
+    return (float)((0.5 * d) * (d > 0.0 ? 2.0 - v : v));
 }
 
 template <int OP, bool WIDE>
