@@ -1363,7 +1363,7 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         out->grid = dim3((unsigned)(wide * four));
     } else if (rows >= kMmWideRows || (ntiles > 1 && wide * two >= 256)) {
         out->fn = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8>) : PG_FN(k_gemm_tile<2, 2, 2, 4>);
-        out->gemm_row_groups = (unsigned)(two == 3 ? 4 : two);
+        out->gemm_row_groups = (unsigned)two;
         out->grid = dim3((unsigned)wide * out->gemm_row_groups);
     } else {
         out->fn = merged ? PG_FN(k_gemm_tile<1, 1, 2, 8>) : PG_FN(k_gemm_tile<1, 1, 2, 4>);
