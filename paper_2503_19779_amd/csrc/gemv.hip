@@ -914,11 +914,7 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
     const int rows = m.rows, n = m.n, cols = m.cols;
     const int ncb = (n + 16 * CT - 1) / (16 * CT);
     const int at = (int)xcd_stretch(blockIdx.x, (unsigned)(ncb * m.row_groups)), cb = at / m.row_groups, rg = at % m.row_groups;
-    // tiles of rows per workgroup: a multiple of RT, so that no two workgroups compute (and update in place) the same rows
-    const int ntiles = (rows + 15) / 16, per = (ntiles + RT * m.row_groups - 1) / (RT * m.row_groups) * RT;
-    const int t0 = rg * per, t1 = (t0 + per < ntiles) ? t0 + per : ntiles;
-    if (t0 >= t1) return;                                // whole workgroup: nothing waits on it
-    const int j0 = cb * 16 * CT;
+    const int r0 = rg * 16 * RT, j0 = cb * 16 * CT;
     const int nkb = (cols + 63) / 64;
     char* mine = ring + wave * kWaveLds;
     const int r8 = lane >> 3;                            // row within the eight of a load instruction
@@ -930,129 +926,124 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
     const unsigned f0 = lds0 + (lane & 15) * 128 + (((lane >> 4) ^ (lane & 7)) * 16), f1 = lds0 + (lane & 15) * 128 + (((4 + (lane >> 4)) ^ (lane & 7)) * 16);
     const bf16_t* wb = m.W + (size_t)j0 * cols;
     const int er = tid / kPerRow, ec = (tid % kPerRow) * NE;           // output stage: a lane finishes NE consecutive columns of one row
-#pragma unroll 1
-    for (int t = t0; t < t1; t += RT) {
-        const int r0 = t * 16;
-        const bf16_t* hb = m.h + (size_t)r0 * cols;
-        unsigned row_at[NL];                             // element offset of the row each load instruction takes here
+    const bf16_t* hb = m.h + (size_t)r0 * cols;
+    unsigned row_at[NL];                             // element offset of the row each load instruction takes here
 #pragma unroll
-        for (int q = 0; q < NL; q++) {
-            const int r = (q < 2 * RT ? q : q - 2 * RT) * 8 + r8, last = (q < 2 * RT ? rows - r0 : n - j0) - 1;
-            row_at[q] = (unsigned)(r < last ? r : last) * (unsigned)cols;
-        }
-        f32x4 acc[PK][RT][CT];
+    for (int q = 0; q < NL; q++) {
+        const int r = (q < 2 * RT ? q : q - 2 * RT) * 8 + r8, last = (q < 2 * RT ? rows - r0 : n - j0) - 1;
+        row_at[q] = (unsigned)(r < last ? r : last) * (unsigned)cols;
+    }
+    f32x4 acc[PK][RT][CT];
 #pragma unroll
-        for (int pk = 0; pk < PK; pk++)
+    for (int pk = 0; pk < PK; pk++)
 #pragma unroll
-            for (int i = 0; i < RT; i++)
+        for (int i = 0; i < RT; i++)
 #pragma unroll
-                for (int j = 0; j < CT; j++) acc[pk][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // the epilogue's table behind the first block's loads: asked for behind all of them it came 1.1 us later
-        auto epilogue_begin = [&] {
-            if (t == t0) emit.prepare();
-            emit.begin(r0 + er, j0 + ec, er < 16 * RT);
-        };
-        // this wave's K-blocks: wave, wave + NW, ...; number b of them belongs to its eighth b % PK
-        const int nb = (nkb - wave + NW - 1) / NW;
-        auto multiply = [&](f32x4 (&sum)[RT][CT], v4u (&f)[2 * F]) {
+            for (int j = 0; j < CT; j++) acc[pk][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the epilogue's table behind the first block's loads: asked for behind all of them it came 1.1 us later
+    auto epilogue_begin = [&] {
+        emit.prepare();
+        emit.begin(r0 + er, j0 + ec, er < 16 * RT);
+    };
+    // this wave's K-blocks: wave, wave + NW, ...; number b of them belongs to its eighth b % PK
+    const int nb = (nkb - wave + NW - 1) / NW;
+    auto multiply = [&](f32x4 (&sum)[RT][CT], v4u (&f)[2 * F]) {
 #pragma unroll
-            for (int s = 0; s < 2; s++)
-#pragma unroll
-                for (int i = 0; i < RT; i++)
-#pragma unroll
-                    for (int j = 0; j < CT; j++)
-                        sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[s * F + i]), __builtin_bit_cast(bf16x8, f[s * F + RT + j]), sum[i][j], 0, 0, 0);
-        };
-        if (__builtin_expect(direct, 1)) {
-            auto issue = [&](int b, int slot) {
-                const int k = (wave + NW * b) * 64 + chunk * 8;
-                const unsigned ke = k < cols ? (unsigned)k : 0u;           // a chunk past the end is read from column 0 and zeroed later
-#pragma unroll
-                for (int q = 0; q < NL; q++)
-                    __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)(q < 2 * RT ? hb : wb) + (row_at[q] + ke)),
-                                                     (__attribute__((address_space(3))) void*)(mine + slot * kBlockLds + q * 1024), 16, 0, 0);
-            };
-            if (nb > 0) issue(0, 0);
-            epilogue_begin();
-            if (S == 2 && nb > 1) issue(1, 1);
-            int slot = 0;
-#pragma unroll 1
-            for (int b0 = 0; b0 < nb; b0 += PK) {
-#pragma unroll
-                for (int pk = 0; pk < PK; pk++) {
-                    const int b = b0 + pk;
-                    if (PK > 1 && b >= nb) break;
-                    // loads complete in order: block b is in once at most the younger block's loads are outstanding (other loads
-                    // among them only make the wait stricter)
-                    if (S == 2 && b + 1 < nb) vm_wait<NL>();
-                    else vm_wait<0>();
-                    v4u f[2 * F];
-                    ring_frags<F>(f0 + slot * kBlockLds, f1 + slot * kBlockLds, f);
-                    if (b + S < nb) issue(b + S, slot);                    // the slot has been read
-                    if (rem && wave + NW * b == nkb - 1) {
-#pragma unroll
-                        for (int s = 0; s < 2; s++)
-                            if ((s * 4 + (lane >> 4)) * 8 >= rem)
-#pragma unroll
-                                for (int i = 0; i < F; i++) f[s * F + i] = v4u{0u, 0u, 0u, 0u};
-                    }
-                    multiply(acc[pk], f);
-                    slot = slot + 1 == S ? 0 : slot + 1;
-                }
-            }
-        } else {
-            unsigned g[NL][4];
-            auto fetch = [&](int b) {
-                const unsigned ke = span_at<false>(cols, (wave + NW * b) * 8 + chunk);
-#pragma unroll
-                for (int q = 0; q < NL; q++) load_any<false>(q < 2 * RT ? hb : wb, row_at[q] + ke, g[q]);
-            };
-            if (nb > 0) fetch(0);
-            epilogue_begin();
-#pragma unroll 1
-            for (int b0 = 0; b0 < nb; b0 += PK) {
-#pragma unroll
-                for (int pk = 0; pk < PK; pk++) {
-                    const int b = b0 + pk;
-                    if (PK > 1 && b >= nb) break;
-#pragma unroll
-                    for (int q = 0; q < NL; q++) {
-                        span_fix<false>(cols, (wave + NW * b) * 8 + chunk, g[q]);
-                        *reinterpret_cast<v4u*>(mine + (q * 8 + r8) * 128 + ((chunk ^ r8) * 16)) = v4u{g[q][0], g[q][1], g[q][2], g[q][3]};
-                    }
-                    if (b + 1 < nb) fetch(b + 1);
-                    v4u f[2 * F];
-                    ring_frags<F>(f0, f1, f);                              // behind the writes above: one wave's LDS operations execute in order
-                    multiply(acc[pk], f);
-                }
-            }
-        }
-#pragma unroll
-        for (int pk = 0; pk < PK; pk++)
+        for (int s = 0; s < 2; s++)
 #pragma unroll
             for (int i = 0; i < RT; i++)
 #pragma unroll
-                for (int j = 0; j < CT; j++) {
-                    mm_drained(acc[pk][i][j]);
-                    float* dst = reinterpret_cast<float*>(mine) + pk * kRed + (i * 16 + (lane >> 4) * 4) * kRedRow + j * 16 + (lane & 15);
-                    const f32x4 v = acc[pk][i][j];
-                    dst[0] = v.x; dst[kRedRow] = v.y; dst[2 * kRedRow] = v.z; dst[3 * kRedRow] = v.w;
-                }
-        lds_barrier();
-        if (er < 16 * RT) {
+                for (int j = 0; j < CT; j++)
+                    sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[s * F + i]), __builtin_bit_cast(bf16x8, f[s * F + RT + j]), sum[i][j], 0, 0, 0);
+    };
+    if (__builtin_expect(direct, 1)) {
+        auto issue = [&](int b, int slot) {
+            const int k = (wave + NW * b) * 64 + chunk * 8;
+            const unsigned ke = k < cols ? (unsigned)k : 0u;           // a chunk past the end is read from column 0 and zeroed later
 #pragma unroll
-            for (int e = 0; e < NE; e++) {
-                float sum = 0.f;
+            for (int q = 0; q < NL; q++)
+                __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)(q < 2 * RT ? hb : wb) + (row_at[q] + ke)),
+                                                 (__attribute__((address_space(3))) void*)(mine + slot * kBlockLds + q * 1024), 16, 0, 0);
+        };
+        if (nb > 0) issue(0, 0);
+        epilogue_begin();
+        if (S == 2 && nb > 1) issue(1, 1);
+        int slot = 0;
+#pragma unroll 1
+        for (int b0 = 0; b0 < nb; b0 += PK) {
 #pragma unroll
-                for (int w = 0; w < 8; w++) {
-                    const float part = reinterpret_cast<const float*>(ring + (w % NW) * kWaveLds)[(w / NW) * kRed + er * kRedRow + ec + e];
-                    sum = w == 0 ? part : sum + part;
+            for (int pk = 0; pk < PK; pk++) {
+                const int b = b0 + pk;
+                if (PK > 1 && b >= nb) break;
+                // loads complete in order: block b is in once at most the younger block's loads are outstanding (other loads
+                // among them only make the wait stricter)
+                if (S == 2 && b + 1 < nb) vm_wait<NL>();
+                else vm_wait<0>();
+                v4u f[2 * F];
+                ring_frags<F>(f0 + slot * kBlockLds, f1 + slot * kBlockLds, f);
+                if (b + S < nb) issue(b + S, slot);                    // the slot has been read
+                if (rem && wave + NW * b == nkb - 1) {
+#pragma unroll
+                    for (int s = 0; s < 2; s++)
+                        if ((s * 4 + (lane >> 4)) * 8 >= rem)
+#pragma unroll
+                            for (int i = 0; i < F; i++) f[s * F + i] = v4u{0u, 0u, 0u, 0u};
                 }
-                emit.put(e, sum);
+                multiply(acc[pk], f);
+                slot = slot + 1 == S ? 0 : slot + 1;
             }
-            emit.end();
         }
-        if (t + RT < t1) __syncthreads();      // the sums are read: the rings are free again
+    } else {
+        unsigned g[NL][4];
+        auto fetch = [&](int b) {
+            const unsigned ke = span_at<false>(cols, (wave + NW * b) * 8 + chunk);
+#pragma unroll
+            for (int q = 0; q < NL; q++) load_any<false>(q < 2 * RT ? hb : wb, row_at[q] + ke, g[q]);
+        };
+        if (nb > 0) fetch(0);
+        epilogue_begin();
+#pragma unroll 1
+        for (int b0 = 0; b0 < nb; b0 += PK) {
+#pragma unroll
+            for (int pk = 0; pk < PK; pk++) {
+                const int b = b0 + pk;
+                if (PK > 1 && b >= nb) break;
+#pragma unroll
+                for (int q = 0; q < NL; q++) {
+                    span_fix<false>(cols, (wave + NW * b) * 8 + chunk, g[q]);
+                    *reinterpret_cast<v4u*>(mine + (q * 8 + r8) * 128 + ((chunk ^ r8) * 16)) = v4u{g[q][0], g[q][1], g[q][2], g[q][3]};
+                }
+                if (b + 1 < nb) fetch(b + 1);
+                v4u f[2 * F];
+                ring_frags<F>(f0, f1, f);                              // behind the writes above: one wave's LDS operations execute in order
+                multiply(acc[pk], f);
+            }
+        }
+    }
+#pragma unroll
+    for (int pk = 0; pk < PK; pk++)
+#pragma unroll
+        for (int i = 0; i < RT; i++)
+#pragma unroll
+            for (int j = 0; j < CT; j++) {
+                mm_drained(acc[pk][i][j]);
+                float* dst = reinterpret_cast<float*>(mine) + pk * kRed + (i * 16 + (lane >> 4) * 4) * kRedRow + j * 16 + (lane & 15);
+                const f32x4 v = acc[pk][i][j];
+                dst[0] = v.x; dst[kRedRow] = v.y; dst[2 * kRedRow] = v.z; dst[3 * kRedRow] = v.w;
+            }
+    lds_barrier();
+    if (er < 16 * RT) {
+#pragma unroll
+        for (int e = 0; e < NE; e++) {
+            float sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < 8; w++) {
+                const float part = reinterpret_cast<const float*>(ring + (w % NW) * kWaveLds)[(w / NW) * kRed + er * kRedRow + ec + e];
+                sum = w == 0 ? part : sum + part;
+            }
+            emit.put(e, sum);
+        }
+        emit.end();
     }
 }
 
@@ -1354,21 +1345,23 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         out->fn = merged ? gemm_cols_form<kEpilogue>(cols) : gemm_cols_form<kAlone>(cols);
         return;
     }
-    // The largest tile that still gives every CU a workgroup, 32 x 32 from kMmWideRows rows.
-    const long long wide = blocks_for(n, 32), two = (ntiles + 1) / 2, four = (ntiles + 3) / 4;
+    // The largest tile that still gives every CU a workgroup: 64 x 32 in 256 (RMSNorm, GEMV, GELU, GEMV and add on 128 rows of 2048
+    // columns, 8192 outputs 44 us a layer, with 32 x 32 tiles 53); 32 x 32 from kMmWideRows rows, or where tiles of 16 x 16 would be
+    // more than two workgroups per CU (us per launch, 32 x 32 / 16 x 16: 64 rows of 4096 columns, 2048 outputs, 512 tiles 12.6 /
+    // 11.0, 2304 outputs, 576 tiles 12.9 / 14.8; 33 rows, 2304 outputs, 432 tiles 11.0 / 10.1; 70 rows, 2048 outputs, 640 tiles 10.8 / 14.0).
+    const long long wide = blocks_for(n, 32), narrow = blocks_for(n, 16), two = (ntiles + 1) / 2, four = (ntiles + 3) / 4;
     if (merged) out->block = dim3(512);
     if (ntiles > 2 && wide * four >= 256) {
         out->fn = merged ? PG_FN(k_gemm_tile<4, 2, 1, 8>) : PG_FN(k_gemm_tile<4, 2, 2, 4>);
         out->gemm_row_groups = (unsigned)four;
         out->grid = dim3((unsigned)(wide * four));
-    } else if (rows >= kMmWideRows || (ntiles > 1 && wide * two >= 256)) {
+    } else if (rows >= kMmWideRows || (ntiles > 1 && narrow * ntiles > 512)) {
         out->fn = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8>) : PG_FN(k_gemm_tile<2, 2, 2, 4>);
         out->gemm_row_groups = (unsigned)two;
         out->grid = dim3((unsigned)wide * out->gemm_row_groups);
     } else {
         out->fn = merged ? PG_FN(k_gemm_tile<1, 1, 2, 8>) : PG_FN(k_gemm_tile<1, 1, 2, 4>);
-        out->gemm_row_groups = (unsigned)(ntiles < 4 ? ntiles : 4);
-        out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
+        out->grid = dim3((unsigned)(narrow * ntiles));
     }
 }
 

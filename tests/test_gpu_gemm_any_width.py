@@ -36,7 +36,8 @@ def test_square_chains(rows, hidden):
 
 @pytest.mark.parametrize("rows,n,cols", [(6, 17, 40), (17, 4097, 33), (33, 8195, 136), (64, 8192, 200), (77, 8192, 71), (128, 8196, 64), (40, 4096, 72), (20, 8193, 1024),
                                          (200, 40, 300), (96, 2050, 56), (11, 15, 64), (5, 300, 8),
-                                         (6, 1, 40), (9, 2, 1030), (33, 5, 136), (64, 12, 4096), (81, 7, 2056), (128, 8, 2048), (70, 3, 33), (200, 16, 1030), (6, 8201, 40)])
+                                         (6, 1, 40), (9, 2, 1030), (33, 5, 136), (64, 12, 4096), (81, 7, 2056), (128, 8, 2048), (70, 3, 33), (200, 16, 1030), (6, 8201, 40),
+                                         (65, 2050, 2304), (80, 2304, 2601), (70, 40, 2304), (18, 4112, 2056)])
 def test_other_output_widths(rows, n, cols):
     """RMSNorm -> GEMV -> GELU -> add -> add with a broadcast operand, n outputs per row; h then comes straight from
     an external, at an address that is no multiple of 16 bytes."""
