@@ -1059,7 +1059,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
                 e.x = pa.ptr[1];
                 e.gain = pa.ptr[2];
                 e.eps = c->k[grp.k0].eps;
-                e.head |= pgk::kEpiPrologue | pgk::kEpiStoreH;
+                e.head |= pgk::kEpiStoreH;
                 if (kind != kGraphCopy) e.head |= ((pr.ind_mask & 1) ? pgk::kEpiXSlot : 0u) | ((pr.ind_mask & 2) ? pgk::kEpiGainSlot : 0u);
                 // e.g.h is the RMSNorm's output in its current copy: where workgroup 0 stores the normalised rows
             }

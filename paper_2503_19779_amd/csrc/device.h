@@ -113,34 +113,9 @@ __device__ __forceinline__ void load_vec(const T* p, unsigned* w) {
     }
 }
 
-// The same fetch through a pointer that says "global memory" outright.  A tensor address that reached the
+// Through a pointer that says "global memory" outright.  A tensor address that reached the
 // kernel through a pointer-table slot or a run-time choice is a generic pointer to the compiler; generic
 // loads are slower and are counted as LDS operations as well, so a wait for LDS would wait for them too.
-template <typename T, bool AL, bool NT = false>
-__device__ __forceinline__ void load_vec_global(const T* p, unsigned* w) {
-    if constexpr (AL) {
-        v4u t;
-        if constexpr (NT) t = __builtin_nontemporal_load((const v4u PG_GLOBAL*)(uintptr_t)p);
-        else t = *(const v4u PG_GLOBAL*)(uintptr_t)p;
-        w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
-    } else if constexpr (sizeof(T) == 4) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) w[i] = ((const unsigned PG_GLOBAL*)(uintptr_t)p)[i];
-    } else {
-        const unsigned short PG_GLOBAL* q = (const unsigned short PG_GLOBAL*)(uintptr_t)p;
-#pragma unroll
-        for (int i = 0; i < 4; i++) w[i] = (unsigned)q[2 * i] | ((unsigned)q[2 * i + 1] << 16);
-    }
-}
-// The 4-byte vector (one fp32 or two bf16 elements) through a global pointer.
-template <typename T, bool AL>
-__device__ __forceinline__ void load_vec4_global(const T* p, unsigned* w) {
-    if constexpr (sizeof(T) == 4 || AL) w[0] = *(const unsigned PG_GLOBAL*)(uintptr_t)p;
-    else {
-        const unsigned short PG_GLOBAL* q = (const unsigned short PG_GLOBAL*)(uintptr_t)p;
-        w[0] = (unsigned)q[0] | ((unsigned)q[1] << 16);
-    }
-}
 template <typename T>
 __device__ __forceinline__ unsigned load_raw_global(const T* p) {
     if constexpr (sizeof(T) == 4) return *(const unsigned PG_GLOBAL*)(uintptr_t)p;

@@ -122,7 +122,6 @@ constexpr unsigned kEpiStore = 1u << 8;   // MergePhase::ind: this kernel's outp
 // runtime then lets it write a shadow copy of that buffer instead, so that no workgroup can read an
 // element another one has already replaced (chain.hip: versions).
 constexpr unsigned kEpiHeadStore = 1u << 16;    // GemvEpiArgs::head: store the GEMV's result
-constexpr unsigned kEpiPrologue = 1u << 17;     // h is not loaded but computed: RMSNorm of x with gain and eps
 constexpr unsigned kEpiXSlot = 1u << 18, kEpiGainSlot = 1u << 19;   // x / gain are pointer-table slots
 constexpr unsigned kEpiStoreH = 1u << 20;       // workgroup 0 stores the normalised rows to g.h
 // Worked out on the host, once (chain.hip, seal_epilogue).  In the table every operand has an address that can be read: one that comes
