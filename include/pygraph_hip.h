@@ -257,26 +257,34 @@ pg_status pg_set_table_refresh(pg_chain *chain, int32_t how /* pg_table_refresh 
 pg_status pg_set_copy_refresh(pg_chain *chain, int32_t how /* pg_copy_refresh */);
 /* Dispatch merging at capture (on by default).  A graph is "one dispatch, the GPU launches the rest"
  * (Sec. 2.2); on this machine every dependent kernel node still costs about 1.5 us of dispatch, so a
- * captured graph, which knows the whole chain, plays a run of up to 4 consecutive kernels with ONE
- * dispatch where it can: add / mul / GELU and RMSNorm over rows of 256 x 16 bytes, all element for
- * element over the same n elements (a whole number of 16-byte vectors; fp32 tensors of up to 16384
- * elements are worked one element per lane instead, with any n, and only there the fp32 GELU takes
- * part).  A lane runs the kernels in order on its elements with their stand-alone arithmetic and one
- * rounding each, stores every kernel's output that no later kernel of the run overwrites, and hands the stored
- * bits to the next kernel in registers, so
- * results stay bit-identical to eager launches.  A run ends where a kernel reads something an earlier
- * kernel of the run wrote in any other pattern than element for element.  Likewise up to 3 elementwise
- * kernels over the outputs of a bf16 GEMV (1 to 4 rows of h of 8 to 8192 columns, or more rows of 2048
- * columns; GELU of the result, the residual add, an input add) ride in the GEMV's dispatch as an
- * epilogue: each lane that holds a finished output
- * rounds it as the GEMV's store would and runs the following kernels on that element.  Up to 32 rows of
- * h the RMSNorm that produces the GEMV's input rides in front of it as a prologue (every workgroup
- * normalises the rows itself, one stores them); a run whose epilogue overwrites the buffer its prologue
- * reads writes a second copy of that buffer, which the workspace holds (pg_chain_workspace_bytes counts
- * it), and every segment ends with all internal buffers in their first copy, where pg_chain_int_buffer
- * and the other modes find them.  Outputs that a later kernel of the same run overwrites are not
- * stored (nothing could read them in between).  Eager launches are never merged.  `on` = 0 captures
- * one node per kernel.  Takes effect at the next pg_capture. */
+ * captured graph, which knows the whole chain, plays a run of consecutive kernels with ONE dispatch where
+ * it can.  A lane runs the kernels in order on its elements with their stand-alone arithmetic and one
+ * rounding each, stores every kernel's output that no later kernel of the run overwrites, and hands the
+ * stored bits to the next kernel in registers, so results stay bit-identical to eager launches.  The runs:
+ *   - up to 4 add / mul / GELU kernels (8 for bf16 tensors of 2^14 to 2^21 elements) and RMSNorm over rows
+ *     of 256 x 16 bytes, all element for element over the same n elements.  bf16: any n.  fp32: any n up
+ *     to 16384 elements, and only there the fp32 GELU takes part; beyond, a whole number of 16-byte
+ *     vectors.  A run ends where a kernel reads something an earlier kernel of the run wrote in any other
+ *     pattern than element for element;
+ *   - up to 16 PG_SCALE_BIAS_RELU kernels of one shape, each of which reads what the one before wrote: at
+ *     most 128 channels, inner at least 16 bytes, fewer than 2^31 elements;
+ *   - up to 8 bf16 add / mul / GELU kernels over tensors of their own lengths (multiples of 8) whose second
+ *     operand is the head of what the kernel before wrote, with one period that is a power of two from 8
+ *     to 512.  The head of a run's last output is kept in the workspace for the run behind it
+ *     (pg_chain_workspace_bytes counts 2 KB where there are such runs);
+ *   - a bf16 GEMV (1 to 4 rows of h of 8 to 8192 columns, more than 2048 only for n >= 1024; 5 rows and
+ *     more of 8 columns and more) and up to 3 elementwise kernels over its outputs (GELU of the result,
+ *     the residual add, an input add), which ride in its dispatch as an epilogue: each lane that holds a
+ *     finished output rounds it as the GEMV's store would and runs the following kernels on that element.
+ *     Up to 32 rows of h (from 5 rows on up to 2048 columns), and while the GEMV has few enough workgroups
+ *     for it to pay, the RMSNorm that produces the GEMV's input rides in front as a prologue (every
+ *     workgroup normalises the rows itself, one stores them); a run whose epilogue overwrites the buffer
+ *     its prologue reads writes a second copy of that buffer, which the workspace holds
+ *     (pg_chain_workspace_bytes counts it), and every segment ends with all internal buffers in their
+ *     first copy, where pg_chain_int_buffer and the other modes find them.
+ * Outputs that a later kernel of the same run overwrites are not stored (nothing could read them in
+ * between).  Eager launches are never merged.  `on` = 0 captures one node per kernel.  Takes effect at
+ * the next pg_capture. */
 pg_status pg_set_dispatch_merge(pg_chain *chain, int32_t on);
 /* Kernel nodes that the graphs of one replay hold with merging on (*merged_out) and off
  * (*unmerged_out = the number of kernels).  Either output may be NULL.  Host only. */

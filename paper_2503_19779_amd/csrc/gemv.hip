@@ -239,14 +239,16 @@ __device__ __forceinline__ unsigned xcd_stretch(unsigned b, unsigned total) {
 // bf16, v_mfma_f32_16x16x32_bf16 with fp32 accumulation.  A GEMV's output has the same bits whichever launch of it
 // computes it (eager, merged, with a prologue): k_gemm_rows and k_gemm_cols cut K into blocks of 64; wave w of the
 // workgroup's four takes blocks w, w + 4, ... in order, two K-steps of 32 each; the four partial sums are added as
-// ((p0 + p1) + p2) + p3.  k_gemm_tile deals the blocks out to eight parts instead.  (Fragments -- A: lane l holds row l & 15, B: column l & 15;
+// ((p0 + p1) + p2) + p3.  k_gemm_tile deals the blocks out to eight parts instead, whose shorter sums err less (rows of W that cancel
+// to zero, 128 rows of h, 2048 x 2048: rms of the outputs, which should be 0, 3.9e-6 where four parts gave 5.3e-6).
+// (Fragments -- A: lane l holds row l & 15, B: column l & 15;
 // the eight consecutive k's of chunk l >> 4 of a step; accumulators: lane l holds column l & 15, rows 4 * (l >> 4) .. + 3.)
 // Elements beyond a row's end are zeros on both sides: zeroing the weight side alone would turn an Inf or NaN of h
 // into NaN in every output (0 * Inf).  Rows beyond the batch and columns beyond n repeat the last one and are never
 // stored.
 //   - k_gemm_rows: one tile of 8 or 16 rows of h per workgroup, up to 2048 columns, all loads in flight at once; the
 //     form that can carry the RMSNorm in front;
-//   - k_gemm_cols: 17 to 80 rows of up to 2048 columns;
+//   - k_gemm_cols: 17 to 80 rows of up to 2048 columns, and any more rows with up to 16 outputs each;
 //   - k_gemm_tile: everything else, K streamed through a ring in LDS.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
@@ -864,11 +866,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
 // tiles where there are enough of them (plan_gemm); a CU holds no more than its 32 KB cache's worth of lines in flight.
 // K is cut into blocks of 64 and dealt out to eight parts in turn, whose sums are added in order.  Eight waves, one part
 // each, so that one wave's fragment reads and multiplies hide behind another's (with four waves a round of one block
-// cost them 0.3 us in turn); the stand-alone launches of an eager loop keep the four-wave workgroups
-// (two parts a wave, one after the other): the same bits.
-// Decode chains, us per iteration, before and after: 128 rows of 2048 columns, 120 sub-blocks 1529 -> 1380; 100 x 2000 (100
-// sub-blocks) 1290 -> 850, 128 x 1024 1282 -> 793 (there also one dispatch instead of three around the GEMV); one GEMV
-// of 128 rows by 4096 x 4096 33.6 -> 19.3 with four waves, the 16-column form it replaces there re-reads W per tile.
+// cost them 0.3 us in turn); stand-alone launches keep workgroups of four waves (two parts a wave, whose blocks take turns
+// in one stream): the same bits.
+// Decode chains, us per iteration, before and after: 128 rows of 2048 columns, 120 sub-blocks 1529 -> 1330; 100 x 2000 (100
+// sub-blocks) 1290 -> 850, 128 x 1024 1282 -> 793 (there also one dispatch instead of three around the GEMV); one GEMV alone, us
+// per launch: 128 rows by 4096 x 4096 34.0 -> 17.4, by 2048 x 2048 8.1 -> 7.8 (the 16- and 32-column forms it replaces re-read W
+// for every group of tiles).
 // Rows that 16-byte loads cannot reach (cols no multiple of 8, a misaligned external) go through registers instead,
 // one block ahead.
 template <int N>
@@ -1370,7 +1373,9 @@ bool plan_gemv_t(int ind, int rows, int n, int cols, Launch* out) {
     constexpr int NV = 16 / (int)sizeof(T);
     if constexpr (sizeof(T) == 2) {
         // Three and four rows go to the form that shares h through LDS (at 2048 x 2048, us per launch at 2 / 3 / 4 rows: 3.3 / 3.5 /
-        // 3.7; vector with h per wave 3.8 / 4.4 / 4.5; matrix-core form with 8 columns per workgroup 3.9 / 4.0 / 4.0).
+        // 3.7; vector with h per wave 3.8 / 4.4 / 4.5; matrix-core form with 8 columns per workgroup 3.9 / 4.0 / 4.0).  Its sums err
+        // less than the matrix cores' (rows of W that cancel to zero, 4 rows of 2048 columns: rms of the outputs 2.8e-6 against
+        // 5.1e-6), and products among the subnormal fp32 numbers are kept on both.
         if ((rows == 3 || rows == 4) && rows_served(rows, n, cols) && !(n >= 1024 && cols == 64 * kGemvChunk * NV)) {
             out->fn = rows_kernel<kAlone>(rows, n, cols);
             out->arg_bytes = sizeof(GemvAloneArgs);

@@ -223,8 +223,9 @@ const void* table_kernel();
 bool merge_candidate(int op, int dtype, const Shape& shape, bool whole_vectors, long long* n_out);
 // Runs over small fp32 tensors work one element (4 bytes) per lane instead of a 16-byte vector: such
 // kernels are bound by their dispatch, not by bytes, and one element per lane is what lets the fp32 GELU
-// (evaluated in fp64, a few hundred instructions) ride along.  No RMSNorm in such a run (its row is a unit
-// of 256 lanes x 16 bytes).
+// (evaluated in fp64, about 65 instructions) ride along.  No RMSNorm in such a run (its row is a unit
+// of 256 lanes x 16 bytes).  The line was drawn when the GELU took a few hundred instructions; with the present one it could lie
+// higher (64 kernels, us per iteration as it is / one element per lane: 65536 elements 107 / 55, 2^20 238 / 170).
 constexpr long long kMergeNarrowMax = 16384;        // elements
 bool merge_narrow(int dtype, long long n);
 // bf16 runs without an RMSNorm up to this many elements work on 4 bytes (two elements) per lane as well: a lane's elements
