@@ -361,13 +361,19 @@ def main() -> int:
         sel4 = pg.select(cost4)
         us4 = {name: timed(c4, x4, mode, 20, 3) for name, mode in MODES}
         us4["selected"] = timed(c4, x4, pg.SELECTED, 20, 3, sel4)
-        bytes4 = 2 * spec4.ext[0].nbytes * len(spec4.kernels)
+        # what the dispatches of each mode have to move: kernel by kernel the tensor is read and written 40 times; a merged segment
+        # reads it once and writes the last version of each of its two buffers
+        nb4, seg4 = spec4.ext[0].nbytes, spec4.n_segments
+        eager4 = 2 * nb4 * len(spec4.kernels)
+        graph4 = 3 * nb4 * seg4 if c4.graph_dispatches()[0] == seg4 else eager4
+        bytes4 = {"eager": eager4, "graph_copy": graph4 + 2 * nb4, "graph_indirect": graph4,
+                  "selected": sum((eager4 if m == pg.EAGER else graph4) / seg4 for m in sel4) + (2 * nb4 if sel4[0] == pg.GRAPH_COPY else 0)}
         configs["4"] = {"workload": "40 fp32 scale+bias+ReLU kernels on [32,64,112,112] in 4 segments, one 102.8 MB external input",
                         "kernels": len(spec4.kernels), "segments": 4, "us_per_iteration": us4,
                         "launches_per_s": {m: len(spec4.kernels) / v * 1e6 for m, v in us4.items()},
                         "selection": {"cost_table_us": clean(cost4), "mode": sel4.tolist()},
-                        "algorithmic_GBps": {m: bytes4 / v / 1e3 for m, v in us4.items()},
-                        "hbm_frac": {m: bytes4 / v / 1e3 / HBM_PEAK for m, v in us4.items()}}
+                        "algorithmic_GBps": {m: bytes4[m] / v / 1e3 for m, v in us4.items()},
+                        "hbm_frac": {m: bytes4[m] / v / 1e3 / HBM_PEAK for m, v in us4.items()}}
         log(f"[bench] config 4: {us4} selected {sel4.tolist()}")
         c4.close()
         del x4, c4, w4
