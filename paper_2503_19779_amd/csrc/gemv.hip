@@ -1081,22 +1081,28 @@ __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h,
                                                const bf16_t* gain, const float& eps, bf16_t* hstore, f32x4* part /* [4]: four wave sums per row */) {
     constexpr int KC = (U + 3) / 4;                      // vectors per lane of the workgroup
     if constexpr (EXACT) cols = 512 * U;
+    // 512-column pieces of a row that every row this form serves has whole (rows_kernel_rb): no end to look for in them
+    constexpr int WHOLE = EXACT ? U : R == 1 ? U - 1 : U == 3 ? 0 : U == 4 ? 3 : U - 4;
+    auto at = [&](int v, bool whole) { return whole ? span_at<true>(cols, v) : span_at<false>(cols, v); };
+    auto fix = [&](int v, bool whole, unsigned* w) { if (!whole) span_fix<false>(cols, v, w); };
+    auto whole_u = [](int u) { return u < WHOLE; };                     // ... vectors u * 64 + lane of a weight row
+    auto whole_c = [](int c) { return (c + 1) * 4 <= WHOLE; };          // ... vectors c * 256 + tid of a row of h
     // vector c of lane tid exists for every lane unless U is no multiple of four: then the last waves have none of the last
     auto mine = [&](int c) { return U % 4 == 0 || c < KC - 1 || tid < 64 * (U % 4); };
     unsigned hv[RB][KC][4], wg[KC][4], ww[R][U][4];
 #pragma unroll
     for (int rr = 0; rr < RB; rr++)
 #pragma unroll
-        for (int c = 0; c < KC; c++) load_any<false>(h + (size_t)rr * cols, mine(c) ? span_at<EXACT>(cols, c * kBlock + tid) : 0u, hv[rr][c]);
+        for (int c = 0; c < KC; c++) load_any<false>(h + (size_t)rr * cols, mine(c) ? at(c * kBlock + tid, whole_c(c)) : 0u, hv[rr][c]);
     if constexpr (PRO)
 #pragma unroll
-        for (int c = 0; c < KC; c++) load_any<false>(gain, mine(c) ? span_at<EXACT>(cols, c * kBlock + tid) : 0u, wg[c]);
+        for (int c = 0; c < KC; c++) load_any<false>(gain, mine(c) ? at(c * kBlock + tid, whole_c(c)) : 0u, wg[c]);
     __builtin_amdgcn_sched_barrier(0);   // h first: loads come back in the order they were issued
 #pragma unroll
     for (int r = 0; r < R; r++) {
         const bf16_t* wrow = W + (size_t)((j0 + r < n) ? j0 + r : n - 1) * cols;   // a ragged last group re-reads the last row
 #pragma unroll
-        for (int u = 0; u < U; u++) load_any<true>(wrow, span_at<EXACT>(cols, u * 64 + lane), ww[r][u]);
+        for (int u = 0; u < U; u++) load_any<true>(wrow, at(u * 64 + lane, whole_u(u)), ww[r][u]);
     }
     __builtin_amdgcn_sched_barrier(0);
     after_issue();
@@ -1104,7 +1110,7 @@ __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h,
     for (int rr = 0; rr < RB; rr++)
 #pragma unroll
         for (int c = 0; c < KC; c++) {
-            span_fix<EXACT>(cols, c * kBlock + tid, hv[rr][c]);
+            fix(c * kBlock + tid, whole_c(c), hv[rr][c]);
             if (!mine(c)) hv[rr][c][0] = hv[rr][c][1] = hv[rr][c][2] = hv[rr][c][3] = 0u;
         }
     if constexpr (PRO) {
@@ -1137,7 +1143,7 @@ __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h,
             for (int c = 0; c < KC; c++) {
                 float fx[8], fg[8], fo[8];
                 Vec<bf16_t, 16>::unpack(hv[rr][c], fx);
-                if (rr == 0) span_fix<EXACT>(cols, c * kBlock + tid, wg[c]);
+                if (rr == 0) fix(c * kBlock + tid, whole_c(c), wg[c]);
                 Vec<bf16_t, 16>::unpack(wg[c], fg);
 #pragma unroll
                 for (int e = 0; e < 8; e++) fo[e] = (fx[e] * scale) * fg[e];
@@ -1173,7 +1179,7 @@ __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h,
         }
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            span_fix<EXACT>(cols, u * 64 + lane, ww[r][u]);
+            fix(u * 64 + lane, whole_u(u), ww[r][u]);
 #pragma unroll
             for (int rr = 0; rr < RB; rr++) sums[rr * R + r] = dot_acc<bf16_t>(ww[r][u], wh[rr], sums[rr * R + r]);
         }

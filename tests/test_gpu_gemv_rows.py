@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows,hidden", [(r, h) for h in (7, 8, 9, 61, 520, 1023, 1024, 1030, 2047, 2049, 2056, 4091, 4096) for r in (1, 2, 3, 4)] +
-                         [(r, h) for h in (6142, 6151, 8191, 8192, 8200) for r in (1, 4)])
+                         [(r, h) for h in (4104, 5000, 6142, 6151, 6144, 7000, 8191, 8192, 8200) for r in (1, 4)])
 def test_rows_of_any_width(rows, hidden):
     spec = decode_chain(batch=rows, layers=3, blocks_per_layer=1, hidden=hidden, n_ext=3)
     h = Harness(spec, capture=False)
