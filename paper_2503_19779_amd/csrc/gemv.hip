@@ -1382,7 +1382,11 @@ bool plan_gemv_t(int ind, int rows, int n, int cols, Launch* out) {
         // 3.7; vector with h per wave 3.8 / 4.4 / 4.5; matrix-core form with 8 columns per workgroup 3.9 / 4.0 / 4.0).  Its sums err
         // less than the matrix cores' (rows of W that cancel to zero, 4 rows of 2048 columns: rms of the outputs 2.8e-6 against
         // 5.1e-6), and products among the subnormal fp32 numbers are kept on both.
-        if ((rows == 3 || rows == 4) && rows_served(rows, n, cols) && !(n >= 1024 && cols == 64 * kGemvChunk * NV)) {
+        // Four rows of more than 4096 columns that leave whole vectors of k_gemv_rows' form empty (forms of 6144 and 8192 columns) stay
+        // with the vector form that takes a row in pieces (4 rows of 5000 columns 16.7 against 16.1, of 7000 29.3 against 27.6; of
+        // 6000 columns 11.2 against 12.3, of 4500, whose last vector that form reads element by element, 16.4 against 18.0).
+        const bool pieces = rows == 4 && cols > 4096 && cols % NV == 0 && (cols + 511) / 512 % 4 != 0;
+        if ((rows == 3 || rows == 4) && rows_served(rows, n, cols) && !pieces && !(n >= 1024 && cols == 64 * kGemvChunk * NV)) {
             out->fn = rows_kernel<kAlone>(rows, n, cols);
             out->arg_bytes = sizeof(GemvAloneArgs);
             out->block = dim3(kBlock);
