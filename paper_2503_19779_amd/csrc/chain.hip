@@ -91,7 +91,7 @@ struct MergeGroup {
     bool sbr = false;                // the run is a chain of scale + bias + ReLU kernels
     bool carry = false;              // the run hands on a carry (kernels.h, CarryRunArgs)
     int carry_m = 0;                 // (carry) its period
-    unsigned carry_units = 0;        // (carry) CarryRunArgs::n_units
+    unsigned carry_unit = 0;         // (carry) elements a workgroup takes
     bool carry_aside = false;        // (carry) the first kernel's carry is what the run before set aside
     bool narrow = false;             // (not head) 4 bytes per lane instead of a 16-byte vector
     long long n = 0;                 // elements every kernel of the run produces
@@ -738,7 +738,10 @@ pg_status make_records(pg_chain* c) {
             g.launch = pgk::Launch();
             g.launch.block = dim3(256);
             if (g.carry) {
-                pgk::plan_carry_run(g.n, &g.launch, &g.carry_units);
+                pgk::plan_carry_run(g.n, &g.launch, &g.carry_unit);
+                unsigned units = 0;
+                for (int i = g.k0; i < g.k1; i++) units += (unsigned)((c->k[i].n + g.carry_unit - 1) / g.carry_unit);
+                g.launch.grid = dim3(units);
             } else if (g.sbr) {
                 if (!pgk::plan_sbr_run(c->k[g.k0].dtype, g.n, c->k[g.k0].inner, &g.launch)) return fail(PG_EINVAL, "kernel %d: no kernel for this run", g.k0);
             } else if (g.head) {
@@ -997,8 +1000,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             memset(&m, 0, sizeof m);
             auto place = [&](int i) { return c->ws + c->carry_off + (size_t)(i & 1) * 2 * pgk::kCarryMax; };
             m.m = (unsigned)grp.carry_m;
-            m.n_units = grp.carry_units;
-            m.n_blocks = grp.launch.grid.x;
+            unsigned units = 0, from = 0;
             for (int i = grp.k0; i < grp.k1; i++, m.n_phase++) {
                 KernelRec& r = c->rec[i];
                 const pg_kernel_desc& d = c->k[i];
@@ -1010,6 +1012,10 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
                 ph.n = (unsigned)d.n;
                 ph.op = (unsigned)d.op;
                 ph.ind = slots & 1u;
+                ph.from = from;
+                if (d.op == PG_GELU) from = (unsigned)m.n_phase;
+                m.unit0[m.n_phase] = units;
+                units += (unsigned)((d.n + grp.carry_unit - 1) / grp.carry_unit);
                 for (int t = i + 1; t < grp.k1; t++) if (c->k[t].out.index == d.out.index) ph.cover = std::max(ph.cover, (unsigned)c->k[t].n);
                 if (i == grp.k0 && d.op != PG_GELU) {
                     m.carry_in = grp.carry_aside ? place(n_carry + 1) : a.ptr[2];
@@ -1018,7 +1024,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             }
             if (c->k[grp.k1 - 1].n >= grp.carry_m) m.carry_out = place(n_carry);
             n_carry++;
-            for (int q = m.n_phase; q < pgk::kCarryRunMax; q++) { m.ph[q] = m.ph[0]; m.ph[q].n = 0; }
+            for (int q = m.n_phase; q < pgk::kCarryRunMax; q++) m.unit0[q] = ~0u;
             le = launch(grp.launch, &m, s);
             continue;
         }

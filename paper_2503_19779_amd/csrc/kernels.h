@@ -183,6 +183,8 @@ struct CarryPhase {
     unsigned cover;         // elements of the output that later kernels of the run overwrite
     unsigned op;
     unsigned ind;           // bit 0: in0 is a pointer-table slot
+    unsigned from;          // the first kernel whose head this kernel's carry depends on: the last GELU before it, or kernel 0
+    unsigned reserved;
 };
 struct CarryRunArgs {
     const void* carry_in;   // the first kernel's second operand, or null
@@ -190,10 +192,9 @@ struct CarryRunArgs {
     unsigned m;             // the period
     unsigned flags;         // bit 0: carry_in is a pointer-table slot
     int n_phase;
-    unsigned n_units;       // units of 256 lanes in the longest kernel; workgroup b of n_blocks takes b, b + n_blocks, ...
-    unsigned n_blocks;
     unsigned reserved;
-    CarryPhase ph[kCarryRunMax];    // entries from n_phase on: the first kernel's operand, n = 0
+    unsigned unit0[kCarryRunMax];   // the workgroup that takes kernel i's first unit; entries from n_phase on: no workgroup's index
+    CarryPhase ph[kCarryRunMax];
 };
 
 struct Launch {
@@ -233,9 +234,10 @@ bool merge_narrow(int dtype, long long n);
 constexpr long long kNarrowBf16Max = 1ll << 19;
 int merge_max_phases(int dtype, long long n);
 const void* merged_kernel(int dtype, bool narrow, int phases);
-// Can this kernel be part of a run with a carry (its operands aside)?  And the launch of a run whose longest kernel has n elements.
+// Can this kernel be part of a run with a carry (its operands aside)?  And the kernel for a run whose longest kernel has n elements;
+// *unit: the elements a workgroup takes.
 bool carry_run_candidate(int op, int dtype, long long n);
-void plan_carry_run(long long n, Launch* out, unsigned* n_units);
+void plan_carry_run(long long n, Launch* out, unsigned* unit);
 // Can this scale + bias + ReLU kernel be part of a run of such kernels?  A 16-byte vector may touch two channels at
 // most, the tables of all channels fit the run's LDS, and element indices fit 32 bits.
 bool sbr_run_candidate(int dtype, long long n, long long inner, long long channels);

@@ -608,17 +608,17 @@ __global__ __launch_bounds__(kBlock) void k_merged(MergedArgs p) {
 
 // ---- runs of kernels that hand on a short carry ---------------------------------------------------------------
 // kernels.h, CarryRunArgs.  What bounds the kernels one by one is their dispatch (3 us a kernel, of which 1.5 the graph's
-// node), since all that makes one wait for the next is the head of its output, m <= 512 elements.  Here every workgroup
-// works that chain of heads out for itself -- two elements a lane, no lane needs another's -- and keeps each kernel's
-// carry in LDS; then it plays all kernels on its own stretch of elements, in order, so that what two of them write to the
-// same place lands in order.  Same arithmetic, one rounding per kernel.  VB bytes per lane: 4 for short
-// tensors (at one wave per SIMD eight elements a lane and kernel in sequence cost more than the memory trip), 16 for long ones,
-// where a workgroup takes every n_blocks-th unit, so that the units that all kernels have (the low ones) are spread out.
-// 256 tensors of 1 KB to 16 MB refreshed by copy and read by 256 kernels: 922 -> 574 us per iteration, of which the copies are 146
-// (four neighbouring units per workgroup 681); 96 tensors up to 1 MB through the pointer table 197 -> 82 (16 bytes per lane 99).
-template <int OP_MAX>
+// node), since all that makes one wait for the next is the head of its output, m <= 512 elements.  Here a workgroup plays
+// one unit of one kernel (a vector of VB bytes per lane) and works the heads it needs out for itself, two elements a lane, from
+// the last GELU before its kernel on: a GELU takes no carry, so nothing before it matters.  No workgroup needs another's results, and
+// the units of all kernels of the run are in flight side by side.  Where two kernels write the same place only the later one
+// stores (cover), so the order the units run in does not matter.  Same arithmetic, one rounding per kernel.
+// What bounds it: a run of short tensors the trip for the arguments, the pointers, the elements (2.8 us with the node); of long ones
+// memory, 3.5 TB/s in and out with that start.  Non-temporal loads and stores: nothing is read twice, and what is left dirty in L2
+// would be written back at the end of the dispatch.  256 tensors of 1 KB to 16 MB through the pointer table, us per iteration:
+// with a workgroup that played all eight kernels on its stretch of elements, one after the other, 443 (its low units, which every
+// kernel has, were the critical path); a unit of one kernel 294; non-temporal 264.  96 tensors up to 1 MB 79 -> 46.
 __device__ __forceinline__ float carry_apply(unsigned op, float a, float b) {
-    static_assert(OP_MAX == kGelu, "add, mul, GELU");
     if (op == (unsigned)kGelu) return ew_apply<kGelu, false>(a, 0.f);
     const float sum = ew_apply<kAdd, false>(a, b), prod = ew_apply<kMul, false>(a, b);
     return op == (unsigned)kAdd ? sum : prod;
@@ -628,105 +628,79 @@ __global__ __launch_bounds__(kBlock) void k_carry_run(CarryRunArgs p) {
     using V = Vec<bf16_t, VB>;
     constexpr int NV = V::NV, NW = V::NW;
     constexpr int P = kCarryRunMax;
-    __shared__ __attribute__((aligned(16))) unsigned carry[P + 1][kCarryMax / 2];      // [i]: what kernel i takes; [i + 1]: what it hands on
+    __shared__ __attribute__((aligned(16))) unsigned carry[kCarryMax / 2];      // what this workgroup's kernel takes
     using SlotPtr = const void* const PG_CONSTANT*;
-    const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();
+    const CarryRunArgs PG_CONSTANT* const ka = (const CarryRunArgs PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();
     const unsigned tid = threadIdx.x, m = p.m;
-    const int np = p.n_phase;
-    // operand addresses, slots resolved, in two batches of scalar loads (entries from n_phase on repeat the first)
-    const bf16_t* in[P];
-    const void* cin = p.carry_in;
-    {
-        SlotPtr at[P], atc = (p.flags & 1u) ? (SlotPtr)(uintptr_t)cin : (SlotPtr)ka;
-        const void* t[P];
+    int k = 0;                                             // this workgroup's kernel
 #pragma unroll
-        for (int i = 0; i < P; i++) at[i] = (p.ph[i].ind & 1u) ? (SlotPtr)(uintptr_t)p.ph[i].in0 : (SlotPtr)ka;
-#pragma unroll
-        for (int i = 0; i < P; i++) t[i] = *at[i];
-        const void* tc = *atc;
-#pragma unroll
-        for (int i = 0; i < P; i++) in[i] = static_cast<const bf16_t*>((p.ph[i].ind & 1u) ? t[i] : p.ph[i].in0);
-        if (p.flags & 1u) cin = tc;
-    }
-    unsigned w[P][NW];
-    auto fetch = [&](unsigned v) {
-#pragma unroll
-        for (int i = 0; i < P; i++) {
-#pragma unroll
-            for (int k = 0; k < NW; k++) w[i][k] = 0u;
-            if (v < p.ph[i].n / NV) {
-                if constexpr (VB == 16) {
-                    const v4u t = *(const v4u_any PG_GLOBAL*)(uintptr_t)(in[i] + (size_t)v * NV);
-                    w[i][0] = t.x; w[i][1] = t.y; w[i][2] = t.z; w[i][3] = t.w;
-                } else {
-                    w[i][0] = *(const u32_any PG_GLOBAL*)(uintptr_t)(in[i] + (size_t)v * NV);
-                }
-            }
-        }
+    for (int j = 1; j < P; j++) k += blockIdx.x >= p.unit0[j] ? 1 : 0;
+    auto operand = [&](int j) {
+        const void* q = ka->ph[j].in0;
+        if (ka->ph[j].ind & 1u) q = *(SlotPtr)(uintptr_t)q;
+        return static_cast<const bf16_t*>(q);
     };
-    // the heads first, then the first unit's elements
+    auto head_of = [&](const bf16_t* q) { return load_raw_global(q + 2 * tid) | (load_raw_global(q + 2 * tid + 1) << 16); };
+    const unsigned op = ka->ph[k].op, nvec = ka->ph[k].n / NV;
+    const unsigned v = (blockIdx.x - ka->unit0[k]) * (unsigned)kBlock + tid;
+    const bf16_t PG_GLOBAL* const in = (const bf16_t PG_GLOBAL*)(uintptr_t)operand(k);
+    const int from = op == (unsigned)kGelu ? k : (int)ka->ph[k].from;
+    // the heads first: loads come back in order
     const bool chain = 2 * tid < m;
-    unsigned hd[P], c = 0u;
+    unsigned hd[P - 1], c = 0u;
 #pragma unroll
-    for (int i = 0; i < P; i++) {
-        hd[i] = 0u;
-        if (chain && 2 * tid < p.ph[i].n) hd[i] = load_raw_global(in[i] + 2 * tid) | (load_raw_global(in[i] + 2 * tid + 1) << 16);
+    for (int t = 0; t < P - 1; t++) {
+        if (from + t >= k) break;
+        const bf16_t* q = operand(from + t);
+        hd[t] = chain ? head_of(q) : 0u;                   // a kernel whose head is handed on has m elements at least
     }
-    if (chain && cin) c = load_raw_global(static_cast<const bf16_t*>(cin) + 2 * tid) | (load_raw_global(static_cast<const bf16_t*>(cin) + 2 * tid + 1) << 16);
-    fetch(blockIdx.x * (unsigned)kBlock + tid);
-    if (chain) {
-        carry[0][tid] = c;
+    if (op != (unsigned)kGelu && from == 0 && p.carry_in && chain)
+        c = head_of(static_cast<const bf16_t*>((p.flags & 1u) ? *(SlotPtr)(uintptr_t)p.carry_in : p.carry_in));
+    unsigned w[NW];
+    const size_t at = (size_t)(v < nvec ? v : nvec - 1) * NV;
+    if constexpr (VB == 16) {
+        const v4u t = __builtin_nontemporal_load((const v4u_any PG_GLOBAL*)(in + at));
+        w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+    } else {
+        w[0] = *(const u32_any PG_GLOBAL*)(in + at);
+    }
+    float fa[NV], fo[NV];
+    if (op == (unsigned)kGelu) {
+        V::unpack(w, fa);
 #pragma unroll
-        for (int i = 0; i < P; i++) {
-            if (i < np) {
-                const unsigned op = p.ph[i].op;
-                c = pack2_bf16(carry_apply<kGelu>(op, __uint_as_float(hd[i] << 16), __uint_as_float(c << 16)),
-                               carry_apply<kGelu>(op, __uint_as_float(hd[i] & 0xffff0000u), __uint_as_float(c & 0xffff0000u)));
-                carry[i + 1][tid] = c;
-            }
+        for (int e = 0; e < NV; e++) fo[e] = ew_apply<kGelu, false>(fa[e], 0.f);
+    } else {
+#pragma unroll
+        for (int t = 0; t < P - 1; t++) {
+            if (from + t >= k) break;
+            const unsigned o = ka->ph[from + t].op;
+            c = pack2_bf16(carry_apply(o, __uint_as_float(hd[t] << 16), __uint_as_float(c << 16)),
+                           carry_apply(o, __uint_as_float(hd[t] & 0xffff0000u), __uint_as_float(c & 0xffff0000u)));
+        }
+        if (chain) carry[tid] = c;
+        lds_barrier();
+        const unsigned cv = (tid % (m / NV)) * NW;         // this lane's vector of the carry: a unit is a whole number of periods
+        unsigned wb[NW];
+        float fb[NV];
+#pragma unroll
+        for (int i = 0; i < NW; i++) wb[i] = carry[cv + i];
+        V::unpack(w, fa);
+        V::unpack(wb, fb);
+#pragma unroll
+        for (int e = 0; e < NV; e++) {
+            const float sum = ew_apply<kAdd, false>(fa[e], fb[e]), prod = ew_apply<kMul, false>(fa[e], fb[e]);
+            fo[e] = op == (unsigned)kAdd ? sum : prod;
         }
     }
-    lds_barrier();
-    if (chain && p.carry_out && blockIdx.x == 0) *(unsigned PG_GLOBAL*)((unsigned PG_GLOBAL*)(uintptr_t)p.carry_out + tid) = c;
-    const unsigned cv = (tid % (m / NV)) * NW;             // this lane's vector of a carry: a unit is a whole number of periods
-#pragma unroll 1
-    for (unsigned unit = blockIdx.x; unit < p.n_units; unit += p.n_blocks) {
-        const unsigned v = unit * (unsigned)kBlock + tid;
-        unsigned cur[P][NW];
-#pragma unroll
-        for (int i = 0; i < P; i++)
-#pragma unroll
-            for (int k = 0; k < NW; k++) cur[i][k] = w[i][k];
-        if (unit + p.n_blocks < p.n_units) fetch(v + p.n_blocks * (unsigned)kBlock);      // the next unit's elements under this one's arithmetic
-#pragma unroll
-        for (int i = 0; i < P; i++) {
-            if (i < np && unit * (unsigned)(kBlock * NV) < p.ph[i].n) {
-                const unsigned op = p.ph[i].op;
-                float fa[NV], fb[NV], fo[NV];
-                unsigned wb[NW], wo[NW];
-                V::unpack(cur[i], fa);
-                if (op == (unsigned)kGelu) {
-#pragma unroll
-                    for (int e = 0; e < NV; e++) fo[e] = ew_apply<kGelu, false>(fa[e], 0.f);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < NW; k++) wb[k] = carry[i][cv + k];
-                    V::unpack(wb, fb);
-#pragma unroll
-                    for (int e = 0; e < NV; e++) {
-                        const float sum = ew_apply<kAdd, false>(fa[e], fb[e]), prod = ew_apply<kMul, false>(fa[e], fb[e]);
-                        fo[e] = op == (unsigned)kAdd ? sum : prod;
-                    }
-                }
-                V::pack(fo, wo);
-                // not stored: a later kernel of the run overwrites it, and nothing reads it in between
-                if (v < p.ph[i].n / NV && v >= p.ph[i].cover / NV) {
-                    if constexpr (VB == 16) store_vec_global(static_cast<bf16_t*>(p.ph[i].out) + (size_t)v * NV, wo);
-                    else *(unsigned PG_GLOBAL*)(uintptr_t)(static_cast<bf16_t*>(p.ph[i].out) + (size_t)v * NV) = wo[0];
-                }
-            }
-        }
-    }
+    unsigned wo[NW];
+    V::pack(fo, wo);
+    auto put = [&](void* q) {
+        if constexpr (VB == 16) __builtin_nontemporal_store(v4u{wo[0], wo[1], wo[2], wo[3]}, (v4u PG_GLOBAL*)(uintptr_t)q + v);
+        else *((unsigned PG_GLOBAL*)(uintptr_t)q + v) = wo[0];
+    };
+    // below `cover` a later kernel of the run overwrites the output, and nothing reads it in between
+    if (v < nvec && v >= ka->ph[k].cover / NV) put(ka->ph[k].out);
+    if (k == p.n_phase - 1 && p.carry_out && v * NV < m) put(p.carry_out);
 }
 
 // ---- batched multi-tensor copy -----------------------------------------------------------------
@@ -954,14 +928,14 @@ const void* merged_kernel(int dtype, bool narrow, int phases) {
 bool carry_run_candidate(int op, int dtype, long long n) {
     return (op == kAdd || op == kMul || op == kGelu) && dtype == kBF16 && n > 0 && n % 8 == 0 && n < (1ll << 31);
 }
-void plan_carry_run(long long n, Launch* out, unsigned* n_units) {
+// 4 bytes a lane up to the line of the element-for-element runs (200 tensors up to 2^18.5 elements: 77 us; with 16 bytes a lane above 2^16
+// elements 91, above 2^13 97).
+void plan_carry_run(long long n, Launch* out, unsigned* unit) {
     const bool narrow = n <= kNarrowBf16Max;
-    const long long units = (n / (narrow ? 2 : 8) + kBlock - 1) / kBlock;
     out->arg_bytes = sizeof(CarryRunArgs);
     out->block = dim3(kBlock);
     out->fn = narrow ? PG_FN(k_carry_run<4>) : PG_FN(k_carry_run<16>);
-    out->grid = dim3((unsigned)(units < 1024 ? units : 1024));
-    *n_units = (unsigned)units;
+    *unit = kBlock * (narrow ? 2u : 8u);
 }
 
 // One vector per lane until that makes four workgroups per CU, eight per lane from there on.

@@ -81,3 +81,15 @@ def test_random_runs(period, seed):
     merged, unmerged = h.chain.graph_dispatches()
     assert merged < unmerged
     _check(h)
+
+
+@pytest.mark.parametrize("period", [8, 512])
+@pytest.mark.parametrize("sizes", [[512, 520, 1024, 512, 2056, 512, 1528, 512, 1032], [(1 << 19) + 8, 2048, 1 << 19, 2056, 4104, (1 << 19) + 2056, 512, 4096, 2040]])
+def test_no_gelu_cuts_the_carry(period, sizes):
+    """Adds and muls alone: the last kernel of a run depends on the head of every one before it; tensors that end within a
+    workgroup's unit, at its edge and behind it, on 4 and on 16 bytes a lane."""
+    ks = [KernelSpec("mul" if i % 3 == 1 else "add", "bf16", i % 2, (Ref(EXT, i), Ref(INT, (i - 1) % 2) if i else Ref(WEIGHT, 0)), n, m=period) for i, n in enumerate(sizes)]
+    spec = ChainSpec(f"no_gelu_{period}_{max(sizes)}", ks, [TensorSpec("bf16", n) for n in sizes], [TensorSpec("bf16", max(sizes))] * 2, [TensorSpec("bf16", 512)], [0, 1], 8300)
+    h = Harness(spec)
+    assert h.chain.graph_dispatches()[0] == 2
+    _check(h)
