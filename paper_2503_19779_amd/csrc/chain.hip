@@ -94,6 +94,7 @@ struct MergeGroup {
     unsigned carry_unit = 0;         // (carry) elements a workgroup takes
     bool carry_aside = false;        // (carry) the first kernel's carry is what the run before set aside
     bool narrow = false;             // (not head) 4 bytes per lane instead of a 16-byte vector
+    bool chain = false;              // (not head) each kernel takes the result of the one before, the second operand is memory (kernels.h, ChainArgs)
     long long n = 0;                 // elements every kernel of the run produces
     int gemv() const { return k0 + (pro ? 1 : 0); }
     // per kernel of the run: where its operands come from (a register slot or memory), which slot keeps its
@@ -528,7 +529,13 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
             for (int t = a + 1; t < np; t++)
                 if (k[g.k0 + t].out.index == k[g.k0 + a].out.index) g.store[a] = false;
         }
-        if (!head && k[g.k0].dtype == PG_BF16 && n <= pgk::kNarrowBf16Max) {
+        g.chain = !head;
+        for (int t = 0; t < np && g.chain; t++)
+            g.chain = k[g.k0 + t].op != PG_RMSNORM && g.src0[t] == (t ? g.dst[t - 1] : (unsigned char)pgk::kMergeFromMemory) &&
+                      (k[g.k0 + t].op == PG_GELU || g.src1[t] == (unsigned char)pgk::kMergeFromMemory);
+        if (g.chain) {
+            g.narrow = n <= pgk::kNarrowChainMax;
+        } else if (!head && k[g.k0].dtype == PG_BF16 && n <= pgk::kNarrowBf16Max) {
             g.narrow = true;
             for (int t = g.k0; t < i; t++) if (k[t].op == PG_RMSNORM) g.narrow = false;
         }
@@ -747,8 +754,8 @@ pg_status make_records(pg_chain* c) {
             } else if (g.head) {
                 pgk::plan_gemv_epilogue(shape_of(c->k[g.gemv()]), g.pro, &g.launch);
             } else {
-                g.launch.fn = pgk::merged_kernel(c->k[g.k0].dtype, g.narrow, g.k1 - g.k0);
-                g.launch.arg_bytes = sizeof(pgk::MergedArgs);
+                g.launch.fn = (g.chain ? pgk::chain_kernel : pgk::merged_kernel)(c->k[g.k0].dtype, g.narrow, g.k1 - g.k0);
+                g.launch.arg_bytes = g.chain ? sizeof(pgk::ChainArgs) : sizeof(pgk::MergedArgs);
                 const long long nv = (g.narrow ? 4 : 16) / (long long)elem_bytes(c->k[g.k0].dtype), nvec = (g.n + nv - 1) / nv;
                 g.launch.grid = dim3((unsigned)((nvec + 255) / 256));       // one workgroup per unit of 256 lanes x 16 bytes
             }
@@ -1086,6 +1093,41 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             seal_epilogue(e);
             le = launch(grp.launch, &e, s);
             if (grp.rename >= 0) second[grp.rename] ^= 1;
+            continue;
+        }
+        if (grp.chain) {
+            pgk::ChainArgs m;
+            memset(&m, 0, sizeof m);
+            m.n = (unsigned)grp.n;
+            unsigned first = 0;              // is the first kernel's first operand a slot?
+            for (int t = 0; t < pgk::kMergeMaxPhases; t++) {
+                const int i = grp.k0 + t;
+                pgk::ChainPhase& ph = m.ph[t];
+                m.m[t] = m.n;
+                ph.in1 = m.in0;
+                if (i >= grp.k1) {
+                    ph.out = m.ph[0].out;
+                    m.ops |= pgk::kChainEnd << (4 * t);
+                    m.slots |= first << t;
+                    continue;
+                }
+                KernelRec& r = c->rec[i];
+                const pg_kernel_desc& d = c->k[i];
+                const ArgBlock a = versioned(i, nullptr);
+                const unsigned slots = kind == kGraphCopy ? 0u : (unsigned)r.ind_mask;
+                ph.out = const_cast<void*>(a.ptr[0]);
+                if (t == 0) {
+                    m.in0 = a.ptr[1];
+                    first = slots & 1u;
+                    m.slots |= first << pgk::kMergeMaxPhases;
+                }
+                ph.in1 = r.n_in > 1 ? a.ptr[2] : m.in0;
+                m.slots |= (r.n_in > 1 ? (slots >> 1) & 1u : first) << t;
+                if (r.n_in > 1 && d.m) m.m[t] = (unsigned)d.m;
+                if (m.m[t] != m.n) m.slots |= pgk::kChainPeriods;
+                m.ops |= ((unsigned)d.op | (grp.store[t] ? 8u : 0u)) << (4 * t);
+            }
+            le = launch(grp.launch, &m, s);
             continue;
         }
         // one dispatch for the run: the kernels' own operands, in order, in one argument struct

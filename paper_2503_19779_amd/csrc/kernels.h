@@ -83,7 +83,7 @@ struct TableArgs {
 constexpr int kMergeShortPhases = 4;      // kernels per merged dispatch
 constexpr int kMergeMaxPhases = 8;        // ... of bf16 kernels over kMergeLongFrom to kMergeLongTo elements
 // Below, runs stay at four kernels (64 kernels on 4096 elements 52 us, on 16384 in runs of eight 48; longer runs of smaller
-// tensors were not measured); above, memory bounds the run and the wider kernel has fewer waves in flight (64 kernels, us in runs of eight / four: 2^20
+// tensors were not measured); above, memory bounds the run and the wider kernel has fewer waves in flight (64 kernels played by k_merged, us in runs of eight / four: 2^20
 // elements 77 / 88, 2^21 108 / 113, 3 * 10^6 149 / 142, 2^23 335 / 306, 2^25 1171 / 994).
 constexpr long long kMergeLongFrom = 16384, kMergeLongTo = 1ll << 21;
 constexpr int kMergeSlots = 3;            // outputs a lane keeps in registers for later kernels of the run
@@ -105,6 +105,24 @@ struct MergedArgs {
     int n_phase;
     MergePhase ph[kMergeMaxPhases];   // entries from n_phase on: meta says "operands from slots", nothing is fetched
 };
+
+// A run of those kernels in which each takes the result of the one before (the first: memory) and a second operand, if it has
+// one, from memory, no RMSNorm among them: the argument block of a chain.
+struct ChainPhase {
+    const void* in1;        // the second operand; GELU, and entries from n_phase on: the first kernel's first operand, fetched and ignored
+    void* out;
+};
+constexpr unsigned kChainPeriods = 1u << 31;        // ChainArgs::slots: some second operand has a period
+struct ChainArgs {
+    const void* in0;        // the first kernel's first operand
+    unsigned n;
+    unsigned slots;         // bit i: ph[i].in1 is a pointer-table slot; bit kMergeMaxPhases: in0 is
+    unsigned ops;           // 4 bits per kernel: op | store << 3; entries from n_phase on: kChainEnd
+    int reserved;
+    ChainPhase ph[kMergeMaxPhases];
+    unsigned m[kMergeMaxPhases];      // periods of the second operands (n: element for element)
+};
+constexpr unsigned kChainEnd = 7;
 
 // The same idea for a GEMV followed by element-for-element kernels over its outputs (GELU of the result,
 // the residual add, an input add): they ride in the GEMV's dispatch as an epilogue.  After the wave's
@@ -225,15 +243,19 @@ bool merge_candidate(int op, int dtype, const Shape& shape, bool whole_vectors, 
 // Runs over small fp32 tensors work one element (4 bytes) per lane instead of a 16-byte vector: such
 // kernels are bound by their dispatch, not by bytes, and one element per lane is what lets the fp32 GELU
 // (evaluated in fp64, about 65 instructions) ride along.  No RMSNorm in such a run (its row is a unit
-// of 256 lanes x 16 bytes).  The line was drawn when the GELU took a few hundred instructions; with the present one it could lie
-// higher (64 kernels, us per iteration as it is / one element per lane: 65536 elements 107 / 55, 2^20 238 / 170).
+// of 256 lanes x 16 bytes).
 constexpr long long kMergeNarrowMax = 16384;        // elements
 bool merge_narrow(int dtype, long long n);
 // bf16 runs without an RMSNorm up to this many elements work on 4 bytes (two elements) per lane as well: a lane's elements
 // are worked out one after the other, and such a tensor makes few waves.
 constexpr long long kNarrowBf16Max = 1ll << 19;
+// Chains (ChainArgs) of either type stay on 4 bytes a lane up to here (64 kernels, us per iteration with 4 / 16 bytes: bf16 700001 elements
+// 47 / 68, 2^20 53 / 59, 2^21 88 / 88, 2^22 174 / 172; fp32, whose GELUs have dispatches of their own, 2^18 100 / 118, 2^20 198 / 231,
+// 2^21 458 / 424).
+constexpr long long kNarrowChainMax = 1ll << 20;
 int merge_max_phases(int dtype, long long n);
 const void* merged_kernel(int dtype, bool narrow, int phases);
+const void* chain_kernel(int dtype, bool narrow, int phases);
 // Can this kernel be part of a run with a carry (its operands aside)?  And the kernel for a run whose longest kernel has n elements;
 // *unit: the elements a workgroup takes.
 bool carry_run_candidate(int op, int dtype, long long n);

@@ -373,8 +373,7 @@ __global__ __launch_bounds__(kBlock) void k_rmsnorm(RmsArgs p) {
 // conditional moves (one copy of the GELU and of the RMSNorm reduction for up to four kernels; an
 // unrolled form with every operand choice resolved at run time by branches was slower: a taken branch
 // costs a one-wave-per-SIMD kernel about as much as a dozen arithmetic instructions).
-// bf16 tensors of any length: the workgroup that owns the last, partial vector fetches element by element.  64 kernels on
-// 100003 bf16 elements: 154 us per iteration with a dispatch each, 81 in runs of eight on 16 bytes per lane, 52 on 4 bytes.
+// bf16 tensors of any length: the workgroup that owns the last, partial vector fetches element by element.
 
 template <typename T, int VB, int P, bool TAIL>
 __device__ __forceinline__ void merged_body(const MergedArgs& p, const T* const* in0, const T* const* in1, float* part) {
@@ -470,52 +469,6 @@ __device__ __forceinline__ void merged_body(const MergedArgs& p, const T* const*
     // sits at the head of the loop below and then also waits, every time round, for the store of the
     // kernel before (loads and stores of a wave share one counter): a microsecond per kernel.
     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
-    {   // A chain -- every kernel takes the result of the one before it (the first: memory) and, if it has a second
-        // operand, takes that from memory; no RMSNorm -- is played straight through: the choice of the operation is
-        // the only thing left to decide per kernel (the operand, slot and table selection of the general loop below
-        // and its taken branches cost a one-wave-per-SIMD kernel more than the arithmetic).  Same operations, same
-        // order, same roundings.
-        bool chain = n_phase >= 1;
-        unsigned prev = kMergeFromMemory;
-#pragma unroll
-        for (int i = 0; i < P; i++) {
-            const unsigned mt = metas[i], op = mt & 0xffu;
-            const bool in = i < n_phase;
-            chain = chain && (!in || (op != (unsigned)kRmsNorm && ((mt >> 8) & 0xffu) == prev && (op == (unsigned)kGelu || ((mt >> 16) & 0xffu) == kMergeFromMemory)));
-            prev = mt >> 24;
-        }
-        if (chain) {
-            unsigned w[NW];
-#pragma unroll
-            for (int k = 0; k < NW; k++) w[k] = ld0[0][k];
-#pragma unroll
-            for (int i = 0; i < P; i++) {
-                if (i >= n_phase) break;
-                const unsigned op = metas[i] & 0xffu;
-                float fa[NV], fb[NV], fo[NV];
-                V::unpack(w, fa);
-                V::unpack(ld1[i], fb);
-                if (op == (unsigned)kGelu) {
-                    if constexpr (!kWide || VB == 4) {
-#pragma unroll
-                        for (int e = 0; e < NV; e++) fo[e] = ew_apply<kGelu, kWide>(fa[e], 0.f);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < NV; e++) fo[e] = fa[e];      // never planned: the fp32 GELU rides only one element per lane
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < NV; e++) {
-                        const float sum = ew_apply<kAdd, kWide>(fa[e], fb[e]), prod = ew_apply<kMul, kWide>(fa[e], fb[e]);
-                        fo[e] = op == (unsigned)kAdd ? sum : prod;
-                    }
-                }
-                V::pack(fo, w);
-                if (act && (inds[i] & kEpiStore)) put(outs[i], w);
-            }
-            return;
-        }
-    }
 #pragma unroll 1
     for (int i = 0; i < n_phase; i++) {
         // this kernel's entry of the table and its fetched operands: uniform selects, no indexing
@@ -604,6 +557,141 @@ __global__ __launch_bounds__(kBlock) void k_merged(MergedArgs p) {
     const bool tail = NV > 1 && p.n % NV != 0 && blockIdx.x == p.n / NV / kBlock;
     if (__builtin_expect(!tail, 1)) merged_body<T, VB, P, false>(p, in0, in1, part);
     else if constexpr (NV > 1) merged_body<T, VB, P, true>(p, in0, in1, part);
+}
+
+// A run that is a chain (kernels.h, ChainArgs).  At these sizes it is bound by its dispatch and by what a lane does in sequence: the trip
+// for the arguments, the one for the operands, the kernels one after the other, the store.  So the arguments come in one batch, every
+// operand is asked for without a branch (a GELU, which has none, fetches the first operand once more), and the choice between the
+// GELU and add / mul is all there is to decide per kernel.  Against the same run played by k_merged, whose table has a branch per operand
+// (64 kernels, us per iteration): 4096 fp32 elements 54 -> 43, 100003 bf16 elements 52 -> 31 (154 with a dispatch per kernel), 2^23
+// 326 -> 304.
+template <typename T, int VB, int P, bool TAIL>
+__device__ __forceinline__ void chain_body(const T* in0, const T* const* in1, const unsigned* ms, unsigned n, bool periods, unsigned ops, T* const* outs) {
+    using V = Vec<T, VB>;
+    constexpr int NV = V::NV, NW = VB / 4;
+    constexpr bool kWide = sizeof(T) == 4;
+    const unsigned v = blockIdx.x * kBlock + threadIdx.x, nvec = n / NV, left = n - nvec * NV;     // left: elements of a last, partial vector
+    const unsigned mine = v < nvec ? (unsigned)NV : (TAIL && v == nvec) ? left : 0u;               // elements this lane owns
+    const unsigned i0 = (mine ? v : nvec - (nvec ? 1u : 0u)) * NV;
+    // NV elements of q from element `at` on, `room` of which there are; TAIL: one by one, none past the end
+    auto fetch = [](const T* q, unsigned at, unsigned room, unsigned* w) {
+        if constexpr (!TAIL) {
+            if constexpr (VB == 4) {
+                w[0] = *(const u32_any PG_GLOBAL*)((const T PG_GLOBAL*)(uintptr_t)q + at);
+            } else {
+                const v4u t = *(const v4u_any PG_GLOBAL*)((const T PG_GLOBAL*)(uintptr_t)q + at);
+                w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < NW; k++) w[k] = 0u;
+#pragma unroll
+            for (int e = 0; e < NV; e++) {
+                const unsigned r = load_raw_global_at(q, at + ((unsigned)e < room ? (unsigned)e : room - 1));
+                if constexpr (sizeof(T) == 4) w[e] = r;
+                else w[e / 2] |= r << (16 * (e & 1));
+            }
+        }
+    };
+    unsigned w[NW], ld[P][NW];
+    fetch(in0, i0, n - i0, w);
+    if (__builtin_expect(!periods, 1)) {
+#pragma unroll
+        for (int i = 0; i < P; i++) fetch(in1[i], i0, n - i0, ld[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < P; i++) {
+            const unsigned m = ms[i];
+            if (m == n) {
+                fetch(in1[i], i0, n - i0, ld[i]);
+            } else if (m % NV == 0) {                              // a vector never wraps around the period
+                fetch(in1[i], i0 % m, NV, ld[i]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < NW; k++) ld[i][k] = 0u;
+#pragma unroll
+                for (int e = 0; e < NV; e++) {
+                    const unsigned r = load_raw_global_at(in1[i], (i0 + e) % m);
+                    if constexpr (sizeof(T) == 4) ld[i][e] = r;
+                    else ld[i][e / 2] |= r << (16 * (e & 1));
+                }
+            }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): all operands here, once; a wait behind a store would wait for the store as well
+#pragma unroll
+    for (int i = 0; i < P; i++) {
+        const unsigned op = (ops >> (4 * i)) & 7u;
+        if (op == kChainEnd) break;
+        float fa[NV], fb[NV], fo[NV];
+        V::unpack(w, fa);
+        V::unpack(ld[i], fb);
+        if (op == (unsigned)kGelu) {
+            if constexpr (!kWide || VB == 4) {
+#pragma unroll
+                for (int e = 0; e < NV; e++) fo[e] = ew_apply<kGelu, kWide>(fa[e], 0.f);
+            } else {
+#pragma unroll
+                for (int e = 0; e < NV; e++) fo[e] = fa[e];      // never planned: the fp32 GELU rides only one element per lane
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < NV; e++) {
+                const float sum = ew_apply<kAdd, kWide>(fa[e], fb[e]), prod = ew_apply<kMul, kWide>(fa[e], fb[e]);
+                fo[e] = op == (unsigned)kAdd ? sum : prod;
+            }
+        }
+        V::pack(fo, w);
+        if ((ops >> (4 * i)) & 8u) {                               // else a later kernel of the run overwrites it
+            if (mine == (unsigned)NV) {
+                if constexpr (VB == 4) ((unsigned PG_GLOBAL*)(uintptr_t)outs[i])[v] = w[0];
+                else ((v4u PG_GLOBAL*)(uintptr_t)outs[i])[v] = v4u{w[0], w[1], w[2], w[3]};
+            } else if constexpr (TAIL) {
+#pragma unroll
+                for (int e = 0; e < NV - 1; e++)
+                    if ((unsigned)e < mine) {
+                        if constexpr (sizeof(T) == 4) ((unsigned PG_GLOBAL*)(uintptr_t)outs[i])[i0 + e] = w[e];
+                        else ((unsigned short PG_GLOBAL*)(uintptr_t)outs[i])[i0 + e] = (unsigned short)(w[e / 2] >> (16 * (e & 1)));
+                    }
+            }
+        }
+    }
+}
+
+template <typename T, int VB, int P>
+__global__ __launch_bounds__(kBlock) void k_chain(ChainArgs p) {
+    using SlotPtr = const void* const PG_CONSTANT*;
+    const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();      // a readable address for a load whose result is not used
+    const void* a0 = p.in0;
+    const unsigned n = p.n, slots = p.slots, ops = p.ops;
+    const void* a1[P];
+    T* outs[P];
+    unsigned ms[P];
+#pragma unroll
+    for (int i = 0; i < P; i++) { a1[i] = p.ph[i].in1; outs[i] = static_cast<T*>(p.ph[i].out); ms[i] = p.m[i]; }
+#pragma unroll
+    for (int i = 0; i < P; i += 4)
+        asm volatile("" : "+s"(a0), "+s"(a1[i]), "+s"(a1[i + 1]), "+s"(a1[i + 2]), "+s"(a1[i + 3]), "+s"(outs[i]), "+s"(outs[i + 1]), "+s"(outs[i + 2]), "+s"(outs[i + 3]),
+                          "+s"(ms[i]), "+s"(ms[i + 1]), "+s"(ms[i + 2]), "+s"(ms[i + 3]));
+    if (slots & ~kChainPeriods) {            // some operand is a pointer-table slot: all in one batch, without branches
+        const void* t1[P];
+        SlotPtr at0 = ((slots >> kMergeMaxPhases) & 1u) ? (SlotPtr)(uintptr_t)a0 : (SlotPtr)ka;
+        const void* t0 = *at0;
+#pragma unroll
+        for (int i = 0; i < P; i++) t1[i] = *(((slots >> i) & 1u) ? (SlotPtr)(uintptr_t)a1[i] : (SlotPtr)ka);
+#pragma unroll
+        for (int i = 0; i < P; i += 4) asm volatile("" : "+s"(t0), "+s"(t1[i]), "+s"(t1[i + 1]), "+s"(t1[i + 2]), "+s"(t1[i + 3]));
+        if ((slots >> kMergeMaxPhases) & 1u) a0 = t0;
+#pragma unroll
+        for (int i = 0; i < P; i++) if ((slots >> i) & 1u) a1[i] = t1[i];
+    }
+    const T* in1[P];
+#pragma unroll
+    for (int i = 0; i < P; i++) in1[i] = static_cast<const T*>(a1[i]);
+    constexpr unsigned NV = Vec<T, VB>::NV;
+    const bool tail = NV > 1 && n % NV != 0 && blockIdx.x == n / NV / kBlock;
+    if (__builtin_expect(!tail, 1)) chain_body<T, VB, P, false>(static_cast<const T*>(a0), in1, ms, n, slots & kChainPeriods, ops, outs);
+    else if constexpr (NV > 1) chain_body<T, VB, P, true>(static_cast<const T*>(a0), in1, ms, n, slots & kChainPeriods, ops, outs);
 }
 
 // ---- runs of kernels that hand on a short carry ---------------------------------------------------------------
@@ -923,6 +1011,14 @@ const void* merged_kernel(int dtype, bool narrow, int phases) {
     if (dtype != kBF16) return nullptr;
     if (narrow) return phases <= kMergeShortPhases ? PG_FN(k_merged<bf16_t, 4, kMergeShortPhases>) : PG_FN(k_merged<bf16_t, 4, kMergeMaxPhases>);
     return phases <= kMergeShortPhases ? PG_FN(k_merged<bf16_t, 16, kMergeShortPhases>) : PG_FN(k_merged<bf16_t, 16, kMergeMaxPhases>);
+}
+
+const void* chain_kernel(int dtype, bool narrow, int phases) {
+    const bool few = phases <= kMergeShortPhases;
+    if (dtype == kF32) return narrow ? PG_FN(k_chain<float, 4, kMergeShortPhases>) : PG_FN(k_chain<float, 16, kMergeShortPhases>);
+    if (dtype != kBF16) return nullptr;
+    if (narrow) return few ? PG_FN(k_chain<bf16_t, 4, kMergeShortPhases>) : PG_FN(k_chain<bf16_t, 4, kMergeMaxPhases>);
+    return few ? PG_FN(k_chain<bf16_t, 16, kMergeShortPhases>) : PG_FN(k_chain<bf16_t, 16, kMergeMaxPhases>);
 }
 
 bool carry_run_candidate(int op, int dtype, long long n) {

@@ -59,3 +59,23 @@ def test_general_runs(n):
     h = Harness(spec)
     assert h.chain.graph_dispatches()[0] < len(ks)
     _check(h)
+
+
+@pytest.mark.parametrize("dtype,n,kernels", [("bf16", 5, 3), ("bf16", 512, 2), ("bf16", 513, 7), ("bf16", 16391, 8), ("bf16", (1 << 20) - 1, 5), ("bf16", (1 << 20) + 1, 3), ("bf16", (1 << 20) + 2056, 8),
+                                             ("f32", 3, 4), ("f32", 257, 3), ("f32", 16384, 4), ("f32", 16388, 2), ("f32", 1 << 20, 2), ("f32", (1 << 20) + 4, 2)])
+def test_chains_with_periods(dtype, n, kernels):
+    """One run of kernels that each take the result of the one before, out of place, every output kept; second operands whole, with a
+    period that holds whole vectors and with ones that a vector wraps around."""
+    ks, seconds = [], [(Ref(EXT, 1), n), (Ref(WEIGHT, 0), 1), (Ref(WEIGHT, 0), 3), (Ref(WEIGHT, 0), 24)]
+    for i in range(kernels):
+        a = Ref(INT, i - 1) if i else Ref(EXT, 0)
+        if i % 3 == 2 and (dtype == "bf16" or n <= 16384):
+            ks.append(KernelSpec("gelu", dtype, i, (a,), n))
+        else:
+            b, m = seconds[i % 4]
+            ks.append(KernelSpec("mul" if i % 2 else "add", dtype, i, (a, b), n, m=m))
+    spec = ChainSpec(f"periods_{dtype}_{n}", ks, [TensorSpec(dtype, n) for _ in range(2)], [TensorSpec(dtype, n) for _ in range(kernels)],
+                     [TensorSpec(dtype, 24, ("normal", 1.0, 0.3))], list(range(kernels)), 8400)
+    h = Harness(spec)
+    assert h.chain.graph_dispatches()[0] == -(-kernels // (8 if dtype == "bf16" and n >= 16384 else 4))
+    _check(h)
