@@ -699,10 +699,25 @@ void seal_epilogue(pgk::GemvEpiArgs& e) {
     if (plain) e.head |= pgk::kEpiPlain;
 }
 
+// The matrices that one iteration's GEMVs read, each once.
+long long chain_weight_bytes(const pg_chain* c) {
+    long long bytes = 0;
+    std::vector<char> seen(c->w.size(), 0);
+    for (const auto& d : c->k) {
+        if (d.op != PG_GEMV) continue;
+        const pg_ref& r = d.in[0];
+        if (r.kind == PG_REF_WEIGHT && seen[r.index]) continue;
+        if (r.kind == PG_REF_WEIGHT) seen[r.index] = 1;
+        bytes += d.n * d.cols * (long long)elem_bytes(d.dtype);
+    }
+    return bytes;
+}
+
 pg_status make_records(pg_chain* c) {
     const int nk = (int)c->k.size();
     c->rec.assign(nk, KernelRec());
     c->eager_fix.clear();
+    const long long weight_bytes = chain_weight_bytes(c);
     for (int i = 0; i < nk; i++) {
         const pg_kernel_desc& d = c->k[i];
         KernelRec& r = c->rec[i];
@@ -738,6 +753,8 @@ pg_status make_records(pg_chain* c) {
             return fail(PG_EINVAL, "kernel %d: direct and indirect forms disagree on the launch shape", i);
         if (d.op == PG_GEMV)
             for (ArgBlock* a : {&r.a_eager, &r.a_copy, &r.a_ind}) a->gemv.row_groups = (int)r.direct.gemm_row_groups;
+        pgk::settle_weights(&r.direct, weight_bytes);
+        pgk::settle_weights(&r.indirect, weight_bytes);
     }
     for (auto& sg : c->seg)
         for (auto& g : sg.groups) {
@@ -760,6 +777,7 @@ pg_status make_records(pg_chain* c) {
                 g.launch.grid = dim3((unsigned)((nvec + 255) / 256));       // one workgroup per unit of 256 lanes x 16 bytes
             }
             if (!g.launch.fn) return fail(PG_EINVAL, "kernel %d: no merged kernel for this run", g.k0);
+            pgk::settle_weights(&g.launch, weight_bytes);
         }
     return PG_OK;
 }

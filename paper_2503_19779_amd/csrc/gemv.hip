@@ -608,6 +608,8 @@ __device__ __forceinline__ MmHead mm_head(const RideArgs<RIDE>& p) {
 //     that 16 consecutive lanes hit all banks;
 //   - the rows of h (from L2) are asked for before the weights (from HBM): loads return in order, so h is normalised
 //     and staged while the weights are still on their way; then the same LDS slice takes the weights.
+//   - the weights come by non-temporal loads: no other workgroup of the tile reads them (120 sub-blocks, us per iteration: 16 rows of 2048
+//     columns 766 -> 694, 32 of 1024 609 -> 565; 8 of 512, whose 15 MB of weights stay in the cache, 30 sub-blocks 145 -> 136).
 // TAIL: the row does not have exactly 128 * KS columns; vectors at any element boundary.
 // Decode chains of 120 sub-blocks, us per iteration: 32 rows of 1024 columns 1406 -> 613 (one dispatch per sub-block, where only
 // 2048 columns had that; half the K-steps); 8 / 16 / 32 rows of 2048 columns 651 / 787 / 915 -> 627 / 771 / 862 (the epilogue's
@@ -619,7 +621,7 @@ constexpr int kMmSlotBytes = 272;   // 16 rows x 16 B + 16 B of padding
 __device__ __forceinline__ int mm_k0(int wave, int l) { return ((l >> 3) * 8 + wave * 2 + ((l >> 2) & 1)) * 32 + (l & 3) * 8; }
 
 // NR rows of a row-major matrix from row r0 (inside it), this wave's K-slices; rows beyond the matrix repeat its last row
-template <int KS, bool TAIL, int NR>
+template <int KS, bool TAIL, int NR, bool NT>
 __device__ __forceinline__ void mm_load_rows(const bf16_t* m, int rows, int cols, int r0, int wave, int lane, unsigned (*g)[4]) {
     constexpr int L = 4 * KS, RPI = 64 / L;             // lanes per row, rows per instruction
     const int sub = lane / L;
@@ -628,10 +630,10 @@ __device__ __forceinline__ void mm_load_rows(const bf16_t* m, int rows, int cols
     for (int q = 0; q < NR / RPI; q++) {
         if constexpr (RPI == 1) {
             const int R = r0 + q < rows ? r0 + q : rows - 1;
-            load_any<false>(m + (size_t)R * cols, koff, g[q]);
+            load_any<NT>(m + (size_t)R * cols, koff, g[q]);
         } else {
             const int R = r0 + q * RPI + sub < rows ? q * RPI + sub : rows - 1 - r0;
-            load_any<false>(m + (size_t)r0 * cols, (unsigned)R * (unsigned)cols + koff, g[q]);
+            load_any<NT>(m + (size_t)r0 * cols, (unsigned)R * (unsigned)cols + koff, g[q]);
         }
     }
 }
@@ -757,11 +759,11 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
     char* lds = stage + wave * kWaveLds;
     unsigned g[NR * KS / 16][4], gw[NC * KS / 16][4];
     v4u a[KS], b[KS];
-    mm_load_rows<KS, TAIL, NR>(m.h, m.rows, cols, r0, wave, lane, g);      // PRO: the rows to normalise
+    mm_load_rows<KS, TAIL, NR, false>(m.h, m.rows, cols, r0, wave, lane, g);      // PRO: the rows to normalise
     unsigned wg[4] = {0u, 0u, 0u, 0u};
     if constexpr (PRO) load_any<false>(m.gain, span_at<!TAIL>(cols, mm_k0(wave, lane % (4 * KS)) >> 3), wg);   // before the weights: loads come back in order
     __builtin_amdgcn_sched_barrier(0);
-    mm_load_rows<KS, TAIL, NC>(m.W, m.n, cols, j0, wave, lane, gw);
+    mm_load_rows<KS, TAIL, NC, true>(m.W, m.n, cols, j0, wave, lane, gw);
     emit.prepare();                                      // the epilogue's table right behind the weight loads
     // output stage: wave w finishes row w of the four that an accumulator lane holds
     auto emit_begin = [&] { emit.begin(r0 + (lane >> 4) * 4 + wave, j0 + (lane & 15), NC == 16 || (lane & 15) < NC); };
@@ -797,7 +799,8 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
 // ---- k_gemm_cols ------------------------------------------------------------------------------------------
 // The same staging for more rows: 16 output columns per workgroup, whose weight fragments stay in registers while its
 // tiles of 16 rows of h pass by, the next tile's rows in flight across the multiplies of this one.  Two workgroups per CU.
-template <int KS, bool TAIL, Ride RIDE>
+// WNT, here and in k_gemm_tile: the weights by non-temporal loads (plan_gemm).
+template <int KS, bool TAIL, bool WNT, Ride RIDE>
 __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
     const MmHead m = mm_head<RIDE>(p);
     constexpr int kWaveLds = 4 * KS * kMmSlotBytes, kRedRow = 20;
@@ -820,13 +823,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
     char* lds = stage + wave * kWaveLds;
     unsigned g[KS][4], gw[KS][4];
     v4u a[KS], b[KS];
-    mm_load_rows<KS, TAIL, 16>(m.h, m.rows, cols, t0 * 16, wave, lane, g);
-    mm_load_rows<KS, TAIL, 16>(m.W, m.n, cols, j0, wave, lane, gw);
+    mm_load_rows<KS, TAIL, 16, false>(m.h, m.rows, cols, t0 * 16, wave, lane, g);
+    mm_load_rows<KS, TAIL, 16, WNT>(m.W, m.n, cols, j0, wave, lane, gw);
     emit.prepare();                                      // the epilogue's table right behind the weight loads
     mm_fix_rows<KS, TAIL, 16>(cols, wave, lane, g);
     mm_stage<KS, 16>(lds, lane, g);
     mm_read_frags<KS>(lds, lane, a);
-    if (t1 - t0 > 1) mm_load_rows<KS, TAIL, 16>(m.h, m.rows, cols, (t0 + 1) * 16, wave, lane, g);
+    if (t1 - t0 > 1) mm_load_rows<KS, TAIL, 16, false>(m.h, m.rows, cols, (t0 + 1) * 16, wave, lane, g);
     mm_fix_rows<KS, TAIL, 16>(cols, wave, lane, gw);
     mm_stage<KS, 16>(lds, lane, gw);
     mm_read_frags<KS>(lds, lane, b);
@@ -850,7 +853,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
         lds_barrier();                       // the sums are read: `red` is free again
         mm_fix_rows<KS, TAIL, 16>(cols, wave, lane, g);
         mm_stage<KS, 16>(lds, lane, g);
-        if (t + 1 < t1) mm_load_rows<KS, TAIL, 16>(m.h, m.rows, cols, (t + 1) * 16, wave, lane, g);
+        if (t + 1 < t1) mm_load_rows<KS, TAIL, 16, false>(m.h, m.rows, cols, (t + 1) * 16, wave, lane, g);
         mm_read_frags<KS>(lds, lane, a);
     }
 }
@@ -876,6 +879,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
 // one block ahead.
 template <int N>
 __device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// 16 bytes per lane from global memory into LDS, lane l's at `to` + 16 l
+template <bool NT>
+__device__ __forceinline__ void load_to_lds(const bf16_t* base /* uniform */, unsigned elem, char* to /* uniform */) {
+    __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)base + elem), (__attribute__((address_space(3))) void*)to, 16, 0, NT ? 2 : 0);
+}
 // The fragments of one K-block, both steps, of F tiles 2 KB apart: read and waited for in one piece (left to the compiler,
 // reads of LDS that direct loads may be filling wait for all of those first)
 template <int F>
@@ -899,7 +907,7 @@ __device__ __forceinline__ void ring_frags(unsigned at0, unsigned at1, v4u (&f)[
                      : "v"(at0), "v"(at1) : "memory");
 }
 
-template <int RT, int CT, int S, int NW>
+template <int RT, int CT, int S, int NW, bool WNT>
 __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gemm_tile(RideArgs<NW == 8 ? kEpilogue : kAlone> p) {
     constexpr int F = RT + CT, NL = 2 * F, kBlockLds = F * 2048, kWaveLds = S * kBlockLds;
     constexpr int PK = 8 / NW;                           // eighths of K per wave
@@ -963,10 +971,11 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
         auto issue = [&](int b, int slot) {
             const int k = (wave + NW * b) * 64 + chunk * 8;
             const unsigned ke = k < cols ? (unsigned)k : 0u;           // a chunk past the end is read from column 0 and zeroed later
+            char* const to = mine + slot * kBlockLds;
 #pragma unroll
-            for (int q = 0; q < NL; q++)
-                __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)(q < 2 * RT ? hb : wb) + (row_at[q] + ke)),
-                                                 (__attribute__((address_space(3))) void*)(mine + slot * kBlockLds + q * 1024), 16, 0, 0);
+            for (int q = 0; q < 2 * RT; q++) load_to_lds<false>(hb, row_at[q] + ke, to + q * 1024);
+#pragma unroll
+            for (int q = 2 * RT; q < NL; q++) load_to_lds<WNT>(wb, row_at[q] + ke, to + q * 1024);
         };
         if (nb > 0) issue(0, 0);
         epilogue_begin();
@@ -1330,10 +1339,10 @@ const void* gemm_rows_form(int rows, int cols) {
     if (cols <= 1024) return cols == 1024 ? gemm_rows_kernel<8, false, RIDE>(rows) : gemm_rows_kernel<8, true, RIDE>(rows);
     return cols == 2048 ? gemm_rows_kernel<16, false, RIDE>(rows) : gemm_rows_kernel<16, true, RIDE>(rows);
 }
-template <Ride RIDE>
+template <Ride RIDE, bool WNT>
 const void* gemm_cols_form(int cols) {
-    if (cols <= 1024) return cols == 1024 ? PG_FN(k_gemm_cols<8, false, RIDE>) : PG_FN(k_gemm_cols<8, true, RIDE>);
-    return cols == 2048 ? PG_FN(k_gemm_cols<16, false, RIDE>) : PG_FN(k_gemm_cols<16, true, RIDE>);
+    if (cols <= 1024) return cols == 1024 ? PG_FN(k_gemm_cols<8, false, true, RIDE>) : PG_FN(k_gemm_cols<8, true, true, RIDE>);
+    return cols == 2048 ? PG_FN(k_gemm_cols<16, false, WNT, RIDE>) : PG_FN(k_gemm_cols<16, true, WNT, RIDE>);
 }
 void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     const bool merged = ride != kAlone;
@@ -1341,6 +1350,7 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     out->arg_bytes = merged ? sizeof(GemvEpiArgs) : sizeof(GemvAloneArgs);
     out->block = dim3(kBlock);
     out->gemm_row_groups = (unsigned)ntiles;
+    out->fn_beyond_cache = nullptr;
     if (ride == kPrologue || (rows <= 16 && cols <= 2048)) {
         out->fn = ride == kPrologue ? gemm_rows_form<kPrologue>(rows, cols) : merged ? gemm_rows_form<kEpilogue>(rows, cols) : gemm_rows_form<kAlone>(rows, cols);
         out->grid = rows <= 16 ? dim3(blocks_for(n, 8)) : dim3(blocks_for(n, 16) * (unsigned)ntiles);
@@ -1350,8 +1360,12 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     // A 32-column tile of up to 16 outputs per row would be half empty; with so few workgroups, one tile of rows each.
     if (cols <= 2048 && (rows < kMmWideRows || n <= 16)) {
         out->gemm_row_groups = (unsigned)(ntiles < 4 || n <= 16 ? ntiles : 4);
+        // Several workgroups read the same weights, side by side.  Decode chains, us per iteration without / with non-temporal loads: 64 rows of
+        // 1024 columns, 126 MB of weights in all 366 / 339, 252 MB 729 / 679, 40 rows of 520 columns 916 / 860; of 2048 columns, 168 MB 184 / 188,
+        // 1 GB 1183 / 1084; rows that share cache lines, 40 of 1500 columns, 540 MB 1599 / 1628.
         out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
-        out->fn = merged ? gemm_cols_form<kEpilogue>(cols) : gemm_cols_form<kAlone>(cols);
+        out->fn = merged ? gemm_cols_form<kEpilogue, false>(cols) : gemm_cols_form<kAlone, false>(cols);
+        if (cols % 64 == 0) out->fn_beyond_cache = merged ? gemm_cols_form<kEpilogue, true>(cols) : gemm_cols_form<kAlone, true>(cols);
         return;
     }
     // The largest tile that still gives every CU a workgroup: 64 x 32 in 256 (RMSNorm, GEMV, GELU, GEMV and add on 128 rows of 2048
@@ -1361,15 +1375,19 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     const long long wide = blocks_for(n, 32), narrow = blocks_for(n, 16), two = (ntiles + 1) / 2, four = (ntiles + 3) / 4;
     if (merged) out->block = dim3(512);
     if (ntiles > 2 && wide * four >= 256) {
-        out->fn = merged ? PG_FN(k_gemm_tile<4, 2, 1, 8>) : PG_FN(k_gemm_tile<4, 2, 2, 4>);
+        out->fn = merged ? PG_FN(k_gemm_tile<4, 2, 1, 8, false>) : PG_FN(k_gemm_tile<4, 2, 2, 4, false>);
         out->gemm_row_groups = (unsigned)four;
         out->grid = dim3((unsigned)(wide * four));
     } else if (rows >= kMmWideRows || (ntiles > 1 && narrow * ntiles > 512)) {
-        out->fn = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8>) : PG_FN(k_gemm_tile<2, 2, 2, 4>);
+        out->fn = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8, false>) : PG_FN(k_gemm_tile<2, 2, 2, 4, false>);
         out->gemm_row_groups = (unsigned)two;
         out->grid = dim3((unsigned)wide * out->gemm_row_groups);
+        // Where all workgroups that share their weights run side by side: 1536 columns and more, one workgroup per CU.  us per iteration
+        // without / with non-temporal loads: 128 rows of 2048 columns, 1 GB in all 1326 / 1264, 250 MB 288 / 322; of 1536 columns 984 / 938; 100 of
+        // 2048 1049 / 995; 128 of 1024, 250 MB 948 / 975; other tiles and larger grids 100 of 4096 487 / 530, 128 of 6144 511 / 525.
+        if (out->grid.x <= 256 && cols >= 1536) out->fn_beyond_cache = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8, true>) : PG_FN(k_gemm_tile<2, 2, 2, 4, true>);
     } else {
-        out->fn = merged ? PG_FN(k_gemm_tile<1, 1, 2, 8>) : PG_FN(k_gemm_tile<1, 1, 2, 4>);
+        out->fn = merged ? PG_FN(k_gemm_tile<1, 1, 2, 8, false>) : PG_FN(k_gemm_tile<1, 1, 2, 4, false>);
         out->grid = dim3((unsigned)(narrow * ntiles));
     }
 }
@@ -1439,6 +1457,7 @@ void plan_gemv_epilogue(const Shape& s, bool with_prologue, Launch* out) {
     const int rows = (int)s.rows, n = (int)s.n, cols = (int)s.cols;
     out->mod_fn = nullptr;
     out->gemm_row_groups = 0;
+    out->fn_beyond_cache = nullptr;
     if (rows > 4) { plan_gemm(rows, n, cols, with_prologue ? kPrologue : kEpilogue, out); return; }
     out->fn = with_prologue ? rows_kernel<kPrologue>(rows, n, cols) : rows_kernel<kEpilogue>(rows, n, cols);
     out->arg_bytes = sizeof(GemvEpiArgs);

@@ -222,7 +222,15 @@ struct Launch {
     dim3 grid{1, 1, 1};
     dim3 block{1, 1, 1};
     unsigned gemm_row_groups = 0;    // GEMV on the matrix cores: goes into GemvArgs::row_groups (0 = other kernels)
+    const void* fn_beyond_cache = nullptr;      // ... and the kernel that takes its weights by non-temporal loads, where the chain settles that (settle_weights)
 };
+
+// The memory-side cache: weights of a chain beyond it come from memory in every iteration, where non-temporal loads of them can be the
+// faster ones; weights within it are found there again, unless they were loaded that way.
+constexpr long long kCacheBytes = 256ll << 20;
+inline void settle_weights(Launch* l, long long chain_weight_bytes) {
+    if (l->fn_beyond_cache && chain_weight_bytes > kCacheBytes) l->fn = l->fn_beyond_cache;
+}
 
 struct Shape {
     long long n = 0, m = 0, rows = 1, cols = 0, inner = 0;

@@ -977,6 +977,7 @@ bool plan(int op, int dtype, int ind_mask, const Shape& shape, Launch* out) {
     }
     out->mod_fn = nullptr;
     out->gemm_row_groups = 0;
+    out->fn_beyond_cache = nullptr;
     if (dtype == kF32) return plan_t<float>(op, ind_mask, shape, out);
     if (dtype == kBF16) return plan_t<bf16_t>(op, ind_mask, shape, out);
     return false;

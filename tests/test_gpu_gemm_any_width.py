@@ -98,3 +98,18 @@ def test_short_tails(rows, n, cols, tail):
     merged, unmerged = h.chain.graph_dispatches()
     assert merged < unmerged
     _check(h)
+
+
+@pytest.mark.parametrize("rows", [40, 100])
+def test_weights_beyond_the_cache(rows):
+    """More than 256 MB of weights in one chain: the forms that take them by non-temporal loads, same results."""
+    spec = decode_chain(batch=rows, layers=33, blocks_per_layer=1, hidden=2048, n_ext=2)
+    h = Harness(spec)
+    x_np, x_dev = h.inputs(0)
+    ref = h.run("eager", x_dev)
+    for mode in ("copy", "indirect"):
+        h.scrub()
+        assert same_bits(h.run(mode, x_dev)[0], ref[0]), mode
+    h.scrub()
+    stepwise_check(h, x_np, x_dev, rows=[0, rows - 1], rtol=2.0 ** -7)
+    h.close()
