@@ -270,18 +270,22 @@ __device__ __forceinline__ unsigned span_at(int cols, int v) {
     const int at = v * 8;
     return (unsigned)(at < cols - 8 ? at : cols - 8);
 }
-// ... and what becomes of it: elements past the row's end are zeros
+// ... and what becomes of it: elements past the row's end are zeros.  The one vector of a row that the end cuts was fetched the same number
+// of elements before its place in every row, so the shift has nothing to decide per lane and only the wave that holds it takes the branch;
+// vectors beyond the end are zeroed by selects.
+__device__ __forceinline__ void span_shift(unsigned s /* elements, up to 7 */, unsigned* w) {
+    if (s & 1u) { w[0] = (w[0] >> 16) | (w[1] << 16); w[1] = (w[1] >> 16) | (w[2] << 16); w[2] = (w[2] >> 16) | (w[3] << 16); w[3] >>= 16; }
+    if (s & 2u) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
+    if (s & 4u) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0u; }
+}
 template <bool EXACT>
 __device__ __forceinline__ void span_fix(int cols, int v, unsigned* w) {
     if constexpr (!EXACT) {
-        const int over = v * 8 + 8 - cols;
-        if (over > 0) {                                  // the fetched vector lies `over` elements before its place
-            const unsigned s = (unsigned)(over < 8 ? over : 8);
-            if (s & 1u) { w[0] = (w[0] >> 16) | (w[1] << 16); w[1] = (w[1] >> 16) | (w[2] << 16); w[2] = (w[2] >> 16) | (w[3] << 16); w[3] >>= 16; }
-            if (s & 2u) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
-            if (s & 4u) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0u; }
-            if (s & 8u) w[0] = w[1] = w[2] = w[3] = 0u;
-        }
+        const int over = v * 8 + 8 - cols;               // the fetched vector lies `over` elements before its place
+        if (const unsigned s = 8u - ((unsigned)cols & 7u); s != 8u)
+            if (over == (int)s) span_shift(s, w);        // the one that the row's end cuts: s is the same in every lane that gets here
+#pragma unroll
+        for (int i = 0; i < 4; i++) w[i] = over >= 8 ? 0u : w[i];
     }
 }
 __device__ __forceinline__ void span_store(bf16_t* row, int cols, int v, const unsigned* w) {
@@ -639,9 +643,19 @@ __device__ __forceinline__ void mm_load_rows(const bf16_t* m, int rows, int cols
 }
 template <int KS, bool TAIL, int NR>
 __device__ __forceinline__ void mm_fix_rows(int cols, int wave, int lane, unsigned (*g)[4]) {
-    if constexpr (TAIL)
+    if constexpr (TAIL) {
+        // (as span_fix, but a lane's vectors lie in the same place of every row: decided once for all of them.  Decided vector by vector, with a
+        // shift by a lane's own count, 16 rows of 1536 columns took 8.8 us a dispatch where 2048 columns took 5.8; now 7.1.)
+        const int over = mm_k0(wave, lane % (4 * KS)) + 8 - cols;
+        if (const unsigned s = 8u - ((unsigned)cols & 7u); s != 8u)
+            if (over == (int)s)
 #pragma unroll
-        for (int q = 0; q < NR * KS / 16; q++) span_fix<false>(cols, mm_k0(wave, lane % (4 * KS)) >> 3, g[q]);
+                for (int q = 0; q < NR * KS / 16; q++) span_shift(s, g[q]);
+#pragma unroll
+        for (int q = 0; q < NR * KS / 16; q++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) g[q][i] = over >= 8 ? 0u : g[q][i];
+    }
 }
 
 // LDS operations of one wave execute in order: these writes cannot overtake the reads before them
@@ -1091,7 +1105,7 @@ __device__ __forceinline__ void gemv_rows_sums(const bf16_t* W, const bf16_t* h,
     constexpr int KC = (U + 3) / 4;                      // vectors per lane of the workgroup
     if constexpr (EXACT) cols = 512 * U;
     // 512-column pieces of a row that every row this form serves has whole (rows_kernel_rb): no end to look for in them
-    constexpr int WHOLE = EXACT ? U : R == 1 ? U - 1 : U == 3 ? 0 : U == 4 ? 3 : U - 4;
+    constexpr int WHOLE = EXACT ? U : U <= 4 ? U - 1 : U - 4;
     auto at = [&](int v, bool whole) { return whole ? span_at<true>(cols, v) : span_at<false>(cols, v); };
     auto fix = [&](int v, bool whole, unsigned* w) { if (!whole) span_fix<false>(cols, v, w); };
     auto whole_u = [](int u) { return u < WHOLE; };                     // ... vectors u * 64 + lane of a weight row
@@ -1306,6 +1320,10 @@ const void* rows_kernel_rb(int n, int cols) {
     case 8192: return PG_FN(k_gemv_rows<2, RB, 16, true, RIDE>);
     default: break;
     }
+    // up to 2048 columns a form per 512, so that only a row's last piece has an end to look for (decode chains of 60 sub-blocks against one
+    // form for up to 1536 columns, us per iteration: 1 row of 1400 columns 198 -> 182, 4 rows 255 -> 243, 3 rows of 1500 242 -> 238)
+    if (u <= 1) return PG_FN(k_gemv_rows<2, RB, 1, false, RIDE>);
+    if (u <= 2) return PG_FN(k_gemv_rows<2, RB, 2, false, RIDE>);
     if (u <= 3) return PG_FN(k_gemv_rows<2, RB, 3, false, RIDE>);
     if (u <= 4) return PG_FN(k_gemv_rows<2, RB, 4, false, RIDE>);
     if (u <= 8) return PG_FN(k_gemv_rows<2, RB, 8, false, RIDE>);
