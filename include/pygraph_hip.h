@@ -144,7 +144,9 @@ pg_status pg_chain_build(const pg_kernel_desc *kernels, int32_t n_kernels,
 /* Capture (paper, Sec. 2.2 stream capture; Sec. 4 "Graph-Capture Layer"): for every segment record
  * its kernels on `hip_stream` twice -- once reading the static placeholders, once reading the
  * pointer table -- instantiate and upload the graphs, and write the static part of the copy
- * kernel's job list into the workspace.  Synchronises the stream before returning.  Calling it
+ * kernel's job list into the workspace.  A segment that comes to 6 dispatches or fewer gets no
+ * graph: its launches and their argument blocks are laid out here, and a replay issues them (a graph
+ * launch costs the host more than that many kernel launches).  Synchronises the stream before returning.  Calling it
  * again re-captures: it first waits for everything queued on the device (a replay of the old graphs
  * may be running on any stream) and destroys the old graphs. */
 pg_status pg_capture(pg_chain *chain, void *hip_stream);
@@ -286,7 +288,7 @@ pg_status pg_set_copy_refresh(pg_chain *chain, int32_t how /* pg_copy_refresh */
  * between).  Eager launches are never merged.  `on` = 0 captures one node per kernel.  Takes effect at
  * the next pg_capture. */
 pg_status pg_set_dispatch_merge(pg_chain *chain, int32_t on);
-/* Kernel nodes that the graphs of one replay hold with merging on (*merged_out) and off
+/* Kernel dispatches that the graphs of one replay, or the launches in place of a graph, come to with merging on (*merged_out) and off
  * (*unmerged_out = the number of kernels).  Either output may be NULL.  Host only. */
 pg_status pg_chain_graph_dispatches(const pg_chain *chain, int32_t *merged_out, int32_t *unmerged_out);
 /* Destroys the graphs and host objects, after waiting for everything queued on the device the chain

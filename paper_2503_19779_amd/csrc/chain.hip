@@ -105,6 +105,18 @@ struct MergeGroup {
     pgk::Launch launch;
 };
 
+// One dispatch of a replay: the launch (of a KernelRec or a MergeGroup, which outlive it) and its argument block.
+struct Dispatch {
+    pgk::Launch* launch;
+    std::vector<unsigned char> args;
+};
+// A segment of up to this many dispatches is replayed by launching them from blocks laid out at capture, a longer one as a graph.  A graph
+// launch takes the host 15 us and 0.9 us per node, a kernel launch 2.2 or, in some processes, 2.6; the GPU needs 1.6 to 3 us per short kernel,
+// so it waits for the former in short segments only.  us per iteration, graph / launched: two segments of 2 scale + bias + ReLU dispatches
+// 44 / 19, four of 1 73 / 23; chains of 2 fp32 elementwise dispatches 18.5 / 8.8, of 8 28 / 21, of 12 35 / 30, of 24 52 / 61.  Beyond 6 a process
+// with slow launches loses: 8 bf16 elementwise dispatches 31 / 25 or 33, and 47 / 46 or 64 where every iteration is waited for.
+constexpr size_t kLaunchedMost = 6;
+
 struct Segment {
     int k0 = 0, k1 = 0;
     std::vector<MergeGroup> groups;  // cover [k0, k1) in order
@@ -112,6 +124,7 @@ struct Segment {
     int copy_list = -1;             // index into copy_lists
     hipGraph_t g_copy = nullptr, g_ind = nullptr;
     hipGraphExec_t x_copy = nullptr, x_ind = nullptr;
+    std::vector<Dispatch> d_copy, d_ind;     // instead of those graphs, where the segment is launched (kLaunchedMost)
     // host-updated variant: explicit kernel nodes in chain order, two executable instances
     hipGraph_t g_upd = nullptr;
     hipGraphExec_t x_upd[2] = {nullptr, nullptr};
@@ -915,6 +928,8 @@ void destroy_graphs(pg_chain* c) {
         if (s.x_copy) (void)hipGraphExecDestroy(s.x_copy);
         if (s.g_copy) (void)hipGraphDestroy(s.g_copy);
         s.x_copy = s.x_ind = nullptr;
+        s.d_copy.clear();
+        s.d_ind.clear();
         s.g_copy = s.g_ind = nullptr;
     }
     c->captured = false;
@@ -989,11 +1004,13 @@ pg_status run_update(pg_chain* c, const void* const* ext, hipStream_t s) {
 // What a captured graph's kernels read their external operands from.
 enum GraphKind { kGraphCopy = 0, kGraphTable = 1, kGraphTableMemcpyNode = 2, kGraphHostTable = 3 };
 
-pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStream_t s, hipGraph_t* g_out, hipGraphExec_t* x_out) {
-    PG_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    hipError_t le = hipSuccess;
-    if (kind == kGraphTableMemcpyNode)   // the graph's first node copies the pointers from its instance's pinned staging
-        le = hipMemcpyAsync(c->ws + c->table_off, c->alt[0].host[inst], c->ext.size() * 8, hipMemcpyHostToDevice, s);
+// What one replay of a segment dispatches, in order.
+std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int inst) {
+    std::vector<Dispatch> out;
+    auto emit = [&](pgk::Launch& l, const void* args) {
+        const unsigned char* at = static_cast<const unsigned char*>(args);
+        out.push_back({&l, std::vector<unsigned char>(at, at + l.arg_bytes)});
+    };
     auto block_of = [&](KernelRec& r) -> ArgBlock& { return kind == kGraphCopy ? r.a_copy : kind == kGraphHostTable ? r.a_host[inst] : r.a_ind; };
     // Which copy of each internal buffer is current (see plan_groups: runs that rename).  Every kernel of
     // the segment gets its internal operands in the current copy; all are back in the first at the end.
@@ -1011,12 +1028,11 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
     };
     int n_carry = 0;                      // runs with a carry so far: two places for what they set aside, in turn
     for (auto& grp : sg.groups) {
-        if (le != hipSuccess) break;
         if (!c->merge || grp.k1 - grp.k0 < 2) {
-            for (int i = grp.k0; i < grp.k1 && le == hipSuccess; i++) {
+            for (int i = grp.k0; i < grp.k1; i++) {
                 KernelRec& r = c->rec[i];
-                ArgBlock a = versioned(i, nullptr);
-                le = launch(kind == kGraphCopy ? r.direct : r.indirect, &a, s);
+                const ArgBlock a = versioned(i, nullptr);
+                emit(kind == kGraphCopy ? r.direct : r.indirect, &a);
             }
             continue;
         }
@@ -1050,7 +1066,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             if (c->k[grp.k1 - 1].n >= grp.carry_m) m.carry_out = place(n_carry);
             n_carry++;
             for (int q = m.n_phase; q < pgk::kCarryRunMax; q++) m.unit0[q] = ~0u;
-            le = launch(grp.launch, &m, s);
+            emit(grp.launch, &m);
             continue;
         }
         if (grp.sbr) {
@@ -1070,7 +1086,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
                 ph.b = a.ptr[3];
                 ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (grp.store[m.n_phase] ? pgk::kEpiStore : 0u);
             }
-            le = launch(grp.launch, &m, s);
+            emit(grp.launch, &m);
             continue;
         }
         if (grp.head) {
@@ -1109,7 +1125,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             }
             for (int q = e.n_epi; q < pgk::kEpiMaxPhases; q++) e.ph[q].meta = (unsigned)PG_GELU;   // operands "from slot 0": fetches nothing, never played
             seal_epilogue(e);
-            le = launch(grp.launch, &e, s);
+            emit(grp.launch, &e);
             if (grp.rename >= 0) second[grp.rename] ^= 1;
             continue;
         }
@@ -1145,7 +1161,7 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
                 if (m.m[t] != m.n) m.slots |= pgk::kChainPeriods;
                 m.ops |= ((unsigned)d.op | (grp.store[t] ? 8u : 0u)) << (4 * t);
             }
-            le = launch(grp.launch, &m, s);
+            emit(grp.launch, &m);
             continue;
         }
         // one dispatch for the run: the kernels' own operands, in order, in one argument struct
@@ -1166,10 +1182,30 @@ pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStrea
             ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (grp.store[m.n_phase] ? pgk::kEpiStore : 0u);
         }
         for (int q = m.n_phase; q < pgk::kMergeMaxPhases; q++) m.ph[q].meta = (unsigned)PG_GELU;   // operands "from slot 0": fetches nothing, never played
-        le = launch(grp.launch, &m, s);
+        emit(grp.launch, &m);
     }
-    for (char v : second)
-        if (v && le == hipSuccess) le = hipErrorAssert;     // plan_groups pairs the renames up; never reached
+    return out;              // (plan_groups pairs the renames up: every buffer is back in its first copy)
+}
+
+pg_status play(std::vector<Dispatch>& d, hipStream_t s) {
+    for (auto& x : d) PG_HIP(launch(*x.launch, x.args.data(), s));
+    return PG_OK;
+}
+
+pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStream_t s, hipGraph_t* g_out, hipGraphExec_t* x_out, std::vector<Dispatch>* few) {
+    std::vector<Dispatch> all = segment_dispatches(c, sg, kind, inst);
+    if (few && all.size() <= kLaunchedMost) {
+        for (auto& x : all)
+            if (!x.launch->mod_fn) PG_HIP(hipGetFuncBySymbol(&x.launch->mod_fn, x.launch->fn));
+        *few = std::move(all);
+        return PG_OK;
+    }
+    PG_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+    hipError_t le = hipSuccess;
+    if (kind == kGraphTableMemcpyNode)   // the graph's first node copies the pointers from its instance's pinned staging
+        le = hipMemcpyAsync(c->ws + c->table_off, c->alt[0].host[inst], c->ext.size() * 8, hipMemcpyHostToDevice, s);
+    for (auto& x : all)
+        if (le == hipSuccess) le = launch(*x.launch, x.args.data(), s);
     hipGraph_t g = nullptr;
     hipError_t ee = hipStreamEndCapture(s, &g);   // always end the capture, even after a failed launch
     if (le != hipSuccess) { if (g) (void)hipGraphDestroy(g); g_hip_err = (int)le; return fail(PG_EHIP, "kernel launch during capture failed: %s", hipGetErrorString(le)); }
@@ -1207,7 +1243,7 @@ pg_status build_alt(pg_chain* c, int v, hipStream_t s) {
     for (auto& sg : c->seg) {
         if (!sg.has_ext) continue;    // such a segment replays its copy graph in every mode
         for (int i = 0; i < 2; i++) {
-            pg_status st = capture_segment(c, sg, v == 0 ? kGraphTableMemcpyNode : kGraphHostTable, i, s, &sg.g_alt[v][i], &sg.x_alt[v][i]);
+            pg_status st = capture_segment(c, sg, v == 0 ? kGraphTableMemcpyNode : kGraphHostTable, i, s, &sg.g_alt[v][i], &sg.x_alt[v][i], nullptr);
             if (st) { destroy_alt_graphs(c); return st; }
         }
     }
@@ -1229,10 +1265,19 @@ pg_status ind_begin(pg_chain* c, const void* const* ext, hipStream_t s, IndCtx& 
     return PG_OK;
 }
 
-hipGraphExec_t ind_exec(pg_chain* c, Segment& sg, const IndCtx& x) {
-    if (!sg.has_ext) return sg.x_copy;
-    if (c->table_how == PG_TABLE_KERNARG || c->table_how == PG_TABLE_MEMCPY) return sg.x_ind;
-    return sg.x_alt[c->table_how - PG_TABLE_GRAPH_MEMCPY][x.inst];
+// The segment's kernels: of the copy graph, and of the indirect one with whichever table mechanism is selected
+pg_status run_copy_form(Segment& sg, hipStream_t s) {
+    if (!sg.d_copy.empty()) return play(sg.d_copy, s);
+    PG_HIP(hipGraphLaunch(sg.x_copy, s));
+    return PG_OK;
+}
+pg_status run_ind_form(pg_chain* c, Segment& sg, const IndCtx& x, hipStream_t s) {
+    if (!sg.has_ext) return run_copy_form(sg, s);
+    hipGraphExec_t g = sg.x_ind;
+    if (c->table_how != PG_TABLE_KERNARG && c->table_how != PG_TABLE_MEMCPY) g = sg.x_alt[c->table_how - PG_TABLE_GRAPH_MEMCPY][x.inst];
+    else if (!sg.d_ind.empty()) return play(sg.d_ind, s);
+    PG_HIP(hipGraphLaunch(g, s));
+    return PG_OK;
 }
 
 pg_status ind_end(pg_chain* c, hipStream_t s, IndCtx& x) {
@@ -1250,15 +1295,13 @@ pg_status run_segment(pg_chain* c, int si, int mode, const void* const* ext, hip
     case PG_EAGER: return run_eager_range(c, sg.k0, sg.k1, ext, s);
     case PG_GRAPH_COPY: {
         if (sg.copy_list >= 0) { pg_status st = run_copy_list(c, sg.copy_list, ext, s); if (st) return st; }
-        PG_HIP(hipGraphLaunch(sg.x_copy, s));
-        return PG_OK;
+        return run_copy_form(sg, s);
     }
     case PG_GRAPH_INDIRECT: {
         if (!sg.has_ext) return fail(PG_EUNAVAIL, "segment %d reads no external operand: indirect mode does not exist for it", si);
         pg_status st = ind_begin(c, ext, s, *ind);
         if (st) return st;
-        PG_HIP(hipGraphLaunch(ind_exec(c, sg, *ind), s));
-        return PG_OK;
+        return run_ind_form(c, sg, *ind, s);
     }
     default: return fail(PG_EINVAL, "bad mode %d for segment %d", mode, si);
     }
@@ -1404,10 +1447,10 @@ pg_status pg_capture(pg_chain* c, void* hip_stream) {
     for (auto& e : c->ring_ev)
         if (!e && !c->ext.empty()) PG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     for (auto& sg : c->seg) {
-        pg_status st = capture_segment(c, sg, kGraphCopy, 0, s, &sg.g_copy, &sg.x_copy);
+        pg_status st = capture_segment(c, sg, kGraphCopy, 0, s, &sg.g_copy, &sg.x_copy, &sg.d_copy);
         if (st) { destroy_graphs(c); return st; }
         if (sg.has_ext) {
-            st = capture_segment(c, sg, kGraphTable, 0, s, &sg.g_ind, &sg.x_ind);
+            st = capture_segment(c, sg, kGraphTable, 0, s, &sg.g_ind, &sg.x_ind, &sg.d_ind);
             if (st) { destroy_graphs(c); return st; }
         } else {
             sg.g_ind = sg.g_copy;   // no external operand: the two graphs would be identical
@@ -1503,7 +1546,8 @@ pg_status pg_replay_copy(pg_chain* c, const void* const* ext, void* hip_stream) 
     if (st) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     if ((st = run_copy_list(c, 0, ext, s))) return st;
-    for (auto& sg : c->seg) PG_HIP(hipGraphLaunch(sg.x_copy, s));
+    for (auto& sg : c->seg)
+        if ((st = run_copy_form(sg, s))) return st;
     return PG_OK;
 }
 
@@ -1513,7 +1557,8 @@ pg_status pg_replay_indirect(pg_chain* c, const void* const* ext, void* hip_stre
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     IndCtx x;
     if ((st = ind_begin(c, ext, s, x))) return st;
-    for (auto& sg : c->seg) PG_HIP(hipGraphLaunch(ind_exec(c, sg, x), s));
+    for (auto& sg : c->seg)
+        if ((st = run_ind_form(c, sg, x, s))) return st;
     return ind_end(c, s, x);
 }
 

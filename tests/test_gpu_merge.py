@@ -388,3 +388,22 @@ def test_runs_of_elementwise_kernels():
         assert same_bits(outs["eager"][0], outs["copy"][0]) and same_bits(outs["eager"][0], outs["indirect"][0])
         assert_close(outs["eager"][0], want, "bf16", "bf16 elementwise chain", rtol=0.25)   # 40 kernels deep: the step checks are elsewhere
     h.close()
+
+
+@pytest.mark.parametrize("kernels,cuts", [(24, 0), (25, 0), (36, 2)])
+def test_segments_around_the_longest_that_is_launched(kernels, cuts):
+    """6 dispatches are launched one by one, 7 go as a graph, and a chain may have segments of both kinds; the same results, also
+    after capturing again with one dispatch per kernel and back."""
+    spec = elementwise_chain(n_kernels=kernels, numel=1000)
+    if cuts:       # 8 kernels in two dispatches, then 28 in seven
+        ks = [dataclasses.replace(k, segment=int(i >= 8)) for i, k in enumerate(spec.kernels)]
+        spec = ChainSpec(spec.name + "_cut", ks, spec.ext, spec.ints, spec.weights, spec.outputs, spec.seed, meta=dict(spec.meta))
+    h = Harness(spec)
+    for merge in (True, False, True):
+        h.chain.set_dispatch_merge(merge)
+        h.chain.capture(h.stream)
+        for t in range(3):
+            _, x_dev = h.inputs(t)
+            outs = _all_modes(h, x_dev)
+            assert same_bits(outs["eager"][0], outs["copy"][0]) and same_bits(outs["eager"][0], outs["indirect"][0]), (merge, t)
+    h.close()
