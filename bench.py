@@ -362,10 +362,10 @@ def main() -> int:
         us4 = {name: timed(c4, x4, mode, 20, 3) for name, mode in MODES}
         us4["selected"] = timed(c4, x4, pg.SELECTED, 20, 3, sel4)
         # what the dispatches of each mode have to move: kernel by kernel the tensor is read and written 40 times; a merged segment
-        # reads it once and writes the last version of each of its two buffers
+        # reads it once and writes its last version, the last segment that of both buffers
         nb4, seg4 = spec4.ext[0].nbytes, spec4.n_segments
         eager4 = 2 * nb4 * len(spec4.kernels)
-        graph4 = 3 * nb4 * seg4 if c4.graph_dispatches()[0] == seg4 else eager4
+        graph4 = nb4 * (2 * seg4 + 1) if c4.graph_dispatches()[0] == seg4 else eager4
         bytes4 = {"eager": eager4, "graph_copy": graph4 + 2 * nb4, "graph_indirect": graph4,
                   "selected": sum((eager4 if m == pg.EAGER else graph4) / seg4 for m in sel4) + (2 * nb4 if sel4[0] == pg.GRAPH_COPY else 0)}
         configs["4"] = {"workload": "40 fp32 scale+bias+ReLU kernels on [32,64,112,112] in 4 segments, one 102.8 MB external input",

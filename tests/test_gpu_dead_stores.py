@@ -1,0 +1,86 @@
+"""Outputs of runs that are overwritten before anything reads them from memory are not stored: what is read later, in the same
+segment or another one, in whatever mode that one is replayed, must be there all the same, and so must every buffer's last version."""
+import dataclasses
+import itertools
+
+import pytest
+
+import paper_2503_19779_amd as pg
+from gpu_util import Harness, same_bits
+from pg_workloads import ChainSpec, KernelSpec, TensorSpec, Ref, EXT, INT, WEIGHT, decode_chain
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(spec):
+    """Every output after every combination of modes, bit for bit what eager launches leave."""
+    spec.outputs[:] = range(len(spec.ints))
+    h = Harness(spec)
+    for t in range(2):
+        _, x = h.inputs(t)
+        h.scrub()
+        want = h.run("eager", x)
+        for mode in ("copy", "indirect", "copy"):
+            h.scrub()
+            got = h.run(mode, x)
+            assert all(same_bits(a, b) for a, b in zip(want, got)), (mode, t)
+        has_ext = [any(r.kind == EXT for k in spec.kernels if k.segment == s for r in k.ins) for s in range(spec.n_segments)]
+        if spec.n_segments > 1:
+            for modes in itertools.product(*[(pg.EAGER, pg.GRAPH_COPY, pg.GRAPH_INDIRECT) if e else (pg.EAGER, pg.GRAPH_COPY) for e in has_ext]):
+                h.scrub()
+                got = h.run("selected", x, list(modes))
+                assert all(same_bits(a, b) for a, b in zip(want, got)), (modes, t)
+    h.close()
+
+
+@pytest.mark.parametrize("cut", [0, 9, 17])
+@pytest.mark.parametrize("reader", [None, 512, 2040, 4096])
+def test_carry_runs(reader, cut):
+    """Three runs over two buffers, the longest tensors first: what the shorter ones behind leave of them stays.  `reader`: between the second and
+    the third run a kernel of its own reads that many elements.  `cut`: a new segment from that kernel on."""
+    sizes = [512, 4096, 2048, 1024, 8192, 520, 1032, 512, 2048, 2056, 512, 512, 1024, 3000, 512, 4104, 512, 1024, 512, 2048]
+    ks, ext = [], []
+    for i, n in enumerate(sizes):
+        op = ("add", "mul", "gelu")[i % 3]
+        a = (Ref(EXT, i),)
+        ks.append(KernelSpec(op, "bf16", i % 2, a if op == "gelu" else a + (Ref(INT, (i - 1) % 2) if i else Ref(WEIGHT, 0),), n, m=512 if op != "gelu" else 0))
+        ext.append(TensorSpec("bf16", n))
+    if reader:
+        ks.insert(16, KernelSpec("gelu", "bf16", 2, (Ref(INT, 0),), reader))
+    ks = [dataclasses.replace(k, segment=int(bool(cut) and i >= cut)) for i, k in enumerate(ks)]
+    spec = ChainSpec(f"dead_carry_{reader}_{cut}", ks, ext, [TensorSpec("bf16", 8192)] * 3, [TensorSpec("bf16", 512)], [], 8500)
+    _check(spec)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("reader", [None, 0, 1])
+def test_scale_bias_relu_segments(dtype, reader):
+    """Three segments of five kernels over two buffers.  `reader`: the second segment begins with a kernel that reads buffer 0 or 1."""
+    n, inner, ch = 2 * 6 * 40, 40, 6
+    ks = []
+    for i in range(15):
+        if i == 5 and reader is not None:
+            ks.append(KernelSpec("add", dtype, 2, (Ref(INT, reader), Ref(EXT, 0)), n - 8, m=n - 8, segment=1))
+        ks.append(KernelSpec("scale_bias_relu", dtype, i % 2, (Ref(INT, (i - 1) % 2) if i else Ref(EXT, 0), Ref(WEIGHT, 2 * (i % 3)), Ref(WEIGHT, 2 * (i % 3) + 1)), n,
+                             segment=i // 5, inner=inner, channels=ch))
+    spec = ChainSpec(f"dead_sbr_{dtype}_{reader}", ks, [TensorSpec(dtype, n)], [TensorSpec(dtype, n)] * 3,
+                     [TensorSpec(dtype, ch, ("normal", float(i % 2 == 0), 0.1)) for i in range(6)], [], 8510)
+    _check(spec)
+
+
+@pytest.mark.parametrize("batch", [1, 3, 16, 24, 40, 100])
+@pytest.mark.parametrize("reader", [None, 1, 2])
+@pytest.mark.parametrize("hidden", [256, 520])
+def test_decoder_blocks(batch, reader, hidden):
+    """Normalised rows (buffer 1) and GEMV results (buffer 2) that the next block overwrites.  `reader`: a kernel behind the second of four blocks, and
+    one at the chain's end in a segment of its own, read one of them."""
+    spec = decode_chain(batch=batch, layers=4, blocks_per_layer=1, hidden=hidden, n_ext=1)
+    n = batch * hidden
+    ks = list(spec.kernels)
+    if reader is not None:
+        ks.insert(8, KernelSpec("add", "bf16", 3, (Ref(INT, reader), Ref(EXT, 0)), n, m=n))
+        ks.append(KernelSpec("add", "bf16", 3, (Ref(INT, 3), Ref(INT, reader)), n, m=n, segment=1))
+    spec = dataclasses.replace(spec, name=f"{spec.name}_dead_{reader}", kernels=ks, ints=spec.ints + [TensorSpec("bf16", n)], outputs=[])
+    if reader is None:
+        spec.ints.pop()
+    _check(spec)
