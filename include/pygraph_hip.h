@@ -285,8 +285,8 @@ pg_status pg_set_copy_refresh(pg_chain *chain, int32_t how /* pg_copy_refresh */
  *     (pg_chain_workspace_bytes counts it), and every segment ends with all internal buffers in their
  *     first copy, where pg_chain_int_buffer and the other modes find them.
  * Outputs of a run that a later kernel of the chain overwrites before anything reads them from memory are
- * not stored; the last version of every internal buffer is.  Eager launches are never merged.  `on` = 0 captures one node per kernel.  Takes effect at
- * the next pg_capture. */
+ * not stored; the last version of every internal buffer is.  Eager launches are never merged.  `on` = 0
+ * captures one node per kernel.  Takes effect at the next pg_capture. */
 pg_status pg_set_dispatch_merge(pg_chain *chain, int32_t on);
 /* Kernel dispatches that the graphs of one replay, or the launches in place of a graph, come to with merging on (*merged_out) and off
  * (*unmerged_out = the number of kernels).  Either output may be NULL.  Host only. */

@@ -1132,7 +1132,14 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
                 ph.out = const_cast<void*>(a.ptr[0]);
                 ph.s = a.ptr[2];
                 ph.b = a.ptr[3];
-                ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (grp.store[m.n_phase] ? pgk::kEpiStore : 0u);
+                const unsigned slots = kind == kGraphCopy ? 0u : (unsigned)r.ind_mask;
+                m.stores |= (unsigned)grp.store[m.n_phase] << m.n_phase;
+                m.slots |= ((slots >> 1) & 1u) << m.n_phase | ((slots >> 2) & 1u) << (16 + m.n_phase);
+            }
+            for (int q = m.n_phase; q < pgk::kSbrRunMax; q++) {
+                m.ph[q].s = m.ph[0].s;
+                m.ph[q].b = m.ph[0].b;
+                m.slots |= (m.slots & 0x10001u) << q;
             }
             emit(grp.launch, &m);
             continue;

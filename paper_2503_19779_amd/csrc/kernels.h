@@ -173,10 +173,8 @@ constexpr int kSbrRunMax = 16;              // kernels per run
 constexpr int kSbrRunMaxChannels = 128;     // one lane per scale and per bias of a kernel when the run's tables are loaded
 struct SbrRunPhase {
     void* out;
-    const void* s;
+    const void* s;          // entries from n_phase on: kernel 0's, fetched and ignored
     const void* b;
-    unsigned ind;           // bit 1 / 2: s / b hold the address of a pointer-table slot; kEpiStore
-    unsigned reserved;
 };
 struct SbrRunArgs {
     const void* x;
@@ -185,7 +183,9 @@ struct SbrRunArgs {
     unsigned channels;
     unsigned x_slot;        // x holds the address of a pointer-table slot
     int n_phase;
-    int reserved;
+    unsigned stores;        // bit i: kernel i's output is stored
+    unsigned slots;         // bit i / 16 + i: kernel i's scale / bias is a pointer-table slot
+    unsigned reserved;
     SbrRunPhase ph[kSbrRunMax];
 };
 

@@ -152,105 +152,185 @@ __global__ __launch_bounds__(kBlock) void k_scale_bias_relu(SbrArgs p) {
 }
 
 // A run of such kernels in one dispatch (kernels.h, SbrRunArgs).  What bounds it is memory: kernel by kernel every one
-// reads and writes the whole tensor; here x comes in once, the elements stay in registers, and what goes out is each
-// buffer's last version (two of them in a chain that alternates between two buffers).  The scales and biases of all
-// kernels and channels are laid out in LDS first, one load per lane and kernel, all in flight behind the loads of x;
-// LDS[kernel][channel] = scale, [channels + channel] = bias.  Same fused multiply-add, same rounding per kernel.
+// reads and writes the whole tensor; here x comes in once, the elements stay in registers, and what goes out is what is read
+// later.  The scales and biases of all kernels and channels are laid out in LDS first, LDS[kernel][channel] = scale,
+// [channels + channel] = bias, one load per lane and kernel: the pointers in batches of eight kernels, all values in flight together, in
+// front of x (asked for kernel by kernel, a pointer, its value and a wait at a time, they took longer than x: ten of them about 10 us).  A
+// wave has one stretch of the tensor, which mostly lies in one channel or two: two scales and biases per kernel for the whole
+// wave, and no division per vector.  Same fused multiply-add, same rounding per kernel.
 // WHOLE: inner is a multiple of the 16-byte vector.  Otherwise a vector may straddle two channels (inner >= NV, so
 // never three) and the last vector of the tensor may be a partial one.  Vectors are fetched at any element boundary.
-// Ten fp32 kernels over [32, 64, 112, 112] per run: 62 us, 5 TB/s of the one read and two writes, where kernel by
-// kernel took 312 (40 kernels in four segments 1248 -> 249 us).  Eight vectors per lane: with two 286 us, four 266,
-// sixteen 295; non-temporal stores, of all outputs or of the ones nothing reads next, change nothing.
+// us per iteration, values asked for one by one / together / together and by stretches: 40 fp32 kernels over [32, 64, 112, 112] in four segments
+// 192 / 148 / 146 (5.6 TB/s of one read and one write per segment), 20 over [32, 64, 111, 111] in two 122 / 95 / 81, 24 over
+// [16, 33, 77, 101] in three 44 / 33 / 27.  Two vectors per lane: with four 147, 83, 27, with eight 150, 87, 29.  Non-temporal loads of x lose, 158:
+// the memory-side cache holds much of what the segment before wrote; non-temporal stores change nothing.
 template <typename T, bool WHOLE, int U>
 __global__ __launch_bounds__(kBlock) void k_sbr_run(SbrRunArgs p) {
     using V = Vec<T, 16>;
     constexpr int NV = V::NV;
-    __shared__ float tab[kSbrRunMax * 2 * kSbrRunMaxChannels];
+    constexpr int kHalf = kSbrRunMax / 2, kTab = 2 * kSbrRunMaxChannels;
+    __shared__ float tab[kSbrRunMax * kTab];
+    using SlotPtr = const void* const PG_CONSTANT*;
+    const void PG_CONSTANT* const ka = (const void PG_CONSTANT*)__builtin_amdgcn_kernarg_segment_ptr();      // a readable address for a load whose result is not used
     const unsigned tid = threadIdx.x;
-    const T* x = static_cast<const T*>(resolve_rt(p.x, p.x_slot));
-    const unsigned n = p.n, inner = p.inner, C = p.channels;
+    const unsigned n = p.n, inner = p.inner, C = p.channels, slots = p.slots, stores = p.stores;
     const int np = p.n_phase;
-    const unsigned nfull = n / NV, left = n - nfull * NV;
-    const unsigned v0 = blockIdx.x * (unsigned)(kBlock * U) + tid;
+    const T* x = static_cast<const T*>(resolve_rt(p.x, p.x_slot));
+    // lane t < 2 C: the scale (t < C) or bias of channel t % C, eight kernels' pointers at a time, then their values, without a wait between them
+    const bool is_b = tid >= C && tid < 2 * C;
+    const unsigned c = tid < C ? tid : is_b ? tid - C : 0u;
+    unsigned raw[kSbrRunMax];
+    auto ask = [&](auto half) {
+        constexpr int at = decltype(half)::value * kHalf;
+        const void* sp[kHalf];
+        const void* bp[kHalf];
+#pragma unroll
+        for (int i = 0; i < kHalf; i++) { sp[i] = p.ph[at + i].s; bp[i] = p.ph[at + i].b; }
+        static_assert(kHalf == 8, "the batches name every kernel");
+        asm volatile("" : "+s"(sp[0]), "+s"(sp[1]), "+s"(sp[2]), "+s"(sp[3]), "+s"(sp[4]), "+s"(sp[5]), "+s"(sp[6]), "+s"(sp[7]),
+                          "+s"(bp[0]), "+s"(bp[1]), "+s"(bp[2]), "+s"(bp[3]), "+s"(bp[4]), "+s"(bp[5]), "+s"(bp[6]), "+s"(bp[7]));
+        if (slots) {
+            auto through = [&](const void* (&q)[kHalf], unsigned mask) {
+                const void* t[kHalf];
+#pragma unroll
+                for (int i = 0; i < kHalf; i++) t[i] = *(((mask >> i) & 1u) ? (SlotPtr)(uintptr_t)q[i] : (SlotPtr)ka);
+                asm volatile("" : "+s"(t[0]), "+s"(t[1]), "+s"(t[2]), "+s"(t[3]), "+s"(t[4]), "+s"(t[5]), "+s"(t[6]), "+s"(t[7]));
+#pragma unroll
+                for (int i = 0; i < kHalf; i++) if ((mask >> i) & 1u) q[i] = t[i];
+            };
+            through(sp, slots >> at);
+            through(bp, slots >> (16 + at));
+        }
+#pragma unroll
+        for (int i = 0; i < kHalf; i++) raw[at + i] = load_raw_global(static_cast<const T*>(is_b ? bp[i] : sp[i]) + c);
+    };
+    ask(std::integral_constant<int, 0>{});
+    if (np > kHalf) ask(std::integral_constant<int, 1>{});
+    const unsigned nfull = n / NV, left = n - nfull * NV;         // nfull >= 1: inner is a vector at least
+    // a wave's vectors are one stretch of U * 64
+    const unsigned wave0 = blockIdx.x * (unsigned)(kBlock * U) + (unsigned)__builtin_amdgcn_readfirstlane(tid >> 6) * (unsigned)(64 * U), v0 = wave0 + (tid & 63);
     unsigned w[U][4];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-        const unsigned v = v0 + (unsigned)u * kBlock;
-        w[u][0] = w[u][1] = w[u][2] = w[u][3] = 0u;
-        if (v < nfull) {
-            const v4u t = *(const v4u_any PG_GLOBAL*)(uintptr_t)(x + (size_t)v * NV);
-            w[u][0] = t.x; w[u][1] = t.y; w[u][2] = t.z; w[u][3] = t.w;
-        } else if (!WHOLE && v == nfull) {
-#pragma unroll
-            for (int e = 0; e < NV - 1; e++)
-                if ((unsigned)e < left) {
-                    const unsigned r = load_raw_global(x + (size_t)nfull * NV + e);
-                    if constexpr (sizeof(T) == 4) w[u][e] = r;
-                    else w[u][e / 2] |= r << (16 * (e & 1));
-                }
-        }
+        const unsigned v = v0 + (unsigned)u * 64;
+        const v4u t = *(const v4u_any PG_GLOBAL*)(uintptr_t)(x + (size_t)(v < nfull ? v : nfull - 1) * NV);
+        w[u][0] = t.x; w[u][1] = t.y; w[u][2] = t.z; w[u][3] = t.w;
     }
-    {
-        const bool is_b = tid >= C;
-        const unsigned c = is_b ? tid - C : tid;
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < 2 * C) {                   // the values are in before x is: loads come back in order
 #pragma unroll
-        for (int i = 0; i < kSbrRunMax; i++) {
-            if (i >= np) break;
-            const T* s = static_cast<const T*>(resolve_rt(p.ph[i].s, p.ph[i].ind & 2u));
-            const T* b = static_cast<const T*>(resolve_rt(p.ph[i].b, p.ph[i].ind & 4u));
-            if (tid < 2 * C) tab[i * (2 * kSbrRunMaxChannels) + tid] = from_raw<T>(load_raw_global((is_b ? b : s) + c));
-        }
+        for (int i = 0; i < kHalf; i++) tab[i * kTab + tid] = from_raw<T>(raw[i]);
+        if (np > kHalf)
+#pragma unroll
+            for (int i = kHalf; i < kSbrRunMax; i++) tab[i * kTab + tid] = from_raw<T>(raw[i]);
     }
-    unsigned c0[U], c1[U], k0[U];       // channel of a vector's first elements, of the others, and how many are the first
+    lds_barrier();
+    if constexpr (!WHOLE) {
+        if (left && wave0 <= nfull && nfull < wave0 + 64 * U) {          // the tensor's last, partial vector
 #pragma unroll
-    for (int u = 0; u < U; u++) {
-        const unsigned i0 = (v0 + (unsigned)u * kBlock) * NV, q = i0 / inner;
-        c0[u] = q % C;
-        if constexpr (!WHOLE) {
-            k0[u] = inner - (i0 - q * inner);
-            c1[u] = c0[u] + 1 == C ? 0u : c0[u] + 1;
-        }
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int i = 0; i < np; i++) {
-        const float* t = tab + i * (2 * kSbrRunMaxChannels);
-        const bool store = (p.ph[i].ind & kEpiStore) != 0;
-        T* o = static_cast<T*>(p.ph[i].out);
+            for (int u = 0; u < U; u++)
+                if (v0 + (unsigned)u * 64 == nfull) {
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            float f[NV];
-            V::unpack(w[u], f);
-            const float s0 = t[c0[u]], b0 = t[C + c0[u]];
-            if constexpr (WHOLE) {
-#pragma unroll
-                for (int e = 0; e < NV; e++) f[e] = sbr_apply(f[e], s0, b0);
-            } else {
-                const float s1 = t[c1[u]], b1 = t[C + c1[u]];
-#pragma unroll
-                for (int e = 0; e < NV; e++) {
-                    const bool first = (unsigned)e < k0[u];
-                    f[e] = sbr_apply(f[e], first ? s0 : s1, first ? b0 : b1);
-                }
-            }
-            V::pack(f, w[u]);
-        }
-        if (store) {
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const unsigned v = v0 + (unsigned)u * kBlock;
-                if (v < nfull) {
-                    store_vec_global(o + (size_t)v * NV, w[u]);
-                } else if (!WHOLE && v == nfull) {
+                    for (int k = 0; k < 4; k++) w[u][k] = 0u;
 #pragma unroll
                     for (int e = 0; e < NV - 1; e++)
                         if ((unsigned)e < left) {
-                            if constexpr (sizeof(T) == 4) *(unsigned PG_GLOBAL*)(uintptr_t)(o + (size_t)nfull * NV + e) = w[u][e];
-                            else *(unsigned short PG_GLOBAL*)(uintptr_t)(o + (size_t)nfull * NV + e) = (unsigned short)(w[u][e / 2] >> (16 * (e & 1)));
+                            const unsigned r = load_raw_global(x + (size_t)nfull * NV + e);
+                            if constexpr (sizeof(T) == 4) w[u][e] = r;
+                            else w[u][e / 2] |= r << (16 * (e & 1));
                         }
+                }
+        }
+    }
+    // the stretch's first and last element
+    const unsigned ea = wave0 * NV < n ? wave0 * NV : n - 1, ez = n - ea > (unsigned)(64 * U * NV) ? ea + (unsigned)(64 * U * NV) - 1 : n - 1;
+    const unsigned qa = ea / inner, ca = qa % C, edge = (qa + 1) * inner;             // its first channel, and where that ends (n is a multiple of inner)
+    // the kernels, one after the other; `apply` has the scales and biases of each
+    auto play = [&](auto&& apply) {
+#pragma unroll 1
+        for (int i = 0; i < np; i++) {
+            apply(tab + i * kTab);
+            if ((stores >> i) & 1u) {
+                T* const o = static_cast<T*>(p.ph[i].out);
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const unsigned v = v0 + (unsigned)u * 64;
+                    if (v < nfull) {
+                        store_vec_global(o + (size_t)v0 * NV + u * 64 * NV, w[u]);
+                    } else if (!WHOLE && v == nfull) {
+#pragma unroll
+                        for (int e = 0; e < NV - 1; e++)
+                            if ((unsigned)e < left) {
+                                if constexpr (sizeof(T) == 4) *(unsigned PG_GLOBAL*)(uintptr_t)(o + (size_t)nfull * NV + e) = w[u][e];
+                                else *(unsigned short PG_GLOBAL*)(uintptr_t)(o + (size_t)nfull * NV + e) = (unsigned short)(w[u][e / 2] >> (16 * (e & 1)));
+                            }
+                    }
                 }
             }
         }
+    };
+    if (ez < edge) {                     // one channel
+        play([&](const float* t) {
+            const float s0 = t[ca], b0 = t[C + ca];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                float f[NV];
+                V::unpack(w[u], f);
+#pragma unroll
+                for (int e = 0; e < NV; e++) f[e] = sbr_apply(f[e], s0, b0);
+                V::pack(f, w[u]);
+            }
+        });
+    } else if (ez - edge < inner) {      // two
+        const unsigned cz = ca + 1 == C ? 0u : ca + 1;
+        int first[U];                    // elements of a vector in the first one: from NV on all of them, up to 0 none
+#pragma unroll
+        for (int u = 0; u < U; u++) first[u] = (int)(edge - (v0 + (unsigned)u * 64) * NV);
+        play([&](const float* t) {
+            const float s0 = t[ca], b0 = t[C + ca], s1 = t[cz], b1 = t[C + cz];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                float f[NV];
+                V::unpack(w[u], f);
+#pragma unroll
+                for (int e = 0; e < NV; e++) {
+                    const bool here = first[u] > (WHOLE ? 0 : e);
+                    f[e] = sbr_apply(f[e], here ? s0 : s1, here ? b0 : b1);
+                }
+                V::pack(f, w[u]);
+            }
+        });
+    } else {
+        unsigned c0[U], c1[U], k0[U];       // channel of a vector's first elements, of the others, and how many are the first
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const unsigned i0 = (v0 + (unsigned)u * 64) * NV, q = i0 / inner;
+            c0[u] = q % C;
+            if constexpr (!WHOLE) {
+                k0[u] = inner - (i0 - q * inner);
+                c1[u] = c0[u] + 1 == C ? 0u : c0[u] + 1;
+            }
+        }
+        play([&](const float* t) {
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                float f[NV];
+                V::unpack(w[u], f);
+                const float s0 = t[c0[u]], b0 = t[C + c0[u]];
+                if constexpr (WHOLE) {
+#pragma unroll
+                    for (int e = 0; e < NV; e++) f[e] = sbr_apply(f[e], s0, b0);
+                } else {
+                    const float s1 = t[c1[u]], b1 = t[C + c1[u]];
+#pragma unroll
+                    for (int e = 0; e < NV; e++) {
+                        const bool here = (unsigned)e < k0[u];
+                        f[e] = sbr_apply(f[e], here ? s0 : s1, here ? b0 : b1);
+                    }
+                }
+                V::pack(f, w[u]);
+            }
+        });
     }
 }
 
@@ -1035,7 +1115,7 @@ void plan_carry_run(long long n, Launch* out, unsigned* unit) {
     *unit = kBlock * (narrow ? 2u : 8u);
 }
 
-// One vector per lane until that makes four workgroups per CU, eight per lane from there on.
+// One vector per lane until that makes four workgroups per CU, two per lane from there on.
 constexpr long long kSbrRunSmall = 4ll * 256 * kBlock;
 bool sbr_run_candidate(int dtype, long long n, long long inner, long long channels) {
     const int nv = dtype == kF32 ? 4 : 8;
@@ -1050,8 +1130,8 @@ static void plan_sbr_run_t(long long n, long long inner, Launch* out) {
         out->fn = whole ? PG_FN(k_sbr_run<T, true, 1>) : PG_FN(k_sbr_run<T, false, 1>);
         out->grid = dim3(blocks_for(nvec, kBlock));
     } else {
-        out->fn = whole ? PG_FN(k_sbr_run<T, true, 8>) : PG_FN(k_sbr_run<T, false, 8>);
-        out->grid = dim3(blocks_for(nvec, kBlock * 8));
+        out->fn = whole ? PG_FN(k_sbr_run<T, true, 2>) : PG_FN(k_sbr_run<T, false, 2>);
+        out->grid = dim3(blocks_for(nvec, kBlock * 2));
     }
 }
 bool plan_sbr_run(int dtype, long long n, long long inner, Launch* out) {

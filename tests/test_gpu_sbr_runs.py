@@ -49,3 +49,29 @@ def test_runs_of_scale_bias_relu(dtype, batch, channels, inner, kernels, nodes):
         h.scrub()
         stepwise_check(h, x_np, x_dev)
     h.close()
+
+
+@pytest.mark.parametrize("kernels", [8, 9, 16])
+@pytest.mark.parametrize("dtype,batch,channels,inner", [("f32", 17, 128, 512), ("f32", 17, 64, 1027), ("f32", 1700, 128, 5), ("f32", 3, 7, 256), ("f32", 4, 8, 260), ("f32", 9, 3, 509),
+                                                        ("bf16", 33, 64, 1024), ("bf16", 17, 125, 1001), ("bf16", 5, 3, 516), ("bf16", 40, 11, 9)])
+def test_stretches_of_one_two_and_many_channels(dtype, batch, channels, inner, kernels):
+    """A wave's stretch that ends where a channel does, just before and behind, or holds many channels, one and two vectors per lane, up to the
+    longest run; scales and biases from weights and from externals."""
+    n = batch * channels * inner
+    ks = [KernelSpec("scale_bias_relu", dtype, k % 2, (Ref(INT, (k - 1) % 2) if k else Ref(EXT, 0), Ref(EXT, 1) if k % 3 == 0 else Ref(WEIGHT, 0),
+                                                       Ref(EXT, 2) if k % 4 == 1 else Ref(WEIGHT, 1)), n, inner=inner, channels=channels) for k in range(kernels)]
+    spec = ChainSpec(f"stretch_{dtype}_{batch}x{channels}x{inner}_{kernels}", ks,
+                     [TensorSpec(dtype, n), TensorSpec(dtype, channels, ("normal", 1.0, 0.1)), TensorSpec(dtype, channels, ("normal", 0.0, 0.1))],
+                     [TensorSpec(dtype, n), TensorSpec(dtype, n)],
+                     [TensorSpec(dtype, channels, ("normal", 1.0, 0.1)), TensorSpec(dtype, channels, ("normal", 0.0, 0.1))], [0, 1], 8600)
+    h = Harness(spec)
+    assert h.chain.graph_dispatches() == (1, kernels)
+    for t in range(2):
+        _, x_dev = h.inputs(t)
+        h.scrub()
+        want = h.run("eager", x_dev)
+        for mode in ("copy", "indirect"):
+            h.scrub()
+            got = h.run(mode, x_dev)
+            assert all(same_bits(a, b) for a, b in zip(want, got)), (mode, t)
+    h.close()
