@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kBlock) void k_scale_bias_relu(SbrArgs p) {
 // WHOLE: inner is a multiple of the 16-byte vector.  Otherwise a vector may straddle two channels (inner >= NV, so
 // never three) and the last vector of the tensor may be a partial one.  Vectors are fetched at any element boundary.
 // us per iteration, values asked for one by one / together / together and by stretches: 40 fp32 kernels over [32, 64, 112, 112] in four segments
-// 192 / 148 / 146 (5.6 TB/s of one read and one write per segment), 20 over [32, 64, 111, 111] in two 122 / 95 / 81, 24 over
+// 192 / 148 / 146 (6.3 TB/s: one read and one write per segment, two in the last), 20 over [32, 64, 111, 111] in two 122 / 95 / 81, 24 over
 // [16, 33, 77, 101] in three 44 / 33 / 27.  Two vectors per lane: with four 147, 83, 27, with eight 150, 87, 29.  Non-temporal loads of x lose, 158:
 // the memory-side cache holds much of what the segment before wrote; non-temporal stores change nothing.
 template <typename T, bool WHOLE, int U>
