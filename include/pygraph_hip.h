@@ -153,7 +153,11 @@ pg_status pg_capture(pg_chain *chain, void *hip_stream);
 
 /* One iteration, kernel by kernel from the host with the caller's pointers (the no-graph
  * baseline, Sec. 2.1).  ext_dev_ptrs [host]: n_ext device pointers [dev], each aligned to its
- * element size; 16-byte aligned pointers take the vector path. */
+ * element size; 16-byte aligned pointers take the vector path.  An external is read-only to the chain;
+ * one that lies in the chain's own internal buffers is read there when the kernel runs (in copy form: when
+ * its segment is refreshed), and replays that need a version which a merged dispatch would not have
+ * stored then issue every dispatch from the host with all versions stored.  No kernel of the same merged
+ * dispatch (pg_set_dispatch_merge) may write what it reads that way. */
 pg_status pg_eager(pg_chain *chain, const void *const *ext_dev_ptrs, void *hip_stream);
 
 /* Kernels [k_begin, k_end) of the chain, launched eagerly as in pg_eager; internal buffers keep

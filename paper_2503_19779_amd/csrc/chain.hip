@@ -103,6 +103,7 @@ struct MergeGroup {
     static constexpr int kMax = std::max({pgk::kMergeMaxPhases, pgk::kEpiMaxPhases + 2, pgk::kSbrRunMax});
     unsigned char src0[kMax] = {}, src1[kMax] = {}, dst[kMax] = {};
     bool store[kMax] = {};
+    bool store_every[kMax] = {};     // ... where every version that leaves the run is stored (versions_seen_outside)
     long long cover[kMax] = {};      // (carry) elements of the output that are overwritten before anything reads them from memory
     pgk::Launch launch;
 };
@@ -127,6 +128,7 @@ struct Segment {
     hipGraph_t g_copy = nullptr, g_ind = nullptr;
     hipGraphExec_t x_copy = nullptr, x_ind = nullptr;
     std::vector<Dispatch> d_copy, d_ind;     // instead of those graphs, where the segment is launched (kLaunchedMost)
+    std::vector<Dispatch> e_copy, e_ind;     // with every version stored (versions_seen_outside); laid out when a call first needs them
     // host-updated variant: explicit kernel nodes in chain order, two executable instances
     hipGraph_t g_upd = nullptr;
     hipGraphExec_t x_upd[2] = {nullptr, nullptr};
@@ -135,6 +137,12 @@ struct Segment {
     // [0] PG_TABLE_GRAPH_MEMCPY, [1] PG_TABLE_HOST
     hipGraph_t g_alt[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
     hipGraphExec_t x_alt[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+};
+
+// Internal buffer `buf` behind kernel `from` and up to kernel `until`: memory does not hold what eager launches would leave there, either
+// because a run did not store it (drop_dead_stores) or because the kernels of the run write it in no order (k_carry_run).
+struct Unstored {
+    int buf, from, until;
 };
 
 // A table mechanism whose host-side buffer is read by the GPU when the graph runs, not when the call
@@ -163,6 +171,7 @@ struct pg_chain {
     std::vector<KernelRec> rec;
     std::vector<Segment> seg;
     std::vector<CopyList> copy_lists;   // [0] = all externals; then one per segment that has any
+    std::vector<Unstored> unstored;
     std::vector<std::pair<int, int>> eager_fix;   // (kernel, operand) pairs that take a caller pointer
     bool captured = false;
     int device = -1;                    // the device pg_capture ran on (graphs, events and pinned memory belong to it)
@@ -193,6 +202,7 @@ struct Layout {
     size_t table_off = 0, carry_off = 0;
     std::vector<CopyList> lists;
     std::vector<Segment> seg;
+    std::vector<Unstored> unstored;
     size_t total = 0;
 };
 
@@ -589,7 +599,7 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
 // The last version of every buffer is stored.  us per iteration, before and after: 256 refreshed tensors of up to 16 MB (338 MB of
 // stores -> 32) 420 -> 386; 40 scale + bias + ReLU kernels on 103 MB in four segments 226 -> 201; decode chains of 120 sub-blocks, 16 rows of 2048
 // columns 716 -> 700, 32 of 1024 544 -> 523, 3 of 520 384 -> 375, 128 of 2048 1271 -> 1259.
-void drop_dead_stores(const pg_kernel_desc* k, int nk, int n_int, std::vector<Segment>& seg) {
+void drop_dead_stores(const pg_kernel_desc* k, int nk, int n_int, std::vector<Segment>& seg, std::vector<Unstored>& unstored) {
     struct Use { int kernel; int operand; long long n; };      // operand -1: writes elements [0, n); else reads them
     std::vector<std::vector<Use>> uses(n_int);
     auto written = [](const pg_kernel_desc& d) { return d.op == PG_RMSNORM ? (long long)d.rows * d.cols : d.op == PG_GEMV ? (long long)d.rows * d.n : (long long)d.n; };
@@ -611,18 +621,25 @@ void drop_dead_stores(const pg_kernel_desc* k, int nk, int n_int, std::vector<Se
         for (size_t gi = 0; gi < sg.groups.size(); gi++) {
             MergeGroup& g = sg.groups[gi];
             const MergeGroup* next = gi + 1 < sg.groups.size() ? &sg.groups[gi + 1] : nullptr;
+            std::copy(std::begin(g.store), std::end(g.store), std::begin(g.store_every));
             for (int i = g.k0; i < g.k1 && g.k1 - g.k0 >= 2; i++) {
                 const auto& u = uses[k[i].out.index];
                 auto at = std::partition_point(u.begin(), u.end(), [&](const Use& x) { return x.kernel < i || (x.kernel == i && x.operand >= 0); });
                 const long long len = written(k[i]);
                 long long cover = 0;
+                int until = i;
                 for (++at; at != u.end() && cover < len; ++at) {         // (the first is kernel i's own write)
-                    if (at->operand < 0) { cover = std::max(cover, at->n); continue; }
+                    if (at->operand < 0) {
+                        if (at->n > cover) { cover = at->n; until = at->kernel; }
+                        continue;
+                    }
                     const bool aside = next && next->carry && next->carry_aside && at->kernel == next->k0 && at->operand == 1 && i == g.k1 - 1;
                     if (at->n > cover && at->kernel >= g.k1 && !aside) break;
                 }
                 if (cover >= len) g.store[i - g.k0] = false;
                 g.cover[i - g.k0] = std::min(cover, len);
+                if (g.carry) unstored.push_back({k[i].out.index, g.k0 - 1, std::max(until, g.k1 - 1)});
+                else if (cover >= len) unstored.push_back({k[i].out.index, i, until});
             }
         }
 }
@@ -699,7 +716,7 @@ void make_layout(const pg_kernel_desc* k, int nk, const pg_tensor_desc* ext, int
                 off = align_up(off + (size_t)ints[g.rename].numel * elem_bytes(ints[g.rename].dtype));
             }
     }
-    drop_dead_stores(k, nk, n_int, L.seg);
+    drop_dead_stores(k, nk, n_int, L.seg, L.unstored);
     L.carry_off = off;
     for (auto& sg : L.seg)
         for (const auto& g : sg.groups)
@@ -976,8 +993,7 @@ void destroy_graphs(pg_chain* c) {
         if (s.x_copy) (void)hipGraphExecDestroy(s.x_copy);
         if (s.g_copy) (void)hipGraphDestroy(s.g_copy);
         s.x_copy = s.x_ind = nullptr;
-        s.d_copy.clear();
-        s.d_ind.clear();
+        for (auto* d : {&s.d_copy, &s.d_ind, &s.e_copy, &s.e_ind}) d->clear();
         s.g_copy = s.g_ind = nullptr;
     }
     c->captured = false;
@@ -1052,8 +1068,9 @@ pg_status run_update(pg_chain* c, const void* const* ext, hipStream_t s) {
 // What a captured graph's kernels read their external operands from.
 enum GraphKind { kGraphCopy = 0, kGraphTable = 1, kGraphTableMemcpyNode = 2, kGraphHostTable = 3 };
 
-// What one replay of a segment dispatches, in order.
-std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int inst) {
+// What one replay of a segment dispatches, in order.  every: with every version stored that leaves a run, and the kernels of runs with a
+// carry, which have no order among them, on their own.
+std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int inst, bool every = false) {
     std::vector<Dispatch> out;
     auto emit = [&](pgk::Launch& l, const void* args) {
         const unsigned char* at = static_cast<const unsigned char*>(args);
@@ -1076,7 +1093,8 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
     };
     int n_carry = 0;                      // runs with a carry so far: two places for what they set aside, in turn
     for (auto& grp : sg.groups) {
-        if (!c->merge || grp.k1 - grp.k0 < 2) {
+        const bool* const store = every ? grp.store_every : grp.store;
+        if (!c->merge || grp.k1 - grp.k0 < 2 || (every && grp.carry)) {
             for (int i = grp.k0; i < grp.k1; i++) {
                 KernelRec& r = c->rec[i];
                 const ArgBlock a = versioned(i, nullptr);
@@ -1133,7 +1151,7 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
                 ph.s = a.ptr[2];
                 ph.b = a.ptr[3];
                 const unsigned slots = kind == kGraphCopy ? 0u : (unsigned)r.ind_mask;
-                m.stores |= (unsigned)grp.store[m.n_phase] << m.n_phase;
+                m.stores |= (unsigned)store[m.n_phase] << m.n_phase;
                 m.slots |= ((slots >> 1) & 1u) << m.n_phase | ((slots >> 2) & 1u) << (16 + m.n_phase);
             }
             for (int q = m.n_phase; q < pgk::kSbrRunMax; q++) {
@@ -1154,14 +1172,14 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
             e.g = ha.gemv;
             e.g.row_groups = (int)grp.launch.gemm_row_groups;
             e.head = (kind == kGraphCopy ? 0u : (unsigned)hr.ind_mask) | ((unsigned)grp.dst[hk - grp.k0] << 8) |
-                     (grp.store[hk - grp.k0] ? pgk::kEpiHeadStore : 0u);
+                     (store[hk - grp.k0] ? pgk::kEpiHeadStore : 0u);
             if (grp.pro) {
                 KernelRec& pr = c->rec[grp.k0];
                 const ArgBlock pa = versioned(grp.k0, &grp);
                 e.x = pa.ptr[1];
                 e.gain = pa.ptr[2];
                 e.eps = c->k[grp.k0].eps;
-                e.head |= grp.store[0] ? pgk::kEpiStoreH : 0u;
+                e.head |= store[0] ? pgk::kEpiStoreH : 0u;
                 if (kind != kGraphCopy) e.head |= ((pr.ind_mask & 1) ? pgk::kEpiXSlot : 0u) | ((pr.ind_mask & 2) ? pgk::kEpiGainSlot : 0u);
                 // e.g.h is the RMSNorm's output in its current copy: where workgroup 0 stores the normalised rows
             }
@@ -1176,7 +1194,7 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
                 ph.in1 = r.n_in > 1 ? a.ptr[2] : nullptr;
                 ph.m = (d.op == PG_ADD || d.op == PG_MUL) ? (unsigned)(d.m ? d.m : d.n) : (unsigned)grp.n;
                 ph.meta = (unsigned)d.op | ((unsigned)grp.src0[t] << 8) | ((unsigned)grp.src1[t] << 16) | ((unsigned)grp.dst[t] << 24);
-                ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (grp.store[t] ? pgk::kEpiStore : 0u);
+                ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (store[t] ? pgk::kEpiStore : 0u);
             }
             for (int q = e.n_epi; q < pgk::kEpiMaxPhases; q++) e.ph[q].meta = (unsigned)PG_GELU;   // operands "from slot 0": fetches nothing, never played
             seal_epilogue(e);
@@ -1214,7 +1232,7 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
                 m.slots |= (r.n_in > 1 ? (slots >> 1) & 1u : first) << t;
                 if (r.n_in > 1 && d.m) m.m[t] = (unsigned)d.m;
                 if (m.m[t] != m.n) m.slots |= pgk::kChainPeriods;
-                m.ops |= ((unsigned)d.op | (grp.store[t] ? 8u : 0u)) << (4 * t);
+                m.ops |= ((unsigned)d.op | (store[t] ? 8u : 0u)) << (4 * t);
             }
             emit(grp.launch, &m);
             continue;
@@ -1234,7 +1252,7 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
             ph.m = (d.op == PG_ADD || d.op == PG_MUL) ? (unsigned)(d.m ? d.m : d.n) : 0u;
             ph.eps = d.op == PG_RMSNORM ? d.eps : 0.f;
             ph.meta = (unsigned)d.op | ((unsigned)grp.src0[m.n_phase] << 8) | ((unsigned)grp.src1[m.n_phase] << 16) | ((unsigned)grp.dst[m.n_phase] << 24);
-            ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (grp.store[m.n_phase] ? pgk::kEpiStore : 0u);
+            ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (store[m.n_phase] ? pgk::kEpiStore : 0u);
         }
         for (int q = m.n_phase; q < pgk::kMergeMaxPhases; q++) m.ph[q].meta = (unsigned)PG_GELU;   // operands "from slot 0": fetches nothing, never played
         emit(grp.launch, &m);
@@ -1320,6 +1338,37 @@ pg_status ind_begin(pg_chain* c, const void* const* ext, hipStream_t s, IndCtx& 
     return PG_OK;
 }
 
+// Does the call read, through an external that lies in the chain's own internal buffers, a version that merged dispatches keep out of
+// memory?  In table form a kernel reads it when it runs, in copy form the segment's refresh does.  (pg_replay_copy refreshes in front of
+// the first kernel, where memory holds the last version of everything.)
+bool versions_seen_outside(const pg_chain* c, const void* const* ext) {
+    const char* const lo = c->ws + c->int_off.front();
+    const char* const hi = c->ws + c->table_off;          // the internal buffers lie side by side, the table behind them
+    auto bytes = [](const pg_tensor_desc& t) { return (size_t)t.numel * elem_bytes(t.dtype); };
+    for (size_t e = 0; e < c->ext.size(); e++) {
+        const char* const p = static_cast<const char*>(ext[e]);
+        if (p >= hi || p + bytes(c->ext[e]) <= lo) continue;
+        for (int i = 0; i < (int)c->rec.size(); i++) {
+            const auto& of = c->rec[i].ext_of;
+            if (std::find(std::begin(of), std::end(of), (int)e) == std::end(of)) continue;
+            const int copied = c->seg[c->k[i].segment].k0;
+            for (const Unstored& u : c->unstored) {
+                const char* const b = c->ws + c->int_off[u.buf];
+                if (p < b + bytes(c->ints[u.buf]) && p + bytes(c->ext[e]) > b && ((u.from < i && i <= u.until) || (u.from < copied && copied <= u.until))) return true;
+            }
+        }
+    }
+    return false;
+}
+
+// The segment's kernels with every version stored; table: operands by the device's table, whatever mechanism is selected (write_table)
+pg_status run_every_version(pg_chain* c, Segment& sg, bool table, hipStream_t s) {
+    table = table && sg.has_ext;
+    auto& d = table ? sg.e_ind : sg.e_copy;
+    if (d.empty()) d = segment_dispatches(c, sg, table ? kGraphTable : kGraphCopy, 0, true);
+    return play(d, s);
+}
+
 // The segment's kernels: of the copy graph, and of the indirect one with whichever table mechanism is selected
 pg_status run_copy_form(Segment& sg, hipStream_t s) {
     if (!sg.d_copy.empty()) return play(sg.d_copy, s);
@@ -1344,16 +1393,20 @@ pg_status ind_end(pg_chain* c, hipStream_t s, IndCtx& x) {
     return PG_OK;
 }
 
-pg_status run_segment(pg_chain* c, int si, int mode, const void* const* ext, hipStream_t s, IndCtx* ind) {
+pg_status run_segment(pg_chain* c, int si, int mode, const void* const* ext, hipStream_t s, IndCtx* ind, bool every = false) {
     Segment& sg = c->seg[si];
     switch (mode) {
     case PG_EAGER: return run_eager_range(c, sg.k0, sg.k1, ext, s);
     case PG_GRAPH_COPY: {
         if (sg.copy_list >= 0) { pg_status st = run_copy_list(c, sg.copy_list, ext, s); if (st) return st; }
-        return run_copy_form(sg, s);
+        return every ? run_every_version(c, sg, false, s) : run_copy_form(sg, s);
     }
     case PG_GRAPH_INDIRECT: {
         if (!sg.has_ext) return fail(PG_EUNAVAIL, "segment %d reads no external operand: indirect mode does not exist for it", si);
+        if (every) {
+            pg_status st = write_table(c, ext, s);
+            return st ? st : run_every_version(c, sg, true, s);
+        }
         pg_status st = ind_begin(c, ext, s, *ind);
         if (st) return st;
         return run_ind_form(c, sg, *ind, s);
@@ -1403,6 +1456,7 @@ pg_status build_chain(const pg_kernel_desc* kernels, int32_t nk, const pg_tensor
     c->carry_off = L.carry_off;
     c->copy_lists = std::move(L.lists);
     c->seg = std::move(L.seg);
+    c->unstored = std::move(L.unstored);
     st = make_records(c);
     if (st) { delete c; return st; }
     *out = c;
@@ -1610,6 +1664,12 @@ pg_status pg_replay_indirect(pg_chain* c, const void* const* ext, void* hip_stre
     pg_status st = check_call(c, ext, hip_stream, true);
     if (st) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    if (versions_seen_outside(c, ext)) {
+        if ((st = write_table(c, ext, s))) return st;
+        for (auto& sg : c->seg)
+            if ((st = run_every_version(c, sg, true, s))) return st;
+        return PG_OK;
+    }
     IndCtx x;
     if ((st = ind_begin(c, ext, s, x))) return st;
     for (auto& sg : c->seg)
@@ -1634,8 +1694,9 @@ pg_status pg_run_selected(pg_chain* c, const uint8_t* mode, const void* const* e
     if (st) return st;
     if (!mode) return fail(PG_EINVAL, "null mode array");
     IndCtx x;
+    const bool every = versions_seen_outside(c, ext);
     for (int si = 0; si < (int)c->seg.size(); si++)
-        if ((st = run_segment(c, si, mode[si], ext, static_cast<hipStream_t>(hip_stream), &x))) return st;
+        if ((st = run_segment(c, si, mode[si], ext, static_cast<hipStream_t>(hip_stream), &x, every))) return st;
     return ind_end(c, static_cast<hipStream_t>(hip_stream), x);
 }
 
