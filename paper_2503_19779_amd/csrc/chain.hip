@@ -777,17 +777,18 @@ void seal_epilogue(pgk::GemvEpiArgs& e) {
     if (plain) e.head |= pgk::kEpiPlain;
 }
 
-// The matrices that one iteration's GEMVs read, each once.
+// The matrices that one iteration's GEMVs read, each once, wherever they are.
 long long chain_weight_bytes(const pg_chain* c) {
-    long long bytes = 0;
-    std::vector<char> seen(c->w.size(), 0);
+    std::vector<long long> w(c->w.size(), 0), ext(c->ext.size(), 0), ints(c->ints.size(), 0);
     for (const auto& d : c->k) {
         if (d.op != PG_GEMV) continue;
         const pg_ref& r = d.in[0];
-        if (r.kind == PG_REF_WEIGHT && seen[r.index]) continue;
-        if (r.kind == PG_REF_WEIGHT) seen[r.index] = 1;
-        bytes += d.n * d.cols * (long long)elem_bytes(d.dtype);
+        long long& b = r.kind == PG_REF_WEIGHT ? w[r.index] : r.kind == PG_REF_EXT ? ext[r.index] : ints[r.index];
+        b = std::max(b, d.n * d.cols * (long long)elem_bytes(d.dtype));
     }
+    long long bytes = 0;
+    for (const auto* v : {&w, &ext, &ints})
+        for (long long b : *v) bytes += b;
     return bytes;
 }
 
