@@ -716,7 +716,7 @@ void make_layout(const pg_kernel_desc* k, int nk, const pg_tensor_desc* ext, int
                 off = align_up(off + (size_t)ints[g.rename].numel * elem_bytes(ints[g.rename].dtype));
             }
     }
-    drop_dead_stores(k, nk, n_int, L.seg, L.unstored);
+    if (ws) drop_dead_stores(k, nk, n_int, L.seg, L.unstored);          // takes no room, and a size query's sizes have not been validated
     L.carry_off = off;
     for (auto& sg : L.seg)
         for (const auto& g : sg.groups)
