@@ -292,6 +292,9 @@ pg_status pg_set_copy_refresh(pg_chain *chain, int32_t how /* pg_copy_refresh */
  * not stored; the last version of every internal buffer is.  Eager launches are never merged.  `on` = 0
  * captures one node per kernel.  Takes effect at the next pg_capture. */
 pg_status pg_set_dispatch_merge(pg_chain *chain, int32_t on);
+/* Up to how many dispatches a segment is replayed by launching them instead of as a graph (pg_capture): 6
+ * unless set, 0 = always a graph.  The results are the same.  Takes effect at the next pg_capture. */
+pg_status pg_set_launched_dispatches(pg_chain *chain, int32_t most);
 /* Kernel dispatches that the graphs of one replay, or the launches in place of a graph, come to with merging on (*merged_out) and off
  * (*unmerged_out = the number of kernels).  Either output may be NULL.  Host only. */
 pg_status pg_chain_graph_dispatches(const pg_chain *chain, int32_t *merged_out, int32_t *unmerged_out);

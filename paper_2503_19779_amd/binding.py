@@ -88,6 +88,7 @@ def lib():
         L.pg_set_table_refresh.argtypes = [vp, i32]
         L.pg_set_copy_refresh.argtypes = [vp, i32]
         L.pg_set_dispatch_merge.argtypes = [vp, i32]
+        L.pg_set_launched_dispatches.argtypes = [vp, i32]
         L.pg_chain_graph_dispatches.argtypes = [vp, C.POINTER(i32), C.POINTER(i32)]
         L.pg_chain_destroy.argtypes = [vp]
         L.pg_chain_destroy.restype = None
@@ -349,6 +350,11 @@ class Chain:
     def set_dispatch_merge(self, on: bool):
         """Takes effect at the next capture()."""
         _check(lib().pg_set_dispatch_merge(self._h, 1 if on else 0))
+
+    def set_launched_dispatches(self, most: int):
+        """Segments of up to `most` dispatches are launched, longer ones replayed as graphs (6 unless set; 0: always graphs).
+        Takes effect at the next capture()."""
+        _check(lib().pg_set_launched_dispatches(self._h, most))
 
     def graph_dispatches(self):
         """(kernel nodes per replay with dispatch merging, without it)."""

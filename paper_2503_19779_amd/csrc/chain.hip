@@ -118,7 +118,7 @@ struct Dispatch {
 // so it waits for the former in short segments only.  us per iteration, graph / launched: two segments of 2 scale + bias + ReLU dispatches
 // 44 / 19, four of 1 73 / 23; chains of 2 fp32 elementwise dispatches 18.5 / 8.8, of 8 28 / 21, of 12 35 / 30, of 24 52 / 61.  Beyond 6 a process
 // with slow launches loses: 8 bf16 elementwise dispatches 31 / 25 or 33, and 47 / 46 or 64 where every iteration is waited for.
-constexpr size_t kLaunchedMost = 6;
+constexpr int kLaunchedMost = 6;
 
 struct Segment {
     int k0 = 0, k1 = 0;
@@ -177,6 +177,7 @@ struct pg_chain {
     int device = -1;                    // the device pg_capture ran on (graphs, events and pinned memory belong to it)
     bool eager_only = false;            // built over the static scratch array: pg_eager_static's private chain
     bool merge = true;                  // captured graphs play runs of small kernels with one dispatch
+    int launched_most = kLaunchedMost;
     int table_how = PG_TABLE_KERNARG;
     int copy_how = PG_COPY_KERNEL;
     // host-updated graphs: which instance the next replay rewrites, and when each was last launched
@@ -1268,7 +1269,7 @@ pg_status play(std::vector<Dispatch>& d, hipStream_t s) {
 
 pg_status capture_segment(pg_chain* c, Segment& sg, int kind, int inst, hipStream_t s, hipGraph_t* g_out, hipGraphExec_t* x_out, std::vector<Dispatch>* few) {
     std::vector<Dispatch> all = segment_dispatches(c, sg, kind, inst);
-    if (few && all.size() <= kLaunchedMost) {
+    if (few && all.size() <= (size_t)c->launched_most) {
         for (auto& x : all)
             if (!x.launch->mod_fn) PG_HIP(hipGetFuncBySymbol(&x.launch->mod_fn, x.launch->fn));
         *few = std::move(all);
@@ -1994,6 +1995,12 @@ pg_status pg_set_table_refresh(pg_chain* c, int32_t how) {
 pg_status pg_set_dispatch_merge(pg_chain* c, int32_t on) {
     if (!c) return fail(PG_EINVAL, "null chain");
     c->merge = on != 0;
+    return PG_OK;
+}
+
+pg_status pg_set_launched_dispatches(pg_chain* c, int32_t most) {
+    if (!c || most < 0) return fail(PG_EINVAL, "null chain or a negative number of dispatches");
+    c->launched_most = most;
     return PG_OK;
 }
 

@@ -54,16 +54,27 @@ def same_bits(a: np.ndarray, b: np.ndarray) -> bool:
 
 
 class Harness:
-    """A chain on cuda:0 with its weights resident, a stream, and graphs captured."""
+    """A chain on cuda:0 with its weights resident, a stream, and graphs captured: graphs of every segment, however short.  Short segments
+    that a program's chain would launch instead are launched by a twin of the chain, which every graph replay is compared with.
+    graphs=False: one chain, its short segments launched."""
 
-    def __init__(self, spec, weights_np=None, capture=True, device="cuda:0"):
+    twin = None
+
+    def __init__(self, spec, weights_np=None, capture=True, device="cuda:0", graphs=True):
         self.spec = spec
         self.device = device
         self.w_np = make_weights(spec) if weights_np is None else weights_np
         self.w_dev = [to_device(w, device) for w in self.w_np]
         self.chain = pg.Chain(spec, self.w_dev, device)
         self.stream = torch.cuda.Stream(device=device)
+        if graphs:
+            self.chain.set_launched_dispatches(0)
+            if self.chain.graph_dispatches()[0] <= 6 * spec.n_segments:
+                self.twin = pg.Chain(spec, self.w_dev, device)
+                self.twin.capture(self.stream)
         self._keep = []
+        if self.twin is not None:
+            self.scrub()             # what no kernel writes is the same in both
         if capture:
             self.chain.capture(self.stream)
 
@@ -77,28 +88,36 @@ class Harness:
         return x_np, x_dev
 
     def run(self, mode: str, ext, modes=None):
-        c = self.chain
-        if mode == "eager":
-            c.eager(ext, self.stream)
-        elif mode == "copy":
-            c.replay_copy(ext, self.stream)
-        elif mode == "indirect":
-            c.replay_indirect(ext, self.stream)
-        elif mode == "selected":
-            c.run_selected(modes, ext, self.stream)
-        else:
-            raise ValueError(mode)
-        self.stream.synchronize()
-        return [c.output(o) for o in self.spec.outputs]
+        outs = []
+        for c in (self.chain, self.twin) if mode != "eager" else (self.chain,):
+            if c is None:
+                continue
+            if mode == "eager":
+                c.eager(ext, self.stream)
+            elif mode == "copy":
+                c.replay_copy(ext, self.stream)
+            elif mode == "indirect":
+                c.replay_indirect(ext, self.stream)
+            elif mode == "selected":
+                c.run_selected(modes, ext, self.stream)
+            else:
+                raise ValueError(mode)
+            self.stream.synchronize()
+            outs.append([c.output(o) for o in self.spec.outputs])
+        for a, b in zip(outs[0], outs[-1]):
+            assert same_bits(a, b), (mode, "launched segments and graphs differ")
+        return outs[0]
 
     def scrub(self):
         """Overwrite every internal buffer and placeholder with NaN patterns, so that a mode cannot
         pass by finding the previous mode's results still in place."""
-        c = self.chain
-        for i, t in enumerate(self.spec.ints):
-            c.int_buffer(i).fill_(float("nan"))
-        for i, t in enumerate(self.spec.ext):
-            c.placeholder(i).fill_(float("nan"))
+        for c in (self.chain, self.twin):
+            if c is None:
+                continue
+            for i, t in enumerate(self.spec.ints):
+                c.int_buffer(i).fill_(float("nan"))
+            for i, t in enumerate(self.spec.ext):
+                c.placeholder(i).fill_(float("nan"))
         torch.cuda.synchronize()
 
     def oracle(self, x_np, k_end=None):
@@ -107,6 +126,8 @@ class Harness:
 
     def close(self):
         self.chain.close()
+        if self.twin is not None:
+            self.twin.close()
 
 
 def check_all_modes(h: Harness, t: int, dtype: str, what: str, rtol=None, out_numel=None):

@@ -90,7 +90,7 @@ def _check_inside(spec, inside):
     """External `e` of inside = {e: buffer} is that internal buffer.  Indirect replays and every combination of modes leave the bits of eager
     launches, with each way of moving the table; each iteration starts from the same contents."""
     spec.outputs[:] = range(len(spec.ints))
-    h = Harness(spec)
+    h = Harness(spec, graphs=False)
     has_ext = [any(r.kind == EXT for k in spec.kernels if k.segment == s for r in k.ins) for s in range(spec.n_segments)]
     for t in range(2):
         _, x = h.inputs(t)

@@ -398,7 +398,7 @@ def test_segments_around_the_longest_that_is_launched(kernels, cuts):
     if cuts:       # 8 kernels in two dispatches, then 28 in seven
         ks = [dataclasses.replace(k, segment=int(i >= 8)) for i, k in enumerate(spec.kernels)]
         spec = ChainSpec(spec.name + "_cut", ks, spec.ext, spec.ints, spec.weights, spec.outputs, spec.seed, meta=dict(spec.meta))
-    h = Harness(spec)
+    h = Harness(spec, graphs=False)
     for merge in (True, False, True):
         h.chain.set_dispatch_merge(merge)
         h.chain.capture(h.stream)

@@ -341,3 +341,14 @@ def test_rmsnorm_rides_in_front_only_while_the_grid_is_small(rows, n, cols, want
     ch = pg.Chain.host_only(spec)
     assert ch.graph_dispatches() == (want, 3)
     ch.close()
+
+
+def test_number_of_dispatches_that_are_launched():
+    ch = pg.Chain.host_only(elementwise_chain())
+    for most in (0, 6, 1 << 20):
+        ch.set_launched_dispatches(most)
+    assert ch.graph_dispatches() == (16, 64)          # the limit chooses how a segment is replayed, not what it dispatches
+    with pytest.raises(pg.PgError) as e:
+        ch.set_launched_dispatches(-1)
+    assert e.value.status == 1
+    ch.close()
