@@ -1400,10 +1400,13 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         out->fn = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8, false>) : PG_FN(k_gemm_tile<2, 2, 2, 4, false>);
         out->gemm_row_groups = (unsigned)two;
         out->grid = dim3((unsigned)wide * out->gemm_row_groups);
-        // Where all workgroups that share their weights run side by side: 1536 columns and more, one workgroup per CU.  us per iteration
-        // without / with non-temporal loads: 128 rows of 2048 columns, 1 GB in all 1326 / 1264, 250 MB 288 / 322; of 1536 columns 984 / 938; 100 of
-        // 2048 1049 / 995; 128 of 1024, 250 MB 948 / 975; other tiles and larger grids 100 of 4096 487 / 530, 128 of 6144 511 / 525.
-        if (out->grid.x <= 256 && cols >= 1536) out->fn_beyond_cache = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8, true>) : PG_FN(k_gemm_tile<2, 2, 2, 4, true>);
+        // Where all workgroups that share their weights run side by side, one per CU, no two rows share a cache line, and there are enough outputs.  us per iteration of decode
+        // chains of 400 MB of weights without / with non-temporal loads: 128 rows of 576 columns 4886 / 4614, 768 2848 / 2602, 1024 1734 / 1620, 1280
+        // 1168 / 1098, 1472 885 / 881, 1536 862 / 830, 2048 540 / 523, 64 of 2304 471 / 451; rows that share cache lines, 128 of 1544 921 / 987, 2000
+        // 618 / 664, 100 of 1928 608 / 711, 64 of 2312 521 / 559; within the cache, 200 MB, 128 of 1024 765 / 815, 2048 236 / 266; other tiles and
+        // larger grids, 100 of 3000 497 / 634, 100 of 2056 795 / 991, 81 of 4096 228 / 262; us per RMSNorm, GEMV and GELU of few outputs, 128 rows of 8192
+        // columns, 64 outputs 21.8 / 25.2, 128 22.0 / 23.4, 256 22.4 / 22.2, 512 22.7 / 22.5; 100 of 4096, 256 outputs 13.0 / 12.7.
+        if (out->grid.x <= 256 && cols % 64 == 0 && n >= 256) out->fn_beyond_cache = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8, true>) : PG_FN(k_gemm_tile<2, 2, 2, 4, true>);
     } else {
         out->fn = merged ? PG_FN(k_gemm_tile<1, 1, 2, 8, false>) : PG_FN(k_gemm_tile<1, 1, 2, 4, false>);
         out->grid = dim3((unsigned)(narrow * ntiles));

@@ -2,10 +2,11 @@
 vector, inside a K-block of 64 columns, on and around 1024 and 2048 columns (K-steps per wave; the prologue's limit),
 fewer K-blocks than waves, ragged column blocks, one and several tiles of rows, every tile size.  Graphs equal eager bit
 for bit and every kernel matches the oracle."""
+import numpy as np
 import pytest
 
 from gpu_util import Harness, same_bits, say, stepwise_check
-from pg_workloads import ChainSpec, KernelSpec, TensorSpec, Ref, EXT, INT, WEIGHT, decode_chain
+from pg_workloads import ChainSpec, KernelSpec, TensorSpec, Ref, EXT, INT, WEIGHT, decode_chain, make_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -112,4 +113,33 @@ def test_weights_beyond_the_cache(rows):
         assert same_bits(h.run(mode, x_dev)[0], ref[0]), mode
     h.scrub()
     stepwise_check(h, x_np, x_dev, rows=[0, rows - 1], rtol=2.0 ** -7)
+    h.close()
+
+
+@pytest.mark.parametrize("rows,n,cols", [(17, 40, 1088), (40, 1030, 1536), (64, 2049, 1984), (80, 33, 1600), (72, 15, 1152), (33, 1030, 1544),
+                                         (81, 37, 64), (81, 300, 64), (100, 1990, 1024), (128, 1990, 1088), (97, 2050, 2048), (128, 24, 4160), (66, 2310, 2304), (100, 1030, 1544), (81, 50, 1601)])
+def test_shapes_in_a_chain_beyond_the_cache(rows, n, cols):
+    """One GEMV of 269 MB makes the rest of the chain use the forms for weights beyond the cache: ragged outputs, K tails, widths without such
+    a form; behind an RMSNorm of its own, with kernels that ride and alone."""
+    big, N, K = 65600, rows * n, rows * cols
+    ks = [KernelSpec("gemv", "bf16", 4, (Ref(WEIGHT, 2), Ref(EXT, 2)), big, rows=5, cols=2048),
+          KernelSpec("rmsnorm", "bf16", 0, (Ref(EXT, 0), Ref(WEIGHT, 1)), cols, rows=rows, cols=cols, eps=1e-6),
+          KernelSpec("gemv", "bf16", 1, (Ref(WEIGHT, 0), Ref(INT, 0)), n, rows=rows, cols=cols),
+          KernelSpec("gelu", "bf16", 1, (Ref(INT, 1),), N),
+          KernelSpec("add", "bf16", 2, (Ref(EXT, 1), Ref(INT, 1)), N, m=N),
+          KernelSpec("gemv", "bf16", 3, (Ref(WEIGHT, 0), Ref(EXT, 0)), n, rows=rows, cols=cols),
+          KernelSpec("rmsnorm", "bf16", 0, (Ref(EXT, 0), Ref(WEIGHT, 1)), cols, rows=rows, cols=cols, eps=1e-6)]
+    spec = ChainSpec(f"beyond_{rows}x{n}x{cols}", ks, [TensorSpec("bf16", K), TensorSpec("bf16", N), TensorSpec("bf16", 5 * 2048)],
+                     [TensorSpec("bf16", K)] + [TensorSpec("bf16", N) for _ in range(3)] + [TensorSpec("bf16", 5 * big)],
+                     [TensorSpec("bf16", n * cols, ("normal", 0.0, 0.05)), TensorSpec("bf16", cols, ("normal", 1.0, 0.1)), TensorSpec("bf16", big * 2048)], [0, 1, 2, 3], 7400)
+    small = make_weights(ChainSpec(spec.name, [], [], [], spec.weights[:2], [], spec.seed))
+    h = Harness(spec, weights_np=small + [np.zeros(big * 2048, np.uint16)])
+    x_np, x_dev = h.inputs(0)
+    ref = h.run("eager", x_dev)
+    for mode in ("copy", "indirect"):
+        h.scrub()
+        got = h.run(mode, x_dev)
+        assert all(same_bits(a, b) for a, b in zip(ref, got)), mode
+    h.scrub()
+    stepwise_check(h, x_np, x_dev, rtol=2.0 ** -7, kernels=range(1, len(ks)))
     h.close()
