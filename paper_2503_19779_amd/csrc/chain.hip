@@ -307,6 +307,10 @@ pg_status validate(const pg_kernel_desc* k, int nk, const pg_tensor_desc* ext, i
     return PG_OK;
 }
 
+// The period of an add's or mul's second operand as the argument blocks hold it: one longer than the tensor (of any length up to 2^40, where the
+// kernels count in 32 bits) is element for element.
+long long period(const pg_kernel_desc& d) { return d.m ? std::min(d.m, d.n) : d.n; }
+
 pgk::Shape shape_of(const pg_kernel_desc& d) {
     pgk::Shape sh;
     sh.n = d.n; sh.m = d.m ? d.m : d.n; sh.rows = d.rows; sh.cols = d.cols; sh.inner = d.inner;
@@ -812,7 +816,7 @@ pg_status make_records(pg_chain* c) {
             for (int j = 0; j < r.n_in; j++) a.ptr[1 + j] = operand_ptr(c, d.in[j], mode);
             switch (d.op) {
             case PG_ADD: case PG_MUL: case PG_GELU:
-                a.ew.n = d.n; a.ew.m = (d.op == PG_GELU) ? d.n : (d.m ? d.m : d.n);
+                a.ew.n = d.n; a.ew.m = d.op == PG_GELU ? d.n : period(d);
                 break;
             case PG_RMSNORM: a.rms.rows = (int)d.rows; a.rms.cols = (int)d.cols; a.rms.eps = d.eps; break;
             case PG_GEMV:
@@ -1194,7 +1198,7 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
                 ph.out = const_cast<void*>(a.ptr[0]);
                 ph.in0 = a.ptr[1];
                 ph.in1 = r.n_in > 1 ? a.ptr[2] : nullptr;
-                ph.m = (d.op == PG_ADD || d.op == PG_MUL) ? (unsigned)(d.m ? d.m : d.n) : (unsigned)grp.n;
+                ph.m = (d.op == PG_ADD || d.op == PG_MUL) ? (unsigned)period(d) : (unsigned)grp.n;
                 ph.meta = (unsigned)d.op | ((unsigned)grp.src0[t] << 8) | ((unsigned)grp.src1[t] << 16) | ((unsigned)grp.dst[t] << 24);
                 ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (store[t] ? pgk::kEpiStore : 0u);
             }
@@ -1232,7 +1236,7 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
                 }
                 ph.in1 = r.n_in > 1 ? a.ptr[2] : m.in0;
                 m.slots |= (r.n_in > 1 ? (slots >> 1) & 1u : first) << t;
-                if (r.n_in > 1 && d.m) m.m[t] = (unsigned)d.m;
+                if (r.n_in > 1) m.m[t] = (unsigned)period(d);
                 if (m.m[t] != m.n) m.slots |= pgk::kChainPeriods;
                 m.ops |= ((unsigned)d.op | (store[t] ? 8u : 0u)) << (4 * t);
             }
@@ -1251,7 +1255,7 @@ std::vector<Dispatch> segment_dispatches(pg_chain* c, Segment& sg, int kind, int
             ph.out = const_cast<void*>(a.ptr[0]);
             ph.in0 = a.ptr[1];
             ph.in1 = r.n_in > 1 ? a.ptr[2] : nullptr;
-            ph.m = (d.op == PG_ADD || d.op == PG_MUL) ? (unsigned)(d.m ? d.m : d.n) : 0u;
+            ph.m = (d.op == PG_ADD || d.op == PG_MUL) ? (unsigned)period(d) : 0u;
             ph.eps = d.op == PG_RMSNORM ? d.eps : 0.f;
             ph.meta = (unsigned)d.op | ((unsigned)grp.src0[m.n_phase] << 8) | ((unsigned)grp.src1[m.n_phase] << 16) | ((unsigned)grp.dst[m.n_phase] << 24);
             ph.ind = (kind == kGraphCopy ? 0u : (unsigned)r.ind_mask) | (store[m.n_phase] ? pgk::kEpiStore : 0u);

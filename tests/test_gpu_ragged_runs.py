@@ -79,3 +79,20 @@ def test_chains_with_periods(dtype, n, kernels):
     h = Harness(spec)
     assert h.chain.graph_dispatches()[0] == -(-kernels // (8 if dtype == "bf16" and n >= 16384 else 4))
     _check(h)
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 1000), ("bf16", 1021), ("bf16", 20000), ("f32", 1021), ("f32", 20000)])
+@pytest.mark.parametrize("more", [1, 8, 5000])
+def test_periods_longer_than_the_tensor(dtype, n, more):
+    """Second operands that are longer than what a kernel takes of them: alone (behind a kernel of another length), in a chain and in a run with two
+    live buffers."""
+    b = (Ref(EXT, 1),)
+    ks = [KernelSpec("add", dtype, 0, (Ref(EXT, 0),) + b, n, m=n + more),
+          KernelSpec("mul", dtype, 0, (Ref(INT, 0),) + b, n, m=n + more),
+          KernelSpec("add", dtype, 3, (Ref(EXT, 0),) + b, n - 5, m=n + more),
+          KernelSpec("mul", dtype, 1, (Ref(EXT, 0),) + b, n, m=n + more),
+          KernelSpec("add", dtype, 2, (Ref(INT, 1), Ref(INT, 0)), n, m=n),
+          KernelSpec("add", dtype, 1, (Ref(INT, 1),) + b, n, m=n + more)]
+    spec = ChainSpec(f"long_periods_{dtype}_{n}_{more}", ks, [TensorSpec(dtype, n), TensorSpec(dtype, n + more)], [TensorSpec(dtype, n)] * 4, [], [0, 1, 2], 8420)
+    h = Harness(spec)
+    _check(h)
