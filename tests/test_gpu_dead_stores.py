@@ -52,6 +52,18 @@ def test_carry_runs(reader, cut):
     _check(spec)
 
 
+@pytest.mark.parametrize("sizes", [[4096, 2048, 1024, 512, 4104, 520], [(1 << 19) + 4096, 2048, 8192, 512, 4104, 520]])
+@pytest.mark.parametrize("writer", [1, 515, 2043, 4099, 4103])
+def test_carry_runs_behind_which_a_vector_is_cut(writer, sizes):
+    """A kernel behind the run, on its own, overwrites a number of elements that is no whole number of vectors, of 4 or of 16 bytes: the rest of the
+    vector it ends in stays what the run left there."""
+    ks = [KernelSpec(("add", "mul")[i % 2], "bf16", i % 2, (Ref(EXT, i), Ref(INT, (i - 1) % 2) if i else Ref(WEIGHT, 0)), n, m=512) for i, n in enumerate(sizes)]
+    ks += [KernelSpec("add", "bf16", b, (Ref(EXT, len(sizes)), Ref(WEIGHT, 0)), writer, m=512) for b in (0, 1) if b == 0 or writer <= 2048]
+    spec = ChainSpec(f"dead_cut_{writer}_{max(sizes)}", ks, [TensorSpec("bf16", n) for n in sizes] + [TensorSpec("bf16", writer)], [TensorSpec("bf16", max(sizes))] * 2,
+                     [TensorSpec("bf16", 512)], [], 8520)
+    _check(spec)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("reader", [None, 0, 1])
 def test_scale_bias_relu_segments(dtype, reader):
