@@ -194,11 +194,13 @@ pg_status pg_eager_static(const pg_kernel_desc *kernels, int32_t n_kernels,
                           int32_t out_int_index, void *out_dev, size_t out_bytes, void *hip_stream);
 
 /* One iteration: one launch of the batched copy kernel (external tensors -> placeholders, device
- * to device), then one graph launch per segment (Sec. 4 "Graph-Capture Layer", baseline). */
+ * to device), then per segment one graph launch or its few kernel launches (pg_capture; Sec. 4
+ * "Graph-Capture Layer", baseline). */
 pg_status pg_replay_copy(pg_chain *chain, const void *const *ext_dev_ptrs, void *hip_stream);
 
-/* One iteration: write the n_ext pointers into the device-resident table (8 bytes each), then one
- * graph launch per segment; kernels dereference their table slots first (Sec. 3, Sec. 4). */
+/* One iteration: write the n_ext pointers into the device-resident table (8 bytes each), then per
+ * segment one graph launch or its few kernel launches; kernels dereference their table slots first
+ * (Sec. 3, Sec. 4). */
 pg_status pg_replay_indirect(pg_chain *chain, const void *const *ext_dev_ptrs, void *hip_stream);
 
 /* One iteration with neither copies nor indirection: a third graph per segment, built from explicit
@@ -265,8 +267,8 @@ pg_status pg_set_copy_refresh(pg_chain *chain, int32_t how /* pg_copy_refresh */
  * (Sec. 2.2); on this machine every dependent kernel node still costs about 1.5 us of dispatch, so a
  * captured graph, which knows the whole chain, plays a run of consecutive kernels with ONE dispatch where
  * it can.  A lane runs the kernels in order on its elements with their stand-alone arithmetic and one
- * rounding each, stores every kernel's output that no later kernel of the run overwrites, and hands the
- * stored bits to the next kernel in registers, so results stay bit-identical to eager launches.  The runs:
+ * rounding each, stores what is read from memory later (below), and hands the rounded bits to the next
+ * kernel in registers, so results stay bit-identical to eager launches.  The runs:
  *   - up to 4 add / mul / GELU kernels (8 for bf16 tensors of 2^14 to 2^21 elements) and RMSNorm over rows
  *     of 256 x 16 bytes, all element for element over the same n elements.  bf16: any n.  fp32: any n up
  *     to 16384 elements, and only there the fp32 GELU takes part; beyond, a whole number of 16-byte

@@ -343,9 +343,9 @@ pgk::Shape shape_of(const pg_kernel_desc& d) {
 // run writes.
 //
 // A fourth: bf16 add / mul / GELU kernels over tensors of their own lengths, whose second operand is the head of what the
-// kernel before wrote (kernels.h, CarryRunArgs).  A workgroup plays the whole run on its stretch of elements, so the
-// kernels' first operands must not be buffers that the run writes; the first kernel's carry may be one if the run
-// before set it aside.
+// kernel before wrote (kernels.h, CarryRunArgs).  A workgroup plays one unit of one kernel, and the units of all kernels run side by side
+// in no order: no buffer may be both a first operand and an output of the run, whichever comes first, nor be read as the first kernel's
+// carry and written, unless the run before set that carry aside; where outputs overlap, `cover` leaves each element to the last kernel.
 void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* ints, const std::vector<long long>& channels,
                  std::vector<MergeGroup>& out) {
     out.clear();
@@ -553,7 +553,7 @@ void plan_groups(const pg_kernel_desc* k, int k0, int k1, const pg_tensor_desc* 
         }
         if (i == g.k0) i++;      // the first kernel itself was refused (only a descriptor that validation rejects gets here): on its own
         g.k1 = i;
-        // an output is stored unless a later kernel of the run overwrites the same buffer (nothing reads memory in between)
+        // an output is stored unless a later kernel of the run overwrites the same buffer; drop_dead_stores takes out more
         for (int a = 0; a < np; a++) {
             g.store[a] = true;
             for (int t = a + 1; t < np; t++)

@@ -612,8 +612,10 @@ __device__ __forceinline__ MmHead mm_head(const RideArgs<RIDE>& p) {
 //     that 16 consecutive lanes hit all banks;
 //   - the rows of h (from L2) are asked for before the weights (from HBM): loads return in order, so h is normalised
 //     and staged while the weights are still on their way; then the same LDS slice takes the weights.
-//   - the weights come by non-temporal loads: no other workgroup of the tile reads them (120 sub-blocks, us per iteration: 16 rows of 2048
-//     columns 766 -> 694, 32 of 1024 609 -> 565; 8 of 512, whose 15 MB of weights stay in the cache, 30 sub-blocks 145 -> 136).
+//   - the weights come by non-temporal loads: no other workgroup of the tile reads them.  Decode chains, us per iteration by plain / non-temporal
+//     loads: 16 rows of 2048 columns, 120 sub-blocks 745 / 676, 32 of 1024 555 / 513; weights that stay in the memory-side cache, 126 MB, 16 of
+//     2048 105 / 99, 8 of 1024 244 / 218, 32 of 1024 297 / 273, 15 MB, 8 of 512 115 / 115.  Behind only where rows of more than 1024 columns share
+//     cache lines: within the cache 16 of 1928 118 / 125, 8 of 2041 110 / 112, beyond it 362 / 367, 338 / 328.
 // TAIL: the row does not have exactly 128 * KS columns; vectors at any element boundary.
 // Decode chains of 120 sub-blocks, us per iteration: 32 rows of 1024 columns 1406 -> 613 (one dispatch per sub-block, where only
 // 2048 columns had that; half the K-steps); 8 / 16 / 32 rows of 2048 columns 651 / 787 / 915 -> 627 / 771 / 862 (the epilogue's
@@ -1321,7 +1323,8 @@ const void* rows_kernel_rb(int n, int cols) {
     default: break;
     }
     // up to 2048 columns a form per 512, so that only a row's last piece has an end to look for (decode chains of 60 sub-blocks against one
-    // form for up to 1536 columns, us per iteration: 1 row of 1400 columns 198 -> 182, 4 rows 255 -> 243, 3 rows of 1500 242 -> 238)
+    // form for up to 1536 columns, us per iteration: 1 row of 1400 columns 198 -> 182, 4 rows 255 -> 243, 3 rows of 1500 242 -> 238; 30 times RMSNorm,
+    // GEMV and GELU, 2048 outputs: 1 / 4 rows of 256 columns 88 / 110 -> 78 / 94, of 512 88 / 110 -> 78 / 94, of 1000 88 / 111 -> 82 / 97)
     if (u <= 1) return PG_FN(k_gemv_rows<2, RB, 1, false, RIDE>);
     if (u <= 2) return PG_FN(k_gemv_rows<2, RB, 2, false, RIDE>);
     if (u <= 3) return PG_FN(k_gemv_rows<2, RB, 3, false, RIDE>);
@@ -1379,8 +1382,9 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     if (cols <= 2048 && (rows < kMmWideRows || n <= 16)) {
         out->gemm_row_groups = (unsigned)(ntiles < 4 || n <= 16 ? ntiles : 4);
         // Several workgroups read the same weights, side by side.  Decode chains, us per iteration without / with non-temporal loads: 64 rows of
-        // 1024 columns, 126 MB of weights in all 366 / 339, 252 MB 729 / 679, 40 rows of 520 columns 916 / 860; of 2048 columns, 168 MB 184 / 188,
-        // 1 GB 1183 / 1084; rows that share cache lines, 40 of 1500 columns, 540 MB 1599 / 1628.
+        // 1024 columns, 126 MB of weights in all 363 / 343, 252 MB 718 / 676, of 1001 columns, 200 MB 843 / 819; of 2048 columns, 200 MB 226 / 233,
+        // 400 MB 488 / 454, 1 GB 1159 / 1077, of 1088 columns, 400 MB 1757 / 1608, 1600 844 / 790; rows that share cache lines, 400 MB, gain less the
+        // longer they are: 40 of 1032 columns 1663 / 1550, 1300 1289 / 1240, 1500 1108 / 1130, 1928 620 / 627.
         out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
         out->fn = merged ? gemm_cols_form<kEpilogue, false>(cols) : gemm_cols_form<kAlone, false>(cols);
         if (cols % 64 == 0) out->fn_beyond_cache = merged ? gemm_cols_form<kEpilogue, true>(cols) : gemm_cols_form<kAlone, true>(cols);

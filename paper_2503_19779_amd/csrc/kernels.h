@@ -77,8 +77,8 @@ struct TableArgs {
 // exactly 256 x 16 bytes -- goes out as ONE dispatch.  The tensor is cut into units of 256 lanes x 16
 // bytes (lane t owns vector t of a unit; an RMSNorm row is one unit), one workgroup per unit.  The lane
 // runs the kernels one after the other, each with its stand-alone arithmetic and its one rounding to
-// the storage type, stores its output unless a later kernel of the run overwrites it, and hands the stored bits on to the next kernel in
-// registers when that kernel reads the same buffer element for element -- so the run costs one trip
+// the storage type, stores its output if something reads it from memory later (chain.hip, drop_dead_stores), and hands the stored bits on to
+// the next kernel in registers when that kernel reads the same buffer element for element -- so the run costs one trip
 // to memory, not one per kernel.  Operands that no kernel of the run produces are fetched up front.
 constexpr int kMergeShortPhases = 4;      // kernels per merged dispatch
 constexpr int kMergeMaxPhases = 8;        // ... of bf16 kernels over kMergeLongFrom to kMergeLongTo elements
@@ -131,7 +131,7 @@ constexpr unsigned kChainEnd = 7;
 // kernels on that one element, operands fetched while the weights were in flight.  No workgroup needs
 // another's results, so nothing has to be waited for.
 constexpr int kEpiMaxPhases = 3;
-constexpr unsigned kEpiStore = 1u << 8;   // MergePhase::ind: this kernel's output is stored (no later kernel of the run overwrites it)
+constexpr unsigned kEpiStore = 1u << 8;   // MergePhase::ind: this kernel's output is stored (something reads it from memory, or it is the buffer's last version)
 // And the RMSNorm in front of the GEMV can ride along as a prologue: every workgroup of the GEMV needs the
 // whole normalised vector anyway, so each one normalises the rows itself (the stand-alone kernel's
 // arithmetic, lane t holding vector t of a row -- exactly where the GEMV wants h in LDS) while its
@@ -168,7 +168,7 @@ struct GemvEpiArgs {
 
 // A run of consecutive per-channel scale + bias + ReLU kernels over one tensor (each reads what the one before it
 // wrote, element for element; same length, same channels): one dispatch that reads x once and keeps the elements in
-// registers from kernel to kernel.  Outputs that a later kernel of the run overwrites are not stored.
+// registers from kernel to kernel.  Outputs that are overwritten before anything reads them from memory are not stored.
 constexpr int kSbrRunMax = 16;              // kernels per run
 constexpr int kSbrRunMaxChannels = 128;     // one lane per scale and per bias of a kernel when the run's tables are loaded
 struct SbrRunPhase {
@@ -198,7 +198,10 @@ struct CarryPhase {
     void* out;
     const void* in0;
     unsigned n;
-    unsigned cover;         // elements of the output that later kernels of the run overwrite
+    // elements of the output that later kernels, of this run or behind it, overwrite before anything reads them from memory: not stored.  Kernels
+    // of the run write multiples of 8, so what two of them store never overlaps.  A kernel behind the run may write any number and cut a
+    // vector: that one is stored whole, and overwritten by a later dispatch.
+    unsigned cover;
     unsigned op;
     unsigned ind;           // bit 0: in0 is a pointer-table slot
     unsigned from;          // the first kernel whose head this kernel's carry depends on: the last GELU before it, or kernel 0
