@@ -146,8 +146,8 @@ pg_status pg_chain_build(const pg_kernel_desc *kernels, int32_t n_kernels,
  * pointer table -- instantiate and upload the graphs, and write the static part of the copy
  * kernel's job list into the workspace.  A segment that comes to 6 dispatches or fewer gets no
  * graph: its launches and their argument blocks are laid out here, and a replay issues them (a graph
- * launch costs the host more than that many kernel launches).  Synchronises the stream before returning.  Calling it
- * again re-captures: it first waits for everything queued on the device (a replay of the old graphs
+ * launch costs the host more than that many kernel launches; pg_set_launched_dispatches).  Synchronises
+ * the stream before returning.  Calling it again re-captures: it first waits for everything queued on the device (a replay of the old graphs
  * may be running on any stream) and destroys the old graphs. */
 pg_status pg_capture(pg_chain *chain, void *hip_stream);
 
