@@ -253,6 +253,15 @@ __device__ __forceinline__ unsigned xcd_stretch(unsigned b, unsigned total) {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
+// 16 bytes at any element boundary, `off` bytes behind a uniform address
+template <bool NT>
+__device__ __forceinline__ void load_at(const bf16_t* base /* uniform */, unsigned off, unsigned* w) {
+    const v4u_any PG_GLOBAL* q = (const v4u_any PG_GLOBAL*)((const char PG_GLOBAL*)(uintptr_t)base + off);
+    v4u t;
+    if constexpr (NT) t = __builtin_nontemporal_load(q);
+    else t = *q;
+    w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+}
 template <bool NT>
 __device__ __forceinline__ void load_any(const bf16_t* base /* uniform */, unsigned elem, unsigned* w) {
     const v4u_any PG_GLOBAL* q = (const v4u_any PG_GLOBAL*)((const bf16_t PG_GLOBAL*)(uintptr_t)base + elem);
@@ -601,10 +610,12 @@ __device__ __forceinline__ MmHead mm_head(const RideArgs<RIDE>& p) {
 }
 
 // ---- k_gemm_rows ------------------------------------------------------------------------------------------
-// One tile of NR (8 or 16) rows of h and NC (8 or 16) output columns per workgroup, rows of up to 128 * KS columns
-// (KS K-steps per wave).  Few rows are bound by the latency of one dispatch and, at 2048 columns, by the stream of weights:
+// One tile of NR (4, 8 or 16) rows of h and NC (8 or 16) output columns per workgroup, rows of up to 128 * KS columns
+// (KS K-steps per wave).  Few rows are bound by the latency of one dispatch, by the stream of weights (loads alone of 96 KB per workgroup take
+// 3.4 us of the 5.6 that 16 rows of 2048 columns take), and with the RMSNorm in front by its instructions, four cycles each:
 //   - 8 columns per workgroup make 2048 columns 256 workgroups, so that every CU pulls weights; half of each multiply
-//     is idle, which costs nothing here.  From 17 rows on, two tiles of rows: 16 columns per workgroup fill the chip;
+//     is idle, which costs nothing here.  Rows to normalise are cut into tiles so that the grid just fills the chip (prologue_tile): every
+//     workgroup normalises its tile anew;
 //   - a fragment read straight from global memory would touch 16 rows x 64 bytes per instruction, at 2048 columns all 4 KB
 //     apart: half cache lines, one cache channel (measured: 0.3 - 1.1 us slower per launch).  Instead each wave loads
 //     its own K-slices of the rows, contiguous bytes of one row (KS = 16) or two (KS = 8) per instruction, and transposes them through its
@@ -619,27 +630,34 @@ __device__ __forceinline__ MmHead mm_head(const RideArgs<RIDE>& p) {
 // TAIL: the row does not have exactly 128 * KS columns; vectors at any element boundary.
 // Decode chains of 120 sub-blocks, us per iteration: 32 rows of 1024 columns 1406 -> 613 (one dispatch per sub-block, where only
 // 2048 columns had that; half the K-steps); 8 / 16 / 32 rows of 2048 columns 651 / 787 / 915 -> 627 / 771 / 862 (the epilogue's
-// table worked out on the host, two operand loads instead of six, workgroups in XCD order).
+// table worked out on the host, two operand loads instead of six, workgroups in XCD order).  Tiles of rows, one barrier in the RMSNorm, row
+// addresses in scalar registers, us per sub-block before / after: 16 rows of 1024 columns 4.06 / 3.33, 32 4.36 / 3.67, 8 3.48 / 3.18, 16 of 520
+// 4.42 / 3.67, 16 of 2048 5.81 / 5.39, 32 6.64 / 6.46.  Eight waves of half the columns each: no faster, the instructions count (16 of 2048 5.63
+// where four waves took 5.58, 32 of 1024 4.00 where they took 3.83).
 constexpr int kMmSlotBytes = 272;   // 16 rows x 16 B + 16 B of padding
 
 // k offset of the 16-byte chunk that lane `l` (of 4 * KS) of wave `wave` loads from a row; the same chunk is fragment
 // step l >> 2, k-chunk l & 3 of that wave.
 __device__ __forceinline__ int mm_k0(int wave, int l) { return ((l >> 3) * 8 + wave * 2 + ((l >> 2) & 1)) * 32 + (l & 3) * 8; }
 
-// NR rows of a row-major matrix from row r0 (inside it), this wave's K-slices; rows beyond the matrix repeat its last row
+// NR rows of a row-major matrix from row r0 (inside it), this wave's K-slices; rows beyond the matrix repeat its last row.  (Everything in front of
+// the last weight load delays the whole kernel, and so does a branch about loads, behind which the compiler waits for more of them than it has to.)
 template <int KS, bool TAIL, int NR, bool NT>
 __device__ __forceinline__ void mm_load_rows(const bf16_t* m, int rows, int cols, int r0, int wave, int lane, unsigned (*g)[4]) {
     constexpr int L = 4 * KS, RPI = 64 / L;             // lanes per row, rows per instruction
     const int sub = lane / L;
     const unsigned koff = span_at<!TAIL>(cols, mm_k0(wave, lane % L) >> 3);
+    const bf16_t* row = m + (size_t)r0 * cols;
+    const unsigned last = (unsigned)(rows - 1 - r0);
 #pragma unroll
     for (int q = 0; q < NR / RPI; q++) {
         if constexpr (RPI == 1) {
-            const int R = r0 + q < rows ? r0 + q : rows - 1;
-            load_any<NT>(m + (size_t)R * cols, koff, g[q]);
+            const bf16_t* at = row + (size_t)((unsigned)q < last ? (unsigned)q : last) * (unsigned)cols;
+            asm("" : "+s"(at));                          // stays a scalar address
+            load_at<NT>(at, koff * 2u, g[q]);
         } else {
-            const int R = r0 + q * RPI + sub < rows ? q * RPI + sub : rows - 1 - r0;
-            load_any<NT>(m + (size_t)r0 * cols, (unsigned)R * (unsigned)cols + koff, g[q]);
+            const unsigned R = (unsigned)(q * RPI + sub) < last ? (unsigned)(q * RPI + sub) : last;
+            load_at<NT>(row, (R * (unsigned)cols + koff) * 2u, g[q]);
         }
     }
 }
@@ -676,28 +694,22 @@ __device__ __forceinline__ void mm_read_frags(const char* lds, int lane, v4u* f)
         f[i] = *reinterpret_cast<const v4u*>(lds + (i * 4 + (lane >> 4)) * kMmSlotBytes + (lane & 15) * 16);
 }
 
-// RMSNorm of the rows just loaded.  A lane holds 16-byte chunk c of every row (every other row at KS = 8), where c runs
-// over a row's chunks across the workgroup, but not in lane order.  The stand-alone kernel's sums must be reproduced bit for bit: per chunk
-// the fused sum of squares in element order (any lane can do that); then the stand-alone kernel's reduction, which
-// is a tree of fixed shape over the chunk sums in chunk order (absent chunks are zeros) -- wave_sum adds neighbours, then pairs of
-// pairs, of quads, of eights (a floating-point add does not care which operand is which), then the four
-// sixteens in order, and the four wave sums in order.  Here the chunk sums go to LDS in chunk order and
-// the workgroup's KS * NR subtrees of sixteen leaves are spread over its lanes, one each; lane r < NR
-// then finishes row r (four sixteens per wave sum, four wave sums) and turns the total into the row's
-// scale; every lane scales its own chunks: (x * scale) * gain, one rounding.  `scratch`: NR * (21 * KS + 1)
-// floats of LDS that nothing else uses until the rows are staged.  hstore: this workgroup also stores the rows.
+// RMSNorm of the rows just loaded.  A lane holds 16-byte chunk c of some of the rows, eight neighbouring lanes the eight chunks of
+// a K-block.  The stand-alone kernel's sums must be reproduced bit for bit: per chunk the fused sum of squares in element order
+// (any lane can do that); then the stand-alone kernel's reduction, which is a tree of fixed shape over the chunk sums in chunk order
+// (absent chunks are zeros) -- wave_sum adds neighbours, then pairs of pairs, of quads, of eights (a floating-point add does not
+// care which operand is which), then the four sixteens in order, and the four wave sums in order.  Here eight lanes add up a
+// K-block's chunks, the sums of the blocks go to LDS, and behind the one barrier every wave finishes all rows by itself: lane 4 r + w wave
+// sum w of row r, its quad the row's scale, which the lanes that hold the row fetch from it; every lane scales its own chunks: (x * scale) *
+// gain, one rounding.  `sq`: NR * (2 * KS + 4) floats.  hstore: this workgroup also stores the rows.
 template <int KS, bool TAIL, int NR>
 __device__ __forceinline__ void mm_rmsnorm_rows(unsigned (*g)[4], const unsigned* wg /* the lane's chunk of the gain */, float eps, bf16_t* hstore,
-                                                int rows, int cols, int wave, int lane, float* scratch) {
+                                                int rows, int cols, int wave, int lane, float* sq) {
     constexpr int L = 4 * KS, RPI = 64 / L, Q = NR / RPI;
-    constexpr int kRow = 20 * KS;              // a row of 16 * KS chunk sums, 8 floats of padding after every 32: the lanes of a wave hold
-                                               // chunks 32 apart, which would otherwise all fall into the same eight banks
-    const int tid = wave * 64 + lane, sub = lane / L;
+    constexpr int NB = 2 * KS, WS = NB / 8, kRow = NB + 4;      // K-blocks and wave sums of a row; a row of `sq`, padded
+    static_assert(NB % 8 == 0 && NR <= 16, "eight blocks to a wave sum, a quad per row");
+    const int sub = lane / L;
     const int k0 = mm_k0(wave, lane % L);
-    float* sq = scratch;                       // [NR][kRow]: chunk sums in chunk order
-    float* six = scratch + NR * kRow;          // [NR][KS]: sums of sixteen chunks
-    float* scale = six + NR * KS;              // [NR]
-    auto at = [](int c) { return c + 8 * (c >> 5); };
     float fx[Q][8];
 #pragma unroll
     for (int q = 0; q < Q; q++) {
@@ -705,34 +717,30 @@ __device__ __forceinline__ void mm_rmsnorm_rows(unsigned (*g)[4], const unsigned
         float acc = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; e++) acc = __builtin_fmaf(fx[q][e], fx[q][e], acc);
-        sq[(q * RPI + sub) * kRow + at(k0 >> 3)] = acc;
+        acc = dpp_add<0xB1>(acc);
+        acc = dpp_add<0x4E>(acc);
+        acc = dpp_add<0x141>(acc);
+        sq[(q * RPI + sub) * kRow + (k0 >> 6)] = acc;            // the same bits from all eight lanes: no branch per row
     }
     lds_barrier();
-    if (tid < KS * NR) {                       // subtree tid: row tid / KS, chunks 16 * (tid % KS) .. + 15
-        const f32x4* leaf = reinterpret_cast<const f32x4*>(sq + (tid / KS) * kRow + at((tid % KS) * 16));
-        const f32x4 l0 = leaf[0], l1 = leaf[1], l2 = leaf[2], l3 = leaf[3];
-        const float q0 = (l0.x + l0.y) + (l0.z + l0.w), q1 = (l1.x + l1.y) + (l1.z + l1.w);
-        const float q2 = (l2.x + l2.y) + (l2.z + l2.w), q3 = (l3.x + l3.y) + (l3.z + l3.w);
-        six[tid] = (q0 + q1) + (q2 + q3);
+    float scale;
+    {
+        const int r = (lane >> 2) < NR ? lane >> 2 : NR - 1, w = (lane & 3) < WS ? lane & 3 : 0;
+        const f32x4* b = reinterpret_cast<const f32x4*>(sq + r * kRow + w * 8);
+        const f32x4 b0 = b[0], b1 = b[1];
+        const float wsum = (((b0.x + b0.y) + (b0.z + b0.w)) + (b1.x + b1.y)) + (b1.z + b1.w);
+        float total = dpp_take<0x00>(wsum);                                // quad_perm: lane 0 of the quad in all four ...
+        if constexpr (WS > 1) total += dpp_take<0x55>(wsum);               // ... lane 1, 2, 3
+        if constexpr (WS > 2) { total += dpp_take<0xAA>(wsum); total += dpp_take<0xFF>(wsum); }
+        scale = 1.0f / sqrtf(total / (float)cols + eps);
     }
-    lds_barrier();
-    if (tid < NR) {
-        const f32x4* sx = reinterpret_cast<const f32x4*>(six + tid * KS);
-        float total = 0.f;
-#pragma unroll
-        for (int w = 0; w < KS / 4; w++) {
-            const float wsum = ((sx[w].x + sx[w].y) + sx[w].z) + sx[w].w;
-            total = w == 0 ? wsum : total + wsum;
-        }
-        scale[tid] = 1.0f / sqrtf(total / (float)cols + eps);
-    }
-    lds_barrier();
     float fg[8];
     Vec<bf16_t, 16>::unpack(wg, fg);
 #pragma unroll
     for (int q = 0; q < Q; q++) {
         float fo[8];
-        const float sc = scale[q * RPI + sub];
+        const float sc = RPI == 1 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scale), q * 4))
+                                  : __int_as_float(__builtin_amdgcn_ds_bpermute((q * RPI + sub) * 16, __float_as_int(scale)));
 #pragma unroll
         for (int e = 0; e < 8; e++) fo[e] = (fx[q][e] * sc) * fg[e];
         Vec<bf16_t, 16>::pack(fo, g[q]);
@@ -749,9 +757,8 @@ __device__ __forceinline__ void mm_rmsnorm_rows(unsigned (*g)[4], const unsigned
     }
 }
 
-// NC = 8: one tile of rows, the grid is the column blocks; NC = 16: (column blocks) x (tiles of rows), column block
-// fastest, so that the tiles of one column block share an XCD's L2.  The workgroups of column block 0 store the
-// normalised rows.
+// The grid is (column blocks) x (tiles of rows), the tiles of one column block next to each other, so that they share an XCD's
+// L2.  The workgroups of column block 0 store the normalised rows.
 template <int KS, bool TAIL, int NR, int NC, Ride RIDE>
 __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void k_gemm_rows(RideArgs<RIDE> p) {
     constexpr bool PRO = RIDE == kPrologue;
@@ -759,18 +766,19 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
     constexpr int kWaveLds = 4 * KS * kMmSlotBytes;
     __shared__ __attribute__((aligned(16))) char stage[4 * kWaveLds];
     __shared__ float red[4 * 64 * 4];
-    static_assert((NR * (21 * KS + 1)) * sizeof(float) <= sizeof stage, "the prologue's sums fit the staging area");
+    __shared__ __attribute__((aligned(16))) float sq[PRO ? NR * (2 * KS + 4) : 4];
     MmEpilogue<1, RIDE != kAlone> emit;
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ncb = (m.n + NC - 1) / NC;
-    const int ntiles = NC == 8 ? 1 : (m.rows + 15) / 16;
+    const unsigned ncb = (unsigned)(m.n + NC - 1) / NC;
+    const unsigned ntiles = (unsigned)m.row_groups & 0xffu, inv = (unsigned)m.row_groups >> 8;      // 65536 / ntiles (plan_gemm)
     // one tile of rows and a grid of several rounds: columns dealt out in turn stream better (us per launch, 5 rows of 2048 columns, 16384
     // outputs 17.6 -> 15.9, 1024 columns, 32768 outputs 16.2 -> 13.9); otherwise a stretch per XCD (below 1024 workgroups 0.1 - 0.3 us
     // faster at every size, and tiles of rows share their columns)
-    const int at = NC == 8 && ncb > 1024 ? (int)blockIdx.x : (int)xcd_stretch(blockIdx.x, (unsigned)(ncb * ntiles)), cb = at / ntiles, tile = at % ntiles;
+    const unsigned at = ntiles == 1 && ncb > 1024 ? blockIdx.x : xcd_stretch(blockIdx.x, ncb * ntiles);
+    const int cb = (int)(ntiles == 1 ? at : (at * inv) >> 16), tile = (int)(at - (unsigned)cb * ntiles);
     const int cols = TAIL ? m.cols : 128 * KS;
-    const int j0 = cb * NC, r0 = tile * 16;
+    const int j0 = cb * NC, r0 = tile * NR;
     if (r0 >= m.rows) return;                            // whole workgroup: nothing waits on it
     char* lds = stage + wave * kWaveLds;
     unsigned g[NR * KS / 16][4], gw[NC * KS / 16][4];
@@ -782,14 +790,13 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
     mm_load_rows<KS, TAIL, NC, true>(m.W, m.n, cols, j0, wave, lane, gw);
     emit.prepare();                                      // the epilogue's table right behind the weight loads
     // output stage: wave w finishes row w of the four that an accumulator lane holds
-    auto emit_begin = [&] { emit.begin(r0 + (lane >> 4) * 4 + wave, j0 + (lane & 15), NC == 16 || (lane & 15) < NC); };
-    if constexpr (NC == 8) emit_begin();
+    auto emit_begin = [&] { emit.begin(r0 + (lane >> 4) * 4 + wave, j0 + (lane & 15), (lane & 15) < NC && (lane >> 4) * 4 < NR); };
+    if constexpr (NC == 8 || NR < 16) emit_begin();
     mm_fix_rows<KS, TAIL, NR>(cols, wave, lane, g);
     if constexpr (PRO) {
         span_fix<!TAIL>(cols, mm_k0(wave, lane % (4 * KS)) >> 3, wg);
         bf16_t* hs = (m.hstore && cb == 0) ? m.hstore + (size_t)r0 * cols : nullptr;
-        mm_rmsnorm_rows<KS, TAIL, NR>(g, wg, emit.eps, hs, m.rows - r0, cols, wave, lane, reinterpret_cast<float*>(stage));
-        lds_barrier();        // the sums are read: the staging area takes the rows now
+        mm_rmsnorm_rows<KS, TAIL, NR>(g, wg, emit.eps, hs, m.rows - r0, cols, wave, lane, sq);
     }
     mm_stage<KS, NR>(lds, lane, g);
     mm_read_frags<KS>(lds, lane, a);
@@ -797,7 +804,7 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
     mm_stage<KS, NC>(lds, lane, gw);
     mm_read_frags<KS>(lds, lane, b);
     __builtin_amdgcn_sched_barrier(0);   // all fragment reads before the first multiply, not one LDS latency per pair
-    if constexpr (NC != 8) emit_begin();
+    if constexpr (NC != 8 && NR == 16) emit_begin();
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < KS; i++)
@@ -1349,21 +1356,40 @@ const void* rows_kernel(int rows, int n, int cols) {
 bool mm_served(long long rows, long long n, long long cols) { return rows > 4 && cols >= 8 && cols <= (1ll << 26) && rows * n <= (1ll << 32); }
 
 template <int KS, bool TAIL, Ride RIDE>
-const void* gemm_rows_kernel(int rows) {
-    if (rows <= 8) return PG_FN(k_gemm_rows<KS, TAIL, 8, 8, RIDE>);
-    if (rows <= 16) return PG_FN(k_gemm_rows<KS, TAIL, 16, 8, RIDE>);
-    if constexpr (RIDE == kPrologue) return PG_FN(k_gemm_rows<KS, TAIL, 16, 16, kPrologue>);
-    else return nullptr;
+const void* gemm_rows_kernel(int nr, int nc) {
+    if constexpr (RIDE == kPrologue) {
+        if (nr == 4) return nc == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 4, 8, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 4, 16, RIDE>);
+        if (nc == 16) return nr == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 8, 16, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 16, 16, RIDE>);
+    }
+    return nr == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 8, 8, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 16, 8, RIDE>);
 }
 template <Ride RIDE>
-const void* gemm_rows_form(int rows, int cols) {
-    if (cols <= 1024) return cols == 1024 ? gemm_rows_kernel<8, false, RIDE>(rows) : gemm_rows_kernel<8, true, RIDE>(rows);
-    return cols == 2048 ? gemm_rows_kernel<16, false, RIDE>(rows) : gemm_rows_kernel<16, true, RIDE>(rows);
+const void* gemm_rows_form(int nr, int nc, int cols) {
+    if (cols <= 512) return cols == 512 ? gemm_rows_kernel<4, false, RIDE>(nr, nc) : gemm_rows_kernel<4, true, RIDE>(nr, nc);
+    if (cols <= 1024) return cols == 1024 ? gemm_rows_kernel<8, false, RIDE>(nr, nc) : gemm_rows_kernel<8, true, RIDE>(nr, nc);
+    return cols == 2048 ? gemm_rows_kernel<16, false, RIDE>(nr, nc) : gemm_rows_kernel<16, true, RIDE>(nr, nc);
 }
 template <Ride RIDE, bool WNT>
 const void* gemm_cols_form(int cols) {
     if (cols <= 1024) return cols == 1024 ? PG_FN(k_gemm_cols<8, false, true, RIDE>) : PG_FN(k_gemm_cols<8, true, true, RIDE>);
     return cols == 2048 ? PG_FN(k_gemm_cols<16, false, WNT, RIDE>) : PG_FN(k_gemm_cols<16, true, WNT, RIDE>);
+}
+// The tile of a workgroup that normalises its own rows: the cheapest whose grid is still one workgroup per CU.  A row costs its bytes and its
+// normalising, an output its bytes.  Decode chains, us per sub-block, rows x outputs of the tile, in brackets the workgroups (measured with a branch per row in
+// the sums of squares; without it all of them are 0.1 - 0.3 faster):
+//   16 rows of 2048 columns  8 x 16 [256] 5.58, 16 x 8 [256] 5.96, 8 x 8 [512] 6.90    8 of 2048  8 x 8 [256] 4.78, 4 x 16 [256] 4.97, 4 x 8 [512] 5.93
+//   32 of 2048  16 x 16 [256] 6.83, 8 x 16 [512] 7.76       32 of 1024  8 x 16 [256] 3.83, 16 x 8 [256] 4.25, 16 x 16 [128] 4.40, 4 x 16 [512] 4.52
+//   16 of 1024  4 x 16 [256] 3.43, 8 x 8 [256] 3.63, 8 x 16 [128] 3.78, 16 x 8 [128] 4.18    8 of 1024  4 x 8 [256] 3.31, 4 x 16 [128] 3.38, 8 x 8 [128] 3.54
+//   16 of 520  4 x 16 [132] 3.86, 8 x 8 [130] 3.94, 4 x 8 [260] 4.11    32 of 400  4 x 16 [200] 3.27, 8 x 8 [200] 3.39, 4 x 8 [400] 3.64
+// Where none fits (more than 2048 outputs at 8 rows, 1024 at 17): 8 outputs up to 16 rows, all of them in one tile, 16 above.
+void prologue_tile(int rows, int n, int cols, int* nr, int* nc) {
+    static const int by_cost[2][5][2] = {{{4, 8}, {4, 16}, {8, 8}, {8, 16}, {16, 16}}, {{4, 8}, {8, 8}, {4, 16}, {8, 16}, {16, 16}}};
+    for (const auto& t : by_cost[cols > 1024])
+        if ((long long)blocks_for(n, t[1]) * blocks_for(rows, t[0]) <= 256) {
+            *nr = t[0];
+            *nc = t[1];
+            return;
+        }
 }
 void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     const bool merged = ride != kAlone;
@@ -1373,8 +1399,12 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     out->gemm_row_groups = (unsigned)ntiles;
     out->fn_beyond_cache = nullptr;
     if (ride == kPrologue || (rows <= 16 && cols <= 2048)) {
-        out->fn = ride == kPrologue ? gemm_rows_form<kPrologue>(rows, cols) : merged ? gemm_rows_form<kEpilogue>(rows, cols) : gemm_rows_form<kAlone>(rows, cols);
-        out->grid = rows <= 16 ? dim3(blocks_for(n, 8)) : dim3(blocks_for(n, 16) * (unsigned)ntiles);
+        int nr = rows <= 8 ? 8 : 16, nc = rows <= 16 ? 8 : 16;
+        if (ride == kPrologue) prologue_tile(rows, n, cols, &nr, &nc);
+        const unsigned tiles = blocks_for(rows, nr);
+        out->fn = ride == kPrologue ? gemm_rows_form<kPrologue>(nr, nc, cols) : merged ? gemm_rows_form<kEpilogue>(nr, nc, cols) : gemm_rows_form<kAlone>(nr, nc, cols);
+        out->gemm_row_groups = tiles | ((65535u + tiles) / tiles) << 8;
+        out->grid = dim3(blocks_for(n, nc) * tiles);
         return;
     }
     // (decode chain of 2048 columns at 48 / 64 rows: 1175 / 1188 us, with k_gemm_tile's 16 x 16 tiles 1254 / 1261)

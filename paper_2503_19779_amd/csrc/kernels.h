@@ -224,7 +224,7 @@ struct Launch {
     unsigned arg_bytes = 0;          // size of the kernel's argument block
     dim3 grid{1, 1, 1};
     dim3 block{1, 1, 1};
-    unsigned gemm_row_groups = 0;    // GEMV on the matrix cores: goes into GemvArgs::row_groups (0 = other kernels)
+    unsigned gemm_row_groups = 0;    // GEMV on the matrix cores: goes into GemvArgs::row_groups (0 = other kernels); k_gemm_rows: tiles of rows | (65536 / tiles, rounded up) << 8
     const void* fn_beyond_cache = nullptr;      // ... and the kernel that takes its weights by non-temporal loads, where the chain settles that (settle_weights)
 };
 
@@ -281,7 +281,7 @@ bool plan_sbr_run(int dtype, long long n, long long inner, Launch* out);
 bool merge_head(int op, int dtype, const Shape& shape, long long* n_out);
 // ... and does it also take the RMSNorm in front?  While the grid is small enough (gemv.hip); the matrix-core forms up to 2048
 // columns, and up to kPrologueMaxRows rows:
-// two tiles of 16 rows, one per workgroup, fill the 256 CUs once; beyond, two workgroups share a CU and each
+// two tiles of 16 rows, one per workgroup, fill the 256 CUs once at 2048 columns; beyond, two workgroups share a CU and each
 // normalises its tile, which costs more than the dispatch it saves (decode chain at 48 rows: 1261 -> 1336 us).
 constexpr int kPrologueMaxRows = 32;
 bool merge_prologue(const Shape& shape);
