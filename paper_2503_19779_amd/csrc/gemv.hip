@@ -392,17 +392,18 @@ struct MmEpilogue {
         }
         if constexpr (NE % 2 == 0) vec = (head & kEpiPlain) && n % VW == 0 && (low & (2u * VW - 1)) == 0;
     }
-    __device__ __forceinline__ void begin(int r, int j, bool col_ok) {
+    __device__ __forceinline__ void index(int r, int j, bool col_ok) {
 #pragma unroll
         for (int e = 0; e < NE; e++) {
             ok[e] = col_ok && r < rows && j + e < n;
             idx[e] = ok[e] ? (unsigned)r * (unsigned)n + (unsigned)(j + e) : 0u;
         }
-        if constexpr (!EPI) return;
-        if (__builtin_expect((head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec), 1)) {      // two operands, in in1 (see kernels.h)
-            fetch(q1[1], ld1[1]);
-            fetch(q1[2], ld1[2]);
-        } else if (head & kEpiPlain) {         // one branch for all: no division where no operand has a period
+    }
+    // the decoder block's tail with a layout that lets it be played straight through
+    __device__ __forceinline__ bool straight() const { return (head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec); }
+    // what any other tail reads
+    __device__ __forceinline__ void fetch_any() {
+        if (head & kEpiPlain) {                // one branch for all: no division where no operand has a period
 #pragma unroll
             for (int i = 0; i < P; i++)
 #pragma unroll
@@ -422,23 +423,43 @@ struct MmEpilogue {
             }
         }
     }
-    // NE columns of a tensor read element for element
-    __device__ __forceinline__ void fetch(const bf16_t* q, unsigned* raw) {
-        if constexpr (NE % 2 == 1) {
+    __device__ __forceinline__ void begin(int r, int j, bool col_ok) {
+        index(r, j, col_ok);
+        if constexpr (!EPI) return;
+        static_assert(!EPI || NE == 1, "several columns a lane: early and late");      // (words taken apart at once would be waited for at once)
+        if (__builtin_expect(straight(), 1)) {             // two operands, in in1 (see kernels.h)
 #pragma unroll
-            for (int e = 0; e < NE; e++) raw[e] = load_raw_global_at(q, idx[e]);
+            for (int i = 1; i < P; i++) ld1[i][0] = load_raw_global_at(q1[i], idx[0]);
         } else {
+            fetch_any();
+        }
+    }
+    // NE even, beside loads that go to LDS directly: while such loads are outstanding the compiler waits for all of them wherever it
+    // meets a register that some load may write, on any path.  So the straight tail's operands go to LDS directly as well, a word of two columns per
+    // lane and piece (kTailBytes of LDS per wave), and other tails fetch theirs when the sums are there.
+    static constexpr int kPieces = NE / 2, kTailBytes = 2 * (kPieces ? kPieces : 1) * 256;
+    __device__ __forceinline__ void early(int r, int j, bool col_ok, char* to /* uniform */) {
+        index(r, j, col_ok);
+        if (__builtin_expect(straight(), 1))
 #pragma unroll
-            for (int e = 0; e < NE; e += VW) {
-                const unsigned short PG_GLOBAL* at = (const unsigned short PG_GLOBAL*)(uintptr_t)q + idx[e];
-                if constexpr (VW == 4) {
-                    const v2u t = *(const v2u PG_GLOBAL*)at;
-                    raw[e] = t.x & 0xffffu; raw[e + 1] = t.x >> 16; raw[e + 2] = t.y & 0xffffu; raw[e + 3] = t.y >> 16;
-                } else {
-                    const unsigned t = *(const unsigned PG_GLOBAL*)at;
-                    raw[e] = t & 0xffffu; raw[e + 1] = t >> 16;
+            for (int i = 1; i < P; i++)
+#pragma unroll
+                for (int e = 0; e < NE; e += 2)
+                    __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const unsigned short PG_GLOBAL*)(uintptr_t)q1[i] + idx[e]),
+                                                     (__attribute__((address_space(3))) void*)(to + ((i - 1) * kPieces + e / 2) * 256), 4, 0, 0);
+    }
+    __device__ __forceinline__ void late(const char* from, int lane) {
+        if (__builtin_expect(straight(), 1)) {
+            __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
+#pragma unroll
+            for (int i = 1; i < P; i++)
+#pragma unroll
+                for (int e = 0; e < NE; e += 2) {
+                    const unsigned t = reinterpret_cast<const unsigned*>(from + ((i - 1) * kPieces + e / 2) * 256)[lane];
+                    ld1[i][e] = t & 0xffffu; ld1[i][e + 1] = t >> 16;
                 }
-            }
+        } else {
+            fetch_any();
         }
     }
     __device__ __forceinline__ void store(bf16_t* o, const unsigned* b) {
@@ -473,7 +494,7 @@ struct MmEpilogue {
 #pragma unroll
         for (int e = 0; e < NE; e++) bits[e] = f32_to_bf16(v[e]);
         if (head & kEpiHeadStore) store(y, bits);
-        if (__builtin_expect((head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec), 1)) {
+        if (__builtin_expect(straight(), 1)) {
             // the same kernels with the same arithmetic and roundings, operands known: GELU of the GEMV's rounded result,
             // then each add takes the value before it and its operand from memory, in the order its descriptor names
 #pragma unroll
@@ -894,6 +915,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
 // each, so that one wave's fragment reads and multiplies hide behind another's (with four waves a round of one block
 // cost them 0.3 us in turn); stand-alone launches keep workgroups of four waves (two parts a wave, whose blocks take turns
 // in one stream): the same bits.
+// The epilogue's operands come into LDS as well (MmEpilogue::early): as loads into registers they made the compiler wait for the first block, for
+// each operand and for the second block in turn before the loop.  us per RMSNorm and GEMV without / with: 128 rows of 2048 columns 10.62 / 10.34, of 1024 7.42 /
+// 7.00, 16 of 3072 10.44 / 10.15, 8 of 4096 12.09 / 11.61, 81 of 520 6.85 / 6.57; two workgroups of 16 x 16 to a CU hide such waits from each
+// other: 20 of 2304 9.63 / 9.79.
 // Decode chains, us per iteration, before and after: 128 rows of 2048 columns, 120 sub-blocks 1529 -> 1330; 100 x 2000 (100
 // sub-blocks) 1290 -> 850, 128 x 1024 1282 -> 793 (there also one dispatch instead of three around the GEMV); one GEMV alone, us
 // per launch: 128 rows by 4096 x 4096 34.0 -> 17.4, by 2048 x 2048 8.1 -> 7.8 (the 16- and 32-column forms it replaces re-read W
@@ -936,13 +961,15 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
     constexpr int PK = 8 / NW;                           // eighths of K per wave
     constexpr int kRedRow = 16 * CT + 4;                 // floats of a row of partial sums, padded: rows 4 apart fall into other banks
     constexpr int kRed = 16 * RT * kRedRow;              // floats of one eighth's partial sums
-    constexpr int NE = RT * CT * 4 >= NW ? RT * CT * 4 / NW : 1, kPerRow = 16 * CT / NE;  // outputs per lane (consecutive columns), lanes per row of the tile
+    constexpr int kEach = RT * CT * 4 / NW, NE = kEach >= 2 ? kEach : NW == 8 ? 2 : 1, kPerRow = 16 * CT / NE;  // outputs per lane (consecutive columns), lanes per row of the tile
     static_assert(PK * kRed * 4 <= kWaveLds, "a wave's partial sums fit its ring");
     static_assert(S == 1 || S == 2, "the waits below name the blocks in flight");
     constexpr Ride RIDE = NW == 8 ? kEpilogue : kAlone;  // four waves: a stand-alone launch
     const MmHead m = mm_head<RIDE>(p);
+    using Emit = MmEpilogue<NE, RIDE != kAlone>;
     __shared__ __attribute__((aligned(128))) char ring[NW * kWaveLds];
-    MmEpilogue<NE, RIDE != kAlone> emit;
+    __shared__ __attribute__((aligned(16))) char tails[RIDE != kAlone ? NW * Emit::kTailBytes : 16];
+    Emit emit;
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = m.rows, n = m.n, cols = m.cols;
@@ -977,7 +1004,8 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
     // the epilogue's table behind the first block's loads: asked for behind all of them it came 1.1 us later
     auto epilogue_begin = [&] {
         emit.prepare();
-        emit.begin(r0 + er, j0 + ec, er < 16 * RT);
+        if constexpr (RIDE == kAlone) emit.index(r0 + er, j0 + ec, er < 16 * RT);
+        else emit.early(r0 + er, j0 + ec, er < 16 * RT, tails + wave * Emit::kTailBytes);
     };
     // this wave's K-blocks: wave, wave + NW, ...; number b of them belongs to its eighth b % PK
     const int nb = (nkb - wave + NW - 1) / NW;
@@ -1066,6 +1094,7 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
                 const f32x4 v = acc[pk][i][j];
                 dst[0] = v.x; dst[kRedRow] = v.y; dst[2 * kRedRow] = v.z; dst[3 * kRedRow] = v.w;
             }
+    if constexpr (RIDE != kAlone) emit.late(tails + wave * Emit::kTailBytes, lane);
     lds_barrier();
     if (er < 16 * RT) {
 #pragma unroll
