@@ -237,10 +237,9 @@ __device__ __forceinline__ unsigned xcd_stretch(unsigned b, unsigned total) {
 
 // ---- five rows of h and more: the matrix cores ----------------------------------------------------------
 // bf16, v_mfma_f32_16x16x32_bf16 with fp32 accumulation.  A GEMV's output has the same bits whichever launch of it
-// computes it (eager, merged, with a prologue): k_gemm_rows and k_gemm_cols cut K into blocks of 64; wave w of the
-// workgroup's four takes blocks w, w + 4, ... in order, two K-steps of 32 each; the four partial sums are added as
-// ((p0 + p1) + p2) + p3.  k_gemm_tile deals the blocks out to eight parts instead, whose shorter sums err less (rows of W that cancel
-// to zero, 128 rows of h, 2048 x 2048: rms of the outputs, which should be 0, 3.9e-6 where four parts gave 5.3e-6).
+// computes it (eager, merged, with a prologue): K is cut into blocks of 64 and these are dealt out to eight parts in turn; a part's blocks are added up in
+// order, two K-steps of 32 each, then parts i and i + 4, then those four sums in order.  Eight waves take a part each, four two each, side by side.  (Four parts err more: rows of W that
+// cancel to zero, 128 rows of h, 2048 x 2048: rms of the outputs, which should be 0, 5.3e-6 where eight give 3.9e-6.)
 // (Fragments -- A: lane l holds row l & 15, B: column l & 15;
 // the eight consecutive k's of chunk l >> 4 of a step; accumulators: lane l holds column l & 15, rows 4 * (l >> 4) .. + 3.)
 // Elements beyond a row's end are zeros on both sides: zeroing the weight side alone would turn an Inf or NaN of h
@@ -249,7 +248,10 @@ __device__ __forceinline__ unsigned xcd_stretch(unsigned b, unsigned total) {
 //   - k_gemm_rows: one tile of 8 or 16 rows of h per workgroup, up to 2048 columns, all loads in flight at once; the
 //     form that can carry the RMSNorm in front;
 //   - k_gemm_cols: 17 to 80 rows of up to 2048 columns, and any more rows with up to 16 outputs each;
+//   - k_gemm_whole: with kernels that ride behind, from 17 rows on, up to 2048 columns, where its grid is one workgroup per CU;
 //   - k_gemm_tile: everything else, K streamed through a ring in LDS.
+template <class Part>
+__device__ __forceinline__ float parts_sum(Part part) { return (((part(0) + part(4)) + (part(1) + part(5))) + (part(2) + part(6))) + (part(3) + part(7)); }
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
@@ -426,10 +428,10 @@ struct MmEpilogue {
     __device__ __forceinline__ void begin(int r, int j, bool col_ok) {
         index(r, j, col_ok);
         if constexpr (!EPI) return;
-        static_assert(!EPI || NE == 1, "several columns a lane: early and late");      // (words taken apart at once would be waited for at once)
-        if (__builtin_expect(straight(), 1)) {             // two operands, in in1 (see kernels.h)
-#pragma unroll
-            for (int i = 1; i < P; i++) ld1[i][0] = load_raw_global_at(q1[i], idx[0]);
+        static_assert(!EPI || NE == 1, "several columns a lane: early and late");
+        if (__builtin_expect((head & kEpiDecoder) && (head & kEpiPlain), 1)) {             // two operands, in in1 (see kernels.h)
+            ld1[1][0] = load_raw_global_at(q1[1], idx[0]);
+            ld1[2][0] = load_raw_global_at(q1[2], idx[0]);
         } else {
             fetch_any();
         }
@@ -447,6 +449,33 @@ struct MmEpilogue {
                 for (int e = 0; e < NE; e += 2)
                     __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const unsigned short PG_GLOBAL*)(uintptr_t)q1[i] + idx[e]),
                                                      (__attribute__((address_space(3))) void*)(to + ((i - 1) * kPieces + e / 2) * 256), 4, 0, 0);
+    }
+    // Beside loads into registers only: two columns' words stay as they come in until late_words(); taking them apart at once would wait for them and
+    // for every load before them.  Other tails fetch theirs late here too, so that every wait on the rows and weights knows what is outstanding.
+    __device__ __forceinline__ void early_words(int r, int j, bool col_ok) {
+        index(r, j, col_ok);
+        if (__builtin_expect(straight(), 1))
+#pragma unroll
+            for (int i = 1; i < P; i++) {
+                if constexpr (NE == 1) ld1[i][0] = load_raw_global_at(q1[i], idx[0]);
+                else
+#pragma unroll
+                    for (int e = 0; e < NE; e += 2) ld1[i][e / 2] = *(const unsigned PG_GLOBAL*)((const unsigned short PG_GLOBAL*)(uintptr_t)q1[i] + idx[e]);
+            }
+    }
+    __device__ __forceinline__ void late_words() {
+        if (__builtin_expect(straight(), 1)) {
+            if constexpr (NE > 1)
+#pragma unroll
+                for (int i = 1; i < P; i++)
+#pragma unroll
+                    for (int e = NE - 2; e >= 0; e -= 2) {
+                        const unsigned t = ld1[i][e / 2];
+                        ld1[i][e] = t & 0xffffu; ld1[i][e + 1] = t >> 16;
+                    }
+        } else {
+            fetch_any();
+        }
     }
     __device__ __forceinline__ void late(const char* from, int lane) {
         if (__builtin_expect(straight(), 1)) {
@@ -568,6 +597,7 @@ struct MmEpilogue {
 // so that they stay between the two, make it independent of that.
 __device__ __forceinline__ void mm_drained(f32x4& acc) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc)); }
 
+__device__ __forceinline__ void mm_drained(f32x4& a, f32x4& b) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(a), "+v"(b)); }
 
 // What rides in a GEMV's dispatch: nothing, elementwise kernels behind it, or those and the RMSNorm in front.
 enum Ride { kAlone, kEpilogue, kPrologue };
@@ -786,7 +816,7 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
     const MmHead m = mm_head<RIDE>(p);
     constexpr int kWaveLds = 4 * KS * kMmSlotBytes;
     __shared__ __attribute__((aligned(16))) char stage[4 * kWaveLds];
-    __shared__ float red[4 * 64 * 4];
+    __shared__ float red[4 * 4 * 64];
     __shared__ __attribute__((aligned(16))) float sq[PRO ? NR * (2 * KS + 4) : 4];
     MmEpilogue<1, RIDE != kAlone> emit;
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
@@ -826,13 +856,14 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
     mm_read_frags<KS>(lds, lane, b);
     __builtin_amdgcn_sched_barrier(0);   // all fragment reads before the first multiply, not one LDS latency per pair
     if constexpr (NC != 8 && NR == 16) emit_begin();
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};         // the wave's two eighths of K, whose blocks take turns
 #pragma unroll
     for (int i = 0; i < KS; i++)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[i]), acc, 0, 0, 0);
-    mm_drained(acc);
+        acc[i / 2 % 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[i]), acc[i / 2 % 2], 0, 0, 0);
+    mm_drained(acc[0], acc[1]);
+    const f32x4 both = acc[0] + acc[1];
     float* dst = red + ((size_t)wave * 64 + lane) * 4;
-    dst[0] = acc.x; dst[1] = acc.y; dst[2] = acc.z; dst[3] = acc.w;
+    dst[0] = both.x; dst[1] = both.y; dst[2] = both.z; dst[3] = both.w;
     __syncthreads();
     const float p0 = red[((size_t)0 * 64 + lane) * 4 + wave], p1 = red[((size_t)1 * 64 + lane) * 4 + wave];
     const float p2 = red[((size_t)2 * 64 + lane) * 4 + wave], p3 = red[((size_t)3 * 64 + lane) * 4 + wave];
@@ -882,13 +913,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
     for (int t = t0;;) {
         __builtin_amdgcn_sched_barrier(0);   // all fragment reads before the first multiply, not one LDS latency per pair
         emit.begin(t * 16 + er, j0 + ec, true);
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};     // the wave's two eighths of K, whose blocks take turns
 #pragma unroll
         for (int i = 0; i < KS; i++)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[i]), acc, 0, 0, 0);
-        mm_drained(acc);
+            acc[i / 2 % 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[i]), __builtin_bit_cast(bf16x8, b[i]), acc[i / 2 % 2], 0, 0, 0);
+        mm_drained(acc[0], acc[1]);
         float* dst = red[wave] + (lane >> 4) * 4 * kRedRow + (lane & 15);
-        dst[0] = acc.x; dst[kRedRow] = acc.y; dst[2 * kRedRow] = acc.z; dst[3 * kRedRow] = acc.w;
+        dst[0] = acc[0].x + acc[1].x; dst[kRedRow] = acc[0].y + acc[1].y; dst[2 * kRedRow] = acc[0].z + acc[1].z; dst[3 * kRedRow] = acc[0].w + acc[1].w;
         lds_barrier();
         const int q = er * kRedRow + ec;
         emit.put(0, ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q]);
@@ -911,14 +942,14 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
 // row r sits at c ^ (r & 7)), so that the fragment reads of eight consecutive lanes touch all banks once.
 // What bounds it is what a CU takes in through its cache ((RT + CT) * 32 bytes * cols per RT * CT * 256 outputs), hence larger
 // tiles where there are enough of them (plan_gemm); a CU holds no more than its 32 KB cache's worth of lines in flight.
-// K is cut into blocks of 64 and dealt out to eight parts in turn, whose sums are added in order.  Eight waves, one part
+// K is cut into blocks of 64 and dealt out to eight parts in turn.  Eight waves, one part
 // each, so that one wave's fragment reads and multiplies hide behind another's (with four waves a round of one block
 // cost them 0.3 us in turn); stand-alone launches keep workgroups of four waves (two parts a wave, whose blocks take turns
 // in one stream): the same bits.
 // The epilogue's operands come into LDS as well (MmEpilogue::early): as loads into registers they made the compiler wait for the first block, for
 // each operand and for the second block in turn before the loop.  us per RMSNorm and GEMV without / with: 128 rows of 2048 columns 10.62 / 10.34, of 1024 7.42 /
 // 7.00, 16 of 3072 10.44 / 10.15, 8 of 4096 12.09 / 11.61, 81 of 520 6.85 / 6.57; two workgroups of 16 x 16 to a CU hide such waits from each
-// other: 20 of 2304 9.63 / 9.79.
+// other, 20 of 2304 9.63 / 9.79, and keep the loads into registers.
 // Decode chains, us per iteration, before and after: 128 rows of 2048 columns, 120 sub-blocks 1529 -> 1330; 100 x 2000 (100
 // sub-blocks) 1290 -> 850, 128 x 1024 1282 -> 793 (there also one dispatch instead of three around the GEMV); one GEMV alone, us
 // per launch: 128 rows by 4096 x 4096 34.0 -> 17.4, by 2048 x 2048 8.1 -> 7.8 (the 16- and 32-column forms it replaces re-read W
@@ -955,20 +986,23 @@ __device__ __forceinline__ void ring_frags(unsigned at0, unsigned at1, v4u (&f)[
                      : "v"(at0), "v"(at1) : "memory");
 }
 
-template <int RT, int CT, int S, int NW, bool WNT>
+// ASIDE: the operands of a straight tail come into LDS beside the ring (MmEpilogue::early).
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+template <int RT, int CT, int S, int NW, bool WNT, bool ASIDE = true>
 __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gemm_tile(RideArgs<NW == 8 ? kEpilogue : kAlone> p) {
     constexpr int F = RT + CT, NL = 2 * F, kBlockLds = F * 2048, kWaveLds = S * kBlockLds;
     constexpr int PK = 8 / NW;                           // eighths of K per wave
     constexpr int kRedRow = 16 * CT + 4;                 // floats of a row of partial sums, padded: rows 4 apart fall into other banks
     constexpr int kRed = 16 * RT * kRedRow;              // floats of one eighth's partial sums
-    constexpr int kEach = RT * CT * 4 / NW, NE = kEach >= 2 ? kEach : NW == 8 ? 2 : 1, kPerRow = 16 * CT / NE;  // outputs per lane (consecutive columns), lanes per row of the tile
+    constexpr int kEach = RT * CT * 4 / NW, NE = kEach >= 2 ? kEach : NW == 8 && ASIDE ? 2 : 1, kPerRow = 16 * CT / NE;  // outputs per lane (consecutive columns), lanes per row of the tile
     static_assert(PK * kRed * 4 <= kWaveLds, "a wave's partial sums fit its ring");
     static_assert(S == 1 || S == 2, "the waits below name the blocks in flight");
     constexpr Ride RIDE = NW == 8 ? kEpilogue : kAlone;  // four waves: a stand-alone launch
     const MmHead m = mm_head<RIDE>(p);
     using Emit = MmEpilogue<NE, RIDE != kAlone>;
-    __shared__ __attribute__((aligned(128))) char ring[NW * kWaveLds];
-    __shared__ __attribute__((aligned(16))) char tails[RIDE != kAlone ? NW * Emit::kTailBytes : 16];
+    constexpr int kTails = RIDE != kAlone && ASIDE ? Emit::kTailBytes : 0;
+    __shared__ __attribute__((aligned(128))) char ring[NW * (kWaveLds + kTails)];
+    char* const tail = ring + NW * kWaveLds + wave_index() * kTails;
     Emit emit;
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1005,7 +1039,8 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
     auto epilogue_begin = [&] {
         emit.prepare();
         if constexpr (RIDE == kAlone) emit.index(r0 + er, j0 + ec, er < 16 * RT);
-        else emit.early(r0 + er, j0 + ec, er < 16 * RT, tails + wave * Emit::kTailBytes);
+        else if constexpr (ASIDE) emit.early(r0 + er, j0 + ec, er < 16 * RT, tail);
+        else emit.begin(r0 + er, j0 + ec, er < 16 * RT);
     };
     // this wave's K-blocks: wave, wave + NW, ...; number b of them belongs to its eighth b % PK
     const int nb = (nkb - wave + NW - 1) / NW;
@@ -1094,18 +1129,138 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
                 const f32x4 v = acc[pk][i][j];
                 dst[0] = v.x; dst[kRedRow] = v.y; dst[2 * kRedRow] = v.z; dst[3 * kRedRow] = v.w;
             }
-    if constexpr (RIDE != kAlone) emit.late(tails + wave * Emit::kTailBytes, lane);
+    if constexpr (RIDE != kAlone && ASIDE) emit.late(tail, lane);
     lds_barrier();
     if (er < 16 * RT) {
 #pragma unroll
         for (int e = 0; e < NE; e++) {
-            float sum = 0.f;
+            auto part = [&](int w) { return reinterpret_cast<const float*>(ring + (w % NW) * kWaveLds)[(w / NW) * kRed + er * kRedRow + ec + e]; };
+            emit.put(e, parts_sum(part));
+        }
+        emit.end();
+    }
+}
+
+// ---- k_gemm_whole --------------------------------------------------------------------------------------------
+// k_gemm_tile's tiles for rows of up to 512 * KB columns where the grid is one workgroup per CU: eight waves, an eighth of K each (KB blocks of 64 columns),
+// all of whose loads are asked for at once, into registers, vectors at any element boundary; block by block they pass through the wave's own part of
+// LDS into fragment order (chunk c of row r at c ^ (r & 7), two buffers, so that a block is written while the one before is multiplied).
+// What bounds it is what a CU takes in: 256 KB at 128 rows of 2048 columns, 5.0 us for the loads alone with their node (a row's lines in two loads of 64
+// bytes, straight into fragment order, 9.4).  h first, then the weights: in alternation the loads alone take 5.9.
+// Registers and not direct loads into LDS: behind those the compiler waits for everything outstanding wherever it needs a register that was loaded.
+// us per RMSNorm and GEMV, k_gemm_cols or k_gemm_tile / this: 64 rows of 2048 columns 9.33 / 8.43, 80 of 2048 11.3 / 9.5, 64 of 1536 9.55 / 7.25, 40 of 1500 10.7 / 8.7, 72 of
+// 1501 16.0 / 10.3, 64 of 520 6.34 / 5.63, 128 of 400 6.34 / 5.42, 100 of 1001 10.2 / 8.7, 128 of 1024 7.08 / 6.60, 64 of 1024 6.11 / 6.13.
+// TAIL: the row's end cuts a block.
+// The fragments of one K-block, both steps, of F tiles 2 KB apart
+template <int F>
+__device__ __forceinline__ void block_frags(unsigned at0, unsigned at1, v4u (&f)[2 * F]) {
 #pragma unroll
-            for (int w = 0; w < 8; w++) {
-                const float part = reinterpret_cast<const float*>(ring + (w % NW) * kWaveLds)[(w / NW) * kRed + er * kRedRow + ec + e];
-                sum = w == 0 ? part : sum + part;
-            }
-            emit.put(e, sum);
+    for (int t = 0; t < F; t++) f[t] = *(const v4u __attribute__((address_space(3)))*)(uintptr_t)(at0 + t * 2048);
+#pragma unroll
+    for (int t = 0; t < F; t++) f[F + t] = *(const v4u __attribute__((address_space(3)))*)(uintptr_t)(at1 + t * 2048);
+}
+template <int RT, int CT, int KB, bool TAIL, bool WNT>
+__global__ __launch_bounds__(512, 2) void k_gemm_whole(GemvEpiArgs p) {
+    constexpr int NW = 8, HL = 2 * RT, WL = 2 * CT, F = RT + CT;      // load instructions per K-block; tiles
+    constexpr int kWave = (KB > 1 ? 2 : 1) * F * 2048, kRedRow = 16 * CT + 4, kRed = 16 * RT * kRedRow;
+    constexpr int NE = RT * CT == 4 ? 2 : 1, kPerRow = 16 * CT / NE;      // outputs per lane (consecutive columns), lanes per row of the tile
+    static_assert(kRed * 4 <= kWave, "a wave's partial sums fit where its blocks were");
+    const MmHead m = mm_head<kEpilogue>(p);
+    __shared__ __attribute__((aligned(128))) char lds[NW * kWave];
+    MmEpilogue<NE, true> emit;
+    emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = m.rows, n = m.n, cols = m.cols;
+    const unsigned ncb = (unsigned)(n + 16 * CT - 1) / (16 * CT), groups = (unsigned)m.row_groups;
+    const unsigned at = xcd_stretch(blockIdx.x, ncb * groups);
+    // at / groups: of at most 256 workgroups (plan_gemm), so half of one is far more than the reciprocal errs
+    const unsigned cb = (unsigned)__builtin_amdgcn_readfirstlane((int)(((float)at + 0.5f) * __builtin_amdgcn_rcpf((float)groups))), rg = at - cb * groups;
+    const int r0 = (int)rg * 16 * RT, j0 = (int)cb * 16 * CT;
+    const int nkb = (cols + 63) / 64, r8 = lane >> 3;
+    const bf16_t* wb = m.W + (size_t)j0 * cols;
+    const bf16_t* hb = m.h + (size_t)r0 * cols;
+    unsigned hrow[HL], wrow[WL], koff[KB];               // byte offsets: the rows of each instruction, this lane's chunk of each block
+#pragma unroll
+    for (int q = 0; q < WL; q++) { const unsigned r = (unsigned)(q * 8 + r8), last = (unsigned)(n - j0 - 1); wrow[q] = (r < last ? r : last) * (unsigned)cols * 2u; }
+#pragma unroll
+    for (int q = 0; q < HL; q++) { const unsigned r = (unsigned)(q * 8 + r8), last = (unsigned)(rows - r0 - 1); hrow[q] = (r < last ? r : last) * (unsigned)cols * 2u; }
+    auto vec = [&](int b) { return (wave + NW * b) * 8 + (lane & 7); };
+#pragma unroll
+    for (int b = 0; b < KB; b++) {                       // only a wave's last block can reach past the row's end, or lie behind it: then the row's first chunk, not multiplied
+        if (b < KB - 1) koff[b] = (unsigned)vec(b) * 16u;
+        else koff[b] = wave + NW * b < nkb ? span_at<!TAIL>(cols, vec(b)) * 2u : 0u;
+    }
+    unsigned gw[KB][WL][4], gh[KB][HL][4];
+#pragma unroll
+    for (int b = 0; b < KB; b++) {
+#pragma unroll
+        for (int q = 0; q < HL; q++) load_at<false>(hb, hrow[q] + koff[b], gh[b][q]);
+        if (b == (KB > 1 ? 1 : 0)) {
+            __builtin_amdgcn_sched_barrier(0);
+            emit.prepare();
+            emit.early_words(r0 + tid / kPerRow, j0 + (tid % kPerRow) * NE, tid / kPerRow < 16 * RT);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < KB; b++)
+#pragma unroll
+        for (int q = 0; q < WL; q++) load_at<WNT>(wb, wrow[q] + koff[b], gw[b][q]);
+    __builtin_amdgcn_sched_barrier(0);
+    char* const mine = lds + wave * kWave;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)mine;
+    const unsigned f0 = lds0 + (lane & 15) * 128 + (((lane >> 4) ^ (lane & 7)) * 16), f1 = lds0 + (lane & 15) * 128 + (((4 + (lane >> 4)) ^ (lane & 7)) * 16);
+    char* const to = mine + r8 * 128 + (((lane & 7) ^ r8) * 16);      // chunk c of row r sits at c ^ (r & 7)
+    f32x4 acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; i++)
+#pragma unroll
+        for (int j = 0; j < CT; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto stage = [&](int b) {
+        char* const at = to + (b & 1) * (F * 2048);
+#pragma unroll
+        for (int q = 0; q < HL; q++) {
+            if (TAIL && b == KB - 1) span_fix<false>(cols, vec(b), gh[b][q]);
+            *reinterpret_cast<v4u*>(at + q * 1024) = v4u{gh[b][q][0], gh[b][q][1], gh[b][q][2], gh[b][q][3]};
+        }
+#pragma unroll
+        for (int q = 0; q < WL; q++) {
+            if (TAIL && b == KB - 1) span_fix<false>(cols, vec(b), gw[b][q]);
+            *reinterpret_cast<v4u*>(at + (RT * 2 + q) * 1024) = v4u{gw[b][q][0], gw[b][q][1], gw[b][q][2], gw[b][q][3]};
+        }
+    };
+    stage(0);
+#pragma unroll
+    for (int b = 0; b < KB; b++) {
+        v4u f[2 * F];
+        block_frags<F>(f0 + (b & 1) * (F * 2048), f1 + (b & 1) * (F * 2048), f);
+        if (b + 1 < KB) stage(b + 1);
+        if (b < KB - 1 || wave + NW * b < nkb) {
+#pragma unroll
+            for (int s = 0; s < 2; s++)
+#pragma unroll
+                for (int i = 0; i < RT; i++)
+#pragma unroll
+                    for (int j = 0; j < CT; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[s * F + i]), __builtin_bit_cast(bf16x8, f[s * F + RT + j]), acc[i][j], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < RT; i++)
+#pragma unroll
+        for (int j = 0; j < CT; j++) {
+            mm_drained(acc[i][j]);
+            float* dst = reinterpret_cast<float*>(mine) + (i * 16 + (lane >> 4) * 4) * kRedRow + j * 16 + (lane & 15);
+            const f32x4 v = acc[i][j];
+            dst[0] = v.x; dst[kRedRow] = v.y; dst[2 * kRedRow] = v.z; dst[3 * kRedRow] = v.w;
+        }
+    emit.late_words();
+    lds_barrier();
+    const int er = tid / kPerRow, ec = (tid % kPerRow) * NE;
+    if (er < 16 * RT) {
+#pragma unroll
+        for (int e = 0; e < NE; e++) {
+            emit.put(e, parts_sum([&](int w) { return reinterpret_cast<const float*>(lds + w * kWave)[er * kRedRow + ec + e]; }));
         }
         emit.end();
     }
@@ -1403,6 +1558,35 @@ const void* gemm_cols_form(int cols) {
     if (cols <= 1024) return cols == 1024 ? PG_FN(k_gemm_cols<8, false, true, RIDE>) : PG_FN(k_gemm_cols<8, true, true, RIDE>);
     return cols == 2048 ? PG_FN(k_gemm_cols<16, false, WNT, RIDE>) : PG_FN(k_gemm_cols<16, true, WNT, RIDE>);
 }
+template <int RT, int CT>
+const void* whole_kernel(int cols, bool beyond_cache) {
+    const int kb = (cols + 511) / 512;
+    if (cols % 64) return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, true, false>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, true, false>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, true, false>) : PG_FN(k_gemm_whole<RT, CT, 4, true, false>);
+    if (beyond_cache) return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, false, true>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, false, true>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, false, true>) : PG_FN(k_gemm_whole<RT, CT, 4, false, true>);
+    return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, false, false>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, false, false>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, false, false>) : PG_FN(k_gemm_whole<RT, CT, 4, false, false>);
+}
+// The cheapest tile whose grid is one workgroup per CU.  us per RMSNorm and GEMV, rows x outputs in tiles of 16: 64 rows of 2048 columns 1 x 2 8.36, 2 x 1 8.55, 1 x 1
+// (512 workgroups) 8.98, 2 x 2 9.58; 48 of 2048 8.18, 8.10, 8.85, 9.32; 128 of 1024 6.47, 6.59, 6.74, 7.11; 64 of 520 1 x 1 5.73, 2 x 1 6.22, 1 x 2 6.28.
+// 2 x 2 against k_gemm_tile's, from kMmWideRows rows: beyond the cache and without shared cache lines 128 of 2048 9.93 / 10.39, 96 of 1536 8.53 / 8.98, 96 of 1152
+// 7.06 / 8.11 (plan_gemm), otherwise not: 100 of 2000 11.05 / 10.21, 128 of 1504 8.73 / 8.46, 128 of 2048 within the cache 9.78 / 9.58.
+bool plan_whole(int rows, int n, int cols, Launch* out) {
+    static const int by_cost[4][2] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}};
+    for (const auto& t : by_cost) {
+        if (t[0] * t[1] == 4 && rows >= kMmWideRows) break;
+        const unsigned groups = blocks_for(rows, 16 * t[0]);
+        if ((long long)blocks_for(n, 16 * t[1]) * groups > 256) continue;
+        auto kernel = [&](bool beyond) {
+            return t[0] == 1 ? (t[1] == 1 ? whole_kernel<1, 1>(cols, beyond) : whole_kernel<1, 2>(cols, beyond)) : t[1] == 1 ? whole_kernel<2, 1>(cols, beyond) : whole_kernel<2, 2>(cols, beyond);
+        };
+        out->fn = kernel(false);
+        if (cols % 64 == 0 && (rows < kMmWideRows || n >= 256)) out->fn_beyond_cache = kernel(true);      // the lines where the other forms have them too
+        out->block = dim3(512);
+        out->gemm_row_groups = groups;
+        out->grid = dim3(blocks_for(n, 16 * t[1]) * groups);
+        return true;
+    }
+    return false;
+}
 // The tile of a workgroup that normalises its own rows: the cheapest whose grid is still one workgroup per CU.  A row costs its bytes and its
 // normalising, an output its bytes.  Decode chains, us per sub-block, rows x outputs of the tile, in brackets the workgroups (measured with a branch per row in
 // the sums of squares; without it all of them are 0.1 - 0.3 faster):
@@ -1436,6 +1620,7 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         out->grid = dim3(blocks_for(n, nc) * tiles);
         return;
     }
+    if (ride == kEpilogue && cols <= 2048 && plan_whole(rows, n, cols, out)) return;
     // (decode chain of 2048 columns at 48 / 64 rows: 1175 / 1188 us, with k_gemm_tile's 16 x 16 tiles 1254 / 1261)
     // A 32-column tile of up to 16 outputs per row would be half empty; with so few workgroups, one tile of rows each.
     if (cols <= 2048 && (rows < kMmWideRows || n <= 16)) {
@@ -1469,9 +1654,10 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         // 618 / 664, 100 of 1928 608 / 711, 64 of 2312 521 / 559; within the cache, 200 MB, 128 of 1024 765 / 815, 2048 236 / 266; other tiles and
         // larger grids, 100 of 3000 497 / 634, 100 of 2056 795 / 991, 81 of 4096 228 / 262; us per RMSNorm, GEMV and GELU of few outputs, 128 rows of 8192
         // columns, 64 outputs 21.8 / 25.2, 128 22.0 / 23.4, 256 22.4 / 22.2, 512 22.7 / 22.5; 100 of 4096, 256 outputs 13.0 / 12.7.
-        if (out->grid.x <= 256 && cols % 64 == 0 && n >= 256) out->fn_beyond_cache = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8, true>) : PG_FN(k_gemm_tile<2, 2, 2, 4, true>);
+        if (out->grid.x <= 256 && cols % 64 == 0 && n >= 256) out->fn_beyond_cache = merged ? (cols <= 2048 ? whole_kernel<2, 2>(cols, true) : PG_FN(k_gemm_tile<2, 2, 2, 8, true>)) : PG_FN(k_gemm_tile<2, 2, 2, 4, true>);
     } else {
-        out->fn = merged ? PG_FN(k_gemm_tile<1, 1, 2, 8, false>) : PG_FN(k_gemm_tile<1, 1, 2, 4, false>);
+        // (more than one workgroup per CU: see k_gemm_tile)
+        out->fn = merged ? (narrow * ntiles <= 256 ? PG_FN(k_gemm_tile<1, 1, 2, 8, false>) : PG_FN(k_gemm_tile<1, 1, 2, 8, false, false>)) : PG_FN(k_gemm_tile<1, 1, 2, 4, false>);
         out->grid = dim3((unsigned)(narrow * ntiles));
     }
 }

@@ -1,0 +1,33 @@
+"""GEMVs of 17 rows and more with kernels behind them, up to 2048 columns: one workgroup per CU, all of its loads at once.  Around the edges of the tiles (16 and 32 rows
+and outputs), of the grid (256 workgroups), of a wave's blocks of 64 columns (512, 1024, 1536), with rows that end inside a vector; tails of every form."""
+import pytest
+
+from gpu_util import Harness, same_bits, stepwise_check
+from pg_workloads import ChainSpec, KernelSpec, TensorSpec, Ref, EXT, INT, WEIGHT
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("tail", ["gelu add add", "mul gelu"])
+@pytest.mark.parametrize("rows,n,cols", [(33, 16, 8), (33, 1, 64), (40, 300, 511), (64, 1024, 512), (64, 1025, 513), (49, 1023, 1024), (128, 512, 1025), (127, 513, 1000), (65, 1700, 1536),
+                                         (64, 2048, 1537), (64, 2049, 2048), (80, 2048, 2048), (72, 2730, 1984), (79, 700, 2047), (100, 2048, 2048), (200, 300, 72), (2000, 20, 130)])
+def test_shapes_and_tails(rows, n, cols, tail):
+    N, K = rows * n, rows * cols
+    ks = [KernelSpec("rmsnorm", "bf16", 0, (Ref(EXT, 0), Ref(WEIGHT, 1)), cols, rows=rows, cols=cols, eps=1e-6),
+          KernelSpec("gemv", "bf16", 1, (Ref(WEIGHT, 0), Ref(INT, 0)), n, rows=rows, cols=cols)]
+    for op in tail.split():
+        src = Ref(INT, ks[-1].out)
+        ks.append(KernelSpec("gelu", "bf16", ks[-1].out + 1, (src,), N) if op == "gelu" else KernelSpec(op, "bf16", ks[-1].out + 1, (Ref(EXT, 1), src), N, m=N))
+    spec = ChainSpec(f"whole_{rows}x{n}x{cols}", ks, [TensorSpec("bf16", K), TensorSpec("bf16", N)], [TensorSpec("bf16", K)] + [TensorSpec("bf16", N) for _ in range(4)],
+                     [TensorSpec("bf16", n * cols, ("normal", 0.0, 0.05)), TensorSpec("bf16", cols, ("normal", 1.0, 0.1))], sorted({k.out for k in ks}), 7600)
+    h = Harness(spec)
+    assert h.chain.graph_dispatches()[0] == 2
+    x_np, x_dev = h.inputs(3)
+    ref = h.run("eager", x_dev)
+    for mode in ("copy", "indirect"):
+        h.scrub()
+        got = h.run(mode, x_dev)
+        assert all(same_bits(a, b) for a, b in zip(ref, got)), mode
+    h.scrub()
+    stepwise_check(h, x_np, x_dev, rtol=2.0 ** -7)      # one bf16 ulp, every kernel
+    h.close()
