@@ -324,7 +324,8 @@ __device__ __forceinline__ void span_store(bf16_t* row, int cols, int v, const u
 // GEMV's own output buffer instead and ignored -- so that every wait on the rows and weights knows how
 // many younger loads are outstanding.
 // EPI = false: nothing rides behind the GEMV, and the stage reads no table, fetches nothing and stores what it is given.
-template <int NE, bool EPI>
+// ANY: two columns a lane where one would do (k_gemm_tile's smallest tile): a straight tail in any layout, as one column has it.
+template <int NE, bool EPI, bool ANY = false>
 struct MmEpilogue {
     static constexpr int P = kEpiMaxPhases;
     bf16_t* y;
@@ -402,7 +403,7 @@ struct MmEpilogue {
         }
     }
     // the decoder block's tail with a layout that lets it be played straight through
-    __device__ __forceinline__ bool straight() const { return (head & kEpiDecoder) && (NE == 1 ? (head & kEpiPlain) != 0 : vec); }
+    __device__ __forceinline__ bool straight() const { return (head & kEpiDecoder) && (NE == 1 || ANY ? (head & kEpiPlain) != 0 : vec); }
     // what any other tail reads
     __device__ __forceinline__ void fetch_any() {
         if (head & kEpiPlain) {                // one branch for all: no division where no operand has a period
@@ -438,17 +439,31 @@ struct MmEpilogue {
     }
     // NE even, beside loads that go to LDS directly: while such loads are outstanding the compiler waits for all of them wherever it
     // meets a register that some load may write, on any path.  So the straight tail's operands go to LDS directly as well, a word of two columns per
-    // lane and piece (kTailBytes of LDS per wave), and other tails fetch theirs when the sums are there.
-    static constexpr int kPieces = NE / 2, kTailBytes = 2 * (kPieces ? kPieces : 1) * 256;
+    // lane and piece (ANY: or a word for each column, where n is odd or an operand lies at an odd element; kTailBytes of LDS per wave), and other tails
+    // fetch theirs when the sums are there.
+    static constexpr int kWords = ANY ? NE : NE / 2, kTailBytes = 2 * (kWords ? kWords : 1) * 256;
+    static __device__ __forceinline__ int word_at(int i, int e) { return ((i - 1) * kWords + (ANY ? e : e / 2)) * 256; }
+    template <bool PAIR>
+    __device__ __forceinline__ void operand_to_lds(int i, int e, char* to /* uniform */) {
+        const void PG_GLOBAL* const at = (const void PG_GLOBAL*)((const unsigned short PG_GLOBAL*)(uintptr_t)q1[i] + idx[e]);
+        auto* const lds = (__attribute__((address_space(3))) void*)to;
+        if constexpr (PAIR) __builtin_amdgcn_global_load_lds(at, lds, 4, 0, 0);
+        else __builtin_amdgcn_global_load_lds(at, lds, 2, 0, 0);
+    }
     __device__ __forceinline__ void early(int r, int j, bool col_ok, char* to /* uniform */) {
         index(r, j, col_ok);
-        if (__builtin_expect(straight(), 1))
+        if (!straight()) return;
+        if (__builtin_expect(!ANY || vec, 1)) {
 #pragma unroll
             for (int i = 1; i < P; i++)
 #pragma unroll
-                for (int e = 0; e < NE; e += 2)
-                    __builtin_amdgcn_global_load_lds((const void PG_GLOBAL*)((const unsigned short PG_GLOBAL*)(uintptr_t)q1[i] + idx[e]),
-                                                     (__attribute__((address_space(3))) void*)(to + ((i - 1) * kPieces + e / 2) * 256), 4, 0, 0);
+                for (int e = 0; e < NE; e += 2) operand_to_lds<true>(i, e, to + word_at(i, e));
+        } else {
+#pragma unroll
+            for (int i = 1; i < P; i++)
+#pragma unroll
+                for (int e = 0; e < NE; e++) operand_to_lds<false>(i, e, to + word_at(i, e));
+        }
     }
     // Beside loads into registers only: two columns' words stay as they come in until late_words(); taking them apart at once would wait for them and
     // for every load before them.  Other tails fetch theirs late here too, so that every wait on the rows and weights knows what is outstanding.
@@ -480,13 +495,18 @@ struct MmEpilogue {
     __device__ __forceinline__ void late(const char* from, int lane) {
         if (__builtin_expect(straight(), 1)) {
             __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
+            auto word = [&](int i, int e) { return reinterpret_cast<const unsigned*>(from + word_at(i, e))[lane]; };
+            if (__builtin_expect(!ANY || vec, 1)) {
 #pragma unroll
-            for (int i = 1; i < P; i++)
+                for (int i = 1; i < P; i++)
 #pragma unroll
-                for (int e = 0; e < NE; e += 2) {
-                    const unsigned t = reinterpret_cast<const unsigned*>(from + ((i - 1) * kPieces + e / 2) * 256)[lane];
-                    ld1[i][e] = t & 0xffffu; ld1[i][e + 1] = t >> 16;
-                }
+                    for (int e = 0; e < NE; e += 2) { const unsigned t = word(i, e); ld1[i][e] = t & 0xffffu; ld1[i][e + 1] = t >> 16; }
+            } else {
+#pragma unroll
+                for (int i = 1; i < P; i++)
+#pragma unroll
+                    for (int e = 0; e < NE; e++) ld1[i][e] = word(i, e);      // zero-extended by the load
+            }
         } else {
             fetch_any();
         }
@@ -949,7 +969,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_gemm_cols(RideArgs<RIDE> p) {
 // The epilogue's operands come into LDS as well (MmEpilogue::early): as loads into registers they made the compiler wait for the first block, for
 // each operand and for the second block in turn before the loop.  us per RMSNorm and GEMV without / with: 128 rows of 2048 columns 10.62 / 10.34, of 1024 7.42 /
 // 7.00, 16 of 3072 10.44 / 10.15, 8 of 4096 12.09 / 11.61, 81 of 520 6.85 / 6.57; two workgroups of 16 x 16 to a CU hide such waits from each
-// other, 20 of 2304 9.63 / 9.79, and keep the loads into registers.
+// other, 20 of 2304 9.63 / 9.79, and keep the loads into registers.  So does the 16 x 16 tile where no 16-byte load reaches the rows (columns no multiple of 8): its
+// rows and weights come through registers then, and beside those the operands' way over LDS gains little and costs up to 6 % (us per GEMV, GELU and two
+// adds through LDS / registers: 33 rows of 2100 columns, 555 outputs 6.05 / 5.71, 6 of 2500, 2000 outputs 7.11 / 6.72, 24 of 2049, 2000 outputs 7.06 / 7.20).
+// An odd number of outputs or an operand at an odd element, 16 rows of 3072 columns, 3001 outputs: 7.4, fetched when the sums are there 7.7, one column
+// a lane with loads into registers 7.6; 8 of 4096, 33 outputs 4.7, 4.95, 4.7.
 // Decode chains, us per iteration, before and after: 128 rows of 2048 columns, 120 sub-blocks 1529 -> 1330; 100 x 2000 (100
 // sub-blocks) 1290 -> 850, 128 x 1024 1282 -> 793 (there also one dispatch instead of three around the GEMV); one GEMV alone, us
 // per launch: 128 rows by 4096 x 4096 34.0 -> 17.4, by 2048 x 2048 8.1 -> 7.8 (the 16- and 32-column forms it replaces re-read W
@@ -999,7 +1023,7 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
     static_assert(S == 1 || S == 2, "the waits below name the blocks in flight");
     constexpr Ride RIDE = NW == 8 ? kEpilogue : kAlone;  // four waves: a stand-alone launch
     const MmHead m = mm_head<RIDE>(p);
-    using Emit = MmEpilogue<NE, RIDE != kAlone>;
+    using Emit = MmEpilogue<NE, RIDE != kAlone, ASIDE && (kEach < NE)>;
     constexpr int kTails = RIDE != kAlone && ASIDE ? Emit::kTailBytes : 0;
     __shared__ __attribute__((aligned(128))) char ring[NW * (kWaveLds + kTails)];
     char* const tail = ring + NW * kWaveLds + wave_index() * kTails;
@@ -1036,8 +1060,7 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
 #pragma unroll
             for (int j = 0; j < CT; j++) acc[pk][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the epilogue's table behind the first block's loads: asked for behind all of them it came 1.1 us later
-    auto epilogue_begin = [&] {
-        emit.prepare();
+    auto operands_begin = [&] {
         if constexpr (RIDE == kAlone) emit.index(r0 + er, j0 + ec, er < 16 * RT);
         else if constexpr (ASIDE) emit.early(r0 + er, j0 + ec, er < 16 * RT, tail);
         else emit.begin(r0 + er, j0 + ec, er < 16 * RT);
@@ -1064,7 +1087,8 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
             for (int q = 2 * RT; q < NL; q++) load_to_lds<WNT>(wb, row_at[q] + ke, to + q * 1024);
         };
         if (nb > 0) issue(0, 0);
-        epilogue_begin();
+        emit.prepare();
+        operands_begin();
         if (S == 2 && nb > 1) issue(1, 1);
         int slot = 0;
 #pragma unroll 1
@@ -1099,7 +1123,11 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
             for (int q = 0; q < NL; q++) load_any<false>(q < 2 * RT ? hb : wb, row_at[q] + ke, g[q]);
         };
         if (nb > 0) fetch(0);
-        epilogue_begin();
+        emit.prepare();
+        // operands on their way to LDS are waited for with the first block's rows and weights, which come into registers here: in the smallest tile
+        // they follow the second block's
+        constexpr bool kBehind = RIDE != kAlone && ASIDE && RT * CT == 1;
+        if (!kBehind || nb == 0) operands_begin();
 #pragma unroll 1
         for (int b0 = 0; b0 < nb; b0 += PK) {
 #pragma unroll
@@ -1112,6 +1140,7 @@ __global__ __launch_bounds__(NW * 64, RT * CT == 1 ? NW / 2 : NW / 4) void k_gem
                     *reinterpret_cast<v4u*>(mine + (q * 8 + r8) * 128 + ((chunk ^ r8) * 16)) = v4u{g[q][0], g[q][1], g[q][2], g[q][3]};
                 }
                 if (b + 1 < nb) fetch(b + 1);
+                if (kBehind && b == 0) operands_begin();
                 v4u f[2 * F];
                 ring_frags<F>(f0, f1, f);                              // behind the writes above: one wave's LDS operations execute in order
                 multiply(acc[pk], f);
@@ -1656,8 +1685,8 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         // columns, 64 outputs 21.8 / 25.2, 128 22.0 / 23.4, 256 22.4 / 22.2, 512 22.7 / 22.5; 100 of 4096, 256 outputs 13.0 / 12.7.
         if (out->grid.x <= 256 && cols % 64 == 0 && n >= 256) out->fn_beyond_cache = merged ? (cols <= 2048 ? whole_kernel<2, 2>(cols, true) : PG_FN(k_gemm_tile<2, 2, 2, 8, true>)) : PG_FN(k_gemm_tile<2, 2, 2, 4, true>);
     } else {
-        // (more than one workgroup per CU: see k_gemm_tile)
-        out->fn = merged ? (narrow * ntiles <= 256 ? PG_FN(k_gemm_tile<1, 1, 2, 8, false>) : PG_FN(k_gemm_tile<1, 1, 2, 8, false, false>)) : PG_FN(k_gemm_tile<1, 1, 2, 4, false>);
+        // (more than one workgroup per CU, rows that 16-byte loads cannot reach: see k_gemm_tile)
+        out->fn = merged ? (narrow * ntiles <= 256 && cols % 8 == 0 ? PG_FN(k_gemm_tile<1, 1, 2, 8, false>) : PG_FN(k_gemm_tile<1, 1, 2, 8, false, false>)) : PG_FN(k_gemm_tile<1, 1, 2, 4, false>);
         out->grid = dim3((unsigned)(narrow * ntiles));
     }
 }
