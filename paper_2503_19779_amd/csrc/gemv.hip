@@ -842,7 +842,8 @@ __global__ __launch_bounds__(kBlock, (RIDE == kPrologue && KS > 8) ? 1 : 2) void
     emit.y = m.y; emit.rows = m.rows; emit.n = m.n; emit.head = m.head; emit.n_epi = m.n_epi; emit.ka = m.ka;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned ncb = (unsigned)(m.n + NC - 1) / NC;
-    const unsigned ntiles = (unsigned)m.row_groups & 0xffu, inv = (unsigned)m.row_groups >> 8;      // 65536 / ntiles (plan_gemm)
+    // (without the RMSNorm one tile holds all rows; read from the arguments instead: 8 rows of 2048 columns alone 3.97 where this takes 3.93, 16 of 777 with a tail 3.45 / 3.39)
+    const unsigned ntiles = PRO ? (unsigned)m.row_groups & 0xffu : 1u, inv = (unsigned)m.row_groups >> 8;      // 65536 / ntiles (plan_gemm)
     // one tile of rows and a grid of several rounds: columns dealt out in turn stream better (us per launch, 5 rows of 2048 columns, 16384
     // outputs 17.6 -> 15.9, 1024 columns, 32768 outputs 16.2 -> 13.9); otherwise a stretch per XCD (below 1024 workgroups 0.1 - 0.3 us
     // faster at every size, and tiles of rows share their columns)
