@@ -1588,28 +1588,46 @@ const void* gemm_cols_form(int cols) {
     if (cols <= 1024) return cols == 1024 ? PG_FN(k_gemm_cols<8, false, true, RIDE>) : PG_FN(k_gemm_cols<8, true, true, RIDE>);
     return cols == 2048 ? PG_FN(k_gemm_cols<16, false, WNT, RIDE>) : PG_FN(k_gemm_cols<16, true, WNT, RIDE>);
 }
-template <int RT, int CT>
-const void* whole_kernel(int cols, bool beyond_cache) {
+template <int RT, int CT, bool TAIL, bool WNT>
+const void* whole_kernel_nt(int cols) {
     const int kb = (cols + 511) / 512;
-    if (cols % 64) return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, true, false>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, true, false>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, true, false>) : PG_FN(k_gemm_whole<RT, CT, 4, true, false>);
-    if (beyond_cache) return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, false, true>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, false, true>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, false, true>) : PG_FN(k_gemm_whole<RT, CT, 4, false, true>);
-    return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, false, false>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, false, false>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, false, false>) : PG_FN(k_gemm_whole<RT, CT, 4, false, false>);
+    if constexpr (TAIL && WNT) {              // (up to 1024 columns and kMmWideRows - 1 rows, where 2 x 1 tiles are never the cheapest)
+        if constexpr (RT > CT) return nullptr;
+        else return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, true, true>) : PG_FN(k_gemm_whole<RT, CT, 2, true, true>);
+    } else {
+        return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, TAIL, WNT>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, TAIL, WNT>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, TAIL, WNT>) : PG_FN(k_gemm_whole<RT, CT, 4, TAIL, WNT>);
+    }
+}
+template <int RT, int CT>
+const void* whole_kernel(int cols, bool nt) {
+    if (cols % 64) return nt ? whole_kernel_nt<RT, CT, true, true>(cols) : whole_kernel_nt<RT, CT, true, false>(cols);
+    return nt ? whole_kernel_nt<RT, CT, false, true>(cols) : whole_kernel_nt<RT, CT, false, false>(cols);
 }
 // The cheapest tile whose grid is one workgroup per CU.  us per RMSNorm and GEMV, rows x outputs in tiles of 16: 64 rows of 2048 columns 1 x 2 8.36, 2 x 1 8.55, 1 x 1
 // (512 workgroups) 8.98, 2 x 2 9.58; 48 of 2048 8.18, 8.10, 8.85, 9.32; 128 of 1024 6.47, 6.59, 6.74, 7.11; 64 of 520 1 x 1 5.73, 2 x 1 6.22, 1 x 2 6.28.
 // 2 x 2 against k_gemm_tile's, from kMmWideRows rows: beyond the cache and without shared cache lines 128 of 2048 9.93 / 10.39, 96 of 1536 8.53 / 8.98, 96 of 1152
 // 7.06 / 8.11 (plan_gemm), otherwise not: 100 of 2000 11.05 / 10.21, 128 of 1504 8.73 / 8.46, 128 of 2048 within the cache 9.78 / 9.58.
+// Weights by plain / non-temporal loads, us per RMSNorm and GEMV with its tail, megabytes of weights in the chain in brackets: up to 1024 columns and 80 rows
+// without shared cache lines 64 rows of 1024 [126] 5.5 / 5.15, [400] 5.2 / 5.1, 64 of 512 [105] 5.1 / 4.8, 33 of 1024, 4096 outputs [50] 8.65 / 8.35; with them 64 of 1000
+// [127] 5.75 / 5.70, [400] 6.15 / 5.69, 40 of 1001 [126] 6.43 / 6.62, [400] 7.00 / 6.65; longer rows 64 of 2048 [200] 7.5 / 8.1, 40 of 1928 [400] 9.4 / 9.8, 40 of 1500 [400]
+// 9.1 / 9.1, [200] 8.0 / 9.15.
 bool plan_whole(int rows, int n, int cols, Launch* out) {
     static const int by_cost[4][2] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}};
     for (const auto& t : by_cost) {
         if (t[0] * t[1] == 4 && rows >= kMmWideRows) break;
         const unsigned groups = blocks_for(rows, 16 * t[0]);
         if ((long long)blocks_for(n, 16 * t[1]) * groups > 256) continue;
-        auto kernel = [&](bool beyond) {
-            return t[0] == 1 ? (t[1] == 1 ? whole_kernel<1, 1>(cols, beyond) : whole_kernel<1, 2>(cols, beyond)) : t[1] == 1 ? whole_kernel<2, 1>(cols, beyond) : whole_kernel<2, 2>(cols, beyond);
+        auto kernel = [&](bool nt) {
+            return t[0] == 1 ? (t[1] == 1 ? whole_kernel<1, 1>(cols, nt) : whole_kernel<1, 2>(cols, nt)) : t[1] == 1 ? whole_kernel<2, 1>(cols, nt) : whole_kernel<2, 2>(cols, nt);
         };
-        out->fn = kernel(false);
-        if (cols % 64 == 0 && (rows < kMmWideRows || n >= 256)) out->fn_beyond_cache = kernel(true);      // the lines where the other forms have them too
+        const bool lines = cols % 64 == 0;               // no two rows share a cache line
+        if (rows < kMmWideRows && cols <= 1024) {
+            out->fn = kernel(lines);
+            if (!lines) out->fn_beyond_cache = kernel(true);
+        } else {
+            out->fn = kernel(false);
+            if (lines && (rows < kMmWideRows || n >= 256)) out->fn_beyond_cache = kernel(true);
+        }
         out->block = dim3(512);
         out->gemm_row_groups = groups;
         out->grid = dim3(blocks_for(n, 16 * t[1]) * groups);

@@ -1,9 +1,10 @@
 """GEMVs of 17 rows and more with kernels behind them, up to 2048 columns: one workgroup per CU, all of its loads at once.  Around the edges of the tiles (16 and 32 rows
 and outputs), of the grid (256 workgroups), of a wave's blocks of 64 columns (512, 1024, 1536), with rows that end inside a vector; tails of every form."""
+import numpy as np
 import pytest
 
 from gpu_util import Harness, same_bits, stepwise_check
-from pg_workloads import ChainSpec, KernelSpec, TensorSpec, Ref, EXT, INT, WEIGHT
+from pg_workloads import ChainSpec, KernelSpec, TensorSpec, Ref, EXT, INT, WEIGHT, make_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -30,4 +31,30 @@ def test_shapes_and_tails(rows, n, cols, tail):
         assert all(same_bits(a, b) for a, b in zip(ref, got)), mode
     h.scrub()
     stepwise_check(h, x_np, x_dev, rtol=2.0 ** -7)      # one bf16 ulp, every kernel
+    h.close()
+
+
+@pytest.mark.parametrize("rows,n,cols", [(33, 17, 8), (49, 33, 66), (64, 1024, 513), (40, 1030, 1000), (40, 2730, 1023), (72, 1640, 511), (80, 2049, 777)])
+def test_shared_lines_in_a_chain_beyond_the_cache(rows, n, cols):
+    """Up to 80 rows and 1024 columns whose rows share cache lines: a GEMV of 269 MB elsewhere in the chain makes them take the weights by non-temporal
+    loads.  Tiles of 1 x 1, 1 x 2 and 2 x 2, one and two blocks a wave."""
+    big, N, K = 65600, rows * n, rows * cols
+    ks = [KernelSpec("gemv", "bf16", 3, (Ref(WEIGHT, 1), Ref(EXT, 2)), big, rows=5, cols=2048),
+          KernelSpec("gemv", "bf16", 0, (Ref(WEIGHT, 0), Ref(EXT, 0)), n, rows=rows, cols=cols),
+          KernelSpec("gelu", "bf16", 1, (Ref(INT, 0),), N),
+          KernelSpec("add", "bf16", 2, (Ref(EXT, 1), Ref(INT, 1)), N, m=N)]
+    spec = ChainSpec(f"lines_{rows}x{n}x{cols}", ks, [TensorSpec("bf16", K), TensorSpec("bf16", N), TensorSpec("bf16", 5 * 2048)],
+                     [TensorSpec("bf16", N) for _ in range(3)] + [TensorSpec("bf16", 5 * big)],
+                     [TensorSpec("bf16", n * cols, ("normal", 0.0, 0.05)), TensorSpec("bf16", big * 2048)], [0, 1, 2], 7610)
+    small = make_weights(ChainSpec(spec.name, [], [], [], spec.weights[:1], [], spec.seed))
+    h = Harness(spec, weights_np=small + [np.zeros(big * 2048, np.uint16)])
+    assert h.chain.graph_dispatches()[0] == 2
+    x_np, x_dev = h.inputs(0)
+    ref = h.run("eager", x_dev)
+    for mode in ("copy", "indirect"):
+        h.scrub()
+        got = h.run(mode, x_dev)
+        assert all(same_bits(a, b) for a, b in zip(ref, got)), mode
+    h.scrub()
+    stepwise_check(h, x_np, x_dev, rtol=2.0 ** -7, kernels=range(1, len(ks)))
     h.close()
