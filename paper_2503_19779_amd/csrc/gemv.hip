@@ -1572,10 +1572,12 @@ bool mm_served(long long rows, long long n, long long cols) { return rows > 4 &&
 template <int KS, bool TAIL, Ride RIDE>
 const void* gemm_rows_kernel(int nr, int nc) {
     if constexpr (RIDE == kPrologue) {
-        if (nr == 4) return nc == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 4, 8, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 4, 16, RIDE>);
-        if (nc == 16) return nr == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 8, 16, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 16, 16, RIDE>);
+        if (nr == 16) return PG_FN(k_gemm_rows<KS, TAIL, 16, 16, RIDE>);
+        if (nr == 8) return nc == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 8, 8, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 8, 16, RIDE>);
+        return nc == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 4, 8, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 4, 16, RIDE>);
+    } else {
+        return nr == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 8, 8, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 16, 8, RIDE>);
     }
-    return nr == 8 ? PG_FN(k_gemm_rows<KS, TAIL, 8, 8, RIDE>) : PG_FN(k_gemm_rows<KS, TAIL, 16, 8, RIDE>);
 }
 template <Ride RIDE>
 const void* gemm_rows_form(int nr, int nc, int cols) {
@@ -1593,7 +1595,7 @@ const void* whole_kernel_nt(int cols) {
     const int kb = (cols + 511) / 512;
     if constexpr (TAIL && WNT) {              // (up to 1024 columns and kMmWideRows - 1 rows, where 2 x 1 tiles are never the cheapest)
         if constexpr (RT > CT) return nullptr;
-        else return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, true, true>) : PG_FN(k_gemm_whole<RT, CT, 2, true, true>);
+        else return kb > 2 ? nullptr : kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, true, true>) : PG_FN(k_gemm_whole<RT, CT, 2, true, true>);
     } else {
         return kb == 1 ? PG_FN(k_gemm_whole<RT, CT, 1, TAIL, WNT>) : kb == 2 ? PG_FN(k_gemm_whole<RT, CT, 2, TAIL, WNT>) : kb == 3 ? PG_FN(k_gemm_whole<RT, CT, 3, TAIL, WNT>) : PG_FN(k_gemm_whole<RT, CT, 4, TAIL, WNT>);
     }
@@ -1642,7 +1644,7 @@ bool plan_whole(int rows, int n, int cols, Launch* out) {
 //   32 of 2048  16 x 16 [256] 6.83, 8 x 16 [512] 7.76       32 of 1024  8 x 16 [256] 3.83, 16 x 8 [256] 4.25, 16 x 16 [128] 4.40, 4 x 16 [512] 4.52
 //   16 of 1024  4 x 16 [256] 3.43, 8 x 8 [256] 3.63, 8 x 16 [128] 3.78, 16 x 8 [128] 4.18    8 of 1024  4 x 8 [256] 3.31, 4 x 16 [128] 3.38, 8 x 8 [128] 3.54
 //   16 of 520  4 x 16 [132] 3.86, 8 x 8 [130] 3.94, 4 x 8 [260] 4.11    32 of 400  4 x 16 [200] 3.27, 8 x 8 [200] 3.39, 4 x 8 [400] 3.64
-// Where none fits (more than 2048 outputs at 8 rows, 1024 at 17): 8 outputs up to 16 rows, all of them in one tile, 16 above.
+// Where none fits (more than 4096 outputs up to 16 rows, which merge_prologue admits up to 8 rows, 2048 above): 8 x 8 up to 8 rows, 16 x 16 above.
 void prologue_tile(int rows, int n, int cols, int* nr, int* nc) {
     static const int by_cost[2][5][2] = {{{4, 8}, {4, 16}, {8, 8}, {8, 16}, {16, 16}}, {{4, 8}, {8, 8}, {4, 16}, {8, 16}, {16, 16}}};
     for (const auto& t : by_cost[cols > 1024])
@@ -1651,6 +1653,8 @@ void prologue_tile(int rows, int n, int cols, int* nr, int* nc) {
             *nc = t[1];
             return;
         }
+    *nr = rows <= 8 ? 8 : 16;
+    *nc = *nr;
 }
 void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     const bool merged = ride != kAlone;
@@ -1660,7 +1664,7 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
     out->gemm_row_groups = (unsigned)ntiles;
     out->fn_beyond_cache = nullptr;
     if (ride == kPrologue || (rows <= 16 && cols <= 2048)) {
-        int nr = rows <= 8 ? 8 : 16, nc = rows <= 16 ? 8 : 16;
+        int nr = rows <= 8 ? 8 : 16, nc = 8;
         if (ride == kPrologue) prologue_tile(rows, n, cols, &nr, &nc);
         const unsigned tiles = blocks_for(rows, nr);
         out->fn = ride == kPrologue ? gemm_rows_form<kPrologue>(nr, nc, cols) : merged ? gemm_rows_form<kEpilogue>(nr, nc, cols) : gemm_rows_form<kAlone>(nr, nc, cols);
