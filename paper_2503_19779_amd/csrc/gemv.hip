@@ -245,10 +245,10 @@ __device__ __forceinline__ unsigned xcd_stretch(unsigned b, unsigned total) {
 // Elements beyond a row's end are zeros on both sides: zeroing the weight side alone would turn an Inf or NaN of h
 // into NaN in every output (0 * Inf).  Rows beyond the batch and columns beyond n repeat the last one and are never
 // stored.
-//   - k_gemm_rows: one tile of 8 or 16 rows of h per workgroup, up to 2048 columns, all loads in flight at once; the
-//     form that can carry the RMSNorm in front;
-//   - k_gemm_cols: 17 to 80 rows of up to 2048 columns, and any more rows with up to 16 outputs each;
+//   - k_gemm_rows: up to 16 rows of up to 2048 columns, one tile of 8 or 16 rows of h per workgroup, all loads in flight at once; the form that can carry
+//     the RMSNorm in front, then up to 32 rows in tiles of 4, 8 or 16;
 //   - k_gemm_whole: with kernels that ride behind, from 17 rows on, up to 2048 columns, where its grid is one workgroup per CU;
+//   - k_gemm_cols: 17 to 80 rows of up to 2048 columns, and any more rows with up to 16 outputs each, alone or where k_gemm_whole's grid is larger;
 //   - k_gemm_tile: everything else, K streamed through a ring in LDS.
 template <class Part>
 __device__ __forceinline__ float parts_sum(Part part) { return (((part(0) + part(4)) + (part(1) + part(5))) + (part(2) + part(6))) + (part(3) + part(7)); }
@@ -694,10 +694,10 @@ __device__ __forceinline__ MmHead mm_head(const RideArgs<RIDE>& p) {
 //     that 16 consecutive lanes hit all banks;
 //   - the rows of h (from L2) are asked for before the weights (from HBM): loads return in order, so h is normalised
 //     and staged while the weights are still on their way; then the same LDS slice takes the weights.
-//   - the weights come by non-temporal loads: no other workgroup of the tile reads them.  Decode chains, us per iteration by plain / non-temporal
-//     loads: 16 rows of 2048 columns, 120 sub-blocks 745 / 676, 32 of 1024 555 / 513; weights that stay in the memory-side cache, 126 MB, 16 of
-//     2048 105 / 99, 8 of 1024 244 / 218, 32 of 1024 297 / 273, 15 MB, 8 of 512 115 / 115.  Behind only where rows of more than 1024 columns share
-//     cache lines: within the cache 16 of 1928 118 / 125, 8 of 2041 110 / 112, beyond it 362 / 367, 338 / 328.
+//   - the weights come by non-temporal loads, although the tiles of rows, up to eight, all read them.  us per sub-block of decode chains by plain / non-temporal
+//     loads, in brackets the megabytes of weights: one tile of rows, 8 of 2048 columns [126] 5.34 / 4.70, [400] 5.07 / 4.30; two, 32 of 2048 6.77 / 6.46, 6.51 / 6.09;
+//     four, 16 of 1024 3.51 / 3.12, 3.58 / 3.07, 32 of 1024 [40] 4.15 / 3.77; eight, 32 of 512 [105] 3.02 / 2.68.  Behind only where rows of more than 1024
+//     columns share cache lines, and not always: 16 of 1928 [126] 6.15 / 6.35, [400] 5.76 / 6.05, 8 of 2041 6.63 / 6.34, 6.34 / 5.96.
 // TAIL: the row does not have exactly 128 * KS columns; vectors at any element boundary.
 // Decode chains of 120 sub-blocks, us per iteration: 32 rows of 1024 columns 1406 -> 613 (one dispatch per sub-block, where only
 // 2048 columns had that; half the K-steps); 8 / 16 / 32 rows of 2048 columns 651 / 787 / 915 -> 627 / 771 / 862 (the epilogue's
@@ -1644,6 +1644,8 @@ bool plan_whole(int rows, int n, int cols, Launch* out) {
 //   32 of 2048  16 x 16 [256] 6.83, 8 x 16 [512] 7.76       32 of 1024  8 x 16 [256] 3.83, 16 x 8 [256] 4.25, 16 x 16 [128] 4.40, 4 x 16 [512] 4.52
 //   16 of 1024  4 x 16 [256] 3.43, 8 x 8 [256] 3.63, 8 x 16 [128] 3.78, 16 x 8 [128] 4.18    8 of 1024  4 x 8 [256] 3.31, 4 x 16 [128] 3.38, 8 x 8 [128] 3.54
 //   16 of 520  4 x 16 [132] 3.86, 8 x 8 [130] 3.94, 4 x 8 [260] 4.11    32 of 400  4 x 16 [200] 3.27, 8 x 8 [200] 3.39, 4 x 8 [400] 3.64
+// 4096 outputs, against one tile of 8 or 16 rows by 8 outputs [512] with the RMSNorm that went with it: 8 rows of 1024 columns 8 x 16 3.71 / 4.71, 16 of 1024
+// 16 x 16 4.17 / 5.50, 16 of 2048 6.74 / 8.29.
 // Where none fits (more than 4096 outputs up to 16 rows, which merge_prologue admits up to 8 rows, 2048 above): 8 x 8 up to 8 rows, 16 x 16 above.
 void prologue_tile(int rows, int n, int cols, int* nr, int* nc) {
     static const int by_cost[2][5][2] = {{{4, 8}, {4, 16}, {8, 8}, {8, 16}, {16, 16}}, {{4, 8}, {8, 8}, {4, 16}, {8, 16}, {16, 16}}};
@@ -1673,14 +1675,16 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         return;
     }
     if (ride == kEpilogue && cols <= 2048 && plan_whole(rows, n, cols, out)) return;
-    // (decode chain of 2048 columns at 48 / 64 rows: 1175 / 1188 us, with k_gemm_tile's 16 x 16 tiles 1254 / 1261)
+    // us per launch alone, k_gemm_cols / k_gemm_tile's tiles: 17 rows of 2048 columns 4.70 / 5.69, 64 6.16 / 6.89, 64 of 1024 3.16 / 4.04; 80 of 2048 7.53 / 7.30, 40 of
+    // 1500 7.37 / 6.61.  With a tail and more outputs than k_gemm_whole takes: 33 of 1024, 8200 outputs 9.0 / 12.2, 64 of 1024, 8192 outputs 10.9 / 8.4, 64 of 2048 20.0 / 13.3:
+    // there, and for long ragged rows, the line is not the best one.
     // A 32-column tile of up to 16 outputs per row would be half empty; with so few workgroups, one tile of rows each.
     if (cols <= 2048 && (rows < kMmWideRows || n <= 16)) {
         out->gemm_row_groups = (unsigned)(ntiles < 4 || n <= 16 ? ntiles : 4);
-        // Several workgroups read the same weights, side by side.  Decode chains, us per iteration without / with non-temporal loads: 64 rows of
-        // 1024 columns, 126 MB of weights in all 363 / 343, 252 MB 718 / 676, of 1001 columns, 200 MB 843 / 819; of 2048 columns, 200 MB 226 / 233,
-        // 400 MB 488 / 454, 1 GB 1159 / 1077, of 1088 columns, 400 MB 1757 / 1608, 1600 844 / 790; rows that share cache lines, 400 MB, gain less the
-        // longer they are: 40 of 1032 columns 1663 / 1550, 1300 1289 / 1240, 1500 1108 / 1130, 1928 620 / 627.
+        // Several workgroups read the same weights, side by side.  us per launch alone without / with non-temporal loads, in brackets the megabytes of weights in
+        // the chain: 64 rows of 1024 columns [126] 3.26 / 3.29, [400] 3.42 / 3.16, of 1001 4.40 / 4.64, 4.63 / 4.56; of 2048 6.05 / 6.53, 6.43 / 6.15, 40 of
+        // 1600 5.99 / 6.25, 6.26 / 6.07, 40 of 1088 4.49 / 4.47, 4.59 / 4.38; longer rows that share cache lines [400] 40 of 1300 5.86 / 6.08, 1500 7.32 / 8.00,
+        // 1928 6.97 / 7.71.
         out->grid = dim3(blocks_for(n, 16) * out->gemm_row_groups);
         out->fn = merged ? gemm_cols_form<kEpilogue, false>(cols) : gemm_cols_form<kAlone, false>(cols);
         if (cols % 64 == 0) out->fn_beyond_cache = merged ? gemm_cols_form<kEpilogue, true>(cols) : gemm_cols_form<kAlone, true>(cols);
@@ -1700,12 +1704,11 @@ void plan_gemm(int rows, int n, int cols, Ride ride, Launch* out) {
         out->fn = merged ? PG_FN(k_gemm_tile<2, 2, 2, 8, false>) : PG_FN(k_gemm_tile<2, 2, 2, 4, false>);
         out->gemm_row_groups = (unsigned)two;
         out->grid = dim3((unsigned)wide * out->gemm_row_groups);
-        // Where all workgroups that share their weights run side by side, one per CU, no two rows share a cache line, and there are enough outputs.  us per iteration of decode
-        // chains of 400 MB of weights without / with non-temporal loads: 128 rows of 576 columns 4886 / 4614, 768 2848 / 2602, 1024 1734 / 1620, 1280
-        // 1168 / 1098, 1472 885 / 881, 1536 862 / 830, 2048 540 / 523, 64 of 2304 471 / 451; rows that share cache lines, 128 of 1544 921 / 987, 2000
-        // 618 / 664, 100 of 1928 608 / 711, 64 of 2312 521 / 559; within the cache, 200 MB, 128 of 1024 765 / 815, 2048 236 / 266; other tiles and
-        // larger grids, 100 of 3000 497 / 634, 100 of 2056 795 / 991, 81 of 4096 228 / 262; us per RMSNorm, GEMV and GELU of few outputs, 128 rows of 8192
-        // columns, 64 outputs 21.8 / 25.2, 128 22.0 / 23.4, 256 22.4 / 22.2, 512 22.7 / 22.5; 100 of 4096, 256 outputs 13.0 / 12.7.
+        // Where all workgroups that share their weights run side by side, one per CU, no two rows share a cache line, and there are enough outputs.  us per
+        // launch alone without / with non-temporal loads, in brackets the megabytes of weights in the chain: 128 rows of 1024 columns [200] 4.72 / 5.35, [400] 5.73 / 5.35,
+        // of 1536 5.58 / 6.72, 6.90 / 6.63, of 2048 6.37 / 7.71, 7.93 / 7.61, 64 of 2304 6.85 / 8.77, 8.82 / 8.56; rows that share cache lines [400] 100 of 2000 8.0 / 9.8;
+        // larger grids [400] 100 of 3000 16.1 / 23.1, 81 of 4096 15.1 / 15.2; few outputs, 128 of 8192, 64 outputs [200] 14.0 / 20.7, 256 [400] 18.8 / 17.6.
+        // With a tail, up to 2048 columns, k_gemm_whole's non-temporal form takes that place: 128 of 2048 [400] 7.38 / 6.68, [200] 6.04 / 6.81, of 1536 6.34 / 5.72.
         if (out->grid.x <= 256 && cols % 64 == 0 && n >= 256) out->fn_beyond_cache = merged ? (cols <= 2048 ? whole_kernel<2, 2>(cols, true) : PG_FN(k_gemm_tile<2, 2, 2, 8, true>)) : PG_FN(k_gemm_tile<2, 2, 2, 4, true>);
     } else {
         // (more than one workgroup per CU, rows that 16-byte loads cannot reach: see k_gemm_tile)
@@ -1760,12 +1763,14 @@ bool merge_head(int op, int dtype, const Shape& s, long long* n_out) {
 }
 
 // Every workgroup normalises its rows anew, which is free while the grid fills the chip once or twice and the more rows the
-// dearer beyond; the separate RMSNorm costs a node.  RMSNorm, GEMV and GELU, us with the RMSNorm in front / on its own, on both
-// sides of each line:
-//   3 to 8 rows    1024 workgroups: 4 rows of 1024 columns 5.8 / 7.0, 8 of 2048 12.1 / 13.0; 4096: 15.3 / 15.0, 36.1 / 34.3
+// dearer beyond; the separate RMSNorm costs a node.  The lines count workgroups of 8 outputs from 5 rows on, whatever the tile that prologue_tile picks.  us with the
+// RMSNorm in front / on its own, on both sides of each line:
+//   3 and 4 rows   (RMSNorm, GEMV and GELU) 1024 workgroups: 4 rows of 1024 columns 5.8 / 7.0; 4096: 15.3 / 15.0
 //                  longer than 4096 columns, 256 workgroups: 4 of 8192 10.5 / 11.4; 512: 19.5 / 17.2
-//   9 to 16 rows   512: 16 of 1024 5.9 / 6.7, 16 of 2048 8.7 / 8.7; 1024: 8.7 / 8.7, 14.5 / 13.6
-//   17 to 32 rows  1024: 32 of 1024 9.6 / 11.1; 4096: 28.7 / 28.6; above 1024 columns, 512: 32 of 2048 9.8 / 9.7; 1024: 15.7 / 15.5
+//   5 to 8 rows    (from here on GELU and two adds) 8192 outputs: 8 of 1024 6.46 / 7.33, 8 of 2048 10.8 / 11.2; 8200: 6.67 / 7.43, 11.3 / 11.3
+//   9 to 16 rows   4096: 16 of 1024 4.19 / 5.86, 16 of 2048 6.81 / 8.04; 4104: 6.16 / 6.37, 9.95 / 9.03
+//   17 to 32 rows  4096: 32 of 1024 5.67 / 6.36; 6000: 7.30 / 7.41; 8192: 8.78 / 7.99; 8200: 9.44 / 9.74; above 1024 columns, 2048: 32 of 2048 6.18 / 6.65; 3000:
+//                  8.89 / 8.30; 4096: 9.06 / 8.56; 4104: 11.3 / 9.5 (on its own: k_gemm_whole, which was not there when these two lines were drawn, at 8192 and 4096)
 // One and two rows: 4096 workgroups of 2048 columns 23.4 / 25.2.
 bool merge_prologue(const Shape& s) {
     if (s.rows <= 2) return true;
